@@ -28,7 +28,9 @@
  *     stride[2] may not exceed 2^20 elements (GF_ERR_UNSUPPORTED beyond).
  *   - `workspace` is a DEVICE pointer of at least gformer_attn_workspace_bytes(...) bytes,
  *     256-byte aligned; may be NULL when that size is 0.  It holds the linear-attention
- *     states carried into each piece and is rewritten by every call that uses it.
+ *     states carried into each piece and is rewritten by every call that uses it.  A GF_F32 call
+ *     on the matrix cores takes any workspace, also none or a smaller one: its linear heads are
+ *     then cut into fewer segments (the result agrees to rounding, the call takes longer).
  *   - `hip_stream` is a hipStream_t (NULL = default stream).  The call enqueues kernels and
  *     returns; it never synchronises.  With params.overlap = 1 and both head groups present
  *     the windowed heads are enqueued on one library-owned, default-priority side stream per
@@ -68,8 +70,9 @@ typedef enum {
 typedef enum { GF_F32 = 0, GF_BF16 = 1 } gf_dtype; /* q, k, v, out share one dtype */
 typedef enum { GF_PHI_ELU1 = 0, GF_PHI_IDENTITY = 1 } gf_phi;
 
-/* Which implementation runs.  GF_IMPL_AUTO picks the MFMA kernels for bf16 and the scalar
- * fp32 kernels for fp32.  GF_IMPL_SCALAR forces the plain-FMA kernels (fp32 arithmetic on
+/* Which implementation runs.  GF_IMPL_AUTO picks the bf16 matrix-core kernels for bf16 and the
+ * single-precision matrix-core kernels (fp32 operands, fp32 accumulation) for fp32; a plan reports
+ * the latter as GF_IMPL_SCALAR, as nothing is rounded below fp32.  GF_IMPL_SCALAR forces the plain-FMA kernels (fp32 arithmetic on
  * either storage type); GF_IMPL_MFMA with GF_F32 is GF_ERR_UNSUPPORTED.
  * GF_IMPL_MFMA runs the windowed heads by one of two kernels with the same results: a streaming
  * kernel (windows of at most 257 tokens; chosen when the call has at least 1024 blocks of 128
@@ -98,7 +101,8 @@ typedef struct gformer_params {
                           /* compute unit) run the general-chunk kernel, causal layers only   */
                           /* in the sense that the bidirectional read-out has no in-chunk     */
                           /* part (there the chunk only sets the granularity of segment_len). */
-                          /* The fp32 kernels work in chunks of 32 whatever is asked.         */
+                          /* The fp32 kernels work in chunks of 32 whatever is asked, and cut  */
+                          /* heads into segments of their own choice.                         */
   int32_t segment_len;    /* 0 = library picks: every linear head is cut into the same whole */
                           /* number of pieces when that fills most of the chip, else the     */
                           /* chunks of all linear heads are cut into equal pieces with no    */
@@ -239,13 +243,15 @@ gf_status gformer_attn_prefill(const void* q, const void* k, const void* v, void
  *             input or each other
  *   workspace : device, gformer_attn_bwd_workspace_bytes bytes, 256-byte aligned: 8 bytes per
  *             token and head (per-row softmax statistics / denominators), rounded up to 256,
- *             plus, for a bidirectional call, two (d*d + d) fp32 sums per linear head
+ *             plus, for a bidirectional call, eight (d*d + d) fp32 sums per linear head.  A GF_F32
+ *             call (GF_IMPL_AUTO) asks for two such sums per segment of every linear head, and
+ *             runs with fewer segments on anything down to the size above
  * Kernels: a bf16 call runs on the matrix cores (params.impl GF_IMPL_AUTO or GF_IMPL_MFMA: bf16
  * products, fp32 accumulation, softmax statistics, denominators and carried sums in fp32; the
  * two operands of the linear heads whose rounding would cost more than the bf16 mode's 2e-2 per
  * row, T' and the in-chunk weights of the numerator, travel as bf16 pairs);
- * GF_IMPL_SCALAR and every fp32 call run on plain-FMA kernels (fp32 arithmetic on either
- * storage type).  The linear heads of a bidirectional call take three sweeps over each head (the
+ * an fp32 call (GF_IMPL_AUTO) on the matrix cores in single precision; GF_IMPL_SCALAR on plain-FMA
+ * kernels (fp32 arithmetic on either storage type).  The linear heads of a bidirectional call take three sweeps over each head (the
  * sums over all keys, dq with the sums over all queries, dk and dv), on the matrix cores for a
  * bf16 call, with the d x d sums and dO / den as bf16 pairs where a difference of nearly equal
  * terms depends on them.  GF_IMPL_MFMA with fp32 storage, GF_IMPL_MFMA_BLOCKED, GF_IMPL_MFMA_STREAM and

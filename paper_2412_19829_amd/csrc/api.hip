@@ -42,7 +42,15 @@ struct Resolved {
   int cph, vcph, piece_chunks, state_sub;
   bool stream;   // MFMA path: the windowed heads go to the streaming kernel
   bool general_chunk;  // MFMA path, causal: the linear read-out goes to the general-chunk kernel
+  bool f32;            // single precision on the matrix cores
+  int f32_seg_len, f32_nseg;
 };
+
+// Single-precision calls run on the matrix cores (fp32 operands and accumulation) unless the caller
+// asks for the plain-FMA kernels, or has more rows or heads than one grid of the former can name.
+bool f32_matrix(const gformer_params* p, int B, int H, int N) {
+  return p->dtype == GF_F32 && p->impl == GF_IMPL_AUTO && (int64_t)B * H * ((N + 15) / 16) < kF32MaxRows / 16;
+}
 
 // One side stream and a fork/join event pair per device, created on first use and kept for the
 // life of the process.  Default priority on purpose.
@@ -218,6 +226,24 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
     pl.linear_blocks = (H1 > 0 && N > 0) ? (int)heads_lin : 0;
     pl.state_blocks = 0;
     pl.workspace_bytes = 0;
+    r->f32 = f32_matrix(p, B, H, N);
+    if (r->f32 && N > 0) {
+      if (H0 > 0) {
+        const int rows = f32_window_rows((int64_t)B * H0, N);
+        pl.windowed_blocks = B * H0 * ((N + rows - 1) / rows);
+      }
+      if (H1 > 0) {
+        const F32Segments f = f32_segments(heads_lin, N, d, UINT64_MAX, 1);
+        r->f32_seg_len = f.len;
+        r->f32_nseg = f.count;
+        pl.segment_len = f.len;
+        pl.n_segments = pl.linear_blocks = (int)(heads_lin * f.count);
+        pl.linear_threads = 4 * d;
+        pl.state_blocks = (int)(heads_lin * (p->bidirectional ? f.count : f.count - 1));
+        if (pl.state_blocks > 0)
+          pl.workspace_bytes = (uint64_t)pl.n_segments * ((uint64_t)d * d + d) * sizeof(float);
+      }
+    }
     return GF_OK;
   }
   pl.chunk = p->chunk ? p->chunk : 64;
@@ -371,7 +397,18 @@ gf_status attn_forward(const void* q, const void* k, const void* v, void* out, v
   if (!q || !k || !v || !out) return GF_ERR_INVALID_ARG;
   if (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)out) & 15u) return GF_ERR_INVALID_ARG;
   if (out == q || out == k || out == v) return GF_ERR_INVALID_ARG;
-  if (r.plan.workspace_bytes > 0) {
+  if (r.f32) {
+    // The workspace is what lets a head be cut into segments; without one (or with a smaller one)
+    // the layer is computed all the same, from fewer segments.
+    if ((uintptr_t)workspace & 255u) workspace = nullptr;
+    if (!workspace) workspace_bytes = 0;
+    if (workspace_bytes < r.plan.workspace_bytes) {
+      const int64_t heads = (int64_t)B * (H - p->n_sparse_heads);
+      const F32Segments f = f32_segments(heads, N, d, workspace_bytes, 1);
+      r.f32_seg_len = f.len;
+      r.f32_nseg = f.count;
+    }
+  } else if (r.plan.workspace_bytes > 0) {
     if (!workspace || workspace_bytes < r.plan.workspace_bytes) return GF_ERR_WORKSPACE;
     if ((uintptr_t)workspace & 255u) return GF_ERR_INVALID_ARG;
   }
@@ -400,6 +437,8 @@ gf_status attn_forward(const void* q, const void* k, const void* v, void* out, v
   a.piece_chunks = r.piece_chunks;
   a.n_pieces = r.plan.n_segments;
   a.state_sub = r.state_sub;
+  a.f32_seg_len = r.f32_seg_len;
+  a.f32_nseg = r.f32_nseg;
   a.ws_states = r.plan.workspace_bytes > 0 ? reinterpret_cast<float*>(workspace) : nullptr;
   a.final_state = final_state;
   a.kring = kring;
@@ -409,7 +448,15 @@ gf_status attn_forward(const void* q, const void* k, const void* v, void* out, v
   const int mask = p->launch_mask ? p->launch_mask : 7;
   const bool bf16 = p->dtype == GF_BF16;
   hipError_t e = hipSuccess;
-  if (r.plan.impl == GF_IMPL_SCALAR) {
+  if (r.f32) {
+    if (mask & GF_LAUNCH_WINDOWED) e = launch_windowed_f32(a, s);
+    if ((mask & GF_LAUNCH_LINEAR_MAIN) && e == hipSuccess) {
+      // the sums over all keys need a slot per head: the plain-FMA kernel keeps its own
+      const uint64_t one = (uint64_t)B * (H - a.H0) * ((uint64_t)d * d + d) * sizeof(float);
+      e = !a.causal && workspace_bytes < one ? launch_linear_scalar(a, bf16, s)
+                                             : launch_linear_f32(a, true, true, s);
+    }
+  } else if (r.plan.impl == GF_IMPL_SCALAR) {
     if ((mask & GF_LAUNCH_WINDOWED) && e == hipSuccess) e = launch_windowed_scalar(a, bf16, s);
     if ((mask & GF_LAUNCH_LINEAR_MAIN) && e == hipSuccess) e = launch_linear_scalar(a, bf16, s);
   } else {
@@ -469,7 +516,8 @@ gf_status gformer_attn_fwd_noalloc(const void* q, const void* k, const void* v, 
   const gf_status st = resolve(B, H, N, d, window, p, &r);
   if (st != GF_OK) return st;
   if (p->overlap != 0) return GF_ERR_UNSUPPORTED;   // the side stream is created on first use
-  if (r.plan.workspace_bytes > kScratchBytes) return GF_ERR_WORKSPACE;
+  // (a single-precision call runs with whatever sums fit)
+  if (!r.f32 && r.plan.workspace_bytes > kScratchBytes) return GF_ERR_WORKSPACE;
   if (B == 0 || H == 0 || N == 0) return GF_OK;
   void* ws = nullptr;
   if (r.plan.workspace_bytes > 0) {
@@ -586,6 +634,16 @@ namespace {
 size_t bwd_stats_bytes(int B, int H, int N) {
   return ((size_t)B * H * N * 2 * sizeof(float) + 255) / 256 * 256;
 }
+// what a call cannot do without; a single-precision call cuts its heads into as many segments as the
+// rest of the workspace holds sums for
+size_t bwd_least_bytes(int B, int H, int N, int d, const gformer_params* p) {
+  size_t need = bwd_stats_bytes(B, H, N);
+  // bidirectional linear heads: the two d x d sums (and their vectors) of every head, each in up
+  // to kBidirStateSlots per-segment partials
+  if (p && p->bidirectional == 1 && p->n_sparse_heads >= 0 && p->n_sparse_heads < H && d > 0)
+    need += (size_t)B * (H - p->n_sparse_heads) * 2 * kBidirStateSlots * ((size_t)d * d + d) * sizeof(float);
+  return need;
+}
 }  // namespace
 
 size_t gformer_attn_bwd_workspace_bytes(int B, int H, int N, int d, int window,
@@ -593,11 +651,17 @@ size_t gformer_attn_bwd_workspace_bytes(int B, int H, int N, int d, int window,
   (void)window;
   if (B <= 0 || H <= 0 || N <= 0) return 0;
   size_t need = bwd_stats_bytes(B, H, N);
-  // bidirectional linear heads: the two d x d sums (and their vectors) of every head, each in up
-  // to kBidirStateSlots per-segment partials
-  if (p && p->bidirectional == 1 && p->n_sparse_heads >= 0 && p->n_sparse_heads < H && d > 0)
-    need += (size_t)B * (H - p->n_sparse_heads) * 2 * kBidirStateSlots * ((size_t)d * d + d) * sizeof(float);
-  return need;
+  if (p && p->dtype == GF_F32 && p->impl == GF_IMPL_AUTO && p->n_sparse_heads >= 0 && p->n_sparse_heads < H && d > 0) {
+    // single precision on the matrix cores: two carried sums per segment (what the call needs is less,
+    // see gformer_attn_bwd)
+    const int64_t heads = (int64_t)B * (H - p->n_sparse_heads);
+    const F32Segments f = f32_segments(heads, N, d, UINT64_MAX, 2);
+    const size_t sums = (size_t)heads * f.count * 2 * ((size_t)d * d + d) * sizeof(float);
+    const size_t least = bwd_least_bytes(B, H, N, d, p);
+    if (f.count > 1 || p->bidirectional == 1) need += sums;
+    return need > least ? need : least;
+  }
+  return bwd_least_bytes(B, H, N, d, p);
 }
 
 gf_status gformer_attn_bwd(const void* q, const void* k, const void* v, const void* dout, void* dq,
@@ -632,7 +696,7 @@ gf_status gformer_attn_bwd(const void* q, const void* k, const void* v, const vo
       if (x == y) return GF_ERR_INVALID_ARG;
   }
   if (dq == dk || dq == dv || dk == dv) return GF_ERR_INVALID_ARG;
-  const size_t need = gformer_attn_bwd_workspace_bytes(B, H, N, d, window, p);
+  const size_t need = bwd_least_bytes(B, H, N, d, p);
   if (!workspace || workspace_bytes < need) return GF_ERR_WORKSPACE;
   if ((uintptr_t)workspace & 255u) return GF_ERR_INVALID_ARG;
 
@@ -662,7 +726,15 @@ gf_status gformer_attn_bwd(const void* q, const void* k, const void* v, const vo
   const bool bf16 = p->dtype == GF_BF16;
   const bool mfma = bf16 && p->impl != GF_IMPL_SCALAR;
   hipError_t e = hipSuccess;
-  if (mfma) {
+  if (f32_matrix(p, B, H, N)) {
+    const int64_t heads = (int64_t)B * (H - a.H0);
+    a.ws_state = reinterpret_cast<float*>(static_cast<char*>(workspace) + bwd_stats_bytes(B, H, N));
+    const F32Segments f = f32_segments(heads, N, d, workspace_bytes - bwd_stats_bytes(B, H, N), 2);
+    a.f32_seg_len = f.len;
+    a.f32_nseg = f.count;
+    e = launch_windowed_backward_f32(a, stream);
+    if (e == hipSuccess) e = launch_linear_backward_f32(a, stream);
+  } else if (mfma) {
     // The linear scans are one workgroup per head and segment: with fewer of those than compute
     // units the rest of the chip is idle for their whole duration.  With overlap = 1 the windowed
     // heads' passes therefore run beside them on the library's side stream (forked from and

@@ -44,6 +44,9 @@ struct AttnArgs {
   // Streaming windowed kernel: every (batch, windowed head) is cut into `win_pieces_per_head`
   // pieces of `win_pairs_per_piece` pairs of 32-query groups (set by its launcher).
   int win_pairs_per_piece, win_pieces_per_head;
+  // Single-precision matrix-core kernels: every linear head in f32_nseg segments of f32_seg_len tokens
+  // (a multiple of 32 unless there is one); ws_states holds [B*(H-H0)][f32_nseg][d*d + d] fp32 sums.
+  int f32_seg_len, f32_nseg;
   float* ws_states;  // [n_pieces*state_sub, d*d + d] fp32: slot j = (A, Z) of its head just
                      // before global chunk j*piece_chunks/state_sub (piece p reads slot p*state_sub)
 };
@@ -104,6 +107,9 @@ struct BwdArgs {
   float* ws_state;    // bidirectional linear heads: [B * (H - H0)][2][4][d*d + d] fp32: the sums
                       // (S, z) and (B, Y) of every head, each in up to four per-segment partials
                       // (matrix row-major [feature][value], then the vector)
+  // single-precision matrix-core kernels: segments as in AttnArgs; ws_state holds the sums (A, Z) and
+  // then (B, Y) of every segment, [2][B*(H-H0)][f32_nseg][d*d + d] fp32
+  int f32_seg_len, f32_nseg;
   int lin_segments;   // workgroups per linear head in the matrix-core scans (set by their launcher)
   int lin_bounds[5];  // segment s covers chunks [lin_bounds[s], lin_bounds[s+1]) (reverse scan: mirrored)
   float* ws;   // [B, H, N, 2] fp32: windowed heads (log-sum-exp, dO.o), linear heads (den, dO.o / den),
@@ -167,6 +173,20 @@ hipError_t launch_fill_rings(const AttnArgs& a, bool bf16, hipStream_t s);
 hipError_t launch_random_features(const FeatureArgs& a, bool bf16, bool mfma, hipStream_t s);
 hipError_t launch_decode(const DecodeArgs& a, bool bf16, hipStream_t s);
 size_t decode_smem_bytes(int d, int window, int H0);
+
+// Single-precision matrix-core kernels.  A head's segments: as many as keep two workgroups on every
+// compute unit, none shorter than 128 tokens, as far as `bytes` hold `sums` carried sums for each.
+constexpr int kMaxSegments = 64;
+struct F32Segments {
+  int len, count;
+};
+F32Segments f32_segments(int64_t heads, int N, int d, uint64_t bytes, int sums);
+int f32_window_rows(int64_t heads, int N);   // resident rows per workgroup of the windowed kernels
+hipError_t launch_windowed_f32(const AttnArgs& a, hipStream_t s);
+hipError_t launch_linear_f32(const AttnArgs& a, bool states, bool read, hipStream_t s);
+hipError_t launch_windowed_backward_f32(const BwdArgs& a, hipStream_t s);
+hipError_t launch_linear_backward_f32(const BwdArgs& a, hipStream_t s);
+constexpr int64_t kF32MaxRows = (int64_t)1 << 26;   // B * heads * N / 16 workgroups stay inside a grid
 
 // Launch geometry shared by the planner and the launchers.
 constexpr int kScalarWindowRows = 16;   // query rows per workgroup, scalar windowed kernel

@@ -1,6 +1,5 @@
-// Plain-FMA kernels: fp32 arithmetic on fp32 or bf16 storage.  They are the fp32 path of the
-// library (reduced-precision operands never reach a matrix core here) and are written for
-// clarity; the MFMA kernels carry the bf16 performance path.
+// Plain-FMA kernels: fp32 arithmetic on fp32 or bf16 storage (GF_IMPL_SCALAR, the second opinion of
+// the tests), written for clarity; the matrix-core kernels carry the performance path of both types.
 #include "common.hpp"
 #include "scalar_util.hpp"
 
