@@ -471,6 +471,10 @@ gf_status attn_forward(const void* q, const void* k, const void* v, void* out, v
     std::lock_guard<std::mutex> lock(g_enqueue_mutex);
     SideStream* side = nullptr;
     if (win && lin && p->overlap) e = side_stream_for_current_device(s, &side);
+    // d = 64: the windowed heads' query blocks ride in the read-out's launch (linear_mfma.hip).  Not the
+    // streaming kernel (other block size), a forced overlap, or a launch mask that names one of the two.
+    const bool together = win && (mask & GF_LAUNCH_LINEAR_MAIN) && !p->overlap && !stream && !r.general_chunk &&
+                          linear_main_takes_windowed(a);
     bool forked = false;
     if (side && e == hipSuccess) {
       // fork: the windowed heads wait for what is already in `s`, then run beside the linear ones
@@ -488,11 +492,12 @@ gf_status attn_forward(const void* q, const void* k, const void* v, void* out, v
       const hipError_t j1 = hipEventRecord(side->join, side->stream);
       const hipError_t j2 = j1 == hipSuccess ? hipStreamWaitEvent(s, side->join, 0) : j1;
       if (e == hipSuccess) e = j2;
-    } else if (win && !side && e == hipSuccess) {
+    } else if (win && !side && !together && e == hipSuccess) {
       e = launch_windowed(s);
     }
     if ((mask & GF_LAUNCH_LINEAR_MAIN) && e == hipSuccess)
-      e = r.general_chunk ? launch_linear_chunk(a, s) : launch_linear_main_mfma(a, s);
+      e = together ? launch_linear_main_windowed_mfma(a, s)
+                   : r.general_chunk ? launch_linear_chunk(a, s) : launch_linear_main_mfma(a, s);
   }
   if (e == hipSuccess) e = launch_fill_rings(a, bf16, s);
   return e == hipSuccess ? GF_OK : GF_ERR_DEVICE;

@@ -166,6 +166,9 @@ StreamPlan windowed_stream_plan(int64_t heads, int N, int wleft, int wright);
 hipError_t launch_windowed_stream(const AttnArgs& a, hipStream_t s);
 hipError_t launch_linear_state_mfma(const AttnArgs& a, hipStream_t s);
 hipError_t launch_linear_main_mfma(const AttnArgs& a, hipStream_t s);
+// The read-out and the windowed heads' query blocks in one launch, where the former takes them along.
+bool linear_main_takes_windowed(const AttnArgs& a);
+hipError_t launch_linear_main_windowed_mfma(const AttnArgs& a, hipStream_t s);
 // The causal read-out for chunks of 64, 128 or 256 tokens (the general form of the kernel above).
 bool linear_chunk_supported(int d, int chunk);
 hipError_t launch_linear_chunk(const AttnArgs& a, hipStream_t s);

@@ -32,6 +32,7 @@
 // kernel (CAUSAL = false) contracts phi(Q) with the head's total state only: K and V are read
 // once, by the state pass.
 #include "linear_common.hpp"
+#include "windowed_block.hpp"
 
 #include <type_traits>
 
@@ -297,14 +298,13 @@ __global__ __launch_bounds__(256) void linear_prefix_kernel(float* ws, int n_hea
 //     EMIT (causal only): every head's (A, Z) after its last token is also written out, for a
 //     decode step to continue from; a separate instantiation so that the plain layer pays nothing.
 template <int D, bool ELU1, bool CAUSAL, bool EMIT>
-__global__ __launch_bounds__(LinCfg<D>::NT, D == 64 ? 2 : 1) void linear_main_kernel(AttnArgs a) {
+__device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, unsigned char* smem_raw) {
   using C = LinCfg<D>;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   LinSmem<D>& sm = *reinterpret_cast<LinSmem<D>*>(smem_raw);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int ln = lane & 31, lh = lane >> 5;
   const int n_heads = a.B * (a.H - a.H0);
-  const int g0 = blockIdx.x * a.piece_chunks;
+  const int g0 = block * a.piece_chunks;
   const int nchunks = piece_chunk_count(a, g0, n_heads);
   if (nchunks <= 0) return;  // uniform
   const int N = a.N;
@@ -733,6 +733,28 @@ __global__ __launch_bounds__(LinCfg<D>::NT, D == 64 ? 2 : 1) void linear_main_ke
   lds_barrier();  // (c)
 }
 
+template <int D, bool ELU1, bool CAUSAL, bool EMIT>
+__global__ __launch_bounds__(LinCfg<D>::NT, D == 64 ? 2 : 1) void linear_main_kernel(AttnArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  linear_main_block<D, ELU1, CAUSAL, EMIT>(a, blockIdx.x, smem_raw);
+}
+
+// The read-out and the windowed heads in one launch (d = 64): blocks [0, n_pieces) are the read-out's,
+// those from the next multiple of 8 on (the XCDs keep their runs) are query blocks of the windowed
+// heads.  At d = 64 a compute unit holds two workgroups and the plan gives it one piece, so the query
+// blocks run beside the pieces instead of in front of them.
+// Same bits as two launches; the whole layer (us, two launches -> one): B=1 H=12 N=2048 w=128 H0=2
+// 36.1 -> 28.1, B=8 H=12 N=4096 w=256 H0=2 78.4 -> 67.4.  At d = 128 a piece's LDS fills its compute unit and
+// nothing can run beside it.
+template <bool ELU1, bool CAUSAL, bool EMIT>
+__global__ __launch_bounds__(256, 2) void linear_main_windowed_kernel(AttnArgs a) {
+  static_assert(LinCfg<64>::NT == kMfmaWindowThreads, "one block size for both kinds of workgroup");
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  const int first = (a.n_pieces + 7) & ~7, block = blockIdx.x;
+  if (block >= first) windowed_block<64, false>(a, block - first, smem_raw);
+  else if (block < a.n_pieces) linear_main_block<64, ELU1, CAUSAL, EMIT>(a, block, smem_raw);
+}
+
 template <int D> hipError_t launch_state_t(const AttnArgs& a, hipStream_t s) {
   using C = LinCfg<D>;
   const int heads = a.B * (a.H - a.H0);
@@ -778,7 +800,26 @@ template <int D> hipError_t launch_main_t(const AttnArgs& a, hipStream_t s) {
   return e != hipSuccess ? e : hipGetLastError();
 }
 
+template <bool CAUSAL, bool EMIT> hipError_t launch_main_windowed_t(const AttnArgs& a, hipStream_t s) {
+  const int smem = (int)(sizeof(LinSmem<64>) > sizeof(WinSmem<64>) ? sizeof(LinSmem<64>) : sizeof(WinSmem<64>));
+  const dim3 grid(((a.n_pieces + 7) & ~7) + (a.N + BR - 1) / BR * a.H0 * a.B), block(256);
+  const auto kern = a.phi == 0 ? linear_main_windowed_kernel<true, CAUSAL, EMIT>
+                               : linear_main_windowed_kernel<false, CAUSAL, EMIT>;
+  const hipError_t e = allow_lds(kern, smem);
+  if (e != hipSuccess) return e;
+  kern<<<grid, block, smem, s>>>(a);
+  return hipGetLastError();
+}
+
 }  // namespace
+
+bool linear_main_takes_windowed(const AttnArgs& a) {
+  return a.d == 64 && a.H0 > 0 && a.H0 < a.H && a.n_pieces > 0 && a.scale >= 0.f;
+}
+hipError_t launch_linear_main_windowed_mfma(const AttnArgs& a, hipStream_t s) {
+  if (!a.causal) return launch_main_windowed_t<false, false>(a, s);
+  return a.final_state ? launch_main_windowed_t<true, true>(a, s) : launch_main_windowed_t<true, false>(a, s);
+}
 
 hipError_t launch_linear_state_mfma(const AttnArgs& a, hipStream_t s) {
   if (a.H - a.H0 <= 0 || a.N <= 0 || a.B <= 0 || !a.ws_states) return hipSuccess;
