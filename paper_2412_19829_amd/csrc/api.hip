@@ -160,6 +160,37 @@ long aligned_piece(long heads_lin, long cph, long kComputeUnits) {
   return piece;
 }
 
+// Chunks per piece of a small call, or 0 where this rule does not apply: no whole-number cut fills the
+// chip, and pieces of eight chunks would leave more than three of eight compute units idle or every
+// piece can be a whole short head.  Such a call takes as long as one
+// piece: its chunks one after another, plus the sums it adds up first.  Uniform segments per head,
+// shorter than eight chunks, trade the former for the latter.  Whole layer, us, pieces of eight
+// against these:  d = 64, linear heads x chunks:  10x8 18.2 / 13.0 (2 chunks a piece), 10x16 24.8 / 14.9
+// (2), 10x32 26.0 / 20.5 (4), 10x64 34.7 / 28.8 (4), 26x16 25.5 / 17.4 (3), 52x16 26.7 / 22.4 (4), 100x10
+// 26.9 / 21.1 (5), 300x5 27.9 / 18.1 (5: a whole head, no carried sums at all).  d = 128, where a sum is
+// four times as large and a compute unit holds one piece: 10x8 33.0 / 30.6 (2), 10x16 42.8 / 38.1 (4),
+// 10x64 61.8 / 55.1 (4), 26x32 60.9 / 54.8 (6), 52x10 47.8 / 40.4 (5).  Two-chunk pieces lose again as
+// soon as a head has more than eight of them (10x32: 23.2) or they crowd the chip (26x16: 19.3).
+long short_piece(long heads, long cph, long cus, int d) {
+  if (cph < 4 || heads <= 0 || heads > 2 * cus) return 0;
+  if (heads * cph > 5 * cus && (heads * 5 < 4 * cus || cph > 8)) return 0;
+  if (d == 128) {
+    if (cph > 64 || heads > cus) return 0;
+    long k = cus * 5 / 8 / heads;
+    if (k > (cph <= 8 ? cph / 2 : cph / 4)) k = cph <= 8 ? cph / 2 : cph / 4;
+    if (k < 1) k = 1;
+    return (cph + k - 1) / k;
+  }
+  long k = cus / heads;
+  if (k > cph / 2) k = cph / 2;
+  if (k < 1) k = 1;
+  long piece = (cph + k - 1) / k;
+  const long per = (cph + piece - 1) / piece;
+  if (per > 8 && piece < 4) piece = 4;
+  else if (piece < 3 && heads * per > cus / 2) piece = 3;
+  return piece;
+}
+
 // Shared by gformer_attn_plan, gformer_attn_workspace_bytes and gformer_attn_fwd.
 // Token i of a windowed head sees keys i - left .. i + right (cut at the sequence ends): the w
 // tokens ending at i, or (bidirectional) the w tokens centred on it.
@@ -176,7 +207,10 @@ int window_right(int window, int bidirectional, int N) {
   return reach < N - 1 ? reach : (N > 1 ? N - 1 : 0);
 }
 
-gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* p, Resolved* r) {
+// With short_pieces = false small calls are cut as they were before that rule existed: what a workspace
+// sized for that cut still gets.
+gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* p, Resolved* r,
+                  bool short_pieces = true) {
   memset(r, 0, sizeof(*r));
   if (!p) return GF_ERR_INVALID_ARG;
   if (p->struct_size != sizeof(gformer_params)) return GF_ERR_INVALID_ARG;
@@ -259,6 +293,8 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
   const long cph = N > 0 ? (N + kStrip - 1) / kStrip : 0;  // real strips per head
   long piece = 0, vcph = cph, pieces = 0, mid = 0, sub = 1;
   if (p->segment_len != 0 && p->segment_len % pl.chunk != 0) return GF_ERR_INVALID_ARG;
+  long own_piece = aligned_piece(heads_lin, cph, kComputeUnits);
+  if (own_piece == 0 && !r->general_chunk && short_pieces) own_piece = short_piece(heads_lin, cph, kComputeUnits, d);
   if (p->bidirectional && heads_lin > 0 && cph > 0) {
     // Bidirectional linear heads: every piece needs the state of its whole head, so pieces never
     // straddle heads (uniform segments per head) and every one of them is summed by the state
@@ -275,14 +311,12 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
     vcph = per_head * piece;
     pieces = heads_lin * per_head;
     mid = pieces;
-  } else if (p->segment_len != 0 ||
-             (heads_lin > 0 && cph > 0 &&
-              (r->general_chunk || aligned_piece(heads_lin, cph, kComputeUnits) > 0))) {
+  } else if (p->segment_len != 0 || (heads_lin > 0 && cph > 0 && (r->general_chunk || own_piece > 0))) {
     // Uniform segments per head: asked for, needed by the general-chunk kernel, or chosen
     // because a whole number of them per head keeps at least 4 of 5 compute units busy.  Pieces
     // that never straddle heads leave the state pass the least to re-read (a head's last segment
     // is never summed).
-    piece = p->segment_len != 0 ? p->segment_len / kStrip : aligned_piece(heads_lin, cph, kComputeUnits);
+    piece = p->segment_len != 0 ? p->segment_len / kStrip : own_piece;
     if (piece == 0) {
       // general-chunk kernel with too few or too many heads for a good whole-number cut: as many
       // pieces per head as there are compute units for, none shorter than 8 strips
@@ -392,6 +426,9 @@ gf_status attn_forward(const void* q, const void* k, const void* v, void* out, v
                        void* hip_stream) {
   Resolved r;
   gf_status st = resolve(B, H, N, d, window, p, &r);
+  if (st != GF_OK) return st;
+  if (!r.f32 && (workspace ? workspace_bytes : 0) < r.plan.workspace_bytes)
+    st = resolve(B, H, N, d, window, p, &r, false);
   if (st != GF_OK) return st;
   if (B == 0 || H == 0 || N == 0) return GF_OK;
   if (!q || !k || !v || !out) return GF_ERR_INVALID_ARG;

@@ -56,11 +56,12 @@ struct AttnArgs {
 // read-out kernel reads a single slot.
 __host__ __device__ inline bool uses_prefix_kernel(const AttnArgs& a) {
   const int ls = a.piece_chunks / a.state_sub;
-  if (!a.causal) return a.vcph / ls > 6;   // every piece adds up its whole head
+  const int most = a.d == 64 ? 8 : 6;   // sums of 16 KB and of 66 KB
+  if (!a.causal) return a.vcph / ls > most;   // every piece adds up its whole head
   // a causal piece adds up the sub-pieces in front of it inside its head; the latest start is
   // the head's last piece when pieces never straddle heads, else the head's last chunk
   const int last_start = a.vcph % a.piece_chunks == 0 ? a.vcph - a.piece_chunks : a.vcph - 1;
-  return last_start / ls > 6;
+  return last_start / ls > most;
 }
 
 // bf16 storage helpers (round to nearest even on store).
