@@ -244,8 +244,8 @@ gf_status gformer_attn_prefill(const void* q, const void* k, const void* v, void
  *   workspace : device, gformer_attn_bwd_workspace_bytes bytes, 256-byte aligned: 8 bytes per
  *             token and head (per-row softmax statistics / denominators), rounded up to 256,
  *             plus, for a bidirectional call, eight (d*d + d) fp32 sums per linear head.  A GF_F32
- *             call (GF_IMPL_AUTO) asks for two such sums per segment of every linear head, and
- *             runs with fewer segments on anything down to the size above
+ *             call (GF_IMPL_AUTO) and a causal GF_BF16 call with d = 64 ask for two such sums per
+ *             segment of every linear head, and run, slower, on anything down to the size above
  * Kernels: a bf16 call runs on the matrix cores (params.impl GF_IMPL_AUTO or GF_IMPL_MFMA: bf16
  * products, fp32 accumulation, softmax statistics, denominators and carried sums in fp32; the
  * two operands of the linear heads whose rounding would cost more than the bf16 mode's 2e-2 per

@@ -267,7 +267,7 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
         pl.windowed_blocks = B * H0 * ((N + rows - 1) / rows);
       }
       if (H1 > 0) {
-        const F32Segments f = f32_segments(heads_lin, N, d, UINT64_MAX, 1);
+        const Segments f = f32_segments(heads_lin, N, d, UINT64_MAX, 1);
         r->f32_seg_len = f.len;
         r->f32_nseg = f.count;
         pl.segment_len = f.len;
@@ -441,7 +441,7 @@ gf_status attn_forward(const void* q, const void* k, const void* v, void* out, v
     if (!workspace) workspace_bytes = 0;
     if (workspace_bytes < r.plan.workspace_bytes) {
       const int64_t heads = (int64_t)B * (H - p->n_sparse_heads);
-      const F32Segments f = f32_segments(heads, N, d, workspace_bytes, 1);
+      const Segments f = f32_segments(heads, N, d, workspace_bytes, 1);
       r.f32_seg_len = f.len;
       r.f32_nseg = f.count;
     }
@@ -676,6 +676,12 @@ namespace {
 size_t bwd_stats_bytes(int B, int H, int N) {
   return ((size_t)B * H * N * 2 * sizeof(float) + 255) / 256 * 256;
 }
+// bf16: the carried sums of the segments
+size_t bwd_segment_bytes(int64_t heads, int N, int d, bool causal) {
+  const Segments f = backward_segments(heads, N, d, causal);
+  if (causal && f.count == 1) return 0;
+  return (size_t)heads * f.count * 2 * ((size_t)d * d + d) * sizeof(float);
+}
 // what a call cannot do without; a single-precision call cuts its heads into as many segments as the
 // rest of the workspace holds sums for
 size_t bwd_least_bytes(int B, int H, int N, int d, const gformer_params* p) {
@@ -697,11 +703,16 @@ size_t gformer_attn_bwd_workspace_bytes(int B, int H, int N, int d, int window,
     // single precision on the matrix cores: two carried sums per segment (what the call needs is less,
     // see gformer_attn_bwd)
     const int64_t heads = (int64_t)B * (H - p->n_sparse_heads);
-    const F32Segments f = f32_segments(heads, N, d, UINT64_MAX, 2);
+    const Segments f = f32_segments(heads, N, d, UINT64_MAX, 2);
     const size_t sums = (size_t)heads * f.count * 2 * ((size_t)d * d + d) * sizeof(float);
     const size_t least = bwd_least_bytes(B, H, N, d, p);
     if (f.count > 1 || p->bidirectional == 1) need += sums;
     return need > least ? need : least;
+  }
+  if (p && p->dtype == GF_BF16 && p->impl != GF_IMPL_SCALAR && d == 64 && p->n_sparse_heads >= 0 && p->n_sparse_heads < H) {
+    const size_t sums = bwd_segment_bytes((int64_t)B * (H - p->n_sparse_heads), N, d, p->bidirectional == 0);
+    const size_t least = bwd_least_bytes(B, H, N, d, p);
+    return need + sums > least ? need + sums : least;
   }
   return bwd_least_bytes(B, H, N, d, p);
 }
@@ -761,7 +772,18 @@ gf_status gformer_attn_bwd(const void* q, const void* k, const void* v, const vo
   a.ws = reinterpret_cast<float*>(workspace);
   a.ws_state = a.causal ? nullptr
                         : reinterpret_cast<float*>(static_cast<char*>(workspace) + bwd_stats_bytes(B, H, N));
+  // The segment walks take the linear heads when the workspace holds their sums; a workspace of the
+  // least size gets the scans that sum what lies in front of (behind) a segment again.
+  const Segments segs = backward_segments((int64_t)B * (H - a.H0), N, d, a.causal);
+  const bool segments = d == 64 && (int64_t)B * (H - a.H0) < (1 << 22) &&   // one grid dimension holds them
+                        workspace_bytes >= bwd_stats_bytes(B, H, N) + bwd_segment_bytes((int64_t)B * (H - a.H0), N, d, a.causal);
   auto launch_linear = [&](hipStream_t on) {
+    if (segments) {
+      a.ws_state = reinterpret_cast<float*>(static_cast<char*>(workspace) + bwd_stats_bytes(B, H, N));
+      a.lin_segment_len = segs.len;
+      a.lin_segments = segs.count;
+      return launch_linear_backward_segments(a, on);
+    }
     return a.causal ? launch_linear_backward_mfma(a, on) : launch_linear_backward_bidir_mfma(a, on);
   };
   hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
@@ -771,7 +793,7 @@ gf_status gformer_attn_bwd(const void* q, const void* k, const void* v, const vo
   if (f32_matrix(p, B, H, N)) {
     const int64_t heads = (int64_t)B * (H - a.H0);
     a.ws_state = reinterpret_cast<float*>(static_cast<char*>(workspace) + bwd_stats_bytes(B, H, N));
-    const F32Segments f = f32_segments(heads, N, d, workspace_bytes - bwd_stats_bytes(B, H, N), 2);
+    const Segments f = f32_segments(heads, N, d, workspace_bytes - bwd_stats_bytes(B, H, N), 2);
     a.f32_seg_len = f.len;
     a.f32_nseg = f.count;
     e = launch_windowed_backward_f32(a, stream);

@@ -1,0 +1,717 @@
+// Backward pass of the linear heads on bf16 matrix cores, heads cut into segments (formulas:
+// backward_scalar.hip; the causal layer, and the layer over all keys with CAUSAL = false).
+//
+// Three walks in chunks of 32 tokens, one workgroup of d/16 waves per segment:
+//   sums   A = sum phi(k) v^T, Z = sum phi(k) of every segment
+//   dq     from the sums of the segments in front:  r_t = A dO_t,  S_tu = phi(q_t).phi(k_u),
+//          T_tu = dO_t.v_u (u <= t inside the chunk),  den_t = sum_u S_tu + phi(q_t).Z + eps,
+//          c_t = (phi(q_t).r_t + sum_u S_tu T_tu) / den_t^2,
+//          dphi(q_t) = r_t / den_t - c_t Z + sum_u (T_tu / den_t - c_t) phi(k_u);
+//          leaves (den, c) of every token and the segment's B = sum phi(q) dO^T / den, Y = sum c phi(q)
+//   dk,dv  from the sums of the segments behind:  dphi(k_u) = B v_u - Y + sum_t (T_tu / den_t - c_t) phi(q_t),
+//          dv_u = B^T phi(k_u) + sum_t S_tu / den_t dO_t
+// c needs no read-out of the forward pass: dO_t.num_t is a product of what dphi(q_t) takes anyway.
+//
+// Wave w owns columns 16w..16w+15 of the carried sums as 16x16 accumulator tiles whose registers,
+// packed to bf16, are the operand of the read-out (v_mfma_f32_16x16x32_bf16, K = 32: tiles 2*kk and
+// 2*kk + 1 hold rows 32*kk + 8*g + 0..3 and + 4..7 of lane group g, which is that instruction's order
+// of k-slots).  So no copy of the sums goes through LDS, the tiles of a chunk are all a workgroup
+// needs there, and several workgroups share a compute unit and cover each other's barriers.
+//
+// Head size 64.  Measured (us, the scans of backward_linear_mfma.hip and the sweeps of backward_bidir_mfma.hip
+// against these): causal, 52 heads x 4096 tokens, 103 + 99 -> 14 (sums) + 6 (scan) + 45 (dq) + 6 + 39 (dk, dv);
+// over all keys, 288 heads x 577, 16 + 43 + 25 -> 12 + 35 + 22.  A scan has one workgroup of four waves on a
+// compute unit (85 KB of LDS) and five barriers per 64 tokens, here two to three workgroups interleave.
+// Traffic 27 MB a tensor: 136 MB and 164 MB, 3.0 and 4.2 TB/s.  At head size 128 a wave's sums take 64 registers:
+// two workgroups on a compute unit leave 128 in all, which spills (830 + 565 us on 104 heads x 8192
+// against 477 + 481), one leaves each chunk's chain of barriers exposed (452 + 415, plus 105 for the sums);
+// chunks in flight (one to three), waves per column block (one or two) and loads issued late were tried
+// on both and none beat the scans, which stay there.
+//
+// Precision: S, T, den, c, Z, Y and the carried sums are fp32; the weights T/den - c, a difference a
+// gradient row sums with signs, enter their products as bf16 pairs (high half + rounded remainder).
+#include <type_traits>
+
+#include "common.hpp"
+#include "mfma.hpp"
+
+namespace gformer {
+namespace {
+
+constexpr int SC = 32;       // tokens per chunk
+constexpr int TRW = SC + 4;  // row stride (floats) of the fp32 products
+constexpr int WRW = SC + 8;  // row stride (bf16) of the weights
+constexpr float kLog2e = 1.4426950408889634f;
+constexpr int kSegmentsInPlace = kBidirStateSlots;   // up to this many a walk adds up the sums it needs itself
+constexpr u32x4 kZero4 = {0u, 0u, 0u, 0u};
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr f32x4 kZeroF4 = {0.f, 0.f, 0.f, 0.f};
+
+template <int D> struct SegCfg {
+  static constexpr int NW = D / 16, NT = 64 * NW;
+  static constexpr int R = D == 128 ? D + 24 : D + 8;  // 12 / 36 dwords mod 64: row and transpose reads
+  static constexpr int KS = D / 32;                    // contraction steps over the head size
+  static constexpr int XT = D / 16;                    // tiles of a carried sum per wave
+  static constexpr int STATE = D * D + D;
+};
+
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ float sum_over_groups(float x) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ f32x4 lds4f(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+
+__device__ __forceinline__ float phi_elu1(float x) {
+  const float e = __builtin_amdgcn_exp2f(x * kLog2e);
+  return x > 0.f ? x + 1.f : e;
+}
+template <bool ELU1> __device__ __forceinline__ u32x4 map8(u32x4 v) {
+  if (!ELU1) return v;
+  u32x4 o;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) o[w] = pack_bf16(phi_elu1(bf16_lo(v[w])), phi_elu1(bf16_hi(v[w])));
+  return o;
+}
+template <bool ELU1> __device__ __forceinline__ float slope_of(float f) {
+  if (!ELU1) return 1.f;
+  return f > 1.f ? 1.f : f;
+}
+__device__ __forceinline__ void get4(const uint16_t* p, float (&f)[4]) {
+  const u32x2 pk = *reinterpret_cast<const u32x2*>(p);
+  f[0] = bf16_lo(pk[0]); f[1] = bf16_hi(pk[0]); f[2] = bf16_lo(pk[1]); f[3] = bf16_hi(pk[1]);
+}
+__device__ __forceinline__ void put4(uint16_t* p, float a, float b, float c, float d) {
+  u32x2 pk;
+  pk[0] = pack_bf16(a, b);
+  pk[1] = pack_bf16(c, d);
+  *reinterpret_cast<u32x2*>(p) = pk;
+}
+// x as a pair of bf16x8: high halves and rounded remainders
+__device__ __forceinline__ void split8(const float (&x)[8], bf16x8& hi, bf16x8& lo) {
+  u32x4 h, l;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    h[w] = pack_bf16(x[2 * w], x[2 * w + 1]);
+    l[w] = pack_bf16(x[2 * w] - bf16_lo(h[w]), x[2 * w + 1] - bf16_hi(h[w]));
+  }
+  hi = as_bf16x8(h);
+  lo = as_bf16x8(l);
+}
+__device__ __forceinline__ void widen8(bf16x8 v, float (&x)[8]) {
+  const u32x4 u = as_u32x4(v);
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    x[2 * w] = bf16_lo(u[w]);
+    x[2 * w + 1] = bf16_hi(u[w]);
+  }
+}
+__device__ __forceinline__ bf16x8 pack8(const float (&x)[8]) {
+  u32x4 u;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) u[w] = pack_bf16(x[2 * w], x[2 * w + 1]);
+  return as_bf16x8(u);
+}
+
+// Operand along the rows of a tile: lane (g, i) takes row i, columns 32*kk + 8*g .. +7.
+__device__ __forceinline__ bf16x8 row8(const uint16_t* row_lane, int kk) { return lds_read16(row_lane + 32 * kk); }
+// Operand down the tokens of a tile: lane (g, i) takes column `col` of the pattern, tokens 8*g .. +7.
+// `at` points at this lane's corner: (8*g + i/4) rows down, the pattern's column for i%4.
+template <int R> __device__ __forceinline__ bf16x8 col8(const uint16_t* at) {
+  const u32x2 a = lds_tr4(at), b = lds_tr4(at + 4 * R);
+  return as_bf16x8(u32x4{a[0], a[1], b[0], b[1]});
+}
+
+// Carried sum of wave w, element [feature][value] of the fp32 array in memory: tile 2*kk + y,
+// register r of lane (g, i) is row 32*kk + 8*g + 4*y + r of column 16*w + i, where the column is a
+// feature and the row a value (BY_VALUE = false) or the other way round.
+template <int D, bool BY_VALUE>
+__device__ __forceinline__ void add_sum(f32x4 (&s)[D / 16], const float* src, int wave, int g, int i) {
+#pragma unroll
+  for (int x = 0; x < D / 16; ++x) {
+    const int row = 32 * (x / 2) + 8 * g + 4 * (x % 2), col = 16 * wave + i;
+    if constexpr (BY_VALUE) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s[x][r] += src[(row + r) * D + col];
+    } else {
+      s[x] += *reinterpret_cast<const f32x4*>(src + col * D + row);
+    }
+  }
+}
+template <int D> __device__ __forceinline__ void put_sum(const f32x4 (&s)[D / 16], float* dst, int wave, int g, int i) {
+#pragma unroll
+  for (int x = 0; x < D / 16; ++x)
+    *reinterpret_cast<f32x4*>(dst + (16 * wave + i) * D + 32 * (x / 2) + 8 * g + 4 * (x % 2)) = s[x];
+}
+template <int D> __device__ __forceinline__ void clear(f32x4 (&s)[D / 16]) {
+#pragma unroll
+  for (int x = 0; x < D / 16; ++x) s[x] = kZeroF4;
+}
+// out[tb] += s^T applied to rows 16*tb + i of a tile
+template <int D>
+__device__ __forceinline__ void read_out(f32x4 (&out)[2], const f32x4 (&s)[D / 16], const uint16_t* rows_lane) {
+  constexpr int R = SegCfg<D>::R;
+#pragma unroll
+  for (int kk = 0; kk < D / 32; ++kk) {
+    u32x4 a;
+    a[0] = pack_bf16(s[2 * kk][0], s[2 * kk][1]);
+    a[1] = pack_bf16(s[2 * kk][2], s[2 * kk][3]);
+    a[2] = pack_bf16(s[2 * kk + 1][0], s[2 * kk + 1][1]);
+    a[3] = pack_bf16(s[2 * kk + 1][2], s[2 * kk + 1][3]);
+    const bf16x8 sa = as_bf16x8(a);
+    out[0] = mfma16(sa, row8(rows_lane, kk), out[0]);
+    out[1] = mfma16(sa, row8(rows_lane + 16 * R, kk), out[1]);
+  }
+}
+// The same with the sum as a bf16 pair.
+template <int D>
+__device__ __forceinline__ void read_out_pair(f32x4 (&out)[2], const f32x4 (&s)[D / 16], const uint16_t* rows_lane) {
+  constexpr int R = SegCfg<D>::R;
+#pragma unroll
+  for (int kk = 0; kk < D / 32; ++kk) {
+    const float x[8] = {s[2 * kk][0], s[2 * kk][1], s[2 * kk][2], s[2 * kk][3],
+                        s[2 * kk + 1][0], s[2 * kk + 1][1], s[2 * kk + 1][2], s[2 * kk + 1][3]};
+    bf16x8 hi, lo;
+    split8(x, hi, lo);
+    const bf16x8 b0 = row8(rows_lane, kk), b1 = row8(rows_lane + 16 * R, kk);
+    out[0] = mfma16(hi, b0, out[0]);
+    out[1] = mfma16(hi, b1, out[1]);
+    out[0] = mfma16(lo, b0, out[0]);
+    out[1] = mfma16(lo, b1, out[1]);
+  }
+}
+// s += sum over the chunk's tokens of (row of a tile)^T (x) `col`
+template <int D>
+__device__ __forceinline__ void add_outer(f32x4 (&s)[D / 16], const uint16_t* wide_lane, bf16x8 col) {
+#pragma unroll
+  for (int x = 0; x < D / 16; ++x) {
+    s[x] = mfma16(col8<SegCfg<D>::R>(wide_lane + 32 * (x / 2) + 4 * (x % 2)), col, s[x]);
+    if (x % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // operands of four tiles in flight, not of all: registers
+  }
+}
+// 16x16 tile of products of rows
+template <int D> __device__ __forceinline__ f32x4 rows_product(const uint16_t* a_lane, const uint16_t* b_lane) {
+  f32x4 acc = kZeroF4;
+#pragma unroll
+  for (int kk = 0; kk < D / 32; ++kk) acc = mfma16(row8(a_lane, kk), row8(b_lane, kk), acc);
+  return acc;
+}
+
+// Whole chunks run as body(t0, true_type), without a condition in front of their loads and stores: with
+// one the compiler waits for everything outstanding, the last stores included, before it stages a
+// chunk.  Loads past the end are clamped to the last row.
+template <typename Body> __device__ __forceinline__ void walk_up(int begin, int end, Body body) {
+  int t0 = begin;
+  for (; t0 + SC <= end; t0 += SC) body(t0, std::true_type{});
+  if (t0 < end) body(t0, std::false_type{});
+}
+template <typename Body> __device__ __forceinline__ void walk_down(int begin, int end, Body body) {
+  int t0 = begin + (end - begin - 1) / SC * SC;
+  if (t0 + SC > end) {
+    body(t0, std::false_type{});
+    t0 -= SC;
+  }
+  for (; t0 >= begin; t0 -= SC) body(t0, std::true_type{});
+}
+
+// What every walk knows about its thread.
+template <int D> struct Seat {
+  int tid, lane, g, i, wave;
+  int row, col;                 // the 16-byte piece of a chunk this thread moves
+  int seg, head, b, h, begin, end, total;   // tokens [begin, end) in `total` chunks
+  int row_at, own_at, wide_at;  // lane corners: rows; own columns down the tokens; all columns down the tokens
+  __device__ __forceinline__ explicit Seat(const BwdArgs& a) {
+    constexpr int R = SegCfg<D>::R;
+    tid = threadIdx.x;
+    lane = tid & 63;
+    g = lane >> 4;
+    i = lane & 15;
+    wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    row = tid / (D / 8);
+    col = 8 * (tid % (D / 8));
+    seg = blockIdx.x % a.lin_segments;
+    head = blockIdx.x / a.lin_segments;
+    const int H1 = a.H - a.H0;
+    b = head / H1;
+    h = a.H0 + head % H1;
+    begin = seg * a.lin_segment_len;
+    end = min(a.N, begin + a.lin_segment_len);
+    total = (end - begin + SC - 1) / SC;
+    row_at = i * R + 8 * g;
+    own_at = (8 * g + (i >> 2)) * R + 16 * wave + 4 * (i & 3);
+    wide_at = (8 * g + (i >> 2)) * R + 8 * (i & 3);
+  }
+  __device__ __forceinline__ u32x4 load(const uint16_t* base, int64_t sn, int t0, int N) const {
+    return *reinterpret_cast<const u32x4*>(base + (int64_t)min(t0 + row, N - 1) * sn + col);
+  }
+};
+template <int D> __device__ __forceinline__ const uint16_t* head_of(const TensorView& t, int b, int h) {
+  return reinterpret_cast<const uint16_t*>(t.base) + b * t.sb + h * t.sh;
+}
+
+// ---- sums of every segment --------------------------------------------------------------------
+template <int D, bool ELU1>
+__global__ __launch_bounds__(SegCfg<D>::NT, 4) void linear_seg_sum_kernel(BwdArgs a, int per_head) {
+  using C = SegCfg<D>;
+  constexpr int R = C::R;
+  __shared__ __attribute__((aligned(16))) uint16_t fk[2][SC * C::R];
+  __shared__ __attribute__((aligned(16))) uint16_t vv[2][SC * C::R];
+  BwdArgs aa = a;
+  aa.lin_segments = per_head;   // segments summed per head: all, or (causal) all but the last
+  const Seat<D> s(aa);
+  const int N = a.N;
+  const uint16_t* kp = head_of<D>(a.k, s.b, s.h);
+  const uint16_t* vp = head_of<D>(a.v, s.b, s.h);
+  f32x4 acc[C::XT];
+  clear<D>(acc);
+  float z = 0.f;
+  u32x4 kr = s.load(kp, a.k.sn, s.begin, N), vr = s.load(vp, a.v.sn, s.begin, N);
+  int it = 0;
+  walk_up(s.begin, s.end, [&](int t0, auto) {
+    const bool valid = t0 + s.row < N;
+    uint16_t *fkt = fk[it & 1], *vvt = vv[it & 1];   // one barrier a chunk: two buffers
+    ++it;
+    *reinterpret_cast<u32x4*>(fkt + s.row * R + s.col) = valid ? map8<ELU1>(kr) : kZero4;
+    *reinterpret_cast<u32x4*>(vvt + s.row * R + s.col) = valid ? vr : kZero4;
+    kr = s.load(kp, a.k.sn, t0 + SC, N);
+    vr = s.load(vp, a.v.sn, t0 + SC, N);
+    lds_barrier();
+    const bf16x8 kc = col8<R>(fkt + s.own_at);
+    add_outer<D>(acc, vvt + s.wide_at, kc);
+    const u32x4 u = as_u32x4(kc);
+#pragma unroll
+    for (int w = 0; w < 4; ++w) z = dot2_ones_bf16(u[w], z);
+  });
+  float* dst = a.ws_state + ((int64_t)s.head * a.lin_segments + s.seg) * C::STATE;
+  put_sum<D>(acc, dst, s.wave, s.g, s.i);
+  z = sum_over_groups(z);
+  if (s.g == 0) dst[D * D + 16 * s.wave + s.i] = z;
+}
+
+// ---- dq, (den, c), and the segment's B and Y ----------------------------------------------------
+template <int D> struct SegQSmem {
+  using C = SegCfg<D>;
+  uint16_t fq[SC * C::R], fk[SC * C::R], vv[SC * C::R], dd[SC * C::R];
+  float t[SC * TRW];             // T, [query][key]
+  float part[2][3][16];          // row sums of S and of S*T per 16x16 tile
+  float red[2][C::NW][SC];       // per-wave parts of phi(q).r and phi(q).Z
+  float own[C::NW][2][SC];       // 1/den and c, each wave's own copy
+  float z[D];
+};
+template <int D, bool ELU1, bool CAUSAL>
+__global__ __launch_bounds__(SegCfg<D>::NT, 3) void linear_seg_q_kernel(BwdArgs a) {
+  using C = SegCfg<D>;
+  constexpr int R = C::R, NW = C::NW;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  SegQSmem<D>& sm = *reinterpret_cast<SegQSmem<D>*>(smem_raw);
+  const Seat<D> s(a);
+  const int g = s.g, i = s.i, wave = s.wave, N = a.N;
+  const uint16_t* qp = head_of<D>(a.q, s.b, s.h);
+  const uint16_t* kp = head_of<D>(a.k, s.b, s.h);
+  const uint16_t* vp = head_of<D>(a.v, s.b, s.h);
+  const uint16_t* dp = head_of<D>(a.dout, s.b, s.h);
+  uint16_t* dq = reinterpret_cast<uint16_t*>(a.dq) + s.b * a.q.sb + s.h * a.q.sh;
+  float* ws = a.ws + ((int64_t)s.b * a.H + s.h) * N * 2;
+  u32x4 qr, kr = kZero4, vr = kZero4, dr;
+  auto load = [&](int t0) {
+    qr = s.load(qp, a.q.sn, t0, N);
+    dr = s.load(dp, a.dout.sn, t0, N);
+    if (CAUSAL) {
+      kr = s.load(kp, a.k.sn, t0, N);
+      vr = s.load(vp, a.v.sn, t0, N);
+    }
+  };
+  load(s.begin);
+  f32x4 as[C::XT], bs[C::XT];   // A and this segment's B, columns are features
+  clear<D>(as);
+  clear<D>(bs);
+  float y = 0.f;
+  {
+    // the sums of the segments in front (all of them over all keys), or their total where a scan ran
+    int first = 0, end = CAUSAL ? s.seg : a.lin_segments;
+    if (a.lin_segments > kSegmentsInPlace) first = s.seg, end = s.seg + 1;
+    float z = 0.f;
+    for (int j = first; j < end; ++j) {
+      const float* src = a.ws_state + ((int64_t)s.head * a.lin_segments + j) * C::STATE;
+      add_sum<D, false>(as, src, wave, g, i);
+      if (s.tid < D) z += src[D * D + s.tid];
+    }
+    if (s.tid < D) sm.z[s.tid] = z;
+  }
+  uint16_t* const piece_q = sm.fq + s.row * R + s.col;
+  auto store_rows = [&](int t0, bool all) {   // the chunk's dq rows, left in the phi(q) tile
+    if (all || t0 + s.row < N)
+      *reinterpret_cast<u32x4*>(dq + (int64_t)(t0 + s.row) * a.q.sn + s.col) = *reinterpret_cast<const u32x4*>(piece_q);
+  };
+  walk_up(s.begin, s.end, [&](int t0, auto steady) {
+    constexpr bool STEADY = decltype(steady)::value;
+    lds_barrier();   // the chunk before is consumed, its dq rows are complete
+    if (t0 > s.begin) store_rows(t0 - SC, true);
+    const bool valid = STEADY || t0 + s.row < N;
+    *reinterpret_cast<u32x4*>(piece_q) = valid ? map8<ELU1>(qr) : kZero4;
+    *reinterpret_cast<u32x4*>(sm.dd + s.row * R + s.col) = valid ? dr : kZero4;
+    if (CAUSAL) {
+      *reinterpret_cast<u32x4*>(sm.fk + s.row * R + s.col) = valid ? map8<ELU1>(kr) : kZero4;
+      *reinterpret_cast<u32x4*>(sm.vv + s.row * R + s.col) = valid ? vr : kZero4;
+    }
+    load(t0 + SC);
+    lds_barrier();
+    if (CAUSAL && wave < 3) {
+      // S and T of 16 queries and 16 keys: lane = query, registers = keys 4*g + r
+      const int tb = wave > 0, ub = wave > 1;
+      const f32x4 sv = rows_product<D>(sm.fk + 16 * ub * R + s.row_at, sm.fq + 16 * tb * R + s.row_at);
+      const f32x4 tv = rows_product<D>(sm.vv + 16 * ub * R + s.row_at, sm.dd + 16 * tb * R + s.row_at);
+      *reinterpret_cast<f32x4*>(sm.t + (16 * tb + i) * TRW + 16 * ub + 4 * g) = tv;
+      float ss = 0.f, st = 0.f;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float x = (tb != ub || 4 * g + r <= i) ? sv[r] : 0.f;
+        ss += x;
+        st = fmaf(x, tv[r], st);
+      }
+      ss = sum_over_groups(ss);
+      st = sum_over_groups(st);
+      if (g == 0) {
+        sm.part[0][wave][i] = ss;
+        sm.part[1][wave][i] = st;
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    f32x4 rv[2] = {kZeroF4, kZeroF4};
+    if constexpr (CAUSAL) read_out<D>(rv, as, sm.dd + s.row_at);
+    else read_out_pair<D>(rv, as, sm.dd + s.row_at);
+    uint16_t* const corner = sm.fq + i * R + 16 * wave + 4 * g;   // this wave's columns of token i (and 16 + i)
+    {
+      const f32x4 zc = lds4f(sm.z + 16 * wave + 4 * g);
+#pragma unroll
+      for (int tb = 0; tb < 2; ++tb) {
+        float qc[4], qr_ = 0.f, qz = 0.f;
+        get4(corner + 16 * tb * R, qc);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          qr_ = fmaf(qc[r], rv[tb][r], qr_);
+          qz = fmaf(qc[r], zc[r], qz);
+        }
+        qr_ = sum_over_groups(qr_);
+        qz = sum_over_groups(qz);
+        if (g == 0) {
+          sm.red[0][wave][16 * tb + i] = qr_;
+          sm.red[1][wave][16 * tb + i] = qz;
+        }
+      }
+    }
+    lds_barrier();   // T and the parts are visible
+    float inv[2], cv[2];
+#pragma unroll
+    for (int tb = 0; tb < 2; ++tb) {
+      const int n = t0 + 16 * tb + i;
+      float qr_ = 0.f, qz = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        qr_ += sm.red[0][w][16 * tb + i];
+        qz += sm.red[1][w][16 * tb + i];
+      }
+      if (CAUSAL) {
+        qz += tb == 0 ? sm.part[0][0][i] : sm.part[0][1][i] + sm.part[0][2][i];
+        qr_ += tb == 0 ? sm.part[1][0][i] : sm.part[1][1][i] + sm.part[1][2][i];
+      }
+      const float den = STEADY || n < N ? qz + a.eps : 1.f;   // rows past the end: dO is zero
+      inv[tb] = 1.f / den;
+      cv[tb] = qr_ * inv[tb] * inv[tb];
+      if (wave == 0 && (STEADY || n < N))   // every wave has the token's values
+        *reinterpret_cast<float2*>(ws + 2 * (int64_t)n) = make_float2(den, cv[tb]);
+      if (g == 0) {
+        sm.own[wave][0][16 * tb + i] = inv[tb];
+        sm.own[wave][1][16 * tb + i] = cv[tb];
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    {
+      // B += phi(q)^T dO / den, Y += c phi(q): 1/den and c of tokens 8*g .. +7
+      float qx[8];
+      widen8(col8<R>(sm.fq + s.own_at), qx);
+      const float* ip = sm.own[wave][0] + 8 * g;
+      const float* cp = sm.own[wave][1] + 8 * g;
+      const f32x4 i0 = lds4f(ip), i1 = lds4f(ip + 4), c0 = lds4f(cp), c1 = lds4f(cp + 4);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        y = fmaf(j < 4 ? c0[j % 4] : c1[j % 4], qx[j], y);
+        qx[j] *= j < 4 ? i0[j % 4] : i1[j % 4];
+      }
+      if constexpr (CAUSAL) {
+        add_outer<D>(bs, sm.dd + s.wide_at, pack8(qx));
+      } else {
+        // over all keys dphi(k) = B v - Y cancels on heads of a few tokens: phi(q) / den as a pair
+        bf16x8 hi, lo;
+        split8(qx, hi, lo);
+        add_outer<D>(bs, sm.dd + s.wide_at, hi);
+        add_outer<D>(bs, sm.dd + s.wide_at, lo);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    bf16x8 kc;
+    if (CAUSAL) kc = col8<R>(sm.fk + s.own_at);
+    {
+      const f32x4 zc = lds4f(sm.z + 16 * wave + 4 * g);
+#pragma unroll
+      for (int tb = 0; tb < 2; ++tb) {
+        f32x4 acc;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[r] = rv[tb][r] * inv[tb] - cv[tb] * zc[r];
+        if (CAUSAL) {
+          // weights of this lane's query over keys 8*g .. +7
+          const float* tp = sm.t + (16 * tb + i) * TRW + 8 * g;
+          const f32x4 ta = lds4f(tp), tc = lds4f(tp + 4);
+          float w[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+            w[j] = 8 * g + j <= 16 * tb + i ? fmaf(j < 4 ? ta[j % 4] : tc[j % 4], inv[tb], -cv[tb]) : 0.f;
+          bf16x8 hi, lo;
+          split8(w, hi, lo);
+          acc = mfma16(kc, hi, acc);
+          acc = mfma16(kc, lo, acc);
+        }
+        float qc[4];
+        get4(corner + 16 * tb * R, qc);
+        put4(corner + 16 * tb * R, acc[0] * slope_of<ELU1>(qc[0]), acc[1] * slope_of<ELU1>(qc[1]),
+             acc[2] * slope_of<ELU1>(qc[2]), acc[3] * slope_of<ELU1>(qc[3]));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    if (CAUSAL) {
+      add_outer<D>(as, sm.vv + s.wide_at, kc);
+      const u32x4 u = as_u32x4(kc);
+      float dz = 0.f;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) dz = dot2_ones_bf16(u[w], dz);
+      dz = sum_over_groups(dz);
+      if (g == 0) sm.z[16 * wave + i] += dz;   // read by this wave alone
+    }
+  });
+  lds_barrier();
+  store_rows(s.begin + (s.total - 1) * SC, false);
+  if (CAUSAL && s.seg == 0) return;   // nothing lies in front of a head's first segment
+  float* dst = a.ws_state + ((int64_t)a.B * (a.H - a.H0) * a.lin_segments + (int64_t)s.head * a.lin_segments + s.seg) * C::STATE;
+  put_sum<D>(bs, dst, wave, g, i);
+  y = sum_over_groups(y);
+  if (g == 0) dst[D * D + 16 * wave + i] = y;
+}
+
+// ---- dk and dv -----------------------------------------------------------------------------------
+template <int D> struct SegKvSmem {
+  using C = SegCfg<D>;
+  uint16_t fq[SC * C::R], fk[SC * C::R], vv[SC * C::R], dd[SC * C::R];
+  uint16_t sw[SC * WRW], wh[SC * WRW], wl[SC * WRW];   // S / den and the pair of T / den - c, [key][query]
+  float inv[SC], cc[SC];
+  float y[D];
+};
+template <int D, bool ELU1, bool CAUSAL>
+__global__ __launch_bounds__(SegCfg<D>::NT, 3) void linear_seg_kv_kernel(BwdArgs a) {
+  using C = SegCfg<D>;
+  constexpr int R = C::R, NW = C::NW;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  SegKvSmem<D>& sm = *reinterpret_cast<SegKvSmem<D>*>(smem_raw);
+  const Seat<D> s(a);
+  const int g = s.g, i = s.i, wave = s.wave, N = a.N;
+  const uint16_t* qp = head_of<D>(a.q, s.b, s.h);
+  const uint16_t* kp = head_of<D>(a.k, s.b, s.h);
+  const uint16_t* vp = head_of<D>(a.v, s.b, s.h);
+  const uint16_t* dp = head_of<D>(a.dout, s.b, s.h);
+  uint16_t* dk = reinterpret_cast<uint16_t*>(a.dk) + s.b * a.k.sb + s.h * a.k.sh;
+  uint16_t* dv = reinterpret_cast<uint16_t*>(a.dv) + s.b * a.v.sb + s.h * a.v.sh;
+  const float* ws = a.ws + ((int64_t)s.b * a.H + s.h) * N * 2;
+  u32x4 qr = kZero4, kr, vr, dr = kZero4;
+  float2 stat = {1.f, 0.f};
+  auto load = [&](int t0) {   // walking down: chunks in front of the segment are not read
+    t0 = max(t0, s.begin);
+    kr = s.load(kp, a.k.sn, t0, N);
+    vr = s.load(vp, a.v.sn, t0, N);
+    if (CAUSAL) {
+      qr = s.load(qp, a.q.sn, t0, N);
+      dr = s.load(dp, a.dout.sn, t0, N);
+      stat = *reinterpret_cast<const float2*>(ws + 2 * (int64_t)min(t0 + (s.tid & (SC - 1)), N - 1));
+    }
+  };
+  const int last = s.begin + (s.total - 1) * SC;
+  load(last);
+  f32x4 b1[C::XT], b2[C::XT];   // B, columns are features (for dk) and columns are values (for dv)
+  clear<D>(b1);
+  clear<D>(b2);
+  {
+    int first = CAUSAL ? s.seg + 1 : 0, end = a.lin_segments;   // the segments behind, or their total
+    if (a.lin_segments > kSegmentsInPlace) first = s.seg, end = s.seg + 1;
+    float yz = 0.f;
+    for (int j = first; j < end; ++j) {
+      const float* src = a.ws_state + ((int64_t)(a.B * (a.H - a.H0) + s.head) * a.lin_segments + j) * C::STATE;
+      add_sum<D, false>(b1, src, wave, g, i);
+      add_sum<D, true>(b2, src, wave, g, i);
+      if (s.tid < D) yz += src[D * D + s.tid];
+    }
+    if (s.tid < D) sm.y[s.tid] = yz;
+  }
+  uint16_t* const piece_k = sm.fk + s.row * R + s.col;
+  uint16_t* const piece_v = sm.vv + s.row * R + s.col;
+  auto store_rows = [&](int t0, bool all) {
+    if (all || t0 + s.row < N) {
+      *reinterpret_cast<u32x4*>(dk + (int64_t)(t0 + s.row) * a.k.sn + s.col) = *reinterpret_cast<const u32x4*>(piece_k);
+      *reinterpret_cast<u32x4*>(dv + (int64_t)(t0 + s.row) * a.v.sn + s.col) = *reinterpret_cast<const u32x4*>(piece_v);
+    }
+  };
+  walk_down(s.begin, s.end, [&](int t0, auto steady) {
+    constexpr bool STEADY = decltype(steady)::value;
+    lds_barrier();   // the chunk before is consumed, its dk and dv rows are complete
+    if (t0 < last) store_rows(t0 + SC, t0 + 2 * SC <= N);
+    const bool valid = STEADY || t0 + s.row < N;
+    *reinterpret_cast<u32x4*>(piece_k) = valid ? map8<ELU1>(kr) : kZero4;
+    *reinterpret_cast<u32x4*>(piece_v) = valid ? vr : kZero4;
+    if (CAUSAL) {
+      *reinterpret_cast<u32x4*>(sm.fq + s.row * R + s.col) = valid ? map8<ELU1>(qr) : kZero4;
+      *reinterpret_cast<u32x4*>(sm.dd + s.row * R + s.col) = valid ? dr : kZero4;
+      if (s.tid < SC) {
+        const bool there = STEADY || t0 + s.tid < N;
+        sm.inv[s.tid] = there ? 1.f / stat.x : 1.f;
+        sm.cc[s.tid] = there ? stat.y : 0.f;
+      }
+    }
+    load(t0 - SC);
+    lds_barrier();
+    if (CAUSAL) {
+      // S / den and T / den - c of 16 keys and 16 queries: lane = key, registers = queries 4*g + r
+      for (int x = wave; x < 6; x += NW) {
+        const int t = x % 3, ub = t > 1, tb = t > 0;
+        const f32x4 inv = lds4f(sm.inv + 16 * tb + 4 * g);
+        const int at = (16 * ub + i) * WRW + 16 * tb + 4 * g;
+        float w[4];
+        if (x < 3) {
+          const f32x4 p = rows_product<D>(sm.fq + 16 * tb * R + s.row_at, sm.fk + 16 * ub * R + s.row_at);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) w[r] = (tb != ub || 4 * g + r >= i) ? p[r] * inv[r] : 0.f;
+          put4(sm.sw + at, w[0], w[1], w[2], w[3]);
+        } else {
+          const f32x4 p = rows_product<D>(sm.dd + 16 * tb * R + s.row_at, sm.vv + 16 * ub * R + s.row_at);
+          const f32x4 c = lds4f(sm.cc + 16 * tb + 4 * g);
+          u32x2 h, l;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) w[r] = (tb != ub || 4 * g + r >= i) ? fmaf(p[r], inv[r], -c[r]) : 0.f;
+          h[0] = pack_bf16(w[0], w[1]);
+          h[1] = pack_bf16(w[2], w[3]);
+          l[0] = pack_bf16(w[0] - bf16_lo(h[0]), w[1] - bf16_hi(h[0]));
+          l[1] = pack_bf16(w[2] - bf16_lo(h[1]), w[3] - bf16_hi(h[1]));
+          *reinterpret_cast<u32x2*>(sm.wh + at) = h;
+          *reinterpret_cast<u32x2*>(sm.wl + at) = l;
+        }
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const f32x4 yc = lds4f(sm.y + 16 * wave + 4 * g);
+    f32x4 dka[2] = {-yc, -yc}, dva[2] = {kZeroF4, kZeroF4};
+    if constexpr (CAUSAL) read_out<D>(dka, b1, sm.vv + s.row_at);
+    else read_out_pair<D>(dka, b1, sm.vv + s.row_at);
+    __builtin_amdgcn_sched_barrier(0);
+    read_out<D>(dva, b2, sm.fk + s.row_at);
+    bf16x8 qcol, dcol;
+    lds_barrier();   // weights visible; every row read of the phi(k) and v tiles is done
+    if (CAUSAL) {
+      qcol = col8<R>(sm.fq + s.own_at);
+      dcol = col8<R>(sm.dd + s.own_at);
+#pragma unroll
+      for (int ub = 0; ub < 2; ++ub) {
+        const int off = (16 * ub + i) * WRW + 8 * g;
+        // the tile of queries 0..15 and keys 16..31 is never written: its weights are zero
+        const bool none = ub == 1 && g < 2;
+        const bf16x8 h = as_bf16x8(none ? kZero4 : as_u32x4(lds_read16(sm.wh + off)));
+        const bf16x8 l = as_bf16x8(none ? kZero4 : as_u32x4(lds_read16(sm.wl + off)));
+        const bf16x8 p = as_bf16x8(none ? kZero4 : as_u32x4(lds_read16(sm.sw + off)));
+        dka[ub] = mfma16(qcol, h, dka[ub]);
+        dva[ub] = mfma16(dcol, p, dva[ub]);
+        dka[ub] = mfma16(qcol, l, dka[ub]);
+      }
+    }
+#pragma unroll
+    for (int ub = 0; ub < 2; ++ub) {
+      uint16_t* kat = sm.fk + (16 * ub + i) * R + 16 * wave + 4 * g;   // this wave's own corner
+      float f[4];
+      get4(kat, f);
+      put4(kat, dka[ub][0] * slope_of<ELU1>(f[0]), dka[ub][1] * slope_of<ELU1>(f[1]),
+           dka[ub][2] * slope_of<ELU1>(f[2]), dka[ub][3] * slope_of<ELU1>(f[3]));
+      put4(sm.vv + (16 * ub + i) * R + 16 * wave + 4 * g, dva[ub][0], dva[ub][1], dva[ub][2], dva[ub][3]);
+    }
+    if (CAUSAL) {
+      const f32x4 i0 = lds4f(sm.inv + 8 * g), i1 = lds4f(sm.inv + 8 * g + 4);
+      const f32x4 c0 = lds4f(sm.cc + 8 * g), c1 = lds4f(sm.cc + 8 * g + 4);
+      float qx[8], dx[8], dy = 0.f;
+      widen8(qcol, qx);
+      widen8(dcol, dx);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float iv = j < 4 ? i0[j % 4] : i1[j % 4];
+        dy = fmaf(j < 4 ? c0[j % 4] : c1[j % 4], qx[j], dy);
+        qx[j] *= iv;
+        dx[j] *= iv;
+      }
+      add_outer<D>(b1, sm.dd + s.wide_at, pack8(qx));
+      add_outer<D>(b2, sm.fq + s.wide_at, pack8(dx));
+      dy = sum_over_groups(dy);
+      if (g == 0) sm.y[16 * wave + i] += dy;   // read by this wave alone
+    }
+  });
+  lds_barrier();
+  store_rows(s.begin, s.begin + SC <= N);
+}
+
+template <int D, bool ELU1> hipError_t launch_t(const BwdArgs& a, hipStream_t s) {
+  using C = SegCfg<D>;
+  const int heads = a.B * (a.H - a.H0), nseg = a.lin_segments, per_head = a.causal ? nseg - 1 : nseg;
+  float* bsums = a.ws_state + (int64_t)heads * nseg * C::STATE;
+  const dim3 grid(heads * nseg), block(C::NT);
+  hipError_t e = hipSuccess;
+  auto launch = [&](auto kern, int smem) {
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    if (e != hipSuccess) return;
+    kern<<<grid, block, smem, s>>>(a);
+    e = hipGetLastError();
+  };
+  if (per_head > 0) {
+    linear_seg_sum_kernel<D, ELU1><<<dim3(heads * per_head), block, 0, s>>>(a, per_head);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (nseg > kSegmentsInPlace) e = launch_segment_scan(a.ws_state, heads, nseg, C::STATE, 0, s);
+  }
+  if (a.causal) launch(linear_seg_q_kernel<D, ELU1, true>, (int)sizeof(SegQSmem<D>));
+  else launch(linear_seg_q_kernel<D, ELU1, false>, (int)sizeof(SegQSmem<D>));
+  if (e == hipSuccess && nseg > kSegmentsInPlace) e = launch_segment_scan(bsums, heads, nseg, C::STATE, 1, s);
+  if (a.causal) launch(linear_seg_kv_kernel<D, ELU1, true>, (int)sizeof(SegKvSmem<D>));
+  else launch(linear_seg_kv_kernel<D, ELU1, false>, (int)sizeof(SegKvSmem<D>));
+  return e;
+}
+
+}  // namespace
+
+// Three workgroups per compute unit and no segment under 128 tokens: 52 heads of 4096 tokens take 50 + 44 us
+// (dq, dk/dv walk) with two, 46 + 40 with three, 51 + 38 with four.  Over all keys a walk reads every sum of
+// its head: four segments at most, as many as the workspace of that form has always held.
+Segments backward_segments(int64_t heads, int N, int d, bool causal) {
+  Segments f{N, 1};
+  if (heads <= 0 || N <= 0 || d != 64) return f;
+  const int64_t chunks = (N + SC - 1) / SC, most = causal ? kMaxSegments : kBidirStateSlots;
+  int64_t n = 3 * (int64_t)device_compute_units() / heads;
+  if (n > most) n = most;
+  if (n > chunks / 4) n = chunks / 4;
+  if (n <= 1) return f;
+  f.len = (int)((chunks + n - 1) / n) * SC;
+  f.count = (N + f.len - 1) / f.len;
+  return f;
+}
+
+hipError_t launch_linear_backward_segments(const BwdArgs& a, hipStream_t s) {
+  if (a.H - a.H0 <= 0 || a.N <= 0 || a.B <= 0) return hipSuccess;
+  const bool elu1 = a.phi == 0;
+  return elu1 ? launch_t<64, true>(a, s) : launch_t<64, false>(a, s);
+}
+
+}  // namespace gformer

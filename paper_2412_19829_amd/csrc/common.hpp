@@ -111,6 +111,7 @@ struct BwdArgs {
   // single-precision matrix-core kernels: segments as in AttnArgs; ws_state holds the sums (A, Z) and
   // then (B, Y) of every segment, [2][B*(H-H0)][f32_nseg][d*d + d] fp32
   int f32_seg_len, f32_nseg;
+  int lin_segment_len;  // bf16 segment walks: tokens per segment (a multiple of 32 unless there is one)
   int lin_segments;   // workgroups per linear head in the matrix-core scans (set by their launcher)
   int lin_bounds[5];  // segment s covers chunks [lin_bounds[s], lin_bounds[s+1]) (reverse scan: mirrored)
   float* ws;   // [B, H, N, 2] fp32: windowed heads (log-sum-exp, dO.o), linear heads (den, dO.o / den),
@@ -181,15 +182,22 @@ size_t decode_smem_bytes(int d, int window, int H0);
 // Single-precision matrix-core kernels.  A head's segments: as many as keep two workgroups on every
 // compute unit, none shorter than 128 tokens, as far as `bytes` hold `sums` carried sums for each.
 constexpr int kMaxSegments = 64;
-struct F32Segments {
+struct Segments {
   int len, count;
 };
-F32Segments f32_segments(int64_t heads, int N, int d, uint64_t bytes, int sums);
+Segments f32_segments(int64_t heads, int N, int d, uint64_t bytes, int sums);
+// In place over [heads][nseg][floats]: mode 0, the sum over the slots before each; 1, behind each; 2, slot 0
+// receives the total.
+hipError_t launch_segment_scan(float* sums, int heads, int nseg, int floats, int mode, hipStream_t s);
 int f32_window_rows(int64_t heads, int N);   // resident rows per workgroup of the windowed kernels
 hipError_t launch_windowed_f32(const AttnArgs& a, hipStream_t s);
 hipError_t launch_linear_f32(const AttnArgs& a, bool states, bool read, hipStream_t s);
 hipError_t launch_windowed_backward_f32(const BwdArgs& a, hipStream_t s);
 hipError_t launch_linear_backward_f32(const BwdArgs& a, hipStream_t s);
+// bf16 backward pass of the linear heads at d = 64, heads cut into segments (lin_segments of lin_segment_len
+// tokens); ws_state holds [2][B*(H-H0)][lin_segments][d*d + d] fp32 sums unless there is one causal segment.
+Segments backward_segments(int64_t heads, int N, int d, bool causal);
+hipError_t launch_linear_backward_segments(const BwdArgs& a, hipStream_t s);
 constexpr int64_t kF32MaxRows = (int64_t)1 << 26;   // B * heads * N / 16 workgroups stay inside a grid
 
 // Launch geometry shared by the planner and the launchers.

@@ -225,9 +225,9 @@ __global__ __launch_bounds__(kLinThreads<D>, 2) void linear_f32_state_kernel(Sta
   if (g == 0) dst[D * D + 16 * wave + i] = z;
 }
 
-// More than kSumInPlace segments: every head's sums become what each segment starts from
+// Every head's sums become what each segment starts from
 // (mode 0: sums of the segments before; 1: of the segments behind; 2: slot 0 receives the total).
-__global__ __launch_bounds__(256) void linear_f32_scan_kernel(float* sums, int nseg, int floats, int mode) {
+__global__ __launch_bounds__(256) void segment_scan_kernel(float* sums, int nseg, int floats, int mode) {
   const int x = blockIdx.x * 256 + threadIdx.x;
   if (x >= floats) return;
   float* p = sums + (int64_t)blockIdx.y * nseg * floats + x;
@@ -688,9 +688,7 @@ hipError_t launch_states(const TensorView& k, const TensorView& v, float* sums, 
   return hipGetLastError();
 }
 hipError_t launch_scan(float* sums, int heads, int nseg, int floats, int mode, hipStream_t s) {
-  if (nseg <= kSumInPlace) return hipSuccess;
-  linear_f32_scan_kernel<<<dim3((floats + 255) / 256, heads), dim3(256), 0, s>>>(sums, nseg, floats, mode);
-  return hipGetLastError();
+  return nseg <= kSumInPlace ? hipSuccess : launch_segment_scan(sums, heads, nseg, floats, mode, s);
 }
 template <typename K, typename A>
 hipError_t launch_walk(K kern, const A& a, int blocks, int threads, int smem, hipStream_t s) {
@@ -733,8 +731,8 @@ template <int D> hipError_t backward(const BwdArgs& a, hipStream_t s) {
 // Three workgroups per compute unit: on 52 heads of 2048 tokens the forward walk takes 51, 42 and 43 us
 // with two, three and four, the dq walk 71, 60 and 65, the dk/dv walk 78, 67 and 73 (more segments mean
 // more sums to read and a longer scan).
-F32Segments f32_segments(int64_t heads, int N, int d, uint64_t bytes, int sums) {
-  F32Segments f{N, 1};
+Segments f32_segments(int64_t heads, int N, int d, uint64_t bytes, int sums) {
+  Segments f{N, 1};
   if (heads <= 0 || N <= 0) return f;
   const int64_t chunks = (N + CH - 1) / CH;
   int64_t n = 3 * (int64_t)device_compute_units() / heads;
@@ -746,6 +744,11 @@ F32Segments f32_segments(int64_t heads, int N, int d, uint64_t bytes, int sums) 
   f.len = (int)((chunks + n - 1) / n) * CH;
   f.count = (N + f.len - 1) / f.len;
   return f;
+}
+
+hipError_t launch_segment_scan(float* sums, int heads, int nseg, int floats, int mode, hipStream_t s) {
+  segment_scan_kernel<<<dim3((floats + 255) / 256, heads), dim3(256), 0, s>>>(sums, nseg, floats, mode);
+  return hipGetLastError();
 }
 
 hipError_t launch_linear_f32(const AttnArgs& a, bool states, bool read, hipStream_t s) {

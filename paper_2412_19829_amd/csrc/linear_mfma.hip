@@ -814,7 +814,8 @@ template <bool CAUSAL, bool EMIT> hipError_t launch_main_windowed_t(const AttnAr
 }  // namespace
 
 bool linear_main_takes_windowed(const AttnArgs& a) {
-  return a.d == 64 && a.H0 > 0 && a.H0 < a.H && a.n_pieces > 0 && a.scale >= 0.f;
+  const int64_t blocks = a.n_pieces + (int64_t)((a.N + BR - 1) / BR) * a.H0 * a.B;
+  return a.d == 64 && a.H0 > 0 && a.H0 < a.H && a.n_pieces > 0 && a.scale >= 0.f && blocks < (1 << 22);
 }
 hipError_t launch_linear_main_windowed_mfma(const AttnArgs& a, hipStream_t s) {
   if (!a.causal) return launch_main_windowed_t<false, false>(a, s);
