@@ -777,12 +777,14 @@ gf_status gformer_attn_bwd(const void* q, const void* k, const void* v, const vo
   const Segments segs = backward_segments((int64_t)B * (H - a.H0), N, d, a.causal);
   const bool segments = d == 64 && (int64_t)B * (H - a.H0) < (1 << 22) &&   // one grid dimension holds them
                         workspace_bytes >= bwd_stats_bytes(B, H, N) + bwd_segment_bytes((int64_t)B * (H - a.H0), N, d, a.causal);
+  const bool together = segments && a.H0 > 0 && a.H0 < a.H && !p->overlap &&
+                        (int64_t)B * a.H0 * ((N + 127) / 128) < (1 << 22);
   auto launch_linear = [&](hipStream_t on) {
     if (segments) {
       a.ws_state = reinterpret_cast<float*>(static_cast<char*>(workspace) + bwd_stats_bytes(B, H, N));
       a.lin_segment_len = segs.len;
       a.lin_segments = segs.count;
-      return launch_linear_backward_segments(a, on);
+      return launch_linear_backward_segments(a, together, on);
     }
     return a.causal ? launch_linear_backward_mfma(a, on) : launch_linear_backward_bidir_mfma(a, on);
   };
@@ -803,7 +805,8 @@ gf_status gformer_attn_bwd(const void* q, const void* k, const void* v, const vo
     // units the rest of the chip is idle for their whole duration.  With overlap = 1 the windowed
     // heads' passes therefore run beside them on the library's side stream (forked from and
     // joined to the caller's stream by events), and the scans are enqueued first so that their
-    // workgroups get their compute units.
+    // workgroups get their compute units.  Without it, the segment walks take the passes along in
+    // their launches (`together`); beside the scans they are launches of their own.
     const bool both = a.H0 > 0 && a.H0 < a.H;
     std::lock_guard<std::mutex> lock(g_enqueue_mutex);
     SideStream* side = nullptr;
@@ -822,7 +825,7 @@ gf_status gformer_attn_bwd(const void* q, const void* k, const void* v, const vo
         if (e == hipSuccess) e = f;
       }
     } else if (e == hipSuccess) {
-      e = launch_windowed_backward_mfma(a, stream);
+      if (!together) e = launch_windowed_backward_mfma(a, stream);
       if (e == hipSuccess) e = launch_linear(stream);
     }
   } else if (a.causal) {

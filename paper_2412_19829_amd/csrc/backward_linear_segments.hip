@@ -32,6 +32,7 @@
 // gradient row sums with signs, enter their products as bf16 pairs (high half + rounded remainder).
 #include <type_traits>
 
+#include "backward_band.hpp"
 #include "common.hpp"
 #include "mfma.hpp"
 
@@ -225,7 +226,7 @@ template <int D> struct Seat {
   int row, col;                 // the 16-byte piece of a chunk this thread moves
   int seg, head, b, h, begin, end, total;   // tokens [begin, end) in `total` chunks
   int row_at, own_at, wide_at;  // lane corners: rows; own columns down the tokens; all columns down the tokens
-  __device__ __forceinline__ explicit Seat(const BwdArgs& a) {
+  __device__ __forceinline__ Seat(const BwdArgs& a, int block, int segments) {
     constexpr int R = SegCfg<D>::R;
     tid = threadIdx.x;
     lane = tid & 63;
@@ -234,8 +235,8 @@ template <int D> struct Seat {
     wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     row = tid / (D / 8);
     col = 8 * (tid % (D / 8));
-    seg = blockIdx.x % a.lin_segments;
-    head = blockIdx.x / a.lin_segments;
+    seg = block % segments;
+    head = block / segments;
     const int H1 = a.H - a.H0;
     b = head / H1;
     h = a.H0 + head % H1;
@@ -255,15 +256,16 @@ template <int D> __device__ __forceinline__ const uint16_t* head_of(const Tensor
 }
 
 // ---- sums of every segment --------------------------------------------------------------------
+template <int D> struct SegSumSmem {
+  uint16_t fk[2][SC * SegCfg<D>::R], vv[2][SC * SegCfg<D>::R];
+};
 template <int D, bool ELU1>
-__global__ __launch_bounds__(SegCfg<D>::NT, 4) void linear_seg_sum_kernel(BwdArgs a, int per_head) {
+__device__ __forceinline__ void seg_sum(const BwdArgs& a, int block, unsigned char* smem_raw) {
   using C = SegCfg<D>;
   constexpr int R = C::R;
-  __shared__ __attribute__((aligned(16))) uint16_t fk[2][SC * C::R];
-  __shared__ __attribute__((aligned(16))) uint16_t vv[2][SC * C::R];
-  BwdArgs aa = a;
-  aa.lin_segments = per_head;   // segments summed per head: all, or (causal) all but the last
-  const Seat<D> s(aa);
+  SegSumSmem<D>& sm = *reinterpret_cast<SegSumSmem<D>*>(smem_raw);
+  // segments summed per head: all, or (causal) all but the last
+  const Seat<D> s(a, block, a.causal ? a.lin_segments - 1 : a.lin_segments);
   const int N = a.N;
   const uint16_t* kp = head_of<D>(a.k, s.b, s.h);
   const uint16_t* vp = head_of<D>(a.v, s.b, s.h);
@@ -274,7 +276,7 @@ __global__ __launch_bounds__(SegCfg<D>::NT, 4) void linear_seg_sum_kernel(BwdArg
   int it = 0;
   walk_up(s.begin, s.end, [&](int t0, auto) {
     const bool valid = t0 + s.row < N;
-    uint16_t *fkt = fk[it & 1], *vvt = vv[it & 1];   // one barrier a chunk: two buffers
+    uint16_t *fkt = sm.fk[it & 1], *vvt = sm.vv[it & 1];   // one barrier a chunk: two buffers
     ++it;
     *reinterpret_cast<u32x4*>(fkt + s.row * R + s.col) = valid ? map8<ELU1>(kr) : kZero4;
     *reinterpret_cast<u32x4*>(vvt + s.row * R + s.col) = valid ? vr : kZero4;
@@ -304,12 +306,11 @@ template <int D> struct SegQSmem {
   float z[D];
 };
 template <int D, bool ELU1, bool CAUSAL>
-__global__ __launch_bounds__(SegCfg<D>::NT, 3) void linear_seg_q_kernel(BwdArgs a) {
+__device__ __forceinline__ void seg_q(const BwdArgs& a, int block, unsigned char* smem_raw) {
   using C = SegCfg<D>;
   constexpr int R = C::R, NW = C::NW;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   SegQSmem<D>& sm = *reinterpret_cast<SegQSmem<D>*>(smem_raw);
-  const Seat<D> s(a);
+  const Seat<D> s(a, block, a.lin_segments);
   const int g = s.g, i = s.i, wave = s.wave, N = a.N;
   const uint16_t* qp = head_of<D>(a.q, s.b, s.h);
   const uint16_t* kp = head_of<D>(a.k, s.b, s.h);
@@ -511,12 +512,11 @@ template <int D> struct SegKvSmem {
   float y[D];
 };
 template <int D, bool ELU1, bool CAUSAL>
-__global__ __launch_bounds__(SegCfg<D>::NT, 3) void linear_seg_kv_kernel(BwdArgs a) {
+__device__ __forceinline__ void seg_kv(const BwdArgs& a, int block, unsigned char* smem_raw) {
   using C = SegCfg<D>;
   constexpr int R = C::R, NW = C::NW;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   SegKvSmem<D>& sm = *reinterpret_cast<SegKvSmem<D>*>(smem_raw);
-  const Seat<D> s(a);
+  const Seat<D> s(a, block, a.lin_segments);
   const int g = s.g, i = s.i, wave = s.wave, N = a.N;
   const uint16_t* qp = head_of<D>(a.q, s.b, s.h);
   const uint16_t* kp = head_of<D>(a.k, s.b, s.h);
@@ -664,29 +664,51 @@ __global__ __launch_bounds__(SegCfg<D>::NT, 3) void linear_seg_kv_kernel(BwdArgs
   store_rows(s.begin, s.begin + SC <= N);
 }
 
-template <int D, bool ELU1> hipError_t launch_t(const BwdArgs& a, hipStream_t s) {
+// ---- launches --------------------------------------------------------------------------------------
+// One walk, and in the same launch the pass over the windowed heads' band that goes with it: blocks
+// [0, linear) are the walk's, those from the next multiple of 8 on (the XCDs keep their runs) the band's.
+// A walk's few long workgroups leave the chip half empty at their end, a band pass hardly starts before it
+// ends; together one fills what the other leaves.  Same bits.  Measured (us a call, forward and backward
+// with recording): 16 x (4 + 2 heads) x 1024 tokens x 64, window 128, causal: 219 apart, 182 together;
+// 64 x (3 + 3) x 256 bidirectional, window 14: 161 and 139.  One pass for dk and dv (four products a tile in
+// place of five, 190 registers, so two workgroups per compute unit): 189 and 145; at three it spills.
+enum Walk { kSumWalk, kQWalk, kKvWalk };
+template <int D, bool ELU1, bool CAUSAL, int WALK>
+__global__ __launch_bounds__(SegCfg<D>::NT, 3) void linear_seg_kernel(BwdArgs a, int linear, int rows) {
+  static_assert(SegCfg<D>::NT == kBandThreads, "one block size for both kinds of workgroup");
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  const int block = blockIdx.x, first = (linear + 7) & ~7;
+  if (block < linear) {
+    if constexpr (WALK == kSumWalk) seg_sum<D, ELU1>(a, block, smem_raw);
+    else if constexpr (WALK == kQWalk) seg_q<D, ELU1, CAUSAL>(a, block, smem_raw);
+    else seg_kv<D, ELU1, CAUSAL>(a, block, smem_raw);
+  } else if (block >= first) {
+    if constexpr (WALK == kSumWalk) windowed_band<D, kStats>(a, block - first, smem_raw);
+    else if constexpr (WALK == kQWalk) windowed_band<D, kDq>(a, block - first, smem_raw);
+    else if (block < first + rows) windowed_band<D, kDk>(a, block - first, smem_raw);   // the longer pass first
+    else if (block >= first + ((rows + 7) & ~7)) windowed_band<D, kDv>(a, block - first - ((rows + 7) & ~7), smem_raw);
+  }
+}
+
+template <int D, bool ELU1, bool CAUSAL> hipError_t launch_t(const BwdArgs& a, bool band, hipStream_t s) {
   using C = SegCfg<D>;
-  const int heads = a.B * (a.H - a.H0), nseg = a.lin_segments, per_head = a.causal ? nseg - 1 : nseg;
+  const int heads = a.B * (a.H - a.H0), nseg = a.lin_segments, per_head = CAUSAL ? nseg - 1 : nseg;
+  const int rows = band ? (a.N + BR - 1) / BR * a.H0 * a.B : 0;   // the band's blocks
   float* bsums = a.ws_state + (int64_t)heads * nseg * C::STATE;
-  const dim3 grid(heads * nseg), block(C::NT);
   hipError_t e = hipSuccess;
-  auto launch = [&](auto kern, int smem) {
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+  auto launch = [&](auto kern, size_t smem, int linear, int band_blocks) {
+    if (e != hipSuccess || linear + rows == 0) return;
+    if (rows > 0 && smem < sizeof(BandSmem<D>)) smem = sizeof(BandSmem<D>);
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return;
-    kern<<<grid, block, smem, s>>>(a);
+    kern<<<dim3(rows > 0 ? ((linear + 7) & ~7) + band_blocks : linear), dim3(C::NT), smem, s>>>(a, linear, rows);
     e = hipGetLastError();
   };
-  if (per_head > 0) {
-    linear_seg_sum_kernel<D, ELU1><<<dim3(heads * per_head), block, 0, s>>>(a, per_head);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (nseg > kSegmentsInPlace) e = launch_segment_scan(a.ws_state, heads, nseg, C::STATE, 0, s);
-  }
-  if (a.causal) launch(linear_seg_q_kernel<D, ELU1, true>, (int)sizeof(SegQSmem<D>));
-  else launch(linear_seg_q_kernel<D, ELU1, false>, (int)sizeof(SegQSmem<D>));
+  launch(linear_seg_kernel<D, ELU1, CAUSAL, kSumWalk>, sizeof(SegSumSmem<D>), heads * per_head, rows);
+  if (e == hipSuccess && nseg > kSegmentsInPlace) e = launch_segment_scan(a.ws_state, heads, nseg, C::STATE, 0, s);
+  launch(linear_seg_kernel<D, ELU1, CAUSAL, kQWalk>, sizeof(SegQSmem<D>), heads * nseg, rows);
   if (e == hipSuccess && nseg > kSegmentsInPlace) e = launch_segment_scan(bsums, heads, nseg, C::STATE, 1, s);
-  if (a.causal) launch(linear_seg_kv_kernel<D, ELU1, true>, (int)sizeof(SegKvSmem<D>));
-  else launch(linear_seg_kv_kernel<D, ELU1, false>, (int)sizeof(SegKvSmem<D>));
+  launch(linear_seg_kernel<D, ELU1, CAUSAL, kKvWalk>, sizeof(SegKvSmem<D>), heads * nseg, ((rows + 7) & ~7) + rows);
   return e;
 }
 
@@ -708,10 +730,10 @@ Segments backward_segments(int64_t heads, int N, int d, bool causal) {
   return f;
 }
 
-hipError_t launch_linear_backward_segments(const BwdArgs& a, hipStream_t s) {
+hipError_t launch_linear_backward_segments(const BwdArgs& a, bool with_windowed, hipStream_t s) {
   if (a.H - a.H0 <= 0 || a.N <= 0 || a.B <= 0) return hipSuccess;
-  const bool elu1 = a.phi == 0;
-  return elu1 ? launch_t<64, true>(a, s) : launch_t<64, false>(a, s);
+  if (a.causal) return a.phi == 0 ? launch_t<64, true, true>(a, with_windowed, s) : launch_t<64, false, true>(a, with_windowed, s);
+  return a.phi == 0 ? launch_t<64, true, false>(a, with_windowed, s) : launch_t<64, false, false>(a, with_windowed, s);
 }
 
 }  // namespace gformer
