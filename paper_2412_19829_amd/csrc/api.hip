@@ -777,8 +777,10 @@ gf_status gformer_attn_bwd(const void* q, const void* k, const void* v, const vo
   const Segments segs = backward_segments((int64_t)B * (H - a.H0), N, d, a.causal);
   const bool segments = d == 64 && (int64_t)B * (H - a.H0) < (1 << 22) &&   // one grid dimension holds them
                         workspace_bytes >= bwd_stats_bytes(B, H, N) + bwd_segment_bytes((int64_t)B * (H - a.H0), N, d, a.causal);
-  const bool together = segments && a.H0 > 0 && a.H0 < a.H && !p->overlap &&
-                        (int64_t)B * a.H0 * ((N + 127) / 128) < (1 << 22);
+  // The linear heads' launches take the windowed heads' passes along: the walks all four, the d = 128 scans
+  // three behind a launch for the statistics.
+  const bool together = (segments || (d == 128 && a.causal && (int64_t)B * H < (1 << 20))) && a.H0 > 0 && a.H0 < a.H &&
+                        !p->overlap && (int64_t)B * a.H0 * ((N + 127) / 128) < (1 << 21);
   auto launch_linear = [&](hipStream_t on) {
     if (segments) {
       a.ws_state = reinterpret_cast<float*>(static_cast<char*>(workspace) + bwd_stats_bytes(B, H, N));
@@ -786,7 +788,7 @@ gf_status gformer_attn_bwd(const void* q, const void* k, const void* v, const vo
       a.lin_segments = segs.count;
       return launch_linear_backward_segments(a, together, on);
     }
-    return a.causal ? launch_linear_backward_mfma(a, on) : launch_linear_backward_bidir_mfma(a, on);
+    return a.causal ? launch_linear_backward_mfma(a, together, on) : launch_linear_backward_bidir_mfma(a, on);
   };
   hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
   const bool bf16 = p->dtype == GF_BF16;
@@ -825,7 +827,7 @@ gf_status gformer_attn_bwd(const void* q, const void* k, const void* v, const vo
         if (e == hipSuccess) e = f;
       }
     } else if (e == hipSuccess) {
-      if (!together) e = launch_windowed_backward_mfma(a, stream);
+      if (!together || !segments) e = launch_windowed_backward_mfma(a, stream, together);
       if (e == hipSuccess) e = launch_linear(stream);
     }
   } else if (a.causal) {

@@ -1,6 +1,6 @@
 // One workgroup's work of a pass over the windowed heads' band (backward_mfma.hip describes the passes), as
 // a device function: the kernels of its own run it, and so do the blocks behind the linear heads' in the
-// launches that hold both (backward_linear_segments.hip).
+// launches that hold both (backward_linear_segments.hip, backward_linear_mfma.hip).
 #pragma once
 
 #include "common.hpp"
@@ -9,10 +9,10 @@
 namespace gformer {
 namespace {
 
-constexpr int BR = 128;              // resident rows per workgroup (4 waves of 32)
 constexpr int BC = 64;               // streamed rows per tile
 constexpr int WR = 32;               // resident rows per wave
-constexpr int kBandThreads = 256;
+constexpr int kBandThreads = 256;    // a workgroup of a launch of its own
+constexpr int band_rows(int threads) { return threads / 64 * WR; }   // resident rows per workgroup
 constexpr float kBandLog2e = 1.4426950408889634f;
 
 enum BandPass { kStats = 0, kDq = 1, kDv = 2, kDk = 3 };
@@ -31,11 +31,12 @@ template <int D> struct BandSmem {
   BandTiles<D> buf[2];
 };
 
-template <int D, int PASS>
+template <int D, int PASS, int NT = kBandThreads>
 __device__ __forceinline__ void windowed_band(const BwdArgs& a, int block, unsigned char* smem_raw) {
+  constexpr int BR = band_rows(NT);
   constexpr int KS = D / 16;
   constexpr int MT = D / 32;
-  constexpr int KCH = BC * D / 8 / kBandThreads;
+  constexpr int KCH = BC * D / 8 / NT;
   constexpr bool RES_Q = PASS == kStats || PASS == kDq;   // resident rows are queries
   constexpr bool HAS_DP = PASS != kDv;
   using Smem = BandSmem<D>;
@@ -113,7 +114,7 @@ __device__ __forceinline__ void windowed_band(const BwdArgs& a, int block, unsig
   const float sc = (a.scale == 0.f ? 1e-30f : a.scale) * kBandLog2e;
 
   // global -> register -> LDS staging of a tile, as in the forward kernel
-  constexpr int C8 = D / 8, RP = kBandThreads / C8;
+  constexpr int C8 = D / 8, RP = NT / C8;
   static_assert(KCH * RP == BC, "tile rows must be covered exactly");
   const int prow = tid / C8, pcol = 8 * (tid % C8);
   const int xsn = (int)str1_t.sn, ysn = (int)str2_t.sn;
@@ -297,10 +298,10 @@ __device__ __forceinline__ void windowed_band(const BwdArgs& a, int block, unsig
     void* base = (PASS == kDq) ? a.dq : (PASS == kDv) ? a.dv : a.dk;
     const TensorView& like = (PASS == kDq) ? a.q : (PASS == kDv) ? a.v : a.k;
     uint16_t* outp = reinterpret_cast<uint16_t*>(base) + b * like.sb + h * like.sh;
-    constexpr int OPIECES = BR * (D / 8) / kBandThreads;
+    constexpr int OPIECES = BR * (D / 8) / NT;
 #pragma unroll
     for (int i = 0; i < OPIECES; ++i) {
-      const int c = tid + i * kBandThreads;
+      const int c = tid + i * NT;
       const int row = c / (D / 8), col = 8 * (c % (D / 8));
       if (i0 + row < N) {
         const u32x4 o = *reinterpret_cast<const u32x4*>(ot + row * OROW + col);

@@ -11,6 +11,7 @@
 //   forward scan:  num = S v + fq A,  den = rowsum(S) + fq.Z + eps,  c = rowdot(dO, num) / den^2,
 //                  dfq = T' fk + g A^T - c Z^T;           then A += fk^T v, Z += colsum(fk)
 //   reverse scan:  dfk = T'^T fq + v B^T - 1 Y^T,  dv = S^T g + fk B;   then B += fq^T g, Y += fq^T c
+// These are the kernels of d = 128, and of d = 64 where the workspace holds no segment sums.
 // One workgroup per (batch, head), segment and scan: with fewer heads than compute units a head
 // is cut into up to four segments, and a workgroup first sums the chunks in front of (behind)
 // its segment in light rounds (the update of the carried sums alone) before it scans the segment.
@@ -20,6 +21,7 @@
 // tokens); the carried d x d sum lives in fp32 accumulators spread over the waves, with a bf16
 // copy in LDS as the operand of the next chunk's products; Z, Y, den and c stay in fp32.
 // The forward scan leaves (den_i, c_i) in the workspace for the reverse scan.
+#include "backward_band.hpp"
 #include "backward_linear_common.hpp"
 
 namespace gformer {
@@ -59,22 +61,21 @@ static_assert(sizeof(LbSmemKv<128>) <= 160 * 1024 && sizeof(LbSmem<128>) <= 160 
               "one workgroup's tiles must fit the LDS of a compute unit");
 
 // ---------------------------------------------------------------------------------------
-// forward scan: dq, and (den_i, c_i) into the workspace.  grid = (H - H0, B)
+// forward scan: dq, and (den_i, c_i) into the workspace
 // ---------------------------------------------------------------------------------------
 template <int D, bool ELU1>
-__global__ __launch_bounds__(LbCfg<D>::NT, 1) void linear_bwd_q_mfma_kernel(BwdArgs a) {
+__device__ __forceinline__ void scan_q(const BwdArgs& a, int block, unsigned char* smem_raw) {
   using C = LbCfg<D>;
   constexpr int MT = C::MT, KS = C::KS, NW = C::NW, NT = C::NT, R = C::R, TPW = C::TPW, PCS = C::PCS;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   LbSmem<D>& sm = *reinterpret_cast<LbSmem<D>*>(smem_raw);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ln = lane & 31, lh = lane >> 5;
-  const int h = a.H0 + blockIdx.x, b = blockIdx.y;
+  const int H1 = a.H - a.H0, h = a.H0 + block % H1, b = block / H1 % a.B, seg = block / (H1 * a.B);
   const HeadCtx<D> hc = head_ctx<D>(a, b, h);
   uint16_t* dqp = reinterpret_cast<uint16_t*>(a.dq) + b * a.q.sb + h * a.q.sh;
   const int N = a.N;
   // this workgroup writes the chunks [cb, ce) of its head; the chunks in front of them are only
   // summed (light rounds: the state update alone)
-  const int cb = a.lin_bounds[blockIdx.z], ce = a.lin_bounds[blockIdx.z + 1];
+  const int cb = a.lin_bounds[seg], ce = a.lin_bounds[seg + 1];
   if (cb >= ce) return;
   const int trl = lds_operand_tr_lane_offset(R, lane) + 8 * lh * R;
 
@@ -429,22 +430,21 @@ __global__ __launch_bounds__(LbCfg<D>::NT, 1) void linear_bwd_q_mfma_kernel(BwdA
 }
 
 // ---------------------------------------------------------------------------------------
-// reverse scan: dk, dv from (den_i, c_i) of the workspace.  grid = (H - H0, B)
+// reverse scan: dk, dv from (den_i, c_i) of the workspace
 // ---------------------------------------------------------------------------------------
 template <int D, bool ELU1>
-__global__ __launch_bounds__(LbCfg<D>::NT, 1) void linear_bwd_kv_mfma_kernel(BwdArgs a) {
+__device__ __forceinline__ void scan_kv(const BwdArgs& a, int block, unsigned char* smem_raw) {
   using C = LbCfg<D>;
   constexpr int MT = C::MT, KS = C::KS, NW = C::NW, NT = C::NT, R = C::R, TPW = C::TPW, PCS = C::PCS;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   LbSmemKv<D>& sm = *reinterpret_cast<LbSmemKv<D>*>(smem_raw);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ln = lane & 31, lh = lane >> 5;
-  const int h = a.H0 + blockIdx.x, b = blockIdx.y;
+  const int H1 = a.H - a.H0, h = a.H0 + block % H1, b = block / H1 % a.B, seg = block / (H1 * a.B);
   const HeadCtx<D> hc = head_ctx<D>(a, b, h);
   uint16_t* dkp = reinterpret_cast<uint16_t*>(a.dk) + b * a.k.sb + h * a.k.sh;
   uint16_t* dvp = reinterpret_cast<uint16_t*>(a.dv) + b * a.v.sb + h * a.v.sh;
   const int N = a.N, nchunks = (N + CH - 1) / CH;
   // this workgroup writes the chunks [cb, ce) of its head; the chunks behind them are only summed
-  const int cb = nchunks - a.lin_bounds[blockIdx.z + 1], ce = nchunks - a.lin_bounds[blockIdx.z];
+  const int cb = nchunks - a.lin_bounds[seg + 1], ce = nchunks - a.lin_bounds[seg];
   if (cb >= ce) return;
   const int trl = lds_operand_tr_lane_offset(R, lane) + 8 * lh * R;
   constexpr int RS = LbSmemKv<D>::RS, RD = LbSmemKv<D>::RD;   // strides of the carried-sum copy and of dO
@@ -742,24 +742,54 @@ __global__ __launch_bounds__(LbCfg<D>::NT, 1) void linear_bwd_kv_mfma_kernel(Bwd
   }
 }
 
-template <int D, bool ELU1> hipError_t launch_lin_bwd_t(const BwdArgs& a, hipStream_t s) {
-  const dim3 grid(a.H - a.H0, a.B, a.lin_segments), block(LbCfg<D>::NT);
-  const int smem = (int)sizeof(LbSmem<D>), smem_kv = (int)sizeof(LbSmemKv<D>);
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(linear_bwd_q_mfma_kernel<D, ELU1>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-  if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute(reinterpret_cast<const void*>(linear_bwd_kv_mfma_kernel<D, ELU1>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, smem_kv);
-  if (e != hipSuccess) return e;
-  linear_bwd_q_mfma_kernel<D, ELU1><<<grid, block, smem, s>>>(a);
-  linear_bwd_kv_mfma_kernel<D, ELU1><<<grid, block, smem_kv, s>>>(a);
-  return hipGetLastError();
+// ---- launches --------------------------------------------------------------------------------------
+// A scan, and behind it in the same launch passes over the windowed heads' band: blocks [0, linear) scan,
+// the `rows` blocks from the next multiple of 8 on (the XCDs keep their runs) are dq's in the forward scan's
+// launch and dk's in the reverse scan's, and behind those in the forward scan's come dv's.
+// A scan is one workgroup per compute unit and rarely as many of them as there are units, the band's passes are
+// many short workgroups: they run on the units the scans leave, and behind the scans that end first.  A band
+// workgroup takes the scans' eight waves (256 resident rows, the same bits as 128).  Measured, all passes apart
+// and together (us): 4 x (6 + 26 heads) x 8192 tokens, window 256: 1155 and 1091; 8 x (6 + 42) x 2048, 128: 888
+// and 796; 1 x (28 + 4) x 4096, 256: 460 and 332; 16 x (30 + 10) x 1024, 128: 723 and 706; 1 x (1 + 1) x 300,
+// 64: 98 and 70.  Two separate bands of 128 rows in a workgroup: the same times, and 726 for the fourth.
+template <int D, bool ELU1, bool REVERSE>
+__global__ __launch_bounds__(LbCfg<D>::NT, 1) void linear_bwd_scan_kernel(BwdArgs a, int linear, int rows) {
+  constexpr int NT = LbCfg<D>::NT;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  // a launch without a band is (heads, batch, segments) large, one with it is one row of blocks
+  const int block = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+  const int first = (linear + 7) & ~7, second = first + ((rows + 7) & ~7);
+  if (block < linear) {
+    if constexpr (REVERSE) scan_kv<D, ELU1>(a, block, smem_raw);
+    else scan_q<D, ELU1>(a, block, smem_raw);
+  } else if constexpr (D == 128) {
+    if (block < first) return;
+    if (block < first + rows) windowed_band<D, REVERSE ? kDk : kDq, NT>(a, block - first, smem_raw);
+    else if (!REVERSE && block >= second) windowed_band<D, kDv, NT>(a, block - second, smem_raw);
+  }
+}
+
+template <int D, bool ELU1> hipError_t launch_lin_bwd_t(const BwdArgs& a, bool band, hipStream_t s) {
+  constexpr int NT = LbCfg<D>::NT, BR = band_rows(NT);
+  const int linear = (a.H - a.H0) * a.B * a.lin_segments, first = (linear + 7) & ~7;
+  const int rows = band ? (a.N + BR - 1) / BR * a.H0 * a.B : 0;
+  hipError_t e = hipSuccess;
+  auto launch = [&](auto kern, size_t smem, int blocks) {
+    if (e != hipSuccess) return;
+    static_assert(D == 64 || (sizeof(BandSmem<D>) <= sizeof(LbSmem<D>) && sizeof(BandSmem<D>) <= sizeof(LbSmemKv<D>)),
+                  "the band's tiles fit the scans' LDS");
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e == hipSuccess) kern<<<rows > 0 ? dim3(blocks) : dim3(a.H - a.H0, a.B, a.lin_segments), dim3(NT), smem, s>>>(a, linear, rows);
+  };
+  launch(linear_bwd_scan_kernel<D, ELU1, false>, sizeof(LbSmem<D>), first + ((rows + 7) & ~7) + rows);
+  launch(linear_bwd_scan_kernel<D, ELU1, true>, sizeof(LbSmemKv<D>), first + rows);
+  return e != hipSuccess ? e : hipGetLastError();
 }
 
 }  // namespace
 
 // Linear heads [H0, H) of a bf16 call; the workspace receives (den_i, c_i) per token.
-hipError_t launch_linear_backward_mfma(const BwdArgs& args, hipStream_t s) {
+hipError_t launch_linear_backward_mfma(const BwdArgs& args, bool with_windowed, hipStream_t s) {
   if (args.H - args.H0 <= 0 || args.N <= 0 || args.B <= 0) return hipSuccess;
   // A head is one sequential scan.  With fewer heads than compute units each head is cut into
   // segments, one workgroup per segment: it first sums the chunks in front of (behind) its
@@ -783,8 +813,8 @@ hipError_t launch_linear_backward_mfma(const BwdArgs& args, hipStream_t s) {
     }
   }
   const bool elu1 = a.phi == 0;
-  if (a.d == 64) return elu1 ? launch_lin_bwd_t<64, true>(a, s) : launch_lin_bwd_t<64, false>(a, s);
-  return elu1 ? launch_lin_bwd_t<128, true>(a, s) : launch_lin_bwd_t<128, false>(a, s);
+  if (a.d == 64) return elu1 ? launch_lin_bwd_t<64, true>(a, false, s) : launch_lin_bwd_t<64, false>(a, false, s);
+  return elu1 ? launch_lin_bwd_t<128, true>(a, with_windowed, s) : launch_lin_bwd_t<128, false>(a, with_windowed, s);
 }
 
 }  // namespace gformer

@@ -693,7 +693,7 @@ __global__ __launch_bounds__(SegCfg<D>::NT, 3) void linear_seg_kernel(BwdArgs a,
 template <int D, bool ELU1, bool CAUSAL> hipError_t launch_t(const BwdArgs& a, bool band, hipStream_t s) {
   using C = SegCfg<D>;
   const int heads = a.B * (a.H - a.H0), nseg = a.lin_segments, per_head = CAUSAL ? nseg - 1 : nseg;
-  const int rows = band ? (a.N + BR - 1) / BR * a.H0 * a.B : 0;   // the band's blocks
+  const int rows = band ? (a.N + band_rows(C::NT) - 1) / band_rows(C::NT) * a.H0 * a.B : 0;   // the band's blocks
   float* bsums = a.ws_state + (int64_t)heads * nseg * C::STATE;
   hipError_t e = hipSuccess;
   auto launch = [&](auto kern, size_t smem, int linear, int band_blocks) {

@@ -32,7 +32,8 @@ __global__ __launch_bounds__(kBandThreads, 2) void windowed_bwd_band_kernel(BwdA
   windowed_band<D, PASS>(a, blockIdx.x, smem_raw);
 }
 
-template <int D> hipError_t launch_windowed_bwd_t(const BwdArgs& a, hipStream_t s) {
+template <int D> hipError_t launch_windowed_bwd_t(const BwdArgs& a, bool statistics_only, hipStream_t s) {
+  constexpr int BR = band_rows(kBandThreads);
   const dim3 grid(((a.N + BR - 1) / BR) * a.H0 * a.B), block(kBandThreads);
   const int smem = (int)sizeof(BandSmem<D>);
   hipError_t e = hipSuccess;
@@ -43,6 +44,7 @@ template <int D> hipError_t launch_windowed_bwd_t(const BwdArgs& a, hipStream_t 
     if (e == hipSuccess) kern<<<grid, block, smem, s>>>(a);
   };
   launch(windowed_bwd_band_kernel<D, kStats>);
+  if (statistics_only) return e != hipSuccess ? e : hipGetLastError();
   launch(windowed_bwd_band_kernel<D, kDq>);
   launch(windowed_bwd_band_kernel<D, kDv>);
   launch(windowed_bwd_band_kernel<D, kDk>);
@@ -52,9 +54,9 @@ template <int D> hipError_t launch_windowed_bwd_t(const BwdArgs& a, hipStream_t 
 }  // namespace
 
 // Windowed heads [0, H0) of a bf16 call; the workspace receives (log2-sum-exp, D_i) per query.
-hipError_t launch_windowed_backward_mfma(const BwdArgs& a, hipStream_t s) {
+hipError_t launch_windowed_backward_mfma(const BwdArgs& a, hipStream_t s, bool statistics_only) {
   if (a.H0 <= 0 || a.N <= 0 || a.B <= 0) return hipSuccess;
-  return a.d == 64 ? launch_windowed_bwd_t<64>(a, s) : launch_windowed_bwd_t<128>(a, s);
+  return a.d == 64 ? launch_windowed_bwd_t<64>(a, statistics_only, s) : launch_windowed_bwd_t<128>(a, statistics_only, s);
 }
 
 }  // namespace gformer

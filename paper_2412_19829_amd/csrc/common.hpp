@@ -121,8 +121,10 @@ struct BwdArgs {
 hipError_t launch_backward_scalar(const BwdArgs& a, bool bf16, bool windowed_heads, bool linear_heads,
                                   hipStream_t s);
 // bf16 matrix-core kernels for the windowed heads and for the linear heads
-hipError_t launch_windowed_backward_mfma(const BwdArgs& a, hipStream_t s);
-hipError_t launch_linear_backward_mfma(const BwdArgs& a, hipStream_t s);
+hipError_t launch_windowed_backward_mfma(const BwdArgs& a, hipStream_t s, bool statistics_only = false);
+// with_windowed (d = 128): the windowed heads' dq, dk and dv passes ride in the scans' launches; their
+// statistics have to be there.
+hipError_t launch_linear_backward_mfma(const BwdArgs& a, bool with_windowed, hipStream_t s);
 // bidirectional linear heads: plain-FMA kernels on either storage type, matrix-core kernels (bf16)
 hipError_t launch_linear_backward_bidir(const BwdArgs& a, bool bf16, hipStream_t s);
 hipError_t launch_linear_backward_bidir_mfma(const BwdArgs& a, hipStream_t s);
