@@ -264,23 +264,35 @@ __global__ __launch_bounds__(256) void linear_prefix_kernel(float* ws, int n_hea
   const int head = blockIdx.y;
   if (x >= state_floats || head >= n_heads) return;
   const int64_t g_lo = (int64_t)head * vcph, g_hi = g_lo + vcph;
+  // in slot order with eight loads in flight: one load and one addition after the other is what bounds it
+  // (forward, 1 x (6 + 26) heads x 32768 x 128: 343.6 -> 341.1 us a call; same bits)
+  auto walk = [&](int64_t j0, int64_t j1, auto&& at) {
+    constexpr int G = 8;
+    for (; j0 < j1; j0 += G) {
+      float v[G];
+#pragma unroll
+      for (int i = 0; i < G; ++i) v[i] = ws[min(j0 + i, j1 - 1) * state_floats + x];
+#pragma unroll
+      for (int i = 0; i < G; ++i)
+        if (j0 + i < j1) at(ws + (j0 + i) * state_floats + x, v[i]);
+    }
+  };
   if (!causal) {
     // bidirectional: the head's first slot receives the sum of all its slots
     const int64_t j0 = g_lo / sub_chunks, j1 = g_hi / sub_chunks;
     float tot = 0.f;
-    for (int64_t j = j0; j < j1; ++j) tot += ws[j * state_floats + x];
+    walk(j0, j1, [&](float* p, float v) { tot += v; });
     ws[j0 * state_floats + x] = tot;
     return;
   }
-  const int64_t total = (int64_t)n_sub * sub_chunks;
+  // slots up to the last at which a read-out piece of this head may start: pieces start every
+  // state_sub slots
+  const int64_t limit = min(g_hi, (int64_t)n_sub * sub_chunks), step = (int64_t)state_sub * sub_chunks;
   float run = 0.f;
-  for (int64_t j = g_lo / sub_chunks + 1; j < n_sub && j * sub_chunks < g_hi; ++j) {
-    const int64_t next_main = (j + state_sub - 1) / state_sub * state_sub * sub_chunks;
-    if (next_main >= g_hi || next_main >= total) break;
-    float* p = ws + j * state_floats + x;
-    run += *p;
+  walk(g_lo / sub_chunks + 1, min((int64_t)n_sub, (limit - 1) / step * state_sub + 1), [&](float* p, float v) {
+    run += v;
     *p = run;
-  }
+  });
 }
 
 // -----------------------------------------------------------------------------------------
