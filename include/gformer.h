@@ -72,8 +72,9 @@ typedef enum { GF_PHI_ELU1 = 0, GF_PHI_IDENTITY = 1 } gf_phi;
 
 /* Which implementation runs.  GF_IMPL_AUTO picks the bf16 matrix-core kernels for bf16 and the
  * single-precision matrix-core kernels (fp32 operands, fp32 accumulation) for fp32; a plan reports
- * the latter as GF_IMPL_SCALAR, as nothing is rounded below fp32.  GF_IMPL_SCALAR forces the plain-FMA kernels (fp32 arithmetic on
- * either storage type); GF_IMPL_MFMA with GF_F32 is GF_ERR_UNSUPPORTED.
+ * the latter as GF_IMPL_SCALAR, as nothing is rounded below fp32.  GF_IMPL_SCALAR forces the
+ * plain-FMA kernels (fp32 arithmetic on either storage type); GF_IMPL_MFMA with GF_F32 is
+ * GF_ERR_UNSUPPORTED.
  * GF_IMPL_MFMA runs the windowed heads by one of two kernels with the same results: a streaming
  * kernel (windows of at most 257 tokens; chosen when the call has at least 1024 blocks of 128
  * queries over all windowed heads) or a kernel that gives each workgroup one block of 128
@@ -244,17 +245,17 @@ gf_status gformer_attn_prefill(const void* q, const void* k, const void* v, void
  *   workspace : device, gformer_attn_bwd_workspace_bytes bytes, 256-byte aligned: 8 bytes per
  *             token and head (per-row softmax statistics / denominators), rounded up to 256,
  *             plus, for a bidirectional call, eight (d*d + d) fp32 sums per linear head.  A GF_F32
- *             call (GF_IMPL_AUTO) and a causal GF_BF16 call with d = 64 ask for two such sums per
+ *             call (GF_IMPL_AUTO) and a GF_BF16 call with d = 64 ask for two such sums per
  *             segment of every linear head, and run, slower, on anything down to the size above
  * Kernels: a bf16 call runs on the matrix cores (params.impl GF_IMPL_AUTO or GF_IMPL_MFMA: bf16
  * products, fp32 accumulation, softmax statistics, denominators and carried sums in fp32; the
  * two operands of the linear heads whose rounding would cost more than the bf16 mode's 2e-2 per
  * row, T' and the in-chunk weights of the numerator, travel as bf16 pairs);
  * an fp32 call (GF_IMPL_AUTO) on the matrix cores in single precision; GF_IMPL_SCALAR on plain-FMA
- * kernels (fp32 arithmetic on either storage type).  The linear heads of a bidirectional call take three sweeps over each head (the
- * sums over all keys, dq with the sums over all queries, dk and dv), on the matrix cores for a
- * bf16 call, with the d x d sums and dO / den as bf16 pairs where a difference of nearly equal
- * terms depends on them.  GF_IMPL_MFMA with fp32 storage, GF_IMPL_MFMA_BLOCKED, GF_IMPL_MFMA_STREAM and
+ * kernels (fp32 arithmetic on either storage type).  The linear heads of a bidirectional call
+ * take three sweeps over each head (the sums over all keys, dq with the sums over all queries, dk
+ * and dv), a bf16 call with the d x d sums and dO / den as bf16 pairs where a difference of nearly
+ * equal terms depends on them.  GF_IMPL_MFMA with fp32 storage, GF_IMPL_MFMA_BLOCKED, GF_IMPL_MFMA_STREAM and
  * GF_IMPL_MFMA_CHUNK are GF_ERR_UNSUPPORTED.  params.launch_mask must be 0; segment_len and chunk
  * are ignored.  params.overlap = 1 (matrix-core kernels, both head groups present): the windowed
  * heads' passes run on the library's side stream beside the linear heads' scans, which leave

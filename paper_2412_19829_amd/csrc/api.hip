@@ -250,7 +250,7 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
   const int H0 = p->n_sparse_heads, H1 = H - H0;
   const long heads_lin = (long)B * H1;
   if (impl == GF_IMPL_SCALAR) {
-    pl.chunk = 32;  // fixed by the fp32 kernel
+    pl.chunk = 32;  // fixed by the fp32 kernels
     pl.segment_len = N;
     pl.n_segments = (H1 > 0 && N > 0) ? (int)heads_lin : 0;  // one workgroup walks a whole head
     if (p->segment_len != 0 && p->segment_len < N) return GF_ERR_UNSUPPORTED;
@@ -723,9 +723,8 @@ gf_status gformer_attn_bwd(const void* q, const void* k, const void* v, const vo
                            void* hip_stream) {
   if (!p) return GF_ERR_INVALID_ARG;
   if (p->struct_size != sizeof(gformer_params)) return GF_ERR_INVALID_ARG;
-  // a bf16 call runs on the matrix-core kernels (AUTO, MFMA) unless SCALAR asks for the plain-FMA
-  // kernels, which are also the fp32 path and, on either storage type, the linear heads of the
-  // bidirectional layer.
+  // a call runs on the matrix-core kernels (bf16: AUTO, MFMA; fp32: AUTO) unless SCALAR asks for the
+  // plain-FMA kernels
   if (p->impl == GF_IMPL_MFMA_BLOCKED || p->impl == GF_IMPL_MFMA_STREAM ||
       p->impl == GF_IMPL_MFMA_CHUNK)
     return GF_ERR_UNSUPPORTED;

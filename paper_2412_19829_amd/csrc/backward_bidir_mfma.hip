@@ -1,5 +1,6 @@
 // Backward pass of the bidirectional linear heads on bf16 matrix cores (section II-B's ratio over
-// all keys, differentiated; formulas at the top of backward_bidir_scalar.hip).
+// all keys, differentiated; formulas at the top of backward_bidir_scalar.hip).  These are the kernels of
+// d = 128, and of d = 64 where the workspace holds no segment sums.
 //
 // With fq = phi(q), fk = phi(k), S = sum_j fk_j v_j^T, z = sum_j fk_j, den_i = fq_i.z + eps,
 // g_i = dO_i / den_i, r_i = S g_i, c_i = fq_i.r_i / den_i:
