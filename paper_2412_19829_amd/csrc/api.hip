@@ -486,13 +486,14 @@ gf_status attn_forward(const void* q, const void* k, const void* v, void* out, v
   const bool bf16 = p->dtype == GF_BF16;
   hipError_t e = hipSuccess;
   if (r.f32) {
-    if (mask & GF_LAUNCH_WINDOWED) e = launch_windowed_f32(a, s);
-    if ((mask & GF_LAUNCH_LINEAR_MAIN) && e == hipSuccess) {
-      // the sums over all keys need a slot per head: the plain-FMA kernel keeps its own
-      const uint64_t one = (uint64_t)B * (H - a.H0) * ((uint64_t)d * d + d) * sizeof(float);
-      e = !a.causal && workspace_bytes < one ? launch_linear_scalar(a, bf16, s)
-                                             : launch_linear_f32(a, true, true, s);
-    }
+    // the sums over all keys need a slot per head: the plain-FMA kernel keeps its own
+    const uint64_t one = (uint64_t)B * (H - a.H0) * ((uint64_t)d * d + d) * sizeof(float);
+    const bool plain = !a.causal && workspace_bytes < one;
+    const bool together = (mask & GF_LAUNCH_WINDOWED) && (mask & GF_LAUNCH_LINEAR_MAIN) && !plain &&
+                          f32_takes_windowed(d, B, H, a.H0, N);
+    if ((mask & GF_LAUNCH_WINDOWED) && !together) e = launch_windowed_f32(a, s);
+    if ((mask & GF_LAUNCH_LINEAR_MAIN) && e == hipSuccess)
+      e = plain ? launch_linear_scalar(a, bf16, s) : launch_linear_f32(a, true, true, together, s);
   } else if (r.plan.impl == GF_IMPL_SCALAR) {
     if ((mask & GF_LAUNCH_WINDOWED) && e == hipSuccess) e = launch_windowed_scalar(a, bf16, s);
     if ((mask & GF_LAUNCH_LINEAR_MAIN) && e == hipSuccess) e = launch_linear_scalar(a, bf16, s);
@@ -799,8 +800,9 @@ gf_status gformer_attn_bwd(const void* q, const void* k, const void* v, const vo
     const Segments f = f32_segments(heads, N, d, workspace_bytes - bwd_stats_bytes(B, H, N), 2);
     a.f32_seg_len = f.len;
     a.f32_nseg = f.count;
-    e = launch_windowed_backward_f32(a, stream);
-    if (e == hipSuccess) e = launch_linear_backward_f32(a, stream);
+    const bool f32_together = !p->overlap && f32_takes_windowed(d, B, H, a.H0, N);
+    if (!f32_together) e = launch_windowed_backward_f32(a, stream);
+    if (e == hipSuccess) e = launch_linear_backward_f32(a, f32_together, stream);
   } else if (mfma) {
     // The linear scans are one workgroup per head and segment: with fewer of those than compute
     // units the rest of the chip is idle for their whole duration.  With overlap = 1 the windowed

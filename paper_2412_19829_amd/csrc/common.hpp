@@ -193,9 +193,11 @@ Segments f32_segments(int64_t heads, int N, int d, uint64_t bytes, int sums);
 hipError_t launch_segment_scan(float* sums, int heads, int nseg, int floats, int mode, hipStream_t s);
 int f32_window_rows(int64_t heads, int N);   // resident rows per workgroup of the windowed kernels
 hipError_t launch_windowed_f32(const AttnArgs& a, hipStream_t s);
-hipError_t launch_linear_f32(const AttnArgs& a, bool states, bool read, hipStream_t s);
+// with_windowed: the windowed heads' workgroups ride in the walks' launches, where f32_takes_windowed allows it
+bool f32_takes_windowed(int d, int B, int H, int H0, int N);
+hipError_t launch_linear_f32(const AttnArgs& a, bool states, bool read, bool with_windowed, hipStream_t s);
 hipError_t launch_windowed_backward_f32(const BwdArgs& a, hipStream_t s);
-hipError_t launch_linear_backward_f32(const BwdArgs& a, hipStream_t s);
+hipError_t launch_linear_backward_f32(const BwdArgs& a, bool with_windowed, hipStream_t s);
 // bf16 backward pass of the linear heads at d = 64, heads cut into segments (lin_segments of lin_segment_len
 // tokens); ws_state holds [2][B*(H-H0)][lin_segments][d*d + d] fp32 sums unless there is one causal segment.
 Segments backward_segments(int64_t heads, int N, int d, bool causal);

@@ -18,6 +18,7 @@
 // Every sum lies in the workspace as A row-major [feature][value], then its vector.
 #include <type_traits>
 
+#include "f32_band.hpp"
 #include "f32_mfma.hpp"
 #include "scalar_util.hpp"
 #include "mfma.hpp"
@@ -267,14 +268,13 @@ template <int D> struct F32FwdSmem {
   float z[D];
 };
 template <int D, bool CAUSAL>
-__global__ __launch_bounds__(kLinThreads<D>, 2) void linear_f32_kernel(AttnArgs a) {
+__device__ __forceinline__ void linear_f32(const AttnArgs& a, int block, unsigned char* smem_raw) {
   constexpr int TR = kF32Row<D>;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   F32FwdSmem<D>& sm = *reinterpret_cast<F32FwdSmem<D>*>(smem_raw);
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, i = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int N = a.N, H1 = a.H - a.H0;
-  const int seg = blockIdx.x % a.f32_nseg, head = blockIdx.x / a.f32_nseg;
+  const int seg = block % a.f32_nseg, head = block / a.f32_nseg;
   const int b = head / H1, h = a.H0 + head % H1;
   const float* qp = reinterpret_cast<const float*>(a.q.base) + b * a.q.sb + h * a.q.sh;
   const float* kp = reinterpret_cast<const float*>(a.k.base) + b * a.k.sb + h * a.k.sh;
@@ -384,14 +384,13 @@ template <int D> struct F32BwdSmem {
   float red[2][D / 16][CH];          // per-wave parts of phi(q).r and phi(q).Z; c of the chunk
 };
 template <int D, bool CAUSAL>
-__global__ __launch_bounds__(kLinThreads<D>, 2) void linear_bwd_q_f32_kernel(BwdArgs a) {
+__device__ __forceinline__ void linear_bwd_q_f32(const BwdArgs& a, int block, unsigned char* smem_raw) {
   constexpr int TR = kF32Row<D>, NW = D / 16;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   F32BwdSmem<D>& sm = *reinterpret_cast<F32BwdSmem<D>*>(smem_raw);
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, i = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int N = a.N, H1 = a.H - a.H0;
-  const int seg = blockIdx.x % a.f32_nseg, head = blockIdx.x / a.f32_nseg;
+  const int seg = block % a.f32_nseg, head = block / a.f32_nseg;
   const int b = head / H1, h = a.H0 + head % H1;
   const float* qp = reinterpret_cast<const float*>(a.q.base) + b * a.q.sb + h * a.q.sh;
   const float* kp = reinterpret_cast<const float*>(a.k.base) + b * a.k.sb + h * a.k.sh;
@@ -548,15 +547,14 @@ __global__ __launch_bounds__(kLinThreads<D>, 2) void linear_bwd_q_f32_kernel(Bwd
 
 // ---- backward, reverse walk: dk and dv -----------------------------------------------------------
 template <int D, bool CAUSAL>
-__global__ __launch_bounds__(kLinThreads<D>, 2) void linear_bwd_kv_f32_kernel(BwdArgs a) {
+__device__ __forceinline__ void linear_bwd_kv_f32(const BwdArgs& a, int block, unsigned char* smem_raw) {
   constexpr int TR = kF32Row<D>, NW = D / 16;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   F32BwdSmem<D>& sm = *reinterpret_cast<F32BwdSmem<D>*>(smem_raw);
   float* cvec = &sm.red[0][0][0];   // c of the chunk's tokens
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, i = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int N = a.N, H1 = a.H - a.H0;
-  const int seg = blockIdx.x % a.f32_nseg, head = blockIdx.x / a.f32_nseg;
+  const int seg = block % a.f32_nseg, head = block / a.f32_nseg;
   const int b = head / H1, h = a.H0 + head % H1;
   const float* qp = reinterpret_cast<const float*>(a.q.base) + b * a.q.sb + h * a.q.sh;
   const float* kp = reinterpret_cast<const float*>(a.k.base) + b * a.k.sb + h * a.k.sh;
@@ -690,15 +688,45 @@ hipError_t launch_states(const TensorView& k, const TensorView& v, float* sums, 
 hipError_t launch_scan(float* sums, int heads, int nseg, int floats, int mode, hipStream_t s) {
   return nseg <= kSumInPlace ? hipSuccess : launch_segment_scan(sums, heads, nseg, floats, mode, s);
 }
-template <typename K, typename A>
-hipError_t launch_walk(K kern, const A& a, int blocks, int threads, int smem, hipStream_t s) {
-  const hipError_t e = allow_lds_f32(kern, smem);
-  if (e != hipSuccess) return e;
-  kern<<<dim3(blocks), dim3(threads), smem, s>>>(a);
-  return hipGetLastError();
+// A walk, and at d = 64 behind it in the same launch (from the next multiple of 8 on, so that the XCDs keep
+// their runs) the `band` workgroups of the windowed heads that go with it.  Same bits as apart.
+// Measured (a training step of 4 x (3 + 13 heads) x 2048 x 64, window 128, us): 319 apart, 294 together; read-out
+// 39 + 22 -> 58, dq 57 + 45 -> 98, dk and dv 64 + 35 -> 99, and three launches less.  The last keeps the windowed
+// heads' 194 registers, so two workgroups share a compute unit where the walk alone has three.
+enum Walk { kReadOut, kQWalk, kKvWalk };
+template <int D, bool CAUSAL, int WALK, typename Args>
+__global__ __launch_bounds__(kLinThreads<D>, 2) void linear_f32_walk_kernel(Args a, int linear, int band) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  const int block = blockIdx.x, first = (linear + 7) & ~7;
+  if (block < linear) {
+    if constexpr (WALK == kReadOut) linear_f32<D, CAUSAL>(a, block, smem_raw);
+    else if constexpr (WALK == kQWalk) linear_bwd_q_f32<D, CAUSAL>(a, block, smem_raw);
+    else linear_bwd_kv_f32<D, CAUSAL>(a, block, smem_raw);
+  } else if constexpr (D == 64) {
+    static_assert(kLinThreads<64> == kF32BandThreads, "one block size for both kinds of workgroup");
+    if (block < first || band == 0) return;
+    if constexpr (WALK == kReadOut) windowed_f32<D, 4>(a, block - first, smem_raw);
+    else if constexpr (WALK == kQWalk) windowed_bwd_q_f32<D, 4>(a, block - first, smem_raw);
+    else windowed_bwd_kv_f32<D, 4>(a, block - first, smem_raw);
+  }
+}
+template <int D, int WALK, typename A>
+hipError_t launch_walk(const A& a, int linear, int band, size_t smem, hipStream_t s) {
+  if (band > 0 && smem < sizeof(F32WinSmem<D>)) smem = sizeof(F32WinSmem<D>);
+  auto launch = [&](auto kern) {
+    const hipError_t e = allow_lds_f32(kern, (int)smem);
+    if (e != hipSuccess) return e;
+    kern<<<dim3(band > 0 ? ((linear + 7) & ~7) + band : linear), dim3(kLinThreads<D>), smem, s>>>(a, linear, band);
+    return hipGetLastError();
+  };
+  return a.causal ? launch(linear_f32_walk_kernel<D, true, WALK, A>) : launch(linear_f32_walk_kernel<D, false, WALK, A>);
+}
+// workgroups of the windowed heads that ride along
+template <int D, typename A> int band_blocks(const A& a, bool with_windowed) {
+  return with_windowed ? (a.N + 63) / 64 * a.H0 * a.B : 0;
 }
 
-template <int D> hipError_t forward(const AttnArgs& a, bool states, bool read, hipStream_t s) {
+template <int D> hipError_t forward(const AttnArgs& a, bool states, bool read, bool with_windowed, hipStream_t s) {
   const int H1 = a.H - a.H0, heads = a.B * H1, blocks = heads * a.f32_nseg;
   hipError_t e = hipSuccess;
   if (states) {
@@ -706,23 +734,19 @@ template <int D> hipError_t forward(const AttnArgs& a, bool states, bool read, h
     if (e == hipSuccess) e = launch_scan(a.ws_states, heads, a.f32_nseg, kLinState<D>, a.causal ? 0 : 2, s);
   }
   if (e != hipSuccess || !read) return e;
-  const int smem = (int)sizeof(F32FwdSmem<D>);
-  return a.causal ? launch_walk(linear_f32_kernel<D, true>, a, blocks, kLinThreads<D>, smem, s)
-                  : launch_walk(linear_f32_kernel<D, false>, a, blocks, kLinThreads<D>, smem, s);
+  return launch_walk<D, kReadOut>(a, blocks, band_blocks<D>(a, with_windowed), sizeof(F32FwdSmem<D>), s);
 }
-template <int D> hipError_t backward(const BwdArgs& a, hipStream_t s) {
+template <int D> hipError_t backward(const BwdArgs& a, bool with_windowed, hipStream_t s) {
   const int H1 = a.H - a.H0, heads = a.B * H1, blocks = heads * a.f32_nseg;
-  const int smem = (int)sizeof(F32BwdSmem<D>);
+  const int band = band_blocks<D>(a, with_windowed);
   float* bsums = a.ws_state + (int64_t)heads * a.f32_nseg * kLinState<D>;
   hipError_t e = launch_states<D>(a.k, a.v, a.ws_state, a.B, a.H0, H1, a.N, a.phi, a.f32_seg_len, a.f32_nseg, a.causal, s);
   if (e == hipSuccess) e = launch_scan(a.ws_state, heads, a.f32_nseg, kLinState<D>, a.causal ? 0 : 2, s);
   if (e == hipSuccess)
-    e = a.causal ? launch_walk(linear_bwd_q_f32_kernel<D, true>, a, blocks, kLinThreads<D>, smem, s)
-                 : launch_walk(linear_bwd_q_f32_kernel<D, false>, a, blocks, kLinThreads<D>, smem, s);
+    e = launch_walk<D, kQWalk>(a, blocks, band, sizeof(F32BwdSmem<D>), s);
   if (e == hipSuccess) e = launch_scan(bsums, heads, a.f32_nseg, kLinState<D>, a.causal ? 1 : 2, s);
   if (e == hipSuccess)
-    e = a.causal ? launch_walk(linear_bwd_kv_f32_kernel<D, true>, a, blocks, kLinThreads<D>, smem, s)
-                 : launch_walk(linear_bwd_kv_f32_kernel<D, false>, a, blocks, kLinThreads<D>, smem, s);
+    e = launch_walk<D, kKvWalk>(a, blocks, band, sizeof(F32BwdSmem<D>), s);
   return e;
 }
 
@@ -751,13 +775,18 @@ hipError_t launch_segment_scan(float* sums, int heads, int nseg, int floats, int
   return hipGetLastError();
 }
 
-hipError_t launch_linear_f32(const AttnArgs& a, bool states, bool read, hipStream_t s) {
-  if (a.H - a.H0 <= 0 || a.N <= 0 || a.B <= 0) return hipSuccess;
-  return a.d == 64 ? forward<64>(a, states, read, s) : forward<128>(a, states, read, s);
+bool f32_takes_windowed(int d, int B, int H, int H0, int N) {
+  return d == 64 && H0 > 0 && H0 < H && N > 0 && B > 0 && f32_window_rows((int64_t)B * H0, N) == 64 &&
+         (int64_t)B * H0 * ((N + 63) / 64) < (1 << 22) && (int64_t)B * (H - H0) < (1 << 20);
 }
-hipError_t launch_linear_backward_f32(const BwdArgs& a, hipStream_t s) {
+
+hipError_t launch_linear_f32(const AttnArgs& a, bool states, bool read, bool with_windowed, hipStream_t s) {
   if (a.H - a.H0 <= 0 || a.N <= 0 || a.B <= 0) return hipSuccess;
-  return a.d == 64 ? backward<64>(a, s) : backward<128>(a, s);
+  return a.d == 64 ? forward<64>(a, states, read, with_windowed, s) : forward<128>(a, states, read, false, s);
+}
+hipError_t launch_linear_backward_f32(const BwdArgs& a, bool with_windowed, hipStream_t s) {
+  if (a.H - a.H0 <= 0 || a.N <= 0 || a.B <= 0) return hipSuccess;
+  return a.d == 64 ? backward<64>(a, with_windowed, s) : backward<128>(a, false, s);
 }
 
 }  // namespace gformer
