@@ -355,11 +355,12 @@ __device__ __forceinline__ void linear_f32(const AttnArgs& a, int block, unsigne
     }
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb) {
-      const float inv = 1.f / (sum_over_groups(den[tb]) + a.eps);
+      // divided, not times the reciprocal: that is infinite below 2.9e-39 (features of small products)
+      const float dt = sum_over_groups(den[tb]) + a.eps;
       const int n = t0 + 16 * tb + i;
       if (STEADY || n < N)
         *reinterpret_cast<f32x4*>(op + (int64_t)n * a.osn + 16 * wave + 4 * g) =
-            num[tb] * inv;
+            num[tb] / dt;
     }
     if (CAUSAL) {
       add_outer<D>(s, sm.fk, vc, g, i);
