@@ -385,12 +385,17 @@ __device__ __forceinline__ void linear_f32(const AttnArgs& a, int block, unsigne
     }
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb) {
-      // divided, not times the reciprocal: that is infinite below 2.9e-39 (features of small products)
+      // the reciprocal of den without its power of two, 2^e: below 2.9e-39 den has none (features of small
+      // products).  Eight divisions a lane instead: 72.4 against 69.9 us on 64 heads x 2048 x 64.
       const float dt = sum_over_groups(den[tb]) + a.eps;
+      const int e = __builtin_amdgcn_frexp_expf(dt) - 1;   // -1 for 0 and infinity, whose reciprocals stay theirs
+      const float inv = 1.f / __builtin_amdgcn_ldexpf(dt, -e);
+      f32x4 o;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) o[j] = __builtin_amdgcn_ldexpf(num[tb][j] * inv, -e);
       const int n = t0 + 16 * tb + i;
       if (STEADY || n < N)
-        *reinterpret_cast<f32x4*>(op + (int64_t)n * a.osn + 16 * wave + 4 * g) =
-            num[tb] / dt;
+        *reinterpret_cast<f32x4*>(op + (int64_t)n * a.osn + 16 * wave + 4 * g) = o;
     }
     if (CAUSAL) {
       add_outer<D>(s, sm.fk, vc, g, i);
