@@ -427,7 +427,10 @@ gf_status attn_forward(const void* q, const void* k, const void* v, void* out, v
   Resolved r;
   gf_status st = resolve(B, H, N, d, window, p, &r);
   if (st != GF_OK) return st;
-  if (!r.f32 && (workspace ? workspace_bytes : 0) < r.plan.workspace_bytes)
+  // a workspace the short pieces cannot use (too small, or not aligned) still serves the longer cut, which often
+  // needs none
+  if (!r.f32 && r.plan.workspace_bytes > 0 &&
+      (!workspace || ((uintptr_t)workspace & 255u) || workspace_bytes < r.plan.workspace_bytes))
     st = resolve(B, H, N, d, window, p, &r, false);
   if (st != GF_OK) return st;
   if (B == 0 || H == 0 || N == 0) return GF_OK;

@@ -60,3 +60,28 @@ def test_a_workspace_for_pieces_of_eight_still_serves(case):
     torch.cuda.synchronize()
     assert np.isfinite(to_host(out)).all()
     check(to_host(out), co.attn_fwd(q, k, v, w, H0), "bf16", str(case))
+
+
+@pytest.mark.gpu
+def test_a_misaligned_workspace_where_pieces_of_eight_need_none():
+    import torch
+    B, H, N, d, w, H0 = 1, 12, 512, 64, 64, 2
+    q, k, v = synth(B, H, N, d, "bf16", 73)
+    p = gb.make_params(n_sparse_heads=H0)
+    need = gb.gformer_attn_workspace_bytes(B, H, N, d, w, p)
+    tq, tk, tv = (to_device(x, "bf16") for x in (q, k, v))
+    ws = torch.zeros(need + 512, dtype=torch.uint8, device="cuda")
+    out = torch.full_like(tq, float("nan"))
+    at = (ws.data_ptr() + 255) // 256 * 256 + 16
+    assert gb.gformer_attn_fwd_raw(tq.data_ptr(), tk.data_ptr(), tv.data_ptr(), out.data_ptr(), B, H, N, d, w, p, at, need,
+                                   torch.cuda.current_stream().cuda_stream) == gb.GF_OK
+    torch.cuda.synchronize()
+    check(to_host(out), co.attn_fwd(q, k, v, w, H0), "bf16", "misaligned")
+    assert not ws.any()   # and nothing was written there
+    # where that cut needs one too, the pointer is refused as it always was
+    tq, tk, tv = (torch.zeros(1, 12, 2048, 64, dtype=torch.bfloat16, device="cuda") for _ in range(3))
+    need = gb.gformer_attn_workspace_bytes(1, 12, 2048, 64, w, p)
+    ws = torch.zeros(need + 512, dtype=torch.uint8, device="cuda")
+    at = (ws.data_ptr() + 255) // 256 * 256 + 16
+    assert gb.gformer_attn_fwd_raw(tq.data_ptr(), tk.data_ptr(), tv.data_ptr(), torch.empty_like(tq).data_ptr(), 1, 12, 2048,
+                                   64, w, p, at, need, torch.cuda.current_stream().cuda_stream) == gb.GF_ERR_INVALID_ARG
