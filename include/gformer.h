@@ -114,11 +114,15 @@ typedef struct gformer_params {
   int32_t impl;           /* gf_impl                                                         */
   int32_t launch_mask;    /* 0 = everything.  Otherwise a bit set of GF_LAUNCH_*: only those */
                           /* kernels are enqueued (profiling aid; the skipped stages' data   */
-                          /* is taken as already present in the workspace).                  */
+                          /* is taken as already present in the workspace).  The linear heads */
+                          /* of a GF_F32 call are one stage: GF_LAUNCH_LINEAR_MAIN runs it,   */
+                          /* GF_LAUNCH_LINEAR_STATE nothing.                                  */
   int32_t overlap;        /* 0: everything is enqueued on `hip_stream` one after another.    */
                           /* 1: the windowed heads run on a library-owned side stream that   */
                           /* forks from and joins `hip_stream`, next to the state pass (in   */
-                          /* gformer_attn_bwd: next to the linear heads' scans).             */
+                          /* gformer_attn_bwd: next to the linear heads' scans).  A GF_F32    */
+                          /* call stays on `hip_stream`, with launches of their own for the   */
+                          /* windowed heads.                                                  */
   int32_t bidirectional;  /* 0: causal (sections III-B, III-C).  1: the encoder / image form of  */
                           /* section IV: windowed heads see the w tokens centred on the token */
                           /* (w/2 to the left, w-1-w/2 to the right, cut at the ends; the     */

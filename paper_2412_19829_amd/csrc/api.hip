@@ -492,11 +492,11 @@ gf_status attn_forward(const void* q, const void* k, const void* v, void* out, v
     // the sums over all keys need a slot per head: the plain-FMA kernel keeps its own
     const uint64_t one = (uint64_t)B * (H - a.H0) * ((uint64_t)d * d + d) * sizeof(float);
     const bool plain = !a.causal && workspace_bytes < one;
-    const bool together = (mask & GF_LAUNCH_WINDOWED) && (mask & GF_LAUNCH_LINEAR_MAIN) && !plain &&
+    const bool together = (mask & GF_LAUNCH_WINDOWED) && (mask & GF_LAUNCH_LINEAR_MAIN) && !plain && !p->overlap &&
                           f32_takes_windowed(d, B, H, a.H0, N);
     if ((mask & GF_LAUNCH_WINDOWED) && !together) e = launch_windowed_f32(a, s);
     if ((mask & GF_LAUNCH_LINEAR_MAIN) && e == hipSuccess)
-      e = plain ? launch_linear_scalar(a, bf16, s) : launch_linear_f32(a, true, true, together, s);
+      e = plain ? launch_linear_scalar(a, bf16, s) : launch_linear_f32(a, together, s);
   } else if (r.plan.impl == GF_IMPL_SCALAR) {
     if ((mask & GF_LAUNCH_WINDOWED) && e == hipSuccess) e = launch_windowed_scalar(a, bf16, s);
     if ((mask & GF_LAUNCH_LINEAR_MAIN) && e == hipSuccess) e = launch_linear_scalar(a, bf16, s);

@@ -195,7 +195,7 @@ int f32_window_rows(int64_t heads, int N);   // resident rows per workgroup of t
 hipError_t launch_windowed_f32(const AttnArgs& a, hipStream_t s);
 // with_windowed: the windowed heads' workgroups ride in the walks' launches, where f32_takes_windowed allows it
 bool f32_takes_windowed(int d, int B, int H, int H0, int N);
-hipError_t launch_linear_f32(const AttnArgs& a, bool states, bool read, bool with_windowed, hipStream_t s);
+hipError_t launch_linear_f32(const AttnArgs& a, bool with_windowed, hipStream_t s);
 hipError_t launch_windowed_backward_f32(const BwdArgs& a, hipStream_t s);
 hipError_t launch_linear_backward_f32(const BwdArgs& a, bool with_windowed, hipStream_t s);
 // bf16 backward pass of the linear heads at d = 64, heads cut into segments (lin_segments of lin_segment_len

@@ -767,14 +767,11 @@ template <int D, typename A> int band_blocks(const A& a, bool with_windowed) {
   return with_windowed ? (a.N + 63) / 64 * a.H0 * a.B : 0;
 }
 
-template <int D> hipError_t forward(const AttnArgs& a, bool states, bool read, bool with_windowed, hipStream_t s) {
+template <int D> hipError_t forward(const AttnArgs& a, bool with_windowed, hipStream_t s) {
   const int H1 = a.H - a.H0, heads = a.B * H1, blocks = heads * a.f32_nseg;
-  hipError_t e = hipSuccess;
-  if (states) {
-    e = launch_states<D>(a.k, a.v, a.ws_states, a.B, a.H0, H1, a.N, a.phi, a.f32_seg_len, a.f32_nseg, a.causal, s);
-    if (e == hipSuccess) e = launch_scan(a.ws_states, heads, a.f32_nseg, kLinState<D>, a.causal ? 0 : 2, s);
-  }
-  if (e != hipSuccess || !read) return e;
+  hipError_t e = launch_states<D>(a.k, a.v, a.ws_states, a.B, a.H0, H1, a.N, a.phi, a.f32_seg_len, a.f32_nseg, a.causal, s);
+  if (e == hipSuccess) e = launch_scan(a.ws_states, heads, a.f32_nseg, kLinState<D>, a.causal ? 0 : 2, s);
+  if (e != hipSuccess) return e;
   return launch_walk<D, kReadOut>(a, blocks, band_blocks<D>(a, with_windowed), sizeof(F32FwdSmem<D>), s);
 }
 template <int D> hipError_t backward(const BwdArgs& a, bool with_windowed, hipStream_t s) {
@@ -821,9 +818,9 @@ bool f32_takes_windowed(int d, int B, int H, int H0, int N) {
          (int64_t)B * H0 * ((N + 63) / 64) < (1 << 22) && (int64_t)B * (H - H0) < (1 << 20);
 }
 
-hipError_t launch_linear_f32(const AttnArgs& a, bool states, bool read, bool with_windowed, hipStream_t s) {
+hipError_t launch_linear_f32(const AttnArgs& a, bool with_windowed, hipStream_t s) {
   if (a.H - a.H0 <= 0 || a.N <= 0 || a.B <= 0) return hipSuccess;
-  return a.d == 64 ? forward<64>(a, states, read, with_windowed, s) : forward<128>(a, states, read, false, s);
+  return a.d == 64 ? forward<64>(a, with_windowed, s) : forward<128>(a, false, s);
 }
 hipError_t launch_linear_backward_f32(const BwdArgs& a, bool with_windowed, hipStream_t s) {
   if (a.H - a.H0 <= 0 || a.N <= 0 || a.B <= 0) return hipSuccess;

@@ -41,3 +41,22 @@ def test_together_gives_the_bits_of_apart(case):
     for g, a in zip(*grads):
         assert bool(torch.isfinite(g).all())
         assert torch.equal(g.view(torch.int32), a.view(torch.int32))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", CASES[:3], ids=lambda c: "x".join(map(str, c)))
+def test_the_linear_heads_are_one_stage(case):
+    """The read-out's mask runs the sums too, the sums' mask nothing; overlap gives the bits of no overlap."""
+    import torch
+    B, H, N, w, H0, bidir = case
+    q, k, v = (to_device(x, "f32") for x in synth(B, H, N, 64, "f32", 97))
+    want, main, over = (torch.full_like(q, float("nan")) for _ in range(3))
+    gb.gformer_attn_fwd(q, k, v, want, w, H0, bidirectional=bidir)
+    gb.gformer_attn_fwd(q, k, v, main, w, H0, bidirectional=bidir, launch_mask=gb.GF_LAUNCH_LINEAR_STATE)
+    assert bool(torch.isnan(main).all())
+    gb.gformer_attn_fwd(q, k, v, main, w, H0, bidirectional=bidir, launch_mask=gb.GF_LAUNCH_LINEAR_MAIN)
+    gb.gformer_attn_fwd(q, k, v, over, w, H0, bidirectional=bidir, overlap=1)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(main[:, :H0]).all())
+    assert torch.equal(main[:, H0:].view(torch.int32), want[:, H0:].view(torch.int32))
+    assert torch.equal(over.view(torch.int32), want.view(torch.int32))
