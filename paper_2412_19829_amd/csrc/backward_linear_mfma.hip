@@ -64,12 +64,11 @@ static_assert(sizeof(LbSmemKv<128>) <= 160 * 1024 && sizeof(LbSmem<128>) <= 160 
 // forward scan: dq, and (den_i, c_i) into the workspace
 // ---------------------------------------------------------------------------------------
 template <int D, bool ELU1>
-__device__ __forceinline__ void scan_q(const BwdArgs& a, int block, unsigned char* smem_raw) {
+__device__ __forceinline__ void scan_q(const BwdArgs& a, int h, int b, int seg, unsigned char* smem_raw) {
   using C = LbCfg<D>;
   constexpr int MT = C::MT, KS = C::KS, NW = C::NW, NT = C::NT, R = C::R, TPW = C::TPW, PCS = C::PCS;
   LbSmem<D>& sm = *reinterpret_cast<LbSmem<D>*>(smem_raw);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ln = lane & 31, lh = lane >> 5;
-  const int H1 = a.H - a.H0, h = a.H0 + block % H1, b = block / H1 % a.B, seg = block / (H1 * a.B);
   const HeadCtx<D> hc = head_ctx<D>(a, b, h);
   uint16_t* dqp = reinterpret_cast<uint16_t*>(a.dq) + b * a.q.sb + h * a.q.sh;
   const int N = a.N;
@@ -433,12 +432,11 @@ __device__ __forceinline__ void scan_q(const BwdArgs& a, int block, unsigned cha
 // reverse scan: dk, dv from (den_i, c_i) of the workspace
 // ---------------------------------------------------------------------------------------
 template <int D, bool ELU1>
-__device__ __forceinline__ void scan_kv(const BwdArgs& a, int block, unsigned char* smem_raw) {
+__device__ __forceinline__ void scan_kv(const BwdArgs& a, int h, int b, int seg, unsigned char* smem_raw) {
   using C = LbCfg<D>;
   constexpr int MT = C::MT, KS = C::KS, NW = C::NW, NT = C::NT, R = C::R, TPW = C::TPW, PCS = C::PCS;
   LbSmemKv<D>& sm = *reinterpret_cast<LbSmemKv<D>*>(smem_raw);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ln = lane & 31, lh = lane >> 5;
-  const int H1 = a.H - a.H0, h = a.H0 + block % H1, b = block / H1 % a.B, seg = block / (H1 * a.B);
   const HeadCtx<D> hc = head_ctx<D>(a, b, h);
   uint16_t* dkp = reinterpret_cast<uint16_t*>(a.dk) + b * a.k.sb + h * a.k.sh;
   uint16_t* dvp = reinterpret_cast<uint16_t*>(a.dv) + b * a.v.sb + h * a.v.sh;
@@ -752,37 +750,45 @@ __device__ __forceinline__ void scan_kv(const BwdArgs& a, int block, unsigned ch
 // and together (us): 4 x (6 + 26 heads) x 8192 tokens, window 256: 1155 and 1091; 8 x (6 + 42) x 2048, 128: 888
 // and 796; 1 x (28 + 4) x 4096, 256: 460 and 332; 16 x (30 + 10) x 1024, 128: 723 and 706; 1 x (1 + 1) x 300,
 // 64: 98 and 70.  Two separate bands of 128 rows in a workgroup: the same times, and 726 for the fourth.
-template <int D, bool ELU1, bool REVERSE>
+// A launch without a band has a kernel without its code, and (heads, batch, segments) for a grid: with the band's
+// branches in it the two scans of 32 heads x 1000 tokens took 83.2 us in place of 81.7, of 8 x 512 63.4 in place of
+// 62.0 (the same on long calls, where the scans' chunks are everything).
+template <int D, bool ELU1, bool REVERSE, bool BAND>
 __global__ __launch_bounds__(LbCfg<D>::NT, 1) void linear_bwd_scan_kernel(BwdArgs a, int linear, int rows) {
   constexpr int NT = LbCfg<D>::NT;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  // a launch without a band is (heads, batch, segments) large, one with it is one row of blocks
-  const int block = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
-  const int first = (linear + 7) & ~7, second = first + ((rows + 7) & ~7);
-  if (block < linear) {
-    if constexpr (REVERSE) scan_kv<D, ELU1>(a, block, smem_raw);
-    else scan_q<D, ELU1>(a, block, smem_raw);
-  } else if constexpr (D == 128) {
-    if (block < first) return;
-    if (block < first + rows) windowed_band<D, REVERSE ? kDk : kDq, NT>(a, block - first, smem_raw);
-    else if (!REVERSE && block >= second) windowed_band<D, kDv, NT>(a, block - second, smem_raw);
+  const int H1 = a.H - a.H0, block = blockIdx.x;
+  int head = block, b = blockIdx.y, seg = blockIdx.z;
+  if constexpr (BAND) {
+    const int first = (linear + 7) & ~7, second = first + ((rows + 7) & ~7);
+    if (block >= first) {
+      if (block < first + rows) windowed_band<D, REVERSE ? kDk : kDq, NT>(a, block - first, smem_raw);
+      else if (!REVERSE && block >= second) windowed_band<D, kDv, NT>(a, block - second, smem_raw);
+      return;
+    }
+    if (block >= linear) return;
+    head = block % H1;
+    b = block / H1 % a.B;
+    seg = block / (H1 * a.B);
   }
+  if constexpr (REVERSE) scan_kv<D, ELU1>(a, a.H0 + head, b, seg, smem_raw);
+  else scan_q<D, ELU1>(a, a.H0 + head, b, seg, smem_raw);
 }
 
-template <int D, bool ELU1> hipError_t launch_lin_bwd_t(const BwdArgs& a, bool band, hipStream_t s) {
+template <int D, bool ELU1, bool BAND> hipError_t launch_lin_bwd_t(const BwdArgs& a, hipStream_t s) {
   constexpr int NT = LbCfg<D>::NT, BR = band_rows(NT);
+  static_assert(!BAND || (sizeof(BandSmem<D>) <= sizeof(LbSmem<D>) && sizeof(BandSmem<D>) <= sizeof(LbSmemKv<D>)),
+                "the band's tiles fit the scans' LDS");
   const int linear = (a.H - a.H0) * a.B * a.lin_segments, first = (linear + 7) & ~7;
-  const int rows = band ? (a.N + BR - 1) / BR * a.H0 * a.B : 0;
+  const int rows = BAND ? (a.N + BR - 1) / BR * a.H0 * a.B : 0;
   hipError_t e = hipSuccess;
   auto launch = [&](auto kern, size_t smem, int blocks) {
     if (e != hipSuccess) return;
-    static_assert(D == 64 || (sizeof(BandSmem<D>) <= sizeof(LbSmem<D>) && sizeof(BandSmem<D>) <= sizeof(LbSmemKv<D>)),
-                  "the band's tiles fit the scans' LDS");
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e == hipSuccess) kern<<<rows > 0 ? dim3(blocks) : dim3(a.H - a.H0, a.B, a.lin_segments), dim3(NT), smem, s>>>(a, linear, rows);
+    if (e == hipSuccess) kern<<<BAND ? dim3(blocks) : dim3(a.H - a.H0, a.B, a.lin_segments), dim3(NT), smem, s>>>(a, linear, rows);
   };
-  launch(linear_bwd_scan_kernel<D, ELU1, false>, sizeof(LbSmem<D>), first + ((rows + 7) & ~7) + rows);
-  launch(linear_bwd_scan_kernel<D, ELU1, true>, sizeof(LbSmemKv<D>), first + rows);
+  launch(linear_bwd_scan_kernel<D, ELU1, false, BAND>, sizeof(LbSmem<D>), first + ((rows + 7) & ~7) + rows);
+  launch(linear_bwd_scan_kernel<D, ELU1, true, BAND>, sizeof(LbSmemKv<D>), first + rows);
   return e != hipSuccess ? e : hipGetLastError();
 }
 
@@ -813,8 +819,9 @@ hipError_t launch_linear_backward_mfma(const BwdArgs& args, bool with_windowed, 
     }
   }
   const bool elu1 = a.phi == 0;
-  if (a.d == 64) return elu1 ? launch_lin_bwd_t<64, true>(a, false, s) : launch_lin_bwd_t<64, false>(a, false, s);
-  return elu1 ? launch_lin_bwd_t<128, true>(a, with_windowed, s) : launch_lin_bwd_t<128, false>(a, with_windowed, s);
+  if (a.d == 64) return elu1 ? launch_lin_bwd_t<64, true, false>(a, s) : launch_lin_bwd_t<64, false, false>(a, s);
+  if (with_windowed) return elu1 ? launch_lin_bwd_t<128, true, true>(a, s) : launch_lin_bwd_t<128, false, true>(a, s);
+  return elu1 ? launch_lin_bwd_t<128, true, false>(a, s) : launch_lin_bwd_t<128, false, false>(a, s);
 }
 
 }  // namespace gformer
