@@ -203,6 +203,18 @@ def _current_stream(t) -> int:
     return raw(t.get_device()) if raw is not None else torch.cuda.current_stream(t.device).cuda_stream
 
 
+def _workspace(nbytes: int, t, stream: Optional[int]):
+    """Workspace of a call on `stream` (None: torch's current one).  It is that stream's memory, so that the
+    allocator, which has it back before the call has run, gives it to nothing that runs beside the call."""
+    import torch
+
+    if stream is None or stream == _current_stream(t):
+        return torch.empty(nbytes, dtype=torch.uint8, device=t.device)
+    theirs = torch.cuda.ExternalStream(stream, device=t.device) if stream else torch.cuda.default_stream(t.device)
+    with torch.cuda.stream(theirs):
+        return torch.empty(nbytes, dtype=torch.uint8, device=t.device)
+
+
 def gformer_attn_fwd(q, k, v, out, window: int, n_sparse_heads: int, *, phi=GF_PHI_ELU1,
                      chunk=0, segment_len=0, impl=GF_IMPL_AUTO, launch_mask=0, overlap=0,
                      bidirectional=0, softmax_scale=1.0, eps=0.0, workspace=None,
@@ -212,7 +224,7 @@ def gformer_attn_fwd(q, k, v, out, window: int, n_sparse_heads: int, *, phi=GF_P
 
     `out` is written in place and returned.  `workspace` is an optional uint8 device tensor
     of at least gformer_attn_workspace_bytes(...) bytes; when omitted and one is needed it is
-    allocated with torch.empty (plumbing: the library itself never allocates).  The call is
+    allocated with torch.empty, for that stream (plumbing: the library itself never allocates).  The call is
     asynchronous on `stream` (a raw hipStream_t; default: torch's current stream)."""
     import torch
 
@@ -239,7 +251,7 @@ def gformer_attn_fwd(q, k, v, out, window: int, n_sparse_heads: int, *, phi=GF_P
     ws_ptr, ws_bytes = 0, 0
     if need > 0:
         if workspace is None:
-            workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
+            workspace = _workspace(need, q, stream)
         ws_ptr, ws_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
     if stream is None:
         stream = _current_stream(q)
@@ -378,7 +390,7 @@ def gformer_attn_prefill(q, k, v, out, kcache, vcache, state, window: int, n_spa
     ws_ptr, ws_bytes = 0, 0
     if need > 0:
         if workspace is None:
-            workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
+            workspace = _workspace(need, q, stream)
         ws_ptr, ws_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
     if stream is None:
         stream = _current_stream(q)
@@ -424,7 +436,7 @@ def gformer_attn_bwd(q, k, v, dout, dq, dk, dv, window: int, n_sparse_heads: int
     ws_ptr, ws_bytes = 0, 0
     if need > 0:
         if workspace is None:
-            workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
+            workspace = _workspace(need, q, stream)
         ws_ptr, ws_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
     if stream is None:
         stream = _current_stream(q)
