@@ -775,11 +775,17 @@ gf_status gformer_attn_bwd(const void* q, const void* k, const void* v, const vo
   a.ws = reinterpret_cast<float*>(workspace);
   a.ws_state = a.causal ? nullptr
                         : reinterpret_cast<float*>(static_cast<char*>(workspace) + bwd_stats_bytes(B, H, N));
-  // The segment walks take the linear heads when the workspace holds their sums; a workspace of the
-  // least size gets the scans that sum what lies in front of (behind) a segment again.
-  const Segments segs = backward_segments((int64_t)B * (H - a.H0), N, d, a.causal);
-  const bool segments = d == 64 && (int64_t)B * (H - a.H0) < (1 << 22) &&   // one grid dimension holds them
-                        workspace_bytes >= bwd_stats_bytes(B, H, N) + bwd_segment_bytes((int64_t)B * (H - a.H0), N, d, a.causal);
+  const bool bf16 = p->dtype == GF_BF16;
+  const bool mfma = bf16 && p->impl != GF_IMPL_SCALAR;
+  // d = 64: the segment walks take the linear heads.  A causal call whose workspace does not hold their sums, or
+  // with more heads than one grid dimension holds, gets the scans that sum what lies in front of (behind) a segment
+  // again; over all keys the least workspace holds the sums, and so many heads would need 550 GB of it.
+  const int64_t lin_heads = (int64_t)B * (H - a.H0);
+  const bool one_grid = lin_heads < (1 << 22);
+  if (mfma && d == 64 && !a.causal && !one_grid) return GF_ERR_UNSUPPORTED;
+  const Segments segs = backward_segments(lin_heads, N, d, a.causal);
+  const bool segments = d == 64 && one_grid &&
+                        workspace_bytes >= bwd_stats_bytes(B, H, N) + bwd_segment_bytes(lin_heads, N, d, a.causal);
   // The linear heads' launches take the windowed heads' passes along: the walks all four, the d = 128 scans
   // three behind a launch for the statistics.
   const bool together = (segments || (d == 128 && a.causal && (int64_t)B * H < (1 << 20))) && a.H0 > 0 && a.H0 < a.H &&
@@ -794,13 +800,10 @@ gf_status gformer_attn_bwd(const void* q, const void* k, const void* v, const vo
     return a.causal ? launch_linear_backward_mfma(a, together, on) : launch_linear_backward_bidir_mfma(a, on);
   };
   hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
-  const bool bf16 = p->dtype == GF_BF16;
-  const bool mfma = bf16 && p->impl != GF_IMPL_SCALAR;
   hipError_t e = hipSuccess;
   if (f32_matrix(p, B, H, N)) {
-    const int64_t heads = (int64_t)B * (H - a.H0);
     a.ws_state = reinterpret_cast<float*>(static_cast<char*>(workspace) + bwd_stats_bytes(B, H, N));
-    const Segments f = f32_segments(heads, N, d, workspace_bytes - bwd_stats_bytes(B, H, N), 2);
+    const Segments f = f32_segments(lin_heads, N, d, workspace_bytes - bwd_stats_bytes(B, H, N), 2);
     a.f32_seg_len = f.len;
     a.f32_nseg = f.count;
     const bool f32_together = !p->overlap && f32_takes_windowed(d, B, H, a.H0, N);
@@ -811,8 +814,8 @@ gf_status gformer_attn_bwd(const void* q, const void* k, const void* v, const vo
     // units the rest of the chip is idle for their whole duration.  With overlap = 1 the windowed
     // heads' passes therefore run beside them on the library's side stream (forked from and
     // joined to the caller's stream by events), and the scans are enqueued first so that their
-    // workgroups get their compute units.  Without it, the segment walks take the passes along in
-    // their launches (`together`); beside the scans they are launches of their own.
+    // workgroups get their compute units.  Without it the passes ride in the walks' and the scans'
+    // launches (`together`) or are launches of their own in front of them.
     const bool both = a.H0 > 0 && a.H0 < a.H;
     std::lock_guard<std::mutex> lock(g_enqueue_mutex);
     SideStream* side = nullptr;

@@ -1,6 +1,6 @@
 // Backward pass of the bidirectional linear heads on bf16 matrix cores (section II-B's ratio over
-// all keys, differentiated; formulas at the top of backward_bidir_scalar.hip).  These are the kernels of
-// d = 128, and of d = 64 where the workspace holds no segment sums.
+// all keys, differentiated; formulas at the top of backward_bidir_scalar.hip), d = 128; the walks of
+// backward_linear_segments.hip are those of d = 64.
 //
 // With fq = phi(q), fk = phi(k), S = sum_j fk_j v_j^T, z = sum_j fk_j, den_i = fq_i.z + eps,
 // g_i = dO_i / den_i, r_i = S g_i, c_i = fq_i.r_i / den_i:
@@ -470,16 +470,14 @@ template <int D, bool ELU1> hipError_t launch_bidir_mfma_t(const BwdArgs& a, hip
 
 }  // namespace
 
-// Bidirectional linear heads [H0, H) of a bf16 call.
+// Bidirectional linear heads [H0, H) of a bf16 call, d = 128.
 hipError_t launch_linear_backward_bidir_mfma(const BwdArgs& args, hipStream_t s) {
   if (args.H - args.H0 <= 0 || args.N <= 0 || args.B <= 0 || !args.ws_state) return hipSuccess;
   BwdArgs a = args;
   const int heads = (a.H - a.H0) * a.B, nchunks = (a.N + CH - 1) / CH;
   // one workgroup per head and segment; segments of at least four chunks, as many as fill the chip
   a.lin_segments = std::max(1, std::min(std::min(kMaxSeg, device_compute_units() / heads), nchunks / 4));
-  const bool elu1 = a.phi == 0;
-  if (a.d == 64) return elu1 ? launch_bidir_mfma_t<64, true>(a, s) : launch_bidir_mfma_t<64, false>(a, s);
-  return elu1 ? launch_bidir_mfma_t<128, true>(a, s) : launch_bidir_mfma_t<128, false>(a, s);
+  return a.phi == 0 ? launch_bidir_mfma_t<128, true>(a, s) : launch_bidir_mfma_t<128, false>(a, s);
 }
 
 }  // namespace gformer

@@ -50,8 +50,9 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr f32x4 kZeroF4 = {0.f, 0.f, 0.f, 0.f};
 
 template <int D> struct SegCfg {
+  static_assert(D == 64, "row stride, LDS and registers are laid out for d = 64");
   static constexpr int NW = D / 16, NT = 64 * NW;
-  static constexpr int R = D == 128 ? D + 24 : D + 8;  // 12 / 36 dwords mod 64: row and transpose reads
+  static constexpr int R = D + 8;                      // 36 dwords: row and transpose reads
   static constexpr int KS = D / 32;                    // contraction steps over the head size
   static constexpr int XT = D / 16;                    // tiles of a carried sum per wave
   static constexpr int STATE = D * D + D;

@@ -30,6 +30,14 @@ def test_gradients(case):
         check_grad(g, r, "bf16", f"{name} {case}", dout)
 
 
+def test_more_heads_over_all_keys_than_a_grid_holds_are_refused():
+    # 2^22 heads; nothing is launched, so the addresses are not looked at
+    p = gb.make_params(bidirectional=1)
+    at = [256 * (i + 1) for i in range(8)]
+    assert gb.gformer_attn_bwd_raw(*at[:7], 1 << 15, 1 << 7, 1, 64, 8, p, at[7], 1 << 50) == gb.GF_ERR_UNSUPPORTED
+    assert gb.gformer_attn_bwd_raw(*at[:7], 1 << 15, 1 << 7, 1, 64, 8, p, at[7], 1 << 38) == gb.GF_ERR_WORKSPACE
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("phi,eps", [(gb.GF_PHI_ELU1, 0.5), (gb.GF_PHI_IDENTITY, 0.0)], ids=["eps", "identity"])
 def test_any_workspace_serves(phi, eps):
