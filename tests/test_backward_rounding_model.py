@@ -1,6 +1,6 @@
 """Which operands of the matrix-core backward pass may be one bf16 and which may not (CPU only).
 
-The matrix-core kernels of the linear heads work in chunks of 64 tokens with bf16 operands
+The scans (d = 128, and d = 64 with the least workspace) of the linear heads work in chunks of 64 tokens with bf16 operands
 (phi(q), phi(k), the in-chunk weights S and T', g = dO/den and the copy of the carried sum) and
 fp32 accumulation.  This file writes those chunked formulas out in numpy, exactly and with the
 operands rounded where a kernel could round them, and compares with the oracle:
@@ -13,6 +13,11 @@ operands rounded where a kernel could round them, and compares with the oracle:
     it is an operand, and S = tril(phiQ phiK^T) as a pair in the numerator and the denominator of
     the forward scan (c = dO.num / den^2 enters every T' of its row), the worst row is back under
     1.5e-2 - which is what the kernels do.  The other operands stay one bf16.
+
+The segment walks (d = 64) take chunks of 32 tokens and divide last: S and T = dO v^T enter c in fp32 (c needs no
+numerator), T/den - c is a bf16 pair, and dO is an operand as it came; phi(q)/den, dO/den, S/den and the copies of the
+carried sums are one bf16 each.  The same two statements for them: exactly the oracle's derivative without rounding,
+and the worst row under 1.5e-2 with it.
 """
 import numpy as np
 
@@ -125,3 +130,56 @@ def test_bf16_pairs_for_the_two_cancelling_operands_bring_every_row_under_the_ba
         worst_pairs = max(worst_pairs, max(float(_gpu_measure(g, r, dout).max()) for g, r in zip(pairs, ref)))
     assert worst_single > 2e-2     # one bf16 per operand misses the bar on some input
     assert worst_pairs < 1.5e-2    # the kernels' choice meets it with room to spare
+
+
+def segment_walks(q, k, v, dout, rounded, chunk=32):
+    """dq, dk, dv of one causal linear head by the dq walk and the dk, dv walk (one segment), whose three bf16 forms
+    of a token's row are phi, the row itself and the row over the denominator."""
+    R = _rb if rounded else (lambda x: x)
+    RT = _pair if rounded else (lambda x: x)
+    N, d = q.shape
+    fq, fk = R(_phi(q)), R(_phi(k))
+    A, Z = np.zeros((d, d)), np.zeros(d)
+    den, c, dfq = np.zeros(N), np.zeros(N), np.zeros((N, d))
+    starts = range(0, N, chunk)
+    for n in starts:
+        sl = slice(n, min(N, n + chunk))
+        S, T = np.tril(fq[sl] @ fk[sl].T), dout[sl] @ v[sl].T
+        r = dout[sl] @ R(A).T
+        den[sl] = S.sum(1) + fq[sl] @ Z
+        c[sl] = ((fq[sl] * r).sum(1) + (S * T).sum(1)) / den[sl] ** 2
+        W = RT(np.tril(T / den[sl][:, None] - c[sl][:, None]))
+        dfq[sl] = r / den[sl][:, None] - c[sl][:, None] * Z[None, :] + W @ fk[sl]
+        A += fk[sl].T @ v[sl]
+        Z += fk[sl].sum(0)
+    B1, B2, Y = np.zeros((d, d)), np.zeros((d, d)), np.zeros(d)
+    dfk, dv = np.zeros((N, d)), np.zeros((N, d))
+    for n in reversed(starts):
+        sl = slice(n, min(N, n + chunk))
+        inv = 1 / den[sl][:, None]
+        W = RT(np.tril((dout[sl] @ v[sl].T) * inv - c[sl][:, None]))
+        P = R(np.tril(fq[sl] @ fk[sl].T) * inv)
+        dfk[sl] = W.T @ fq[sl] + v[sl] @ R(B1).T - Y[None, :]
+        dv[sl] = P.T @ dout[sl] + fk[sl] @ R(B2)
+        B1 += R(fq[sl] * inv).T @ dout[sl]
+        B2 += fq[sl].T @ R(dout[sl] * inv)
+        Y += fq[sl].T @ c[sl]
+    slope = lambda f: np.where(f > 1, 1.0, f)
+    return dfq * slope(fq), dfk * slope(fk), dv
+
+
+def test_segment_walks_are_the_oracles_derivative():
+    (q, k, v, dout), ref = _case()
+    for g, r in zip(segment_walks(q, k, v, dout, rounded=False), ref):
+        assert np.abs(g - r).max() <= 1e-10 * max(1.0, np.abs(r).max())
+
+
+def test_segment_walks_with_their_roundings_stay_under_the_bar():
+    rng = np.random.default_rng(2)
+    worst = 0.0
+    for _ in range(12):
+        N, seed = int(rng.integers(100, 500)), int(rng.integers(0, 10 ** 6))
+        (q, k, v, dout), ref = _case(N, 64, seed)
+        got = segment_walks(q, k, v, dout, rounded=True)
+        worst = max(worst, max(float(_gpu_measure(g, r, dout).max()) for g, r in zip(got, ref)))
+    assert worst < 1.5e-2

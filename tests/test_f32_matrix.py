@@ -152,3 +152,27 @@ def test_plan_cuts_heads_into_segments():
         assert per == 1 or (pl.segment_len % 32 == 0 and pl.segment_len >= 128 and pl.n_segments <= 3 * 256)
         assert pl.workspace_bytes == ((pl.n_segments * (d * d + d) * 4) if per > 1 or bidir else 0)
         assert pl.workspace_bytes <= gb.GFORMER_NOALLOC_SCRATCH_BYTES or per == 1
+
+
+@pytest.mark.gpu
+def test_feature_map_over_its_whole_range():
+    """phi alone: after one token the carried Z is phi(k).  The argument's reduction leaves 2^-25 in the exponent, the
+    power of two has one ulp: 2 ulp of a normal result, half a unit of the last place of a denormal one besides."""
+    import torch
+    B, H, d = 4, 64, 128
+    k = -np.exp(np.random.default_rng(99).uniform(np.log(1e-8), np.log(104.5), (B, H, 1, d))).astype(np.float32)
+    edges = [0.0, -0.0, -1e-45, -1e-38, -0.34657359, -0.34657362, -0.5, -1.0, -87.33654, -87.33655, -88.0, -103.27893, -103.9,
+             -103.97208, -103.97209, -104.0, -150.0, -np.inf, 1e-8, 0.5, 3.0, 1e30]
+    k[0, 0, 0, :len(edges)] = edges
+    tk = torch.from_numpy(k).cuda()
+    st = torch.full((B, H, d * d + d), float("nan"), device="cuda")
+    out = torch.full_like(tk, float("nan"))
+    gb.gformer_attn_prefill(tk, tk, torch.zeros_like(tk), out, None, None, st, 1, 0)
+    torch.cuda.synchronize()
+    got = st[..., d * d:].cpu().numpy().astype(np.float64)
+    x = k[:, :, 0].astype(np.float64)
+    ref = np.where(x > 0, x + 1, np.exp(np.minimum(x, 0)))
+    assert (np.abs(got - ref) <= 2 * 2.0 ** -23 * ref + 2.0 ** -149).all()
+    tk[..., 0] = float("nan")
+    gb.gformer_attn_prefill(tk, tk, torch.zeros_like(tk), out, None, None, st, 1, 0)
+    assert bool(torch.isnan(st[..., d * d]).all()) and not bool(torch.isnan(st[..., d * d + 1:]).any())
