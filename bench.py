@@ -460,12 +460,10 @@ def main() -> int:
                                           wl.d, wl.window, pb, ws_b.data_ptr(), need_b, stream)
             if st_ != gb.GF_OK:
                 raise gb.GformerError(st_, gb.gformer_status_string(st_))
-        backward()
-        torch.cuda.synchronize()
+        ramp(backward)
         t_bwd = event_time(backward, 20)
         pb.overlap = 1      # the windowed heads' passes beside the linear heads' scans
-        backward()
-        torch.cuda.synchronize()
+        ramp(backward)
         t_bwd_overlap = event_time(backward, 20)
         pbi = gb.make_params(dtype=gb.GF_BF16, n_sparse_heads=H0, bidirectional=1)
         need_bi = gb.gformer_attn_bwd_workspace_bytes(wl.B, wl.H, wl.N, wl.d, wl.window, pbi)
@@ -477,14 +475,14 @@ def main() -> int:
                                           wl.d, wl.window, pbi, ws_bi.data_ptr(), need_bi, stream)
             if st_ != gb.GF_OK:
                 raise gb.GformerError(st_, gb.gformer_status_string(st_))
-        backward_bidir()
-        torch.cuda.synchronize()
+        ramp(backward_bidir)
         t_bwd_bidir = event_time(backward_bidir, 20)
         modes["backward"] = {"ms": round(t_bwd * 1e3, 3), "tokens_per_s": round(wl.B * wl.N / t_bwd, 1),
                              "ms_overlap_1": round(t_bwd_overlap * 1e3, 3),
                              "ms_bidirectional": round(t_bwd_bidir * 1e3, 3),
-                             "note": "gformer_attn_bwd, bf16 matrix-core kernels: four band passes over the "
-                                     "windowed heads, a forward and a reverse chunk scan over the linear heads"}
+                             "note": "gformer_attn_bwd, bf16 matrix-core kernels: the windowed heads' statistics, then "
+                                     "a forward and a reverse chunk scan over the linear heads with the windowed "
+                                     "heads' dq, dv and dk passes in their launches"}
         # The contract's fifth configuration: a 12-layer decoder around the library, reporting the
         # attention share of the layer time (the harness lives in bench_decoder12.py).
         import bench_decoder12
