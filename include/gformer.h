@@ -47,7 +47,10 @@
  *   - Supported: d in {64, 128}; any N >= 0 (N == 0 or B*H == 0 is a no-op); any window >= 1
  *     (window >= N is full causal attention); 0 <= n_sparse_heads <= H;
  *     chunk in {0, 64, 128, 256} (256 only with d = 64).  Everything else returns
- *     GF_ERR_UNSUPPORTED; nothing falls back silently.
+ *     GF_ERR_UNSUPPORTED.  A call runs the kernels its parameters name; GF_F32 with GF_IMPL_AUTO
+ *     runs the plain-FMA kernels instead of the matrix-core ones where B * H * ceil(N / 16)
+ *     reaches 2^22, and for the linear heads of a bidirectional call whose workspace holds less
+ *     than one (d*d + d) fp32 sum per head.
  */
 #ifndef GFORMER_H
 #define GFORMER_H
@@ -187,11 +190,14 @@ gf_status gformer_attn_fwd(const void* q, const void* k, const void* v, void* ou
  * loads the library holds its own copy until the process ends).  The call allocates and frees
  * nothing, on the host or on the device, and creates no stream or event.
  *   - gformer_attn_workspace_bytes(...) > GFORMER_NOALLOC_SCRATCH_BYTES: GF_ERR_WORKSPACE, before
- *     anything is launched (the headline layer B=4 H=32 N=8192 d=128 needs 52.4 MiB, 64.5 MiB with all heads linear).
+ *     anything is launched; a GF_F32 call runs with the sums that fit, as gformer_attn_fwd does with
+ *     a workspace of that size, and its results are that call's (the headline layer B=4 H=32 N=8192 d=128 needs 52.4 MiB, 64.5 MiB with all heads linear).
  *   - params.overlap = 1 (library-owned side stream, created on first use): GF_ERR_UNSUPPORTED.
  *   - Call it with the device of `hip_stream` current.  The first call on a device looks up that
  *     device's address of the array (hipGetSymbolAddress, no allocation); make that first call
  *     outside stream capture.
+ *   - Every call with gformer_attn_workspace_bytes(...) > 0 uses the array: among them GF_F32 calls
+ *     and short GF_BF16 calls whose linear heads are cut into segments or short pieces.
  *   - All calls on one device share the one array, which keeps the last call's contents: nothing
  *     in it has to start at zero (every slot a call reads was written by that same call), but two
  *     calls that overlap in time on one device (different streams, or graph branches) race.
@@ -253,15 +259,16 @@ gf_status gformer_attn_prefill(const void* q, const void* k, const void* v, void
  *             segment of every linear head, and run, slower, on anything down to the size above
  * Kernels: a bf16 call runs on the matrix cores (params.impl GF_IMPL_AUTO or GF_IMPL_MFMA: bf16
  * products, fp32 accumulation, softmax statistics, denominators and carried sums in fp32; the
- * two operands of the linear heads whose rounding would cost more than the bf16 mode's 2e-2 per
- * row, T' and the in-chunk weights of the numerator, travel as bf16 pairs);
+ * operands of the linear heads whose rounding would cost more than the bf16 mode's 2e-2 per row
+ * travel as bf16 pairs: T' = dO.v / den - c, and at d = 128 the in-chunk weights of the numerator,
+ * which the d = 64 kernels keep in fp32);
  * an fp32 call (GF_IMPL_AUTO) on the matrix cores in single precision; GF_IMPL_SCALAR on plain-FMA
  * kernels (fp32 arithmetic on either storage type).  The linear heads of a bidirectional call
  * take three sweeps over each head (the sums over all keys, dq with the sums over all queries, dk
  * and dv), a bf16 call with the d x d sums and dO / den as bf16 pairs where a difference of nearly
  * equal terms depends on them.  GF_IMPL_MFMA with fp32 storage, GF_IMPL_MFMA_BLOCKED, GF_IMPL_MFMA_STREAM and
  * GF_IMPL_MFMA_CHUNK are GF_ERR_UNSUPPORTED.  params.launch_mask must be 0; segment_len and chunk
- * are ignored.  params.overlap = 1 (matrix-core kernels, both head groups present): the windowed
+ * are ignored.  params.overlap = 1 (bf16 matrix-core kernels, both head groups present): the windowed
  * heads' passes run on the library's side stream beside the linear heads' scans, which leave
  * compute units idle when there are fewer heads than units; same fork/join as in
  * gformer_attn_fwd, same results.

@@ -105,7 +105,8 @@ struct BwdArgs {
   int H0;
   int phi;
   float scale, eps;
-  float* ws_state;    // bidirectional linear heads: [B * (H - H0)][2][4][d*d + d] fp32: the sums
+  float* ws_state;    // bidirectional linear heads (plain-FMA kernels, and the bf16 sweeps of d = 128):
+                      // [B * (H - H0)][2][4][d*d + d] fp32: the sums
                       // (S, z) and (B, Y) of every head, each in up to four per-segment partials
                       // (matrix row-major [feature][value], then the vector)
   // single-precision matrix-core kernels: segments as in AttnArgs; ws_state holds the sums (A, Z) and
@@ -181,7 +182,7 @@ hipError_t launch_random_features(const FeatureArgs& a, bool bf16, bool mfma, hi
 hipError_t launch_decode(const DecodeArgs& a, bool bf16, hipStream_t s);
 size_t decode_smem_bytes(int d, int window, int H0);
 
-// Single-precision matrix-core kernels.  A head's segments: as many as keep two workgroups on every
+// Single-precision matrix-core kernels.  A head's segments: as many as keep three workgroups on every
 // compute unit, none shorter than 128 tokens, as far as `bytes` hold `sums` carried sums for each.
 constexpr int kMaxSegments = 64;
 struct Segments {

@@ -34,8 +34,8 @@ constexpr int kSumInPlace = 8;
 
 // phi(x) = elu(x) + 1 without a branch (52 against 55 us for the forward walk; written as `x > 0 ? x + 1 : expf(x)` every element gets its own
 // jump around the exponential, and the library's expf spends a third of its instructions on ranges
-// that do not occur here).  exp(x) = 2^n 2^f with n = round(x log2 e), f = x log2 e - n from one fused
-// multiply-add and the constant's low part; v_exp_f32 is good to 1 ulp there and ldexp rounds small
+// that do not occur here).  exp(x) = 2^n 2^f with n = round(x log2 e), f = x log2 e - n (Cody and Waite's reduction: log2 e as a
+// float and the rest, in fused multiply-adds); v_exp_f32 is good to 1 ulp there and ldexp rounds small
 // results once.  A NaN compares false and comes back through x + 1.
 __device__ __forceinline__ float elu1_f32(float x) {
   constexpr float kLog2eHi = 1.44269502162933349609375f, kLog2eLo = 1.92596299112661746887e-8f;

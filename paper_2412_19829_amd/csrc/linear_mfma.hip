@@ -265,7 +265,7 @@ __global__ __launch_bounds__(256) void linear_prefix_kernel(float* ws, int n_hea
   if (x >= state_floats || head >= n_heads) return;
   const int64_t g_lo = (int64_t)head * vcph, g_hi = g_lo + vcph;
   // in slot order with eight loads in flight: one load and one addition after the other is what bounds it
-  // (forward, 1 x (6 + 26) heads x 32768 x 128: 343.6 -> 341.1 us a call; same bits)
+  // (1 x (6 + 26) heads x 32768 x 128: 10.0 -> 7.8 us, of a call of 341; same bits)
   auto walk = [&](int64_t j0, int64_t j1, auto&& at) {
     constexpr int G = 8;
     for (; j0 < j1; j0 += G) {

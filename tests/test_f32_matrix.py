@@ -176,3 +176,24 @@ def test_feature_map_over_its_whole_range():
     tk[..., 0] = float("nan")
     gb.gformer_attn_prefill(tk, tk, torch.zeros_like(tk), out, None, None, st, 1, 0)
     assert bool(torch.isnan(st[..., d * d]).all()) and not bool(torch.isnan(st[..., d * d + 1:]).any())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [(1, 3, 1100, 64, 1, 0), (1, 2, 700, 128, 0, 1), (20, 64, 33, 128, 0, 1)],
+                         ids=lambda c: "x".join(map(str, c)))
+def test_noalloc_gives_the_bits_of_a_workspace_of_its_size(case):
+    """The last case asks for more than the library's array holds: not one sum per head, so plain FMAs in both."""
+    import torch
+    B, H, N, d, H0, bidir = case
+    q, k, v = (torch.randn(B, H, N, d, device="cuda", generator=torch.Generator("cuda").manual_seed(s)) for s in (1, 2, 3))
+    p = gb.make_params(dtype=gb.GF_F32, n_sparse_heads=H0, bidirectional=bidir)
+    held = gb.GFORMER_NOALLOC_SCRATCH_BYTES
+    assert (gb.gformer_attn_workspace_bytes(B, H, N, d, 9, p) > held) == (B == 20)
+    ws = torch.full((held,), 0xff, dtype=torch.uint8, device="cuda")
+    got, want = torch.full_like(q, float("nan")), torch.full_like(q, float("nan"))
+    at = (q.data_ptr(), k.data_ptr(), v.data_ptr())
+    stream = torch.cuda.current_stream().cuda_stream
+    assert gb.gformer_attn_fwd_raw(*at, want.data_ptr(), B, H, N, d, 9, p, ws.data_ptr(), held, stream) == gb.GF_OK
+    assert gb.gformer_attn_fwd_noalloc_raw(*at, got.data_ptr(), B, H, N, d, 9, p, stream) == gb.GF_OK
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(want).all()) and torch.equal(got.view(torch.int32), want.view(torch.int32))
