@@ -196,6 +196,23 @@ __device__ __forceinline__ void add_outer(f32x4 (&s)[D / 16], const uint16_t* wi
     if (x % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // operands of four tiles in flight, not of all: registers
   }
 }
+// The same with `col` as a bf16 pair.
+template <int D>
+__device__ __forceinline__ void add_outer_pair(f32x4 (&s)[D / 16], const uint16_t* wide_lane, const float (&col)[8]) {
+  bf16x8 hi, lo;
+  split8(col, hi, lo);
+#pragma unroll
+  for (int x0 = 0; x0 < D / 16; x0 += 4) {
+    bf16x8 w[4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) w[x] = col8<SegCfg<D>::R>(wide_lane + 32 * ((x0 + x) / 2) + 4 * (x % 2));
+#pragma unroll
+    for (int x = 0; x < 4; ++x) s[x0 + x] = mfma16(w[x], hi, s[x0 + x]);
+#pragma unroll
+    for (int x = 0; x < 4; ++x) s[x0 + x] = mfma16(w[x], lo, s[x0 + x]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
 // 16x16 tile of products of rows
 template <int D> __device__ __forceinline__ f32x4 rows_product(const uint16_t* a_lane, const uint16_t* b_lane) {
   f32x4 acc = kZeroF4;
@@ -306,7 +323,7 @@ template <int D> struct SegQSmem {
   float own[C::NW][2][SC];       // 1/den and c, each wave's own copy
   float z[D];
 };
-template <int D, bool ELU1, bool CAUSAL>
+template <int D, bool ELU1, bool CAUSAL, bool PAIR>
 __device__ __forceinline__ void seg_q(const BwdArgs& a, int block, unsigned char* smem_raw) {
   using C = SegCfg<D>;
   constexpr int R = C::R, NW = C::NW;
@@ -385,8 +402,8 @@ __device__ __forceinline__ void seg_q(const BwdArgs& a, int block, unsigned char
     }
     __builtin_amdgcn_sched_barrier(0);
     f32x4 rv[2] = {kZeroF4, kZeroF4};
-    if constexpr (CAUSAL) read_out<D>(rv, as, sm.dd + s.row_at);
-    else read_out_pair<D>(rv, as, sm.dd + s.row_at);
+    if constexpr (PAIR) read_out_pair<D>(rv, as, sm.dd + s.row_at);
+    else read_out<D>(rv, as, sm.dd + s.row_at);
     uint16_t* const corner = sm.fq + i * R + 16 * wave + 4 * g;   // this wave's columns of token i (and 16 + i)
     {
       const f32x4 zc = lds4f(sm.z + 16 * wave + 4 * g);
@@ -449,10 +466,7 @@ __device__ __forceinline__ void seg_q(const BwdArgs& a, int block, unsigned char
         add_outer<D>(bs, sm.dd + s.wide_at, pack8(qx));
       } else {
         // over all keys dphi(k) = B v - Y cancels on heads of a few tokens: phi(q) / den as a pair
-        bf16x8 hi, lo;
-        split8(qx, hi, lo);
-        add_outer<D>(bs, sm.dd + s.wide_at, hi);
-        add_outer<D>(bs, sm.dd + s.wide_at, lo);
+        add_outer_pair<D>(bs, sm.dd + s.wide_at, qx);
       }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -512,7 +526,7 @@ template <int D> struct SegKvSmem {
   float inv[SC], cc[SC];
   float y[D];
 };
-template <int D, bool ELU1, bool CAUSAL>
+template <int D, bool ELU1, bool CAUSAL, bool PAIR>
 __device__ __forceinline__ void seg_kv(const BwdArgs& a, int block, unsigned char* smem_raw) {
   using C = SegCfg<D>;
   constexpr int R = C::R, NW = C::NW;
@@ -611,8 +625,7 @@ __device__ __forceinline__ void seg_kv(const BwdArgs& a, int block, unsigned cha
     __builtin_amdgcn_sched_barrier(0);
     const f32x4 yc = lds4f(sm.y + 16 * wave + 4 * g);
     f32x4 dka[2] = {-yc, -yc}, dva[2] = {kZeroF4, kZeroF4};
-    if constexpr (CAUSAL) read_out<D>(dka, b1, sm.vv + s.row_at);
-    else read_out_pair<D>(dka, b1, sm.vv + s.row_at);
+    read_out_pair<D>(dka, b1, sm.vv + s.row_at);
     __builtin_amdgcn_sched_barrier(0);
     read_out<D>(dva, b2, sm.fk + s.row_at);
     bf16x8 qcol, dcol;
@@ -655,7 +668,8 @@ __device__ __forceinline__ void seg_kv(const BwdArgs& a, int block, unsigned cha
         qx[j] *= iv;
         dx[j] *= iv;
       }
-      add_outer<D>(b1, sm.dd + s.wide_at, pack8(qx));
+      if constexpr (PAIR) add_outer_pair<D>(b1, sm.dd + s.wide_at, qx);
+      else add_outer<D>(b1, sm.dd + s.wide_at, pack8(qx));
       add_outer<D>(b2, sm.fq + s.wide_at, pack8(dx));
       dy = sum_over_groups(dy);
       if (g == 0) sm.y[16 * wave + i] += dy;   // read by this wave alone
@@ -674,15 +688,15 @@ __device__ __forceinline__ void seg_kv(const BwdArgs& a, int block, unsigned cha
 // 64 x (3 + 3) x 256 bidirectional, window 14: 161 and 139.  One pass for dk and dv (four products a tile in
 // place of five, 190 registers, so two workgroups per compute unit): 189 and 145; at three it spills.
 enum Walk { kSumWalk, kQWalk, kKvWalk };
-template <int D, bool ELU1, bool CAUSAL, int WALK>
+template <int D, bool ELU1, bool CAUSAL, bool PAIR, int WALK>
 __global__ __launch_bounds__(SegCfg<D>::NT, 3) void linear_seg_kernel(BwdArgs a, int linear, int rows) {
   static_assert(SegCfg<D>::NT == kBandThreads, "one block size for both kinds of workgroup");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   const int block = blockIdx.x, first = (linear + 7) & ~7;
   if (block < linear) {
     if constexpr (WALK == kSumWalk) seg_sum<D, ELU1>(a, block, smem_raw);
-    else if constexpr (WALK == kQWalk) seg_q<D, ELU1, CAUSAL>(a, block, smem_raw);
-    else seg_kv<D, ELU1, CAUSAL>(a, block, smem_raw);
+    else if constexpr (WALK == kQWalk) seg_q<D, ELU1, CAUSAL, PAIR>(a, block, smem_raw);
+    else seg_kv<D, ELU1, CAUSAL, PAIR>(a, block, smem_raw);
   } else if (block >= first) {
     if constexpr (WALK == kSumWalk) windowed_band<D, kStats>(a, block - first, smem_raw);
     else if constexpr (WALK == kQWalk) windowed_band<D, kDq>(a, block - first, smem_raw);
@@ -691,7 +705,7 @@ __global__ __launch_bounds__(SegCfg<D>::NT, 3) void linear_seg_kernel(BwdArgs a,
   }
 }
 
-template <int D, bool ELU1, bool CAUSAL> hipError_t launch_t(const BwdArgs& a, bool band, hipStream_t s) {
+template <int D, bool ELU1, bool CAUSAL, bool PAIR> hipError_t launch_t(const BwdArgs& a, bool band, hipStream_t s) {
   using C = SegCfg<D>;
   const int heads = a.B * (a.H - a.H0), nseg = a.lin_segments, per_head = CAUSAL ? nseg - 1 : nseg;
   const int rows = band ? (a.N + band_rows(C::NT) - 1) / band_rows(C::NT) * a.H0 * a.B : 0;   // the band's blocks
@@ -705,11 +719,11 @@ template <int D, bool ELU1, bool CAUSAL> hipError_t launch_t(const BwdArgs& a, b
     kern<<<dim3(rows > 0 ? ((linear + 7) & ~7) + band_blocks : linear), dim3(C::NT), smem, s>>>(a, linear, rows);
     e = hipGetLastError();
   };
-  launch(linear_seg_kernel<D, ELU1, CAUSAL, kSumWalk>, sizeof(SegSumSmem<D>), heads * per_head, rows);
+  launch(linear_seg_kernel<D, ELU1, CAUSAL, !CAUSAL, kSumWalk>, sizeof(SegSumSmem<D>), heads * per_head, rows);
   if (e == hipSuccess && nseg > kSegmentsInPlace) e = launch_segment_scan(a.ws_state, heads, nseg, C::STATE, 0, s);
-  launch(linear_seg_kernel<D, ELU1, CAUSAL, kQWalk>, sizeof(SegQSmem<D>), heads * nseg, rows);
+  launch(linear_seg_kernel<D, ELU1, CAUSAL, PAIR, kQWalk>, sizeof(SegQSmem<D>), heads * nseg, rows);
   if (e == hipSuccess && nseg > kSegmentsInPlace) e = launch_segment_scan(bsums, heads, nseg, C::STATE, 1, s);
-  launch(linear_seg_kernel<D, ELU1, CAUSAL, kKvWalk>, sizeof(SegKvSmem<D>), heads * nseg, ((rows + 7) & ~7) + rows);
+  launch(linear_seg_kernel<D, ELU1, CAUSAL, PAIR, kKvWalk>, sizeof(SegKvSmem<D>), heads * nseg, ((rows + 7) & ~7) + rows);
   return e;
 }
 
@@ -731,10 +745,19 @@ Segments backward_segments(int64_t heads, int N, int d, bool causal) {
   return f;
 }
 
+// Roundings.  Over all keys, and for causal calls of less than 256 tokens, the sums in the read-outs and phi(q) / den
+// in the dk walk are bf16 pairs; longer causal calls have a pair in dk's read-out alone.  A chunk of 32 tokens
+// leaves more of a row to the carried sums than the scans' 64 do, whose in-chunk weights are pairs: with one bf16 in
+// dk's read-out dk was 3-5 % further from 64 bits than the scans' over all lengths (4096 tokens: 3.15e-3 of its norm
+// against 3.06e-3; a pair: 2.86e-3), and short heads need the others as well (100 tokens, dq and dk: scans 4.04e-3 and
+// 2.66e-3, one pair 4.08e-3 and 2.68e-3, all 3.82e-3 and 2.55e-3; from 150 on the one is enough).  The pair in the
+// read-out costs 1 us of 114 (64 heads x 4096), all of them 6.
 hipError_t launch_linear_backward_segments(const BwdArgs& a, bool with_windowed, hipStream_t s) {
   if (a.H - a.H0 <= 0 || a.N <= 0 || a.B <= 0) return hipSuccess;
-  if (a.causal) return a.phi == 0 ? launch_t<64, true, true>(a, with_windowed, s) : launch_t<64, false, true>(a, with_windowed, s);
-  return a.phi == 0 ? launch_t<64, true, false>(a, with_windowed, s) : launch_t<64, false, false>(a, with_windowed, s);
+  const bool elu1 = a.phi == 0;
+  if (!a.causal) return elu1 ? launch_t<64, true, false, true>(a, with_windowed, s) : launch_t<64, false, false, true>(a, with_windowed, s);
+  if (a.N < 256) return elu1 ? launch_t<64, true, true, true>(a, with_windowed, s) : launch_t<64, false, true, true>(a, with_windowed, s);
+  return elu1 ? launch_t<64, true, true, false>(a, with_windowed, s) : launch_t<64, false, true, false>(a, with_windowed, s);
 }
 
 }  // namespace gformer

@@ -15,9 +15,10 @@ operands rounded where a kernel could round them, and compares with the oracle:
     1.5e-2 - which is what the kernels do.  The other operands stay one bf16.
 
 The segment walks (d = 64) take chunks of 32 tokens and divide last: S and T = dO v^T enter c in fp32 (c needs no
-numerator), T/den - c is a bf16 pair, and dO is an operand as it came; phi(q)/den, dO/den, S/den and the copies of the
-carried sums are one bf16 each.  The same two statements for them: exactly the oracle's derivative without rounding,
-and the worst row under 1.5e-2 with it.
+numerator), T/den - c is a bf16 pair, so is the copy of the carried sum that dk reads, and dO is an operand as it
+came; phi(q)/den, dO/den, S/den and the other copies are one bf16 each (below 256 tokens phi(q)/den and dq's copy are
+pairs too).  The same two statements for them: exactly the oracle's derivative without rounding, and the worst row
+under 1.5e-2 with it.
 """
 import numpy as np
 
@@ -138,6 +139,7 @@ def segment_walks(q, k, v, dout, rounded, chunk=32):
     R = _rb if rounded else (lambda x: x)
     RT = _pair if rounded else (lambda x: x)
     N, d = q.shape
+    RS = RT if N < 256 else R
     fq, fk = R(_phi(q)), R(_phi(k))
     A, Z = np.zeros((d, d)), np.zeros(d)
     den, c, dfq = np.zeros(N), np.zeros(N), np.zeros((N, d))
@@ -145,7 +147,7 @@ def segment_walks(q, k, v, dout, rounded, chunk=32):
     for n in starts:
         sl = slice(n, min(N, n + chunk))
         S, T = np.tril(fq[sl] @ fk[sl].T), dout[sl] @ v[sl].T
-        r = dout[sl] @ R(A).T
+        r = dout[sl] @ RS(A).T
         den[sl] = S.sum(1) + fq[sl] @ Z
         c[sl] = ((fq[sl] * r).sum(1) + (S * T).sum(1)) / den[sl] ** 2
         W = RT(np.tril(T / den[sl][:, None] - c[sl][:, None]))
@@ -159,9 +161,9 @@ def segment_walks(q, k, v, dout, rounded, chunk=32):
         inv = 1 / den[sl][:, None]
         W = RT(np.tril((dout[sl] @ v[sl].T) * inv - c[sl][:, None]))
         P = R(np.tril(fq[sl] @ fk[sl].T) * inv)
-        dfk[sl] = W.T @ fq[sl] + v[sl] @ R(B1).T - Y[None, :]
+        dfk[sl] = W.T @ fq[sl] + v[sl] @ RT(B1).T - Y[None, :]
         dv[sl] = P.T @ dout[sl] + fk[sl] @ R(B2)
-        B1 += R(fq[sl] * inv).T @ dout[sl]
+        B1 += RS(fq[sl] * inv).T @ dout[sl]
         B2 += fq[sl].T @ R(dout[sl] * inv)
         Y += fq[sl].T @ c[sl]
     slope = lambda f: np.where(f > 1, 1.0, f)

@@ -3,12 +3,14 @@ and segments end, few segments (a walk adds up their sums) and many (a scan ran)
 layer, and a workspace of the least size, which takes the scans instead.  Tolerance: the bf16 mode's."""
 from __future__ import annotations
 
+import numpy as np
 import pytest
 
 from oracle import cpu_oracle as co
 from paper_2412_19829_amd import binding as gb
 from paper_2412_19829_amd import inputs as gi
 from tests.gpu_util import to_device, to_host
+from tests.test_backward_rounding_model import chunked_linear_bwd
 from tests.test_gpu_parity import check_grad, run_bwd, synth
 
 # B, H, N, bidirectional, segments per head (256 compute units)
@@ -40,6 +42,25 @@ def test_gradients(case):
     ref = co.attn_bwd(q, k, v, dout, 8, 0, bidirectional=bool(bidir))
     for g, r, name in zip(run_bwd(q, k, v, dout, "bf16", 8, 0, bidirectional=bidir), ref, ("dq", "dk", "dv")):
         check_grad(g, r, "bf16", f"{name} {case}", dout)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("N", [64, 100, 235, 255, 256, 1000])
+def test_no_further_from_64_bits_than_the_scans(N):
+    """The scans keep more of a row's weights as pairs: no gradient of the walks may be further from the oracle's than
+    theirs (by their rounding model).  Over 24 heads two such errors agree to a percent of themselves."""
+    B, H = 2, 12
+    q, k, v = synth(B, H, N, 64, "bf16", 57)
+    dout = synth(B, H, N, 64, "bf16", 58)[2]
+    ref = co.attn_bwd(q, k, v, dout, 8, 0)
+    scans = [np.empty_like(r) for r in ref]
+    for b in range(B):
+        for h in range(H):
+            one = (x[b, h].astype(np.float64) for x in (q, k, v, dout))
+            for s, g in zip(scans, chunked_linear_bwd(*one, rounded=True, pairs=True)):
+                s[b, h] = gi.round_to_bf16(g.astype(np.float32))
+    for g, s, r, name in zip(run_bwd(q, k, v, dout, "bf16", 8, 0), scans, ref, ("dq", "dk", "dv")):
+        assert np.linalg.norm(g - r) <= 1.01 * np.linalg.norm(s - r), name
 
 
 def test_more_heads_over_all_keys_than_a_grid_holds_are_refused():
