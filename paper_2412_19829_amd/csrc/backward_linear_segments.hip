@@ -19,7 +19,7 @@
 // needs there, and several workgroups share a compute unit and cover each other's barriers.
 //
 // Head size 64.  Measured (us, the scans of backward_linear_mfma.hip and the sweeps of backward_bidir_mfma.hip
-// against these): causal, 52 heads x 4096 tokens, 103 + 99 -> 14 (sums) + 6 (scan) + 45 (dq) + 6 + 39 (dk, dv);
+// against these): causal, 52 heads x 4096 tokens, 103 + 99 -> 14 (sums) + 6 (scan) + 45 (dq) + 6 + 40 (dk, dv);
 // over all keys, 288 heads x 577, 16 + 43 + 25 -> 12 + 35 + 22.  A scan has one workgroup of four waves on a
 // compute unit (85 KB of LDS) and five barriers per 64 tokens, here two to three workgroups interleave.
 // Traffic 27 MB a tensor: 136 MB and 164 MB, 3.0 and 4.2 TB/s.  At head size 128 a wave's sums take 64 registers:
@@ -29,7 +29,8 @@
 // on both and none beat the scans, which stay there.
 //
 // Precision: S, T, den, c, Z, Y and the carried sums are fp32; the weights T/den - c, a difference a
-// gradient row sums with signs, enter their products as bf16 pairs (high half + rounded remainder).
+// gradient row sums with signs, enter their products as bf16 pairs (high half + rounded remainder), and so do some
+// of the carried sums and of phi(q) / den (which and why: launch_linear_backward_segments).
 #include <type_traits>
 
 #include "backward_band.hpp"
