@@ -203,12 +203,12 @@ def _current_stream(t) -> int:
     return raw(t.get_device()) if raw is not None else torch.cuda.current_stream(t.device).cuda_stream
 
 
-def _workspace(nbytes: int, t, stream: Optional[int]):
-    """Workspace of a call on `stream` (None: torch's current one).  It is that stream's memory, so that the
-    allocator, which has it back before the call has run, gives it to nothing that runs beside the call."""
+def _workspace(nbytes: int, t, stream: int):
+    """Workspace of a call on a stream that the caller names.  It is that stream's memory, so that the allocator,
+    which has it back before the call has run, gives it to nothing that runs beside the call."""
     import torch
 
-    if stream is None or stream == _current_stream(t):
+    if stream == _current_stream(t):
         return torch.empty(nbytes, dtype=torch.uint8, device=t.device)
     theirs = torch.cuda.ExternalStream(stream, device=t.device) if stream else torch.cuda.default_stream(t.device)
     with torch.cuda.stream(theirs):
@@ -251,7 +251,8 @@ def gformer_attn_fwd(q, k, v, out, window: int, n_sparse_heads: int, *, phi=GF_P
     ws_ptr, ws_bytes = 0, 0
     if need > 0:
         if workspace is None:
-            workspace = _workspace(need, q, stream)
+            workspace = (torch.empty(need, dtype=torch.uint8, device=q.device) if stream is None
+                         else _workspace(need, q, stream))
         ws_ptr, ws_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
     if stream is None:
         stream = _current_stream(q)
@@ -390,7 +391,8 @@ def gformer_attn_prefill(q, k, v, out, kcache, vcache, state, window: int, n_spa
     ws_ptr, ws_bytes = 0, 0
     if need > 0:
         if workspace is None:
-            workspace = _workspace(need, q, stream)
+            workspace = (torch.empty(need, dtype=torch.uint8, device=q.device) if stream is None
+                         else _workspace(need, q, stream))
         ws_ptr, ws_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
     if stream is None:
         stream = _current_stream(q)
@@ -436,7 +438,8 @@ def gformer_attn_bwd(q, k, v, dout, dq, dk, dv, window: int, n_sparse_heads: int
     ws_ptr, ws_bytes = 0, 0
     if need > 0:
         if workspace is None:
-            workspace = _workspace(need, q, stream)
+            workspace = (torch.empty(need, dtype=torch.uint8, device=q.device) if stream is None
+                         else _workspace(need, q, stream))
         ws_ptr, ws_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
     if stream is None:
         stream = _current_stream(q)
