@@ -291,6 +291,19 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
   r->general_chunk = !p->bidirectional && (cm > 1 || p->impl == GF_IMPL_MFMA_CHUNK);
   if (r->general_chunk && H1 > 0 && !linear_chunk_supported(d, pl.chunk)) return GF_ERR_UNSUPPORTED;
   const long cph = N > 0 ? (N + kStrip - 1) / kStrip : 0;  // real strips per head
+  pl.windowed_threads = kMfmaWindowThreads;
+  const long query_blocks = (H0 > 0 && N > 0) ? (long)B * H0 * ((N + kMfmaWindowRows - 1) / kMfmaWindowRows) : 0;
+  pl.windowed_blocks = (int)query_blocks;
+  {
+    const StreamPlan sp = windowed_stream_plan((int64_t)B * H0, N, window_left(window, p->bidirectional, N),
+                                               window_right(window, p->bidirectional, N));
+    if (p->impl == GF_IMPL_MFMA_STREAM && H0 > 0 && !sp.applies) return GF_ERR_UNSUPPORTED;
+    r->stream = p->impl == GF_IMPL_MFMA_STREAM || (p->impl != GF_IMPL_MFMA_BLOCKED && sp.preferred);
+    if (r->stream && H0 > 0 && N > 0) {
+      pl.windowed_threads = sp.threads;
+      pl.windowed_blocks = (int)sp.blocks;
+    }
+  }
   long piece = 0, vcph = cph, pieces = 0, mid = 0, sub = 1;
   if (p->segment_len != 0 && p->segment_len % pl.chunk != 0) return GF_ERR_INVALID_ARG;
   long own_piece = aligned_piece(heads_lin, cph, kComputeUnits);
@@ -331,10 +344,13 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
     pieces = heads_lin * per_head;
     // The state pass walks a head's segments but the last one.  A workgroup of it is bound by
     // its own chunk-by-chunk walk, so segments are cut into up to four sub-pieces as long as the
-    // sub-pieces stay 4 chunks or longer and fit two workgroups per compute unit.
+    // sub-pieces stay 4 chunks or longer and fit two workgroups per compute unit.  At d = 128 the windowed heads' query
+    // blocks share its launch: where both fit the chip at once without a cut, the cut leaves room for them (prefill of
+    // 2 x 32 x 3001: 156 sums of 12 chunks beside 288 query blocks 36 us, 312 of 6, which need a second round, 43).
     const long carried = heads_lin * (per_head > 0 ? per_head - 1 : 0);
+    const long beside = d == 128 && !r->stream && carried + query_blocks <= 2 * kComputeUnits ? query_blocks : 0;
     for (sub = 4; sub > 1; sub /= 2)
-      if (piece % sub == 0 && piece / sub >= 4 && carried * sub <= 2 * kComputeUnits) break;
+      if (piece % sub == 0 && piece / sub >= 4 && carried * sub + beside <= 2 * kComputeUnits) break;
     mid = carried * sub;
   } else if (heads_lin > 0 && cph > 0) {
     // One workgroup per compute unit (its LDS holds one), each with the same number of chunks;
@@ -362,18 +378,6 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
   r->state_sub = (int)sub;
   pl.segment_len = (int)(piece * kStrip);
   pl.n_segments = (int)pieces;
-  pl.windowed_threads = kMfmaWindowThreads;
-  pl.windowed_blocks = (H0 > 0 && N > 0) ? B * H0 * ((N + kMfmaWindowRows - 1) / kMfmaWindowRows) : 0;
-  {
-    const StreamPlan sp = windowed_stream_plan((int64_t)B * H0, N, window_left(window, p->bidirectional, N),
-                                               window_right(window, p->bidirectional, N));
-    if (p->impl == GF_IMPL_MFMA_STREAM && H0 > 0 && !sp.applies) return GF_ERR_UNSUPPORTED;
-    r->stream = p->impl == GF_IMPL_MFMA_STREAM || (p->impl != GF_IMPL_MFMA_BLOCKED && sp.preferred);
-    if (r->stream && H0 > 0 && N > 0) {
-      pl.windowed_threads = sp.threads;
-      pl.windowed_blocks = (int)sp.blocks;
-    }
-  }
   pl.linear_threads = mfma_linear_threads(d);
   pl.linear_blocks = (int)pieces;
   pl.state_blocks = (int)mid;
@@ -514,8 +518,10 @@ gf_status attn_forward(const void* q, const void* k, const void* v, void* out, v
     if (win && lin && p->overlap) e = side_stream_for_current_device(s, &side);
     // d = 64: the windowed heads' query blocks ride in the read-out's launch (linear_mfma.hip).  Not the
     // streaming kernel (other block size), a forced overlap, or a launch mask that names one of the two.
-    const bool together = win && (mask & GF_LAUNCH_LINEAR_MAIN) && !p->overlap && !stream && !r.general_chunk &&
-                          linear_main_takes_windowed(a);
+    // d = 128: in the state pass's, under the same conditions.
+    const bool joint = win && !p->overlap && !stream;
+    const bool together = joint && (mask & GF_LAUNCH_LINEAR_MAIN) && !r.general_chunk && linear_main_takes_windowed(a);
+    const bool with_state = joint && (mask & GF_LAUNCH_LINEAR_STATE) && linear_state_takes_windowed(a);
     bool forked = false;
     if (side && e == hipSuccess) {
       // fork: the windowed heads wait for what is already in `s`, then run beside the linear ones
@@ -526,21 +532,22 @@ gf_status attn_forward(const void* q, const void* k, const void* v, void* out, v
     }
     // The read-out kernel wants every compute unit at once (one piece each), so only the state
     // pass, whose small workgroups pack two to a unit, shares the chip with the windowed heads.
-    if ((mask & GF_LAUNCH_LINEAR_STATE) && e == hipSuccess) e = launch_linear_state_mfma(a, s);
+    if ((mask & GF_LAUNCH_LINEAR_STATE) && e == hipSuccess) e = launch_linear_state_mfma(a, with_state, s);
     if (forked) {
       // join, also after a failed launch: a side stream left waiting on the fork would break a
       // capture in progress and leave `s` unordered against what did get enqueued
       const hipError_t j1 = hipEventRecord(side->join, side->stream);
       const hipError_t j2 = j1 == hipSuccess ? hipStreamWaitEvent(s, side->join, 0) : j1;
       if (e == hipSuccess) e = j2;
-    } else if (win && !side && !together && e == hipSuccess) {
+    } else if (win && !side && !together && !with_state && e == hipSuccess) {
       e = launch_windowed(s);
     }
     if ((mask & GF_LAUNCH_LINEAR_MAIN) && e == hipSuccess)
       e = together ? launch_linear_main_windowed_mfma(a, s)
                    : r.general_chunk ? launch_linear_chunk(a, s) : launch_linear_main_mfma(a, s);
   }
-  if (e == hipSuccess) e = launch_fill_rings(a, bf16, s);
+  // (the query blocks of the bf16 kernels fill the rings themselves)
+  if (e == hipSuccess && (r.plan.impl == GF_IMPL_SCALAR || r.stream)) e = launch_fill_rings(a, bf16, s);
   return e == hipSuccess ? GF_OK : GF_ERR_DEVICE;
 }
 

@@ -169,7 +169,9 @@ struct StreamPlan {
 };
 StreamPlan windowed_stream_plan(int64_t heads, int N, int wleft, int wright);
 hipError_t launch_windowed_stream(const AttnArgs& a, hipStream_t s);
-hipError_t launch_linear_state_mfma(const AttnArgs& a, hipStream_t s);
+// with_windowed: the windowed heads' query blocks ride in the state pass's launch, where that takes them along.
+bool linear_state_takes_windowed(const AttnArgs& a);
+hipError_t launch_linear_state_mfma(const AttnArgs& a, bool with_windowed, hipStream_t s);
 hipError_t launch_linear_main_mfma(const AttnArgs& a, hipStream_t s);
 // The read-out and the windowed heads' query blocks in one launch, where the former takes them along.
 bool linear_main_takes_windowed(const AttnArgs& a);

@@ -34,6 +34,7 @@
 #include "linear_common.hpp"
 #include "windowed_block.hpp"
 
+#include <algorithm>
 #include <type_traits>
 
 // Register sets of the read-out kernel's producers (chunks of loads in flight): 2 or 3.  Three
@@ -134,124 +135,178 @@ __device__ __forceinline__ float update_state(f32x16 (&sacc)[LinCfg<D>::ET], con
 //     over the chunks of that head lying in sub-piece j-1 and writes them to workspace slot j.
 //     Waves [0, NWC) contract; waves [NWC, 2 NWC) load, map and stage the next chunk.
 // -----------------------------------------------------------------------------------------
-template <int D, bool ELU1>
-__global__ __launch_bounds__(LinCfg<D>::NT, 2) void linear_state_kernel(AttnArgs a) {
-  using C = LinCfg<D>;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  StateSmem<D>& sm = *reinterpret_cast<StateSmem<D>*>(smem_raw);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int ln = lane & 31, lh = lane >> 5;
+// What workgroup `block` of `total` sums: workspace slot `slot`, chunks [lc0, lc1) of `head`; false: nothing.
+struct StateJob {
+  int slot, head, lc0, lc1;
+};
+__device__ __forceinline__ bool state_job(const AttnArgs& a, int block, int total, StateJob& j) {
   const int ls = a.piece_chunks / a.state_sub;
   // Workgroups are dealt round-robin to the 8 XCDs.  Which sub-pieces have something to sum is
   // periodic in the block index (with two segments per head every second group of state_sub
   // blocks is idle), and a period that divides 8 would leave whole XCDs without work: give each
   // XCD one contiguous run of the logical block order instead.
-  int lb = blockIdx.x;
-  {
-    constexpr int kXcds = 8;
-    const int total = gridDim.x, per = total / kXcds, rem = total % kXcds;
-    const int xcd = lb % kXcds, slot = lb / kXcds;
-    lb = xcd * per + min(xcd, rem) + slot;
-  }
-  int q, head, lc0, lc1;                     // workspace slot; chunks [lc0, lc1) of `head`
+  constexpr int kXcds = 8;
+  const int per = total / kXcds, rem = total % kXcds;
+  const int xcd = block % kXcds;
+  const int lb = xcd * per + min(xcd, rem) + block / kXcds;
   if (a.causal) {
-    q = lb + 1;
-    const int e = q * ls;                    // the boundary, as a global chunk index
-    if (e % a.vcph == 0) return;             // on a head boundary: nothing is carried
-    head = e / a.vcph;
-    const int next_main = (q + a.state_sub - 1) / a.state_sub * a.piece_chunks;
-    if (next_main >= (head + 1) * a.vcph || next_main >= a.n_pieces * a.piece_chunks)
-      return;                                // no piece starts later in this head: nobody reads it
-    lc1 = e % a.vcph;
-    lc0 = max(lc1 - ls, 0);
+    j.slot = lb + 1;
+    const int e = j.slot * ls;               // the boundary, as a global chunk index
+    if (e % a.vcph == 0) return false;       // on a head boundary: nothing is carried
+    j.head = e / a.vcph;
+    const int next_main = (j.slot + a.state_sub - 1) / a.state_sub * a.piece_chunks;
+    if (next_main >= (j.head + 1) * a.vcph || next_main >= a.n_pieces * a.piece_chunks)
+      return false;                          // no piece starts later in this head: nobody reads it
+    j.lc1 = e % a.vcph;
+    j.lc0 = max(j.lc1 - ls, 0);
   } else {
     // bidirectional: every sub-piece is summed (pieces never straddle heads in this mode);
     // slot q holds the sum over sub-piece q itself
-    q = lb;
-    head = q * ls / a.vcph;
-    lc0 = q * ls % a.vcph;
-    lc1 = min(lc0 + ls, a.cph);
-    if (lc0 >= lc1) return;                  // virtual padding only (the planner avoids it)
+    j.slot = lb;
+    j.head = j.slot * ls / a.vcph;
+    j.lc0 = j.slot * ls % a.vcph;
+    j.lc1 = min(j.lc0 + ls, a.cph);
+    if (j.lc0 >= j.lc1) return false;        // virtual padding only (the planner avoids it)
   }
-  const HeadPtrs<D> hp = head_ptrs<D>(a, head);
-  const int N = a.N;
-  const int nchunks = lc1 - lc0;
+  return true;
+}
 
-  if (wave >= C::NWC) {
-    // ---- producers ----
-    const Staging<D> st(tid - C::NTC);
-    const PieceOffsets<D> ko(st, a.k.sn), vo(st, a.v.sn);
-    u32x4 ka[C::PIECES], va[C::PIECES], kb[C::PIECES], vb[C::PIECES];
-    auto load = [&](u32x4 (&kr)[C::PIECES], u32x4 (&vr)[C::PIECES], int n) {
-      const int t0 = (lc0 + n) * CH;
-      // plain loads here: with two small workgroups per compute unit they measured 6 % faster
-      // than the non-temporal ones the one-per-unit read-out kernel prefers (43 against 46 us)
-      load_chunk<D, false>(kr, hp.k, t0, N, ko);
-      load_chunk<D, false>(vr, hp.v, t0, N, vo);
-    };
-    auto stage = [&](const u32x4 (&kr)[C::PIECES], const u32x4 (&vr)[C::PIECES], int n) {
-      const int t0 = (lc0 + n) * CH;
-      StateTiles<D>& b = sm.buf[n & 1];
-      const bool full = t0 + CH <= N;  // uniform; only a head's last chunk can be ragged
-#pragma unroll
-      for (int i = 0; i < C::PIECES; ++i) {
-        const int row = st.r0 + i * C::RP;
-        const bool valid = full || t0 + row < N;  // rows past the end contribute nothing
-        const u32x4 fk = map_features<ELU1>(kr[i]);
-        *reinterpret_cast<u32x4*>(&b.fk[row * C::KROW + st.col]) = valid ? fk : kZero4;
-        *reinterpret_cast<u32x4*>(&b.v[row * C::VROW + st.col]) = valid ? vr[i] : kZero4;
-      }
-    };
-    // chunk m travels in set m % 2; a set is reloaded (two chunks ahead) as soon as it is staged.
-    // A sub-piece of more than four chunks runs a condition-free lead-in and condition-free
-    // steady rounds, so that the compiler's wait counters know exactly which loads are in
-    // flight; only its last rounds (and short sub-pieces) test before every load and stage.
-    auto lead_in = [&](auto steady) {
-      constexpr bool S = decltype(steady)::value;
-      load(ka, va, 0);
-      if (S || nchunks > 1) load(kb, vb, 1);
-      stage(ka, va, 0);
-      if (S || nchunks > 2) load(ka, va, 2);
-      lds_barrier();
-    };
-    auto round2 = [&](int n, auto steady) {
-      constexpr bool S = decltype(steady)::value;
-      if (S || n + 1 < nchunks) stage(kb, vb, n + 1);
-      if (S || n + 3 < nchunks) load(kb, vb, n + 3);
-      lds_barrier();
-      if (!S && n + 1 >= nchunks) return false;
-      if (S || n + 2 < nchunks) stage(ka, va, n + 2);
-      if (S || n + 4 < nchunks) load(ka, va, n + 4);
-      lds_barrier();
-      return true;
-    };
-    int n = 0;
-    if (nchunks > 4) {
-      lead_in(std::true_type{});
-      for (; n + 4 < nchunks; n += 2) round2(n, std::true_type{});
-    } else {
-      lead_in(std::false_type{});
-    }
-    for (; n < nchunks; n += 2)
-      if (!round2(n, std::false_type{})) break;
-    return;
+// Moves chunks from memory to the LDS buffers, mapped: thread `ptid` of 64 * NWC.
+template <int D, bool ELU1> struct StateMover {
+  using C = LinCfg<D>;
+  struct Set { u32x4 k[C::PIECES], v[C::PIECES]; };
+  const Staging<D> st;
+  const PieceOffsets<D> ko, vo;
+  const uint16_t *kp, *vp;
+  StateTiles<D>* const buf;
+  const int lc0, N;
+  __device__ __forceinline__ StateMover(const AttnArgs& a, const StateJob& j, StateSmem<D>& sm, int ptid)
+      : st(ptid), ko(st, a.k.sn), vo(st, a.v.sn), buf(sm.buf), lc0(j.lc0), N(a.N) {
+    const HeadPtrs<D> hp = head_ptrs<D>(a, j.head);
+    kp = hp.k;
+    vp = hp.v;
   }
-  // ---- consumers ----
+  __device__ __forceinline__ void load(Set& s, int n) const {
+    const int t0 = (lc0 + n) * CH;
+    // plain loads here: with two small workgroups per compute unit they measured 6 % faster
+    // than the non-temporal ones the one-per-unit read-out kernel prefers (43 against 46 us)
+    load_chunk<D, false>(s.k, kp, t0, N, ko);
+    load_chunk<D, false>(s.v, vp, t0, N, vo);
+  }
+  __device__ __forceinline__ void stage(const Set& s, int n) const {
+    const int t0 = (lc0 + n) * CH;
+    StateTiles<D>& b = buf[n & 1];
+    const bool full = t0 + CH <= N;  // uniform; only a head's last chunk can be ragged
+#pragma unroll
+    for (int i = 0; i < C::PIECES; ++i) {
+      const int row = st.r0 + i * C::RP;
+      const bool valid = full || t0 + row < N;  // rows past the end contribute nothing
+      const u32x4 fk = map_features<ELU1>(s.k[i]);
+      *reinterpret_cast<u32x4*>(&b.fk[row * C::KROW + st.col]) = valid ? fk : kZero4;
+      *reinterpret_cast<u32x4*>(&b.v[row * C::VROW + st.col]) = valid ? s.v[i] : kZero4;
+    }
+  }
+};
+// Chunk m travels in set m % 2; a set is reloaded (two chunks ahead) as soon as it is staged.
+// A sub-piece of more than four chunks runs a condition-free lead-in and condition-free
+// steady rounds, so that the compiler's wait counters know exactly which loads are in
+// flight; only its last rounds (and short sub-pieces) test before every load and stage.
+// `contract(n)` is this wave's share of the products of chunk n, between two barriers.
+template <typename Mover, typename Contract>
+__device__ __forceinline__ void walk_state(const Mover& mv, int nchunks, Contract contract) {
+  typename Mover::Set sa, sb;
+  auto lead_in = [&](auto steady) {
+    constexpr bool S = decltype(steady)::value;
+    mv.load(sa, 0);
+    if (S || nchunks > 1) mv.load(sb, 1);
+    mv.stage(sa, 0);
+    if (S || nchunks > 2) mv.load(sa, 2);
+    lds_barrier();
+  };
+  auto round2 = [&](int n, auto steady) {
+    constexpr bool S = decltype(steady)::value;
+    if (S || n + 1 < nchunks) mv.stage(sb, n + 1);
+    if (S || n + 3 < nchunks) mv.load(sb, n + 3);
+    contract(n);
+    lds_barrier();
+    if (!S && n + 1 >= nchunks) return false;
+    if (S || n + 2 < nchunks) mv.stage(sa, n + 2);
+    if (S || n + 4 < nchunks) mv.load(sa, n + 4);
+    contract(n + 1);
+    lds_barrier();
+    return true;
+  };
+  int n = 0;
+  if (nchunks > 4) {
+    lead_in(std::true_type{});
+    for (; n + 4 < nchunks; n += 2) round2(n, std::true_type{});
+  } else {
+    lead_in(std::false_type{});
+  }
+  for (; n < nchunks; n += 2)
+    if (!round2(n, std::false_type{})) break;
+}
+
+// NT = LinCfg::NT threads: half of the waves contract, half load, map and stage the next chunk.  Half as many
+// (d = 128, beside query blocks of 256 threads): every wave does both, its value columns' products next to its
+// quarter of the staging; alone this form takes 0.5 % longer (the layer of 4 x 32 x 8192, us: 280.6 against 279.6).
+template <int D, bool ELU1, int NT>
+__device__ __forceinline__ void linear_state_block(const AttnArgs& a, int block, int total, unsigned char* smem_raw) {
+  using C = LinCfg<D>;
+  StateSmem<D>& sm = *reinterpret_cast<StateSmem<D>*>(smem_raw);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int ln = lane & 31, lh = lane >> 5;
+  StateJob j;
+  if (!state_job(a, block, total, j)) return;   // uniform
+  const int nchunks = j.lc1 - j.lc0;
   f32x16 sacc[C::ET];
 #pragma unroll
   for (int i = 0; i < C::ET; ++i)
 #pragma unroll
     for (int r = 0; r < 16; ++r) sacc[i][r] = 0.f;
   float zacc = 0.f;
-  lds_barrier();
-  for (int n = 0; n < nchunks; ++n) {
-    zacc += update_state<D>(sacc, sm.buf[n & 1].fk, sm.buf[n & 1].v, wave, lane);
+  auto contract = [&](int n) { zacc += update_state<D>(sacc, sm.buf[n & 1].fk, sm.buf[n & 1].v, wave, lane); };
+  if constexpr (NT == C::NTC) {
+    walk_state(StateMover<D, ELU1>(a, j, sm, tid), nchunks, contract);
+  } else {
+    static_assert(NT == C::NT, "contracting and staging waves");
+    if (wave >= C::NWC) {
+      walk_state(StateMover<D, ELU1>(a, j, sm, tid - C::NTC), nchunks, [](int) {});
+      return;
+    }
     lds_barrier();
+    for (int n = 0; n < nchunks; ++n) {
+      contract(n);
+      lds_barrier();
+    }
   }
-  float* dst = a.ws_states + (int64_t)q * C::STATE;
+  float* dst = a.ws_states + (int64_t)j.slot * C::STATE;
   state_store<D>(dst, sacc, wave, lane);
   zacc += __shfl_xor(zacc, 32, 64);
   if (lh == 0) dst[D * D + 32 * wave + ln] = zacc;
+}
+
+template <int D, bool ELU1>
+__global__ __launch_bounds__(LinCfg<D>::NT, 2) void linear_state_kernel(AttnArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  linear_state_block<D, ELU1, LinCfg<D>::NT>(a, blockIdx.x, gridDim.x, smem_raw);
+}
+
+// The sums and the windowed heads in one launch (d = 128): first one kind's blocks, from the next multiple of 8 on
+// (the XCDs keep their runs) the other's.  Either kernel by itself leaves part of the chip idle (few blocks, each a
+// chain through its chunks or tiles) and the two wait on different things (memory; vector and matrix units).  Whichever
+// block is the longer chain goes first, so that the short ones fill what it leaves.  Same bits as two launches; the
+// whole layer (us, two launches -> one, windowed blocks first / sums first): prefill of 2 x 32 x 3001, window 256, H0 = 6
+// (7 tiles, 12 chunks) 91.2 -> 70.8 / 71.1; 1 x 32 x 4096, window 512 (11 tiles, 8 chunks) 80.8 -> 62.4 / 66.7;
+// 2 x 32 x 3001, window 64, H0 = 16 (4, 4) 87.6 -> 78.8 / 84.4; 1 x 16 x 20000, window 256 (7, 17) 108.9 -> 117.3 / 106.7;
+// 1 x 32 x 32768, window 512 (11, 57) 343 -> 346 / 342; 2 x 16 x 1000, window 128 42.7 -> 33.3 either way.
+template <bool ELU1>
+__global__ __launch_bounds__(kMfmaWindowThreads, 2) void linear_state_windowed_kernel(AttnArgs a, int sums, int blocks, bool sums_first) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  const int sum_at = sums_first ? 0 : (blocks + 7) & ~7, win_at = sums_first ? (sums + 7) & ~7 : 0;
+  const int sum = (int)blockIdx.x - sum_at, block = (int)blockIdx.x - win_at;
+  if (sum >= 0 && sum < sums) linear_state_block<128, ELU1, kMfmaWindowThreads>(a, sum, sums, smem_raw);
+  else if (block >= 0 && block < blocks) windowed_block<128, false>(a, block, smem_raw);
 }
 
 // (2) Slot j holds the sums over the part of its head that lies in sub-piece j-1.  Inside every
@@ -767,18 +822,29 @@ __global__ __launch_bounds__(256, 2) void linear_main_windowed_kernel(AttnArgs a
   else if (block < a.n_pieces) linear_main_block<64, ELU1, CAUSAL, EMIT>(a, block, smem_raw);
 }
 
-template <int D> hipError_t launch_state_t(const AttnArgs& a, hipStream_t s) {
+int state_blocks(const AttnArgs& a) { return a.n_pieces * a.state_sub - (a.causal ? 1 : 0); }
+
+template <int D> hipError_t launch_state_t(const AttnArgs& a, bool with_windowed, hipStream_t s) {
   using C = LinCfg<D>;
-  const int heads = a.B * (a.H - a.H0);
-  const int smem = (int)sizeof(StateSmem<D>);
-  const dim3 grid(a.n_pieces * a.state_sub - (a.causal ? 1 : 0)), block(C::NT);
-  hipError_t e;
-  if (a.phi == 0) {
-    if ((e = allow_lds(linear_state_kernel<D, true>, smem)) != hipSuccess) return e;
-    linear_state_kernel<D, true><<<grid, block, smem, s>>>(a);
-  } else {
-    if ((e = allow_lds(linear_state_kernel<D, false>, smem)) != hipSuccess) return e;
-    linear_state_kernel<D, false><<<grid, block, smem, s>>>(a);
+  const int heads = a.B * (a.H - a.H0), sums = state_blocks(a);
+  int smem = (int)sizeof(StateSmem<D>);
+  hipError_t e = hipSuccess;
+  if constexpr (D == 128) {
+    if (with_windowed) {
+      if (smem < (int)sizeof(WinSmem<D>)) smem = (int)sizeof(WinSmem<D>);
+      const int blocks = (a.N + BR - 1) / BR * a.H0 * a.B;
+      const int tiles = std::min((a.wleft + a.wright + BR - 1) / BC, (a.N - 1) / BC) + 1;   // of a query block's band
+      const bool sums_first = a.piece_chunks / a.state_sub > tiles;
+      const dim3 grid(sums_first ? ((sums + 7) & ~7) + blocks : ((blocks + 7) & ~7) + sums);
+      const auto kern = a.phi == 0 ? linear_state_windowed_kernel<true> : linear_state_windowed_kernel<false>;
+      if ((e = allow_lds(kern, smem)) != hipSuccess) return e;
+      kern<<<grid, dim3(kMfmaWindowThreads), smem, s>>>(a, sums, blocks, sums_first);
+    }
+  }
+  if (!with_windowed) {
+    const auto kern = a.phi == 0 ? linear_state_kernel<D, true> : linear_state_kernel<D, false>;
+    if ((e = allow_lds(kern, smem)) != hipSuccess) return e;
+    kern<<<dim3(sums), dim3(C::NT), smem, s>>>(a);
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (uses_prefix_kernel(a)) {
@@ -834,10 +900,16 @@ hipError_t launch_linear_main_windowed_mfma(const AttnArgs& a, hipStream_t s) {
   return a.final_state ? launch_main_windowed_t<true, true>(a, s) : launch_main_windowed_t<true, false>(a, s);
 }
 
-hipError_t launch_linear_state_mfma(const AttnArgs& a, hipStream_t s) {
-  if (a.H - a.H0 <= 0 || a.N <= 0 || a.B <= 0 || !a.ws_states) return hipSuccess;
-  if (a.causal && a.n_pieces <= 1) return hipSuccess;
-  return a.d == 64 ? launch_state_t<64>(a, s) : launch_state_t<128>(a, s);
+static bool has_state_pass(const AttnArgs& a) {
+  return a.H - a.H0 > 0 && a.N > 0 && a.B > 0 && a.ws_states && !(a.causal && a.n_pieces <= 1);
+}
+bool linear_state_takes_windowed(const AttnArgs& a) {
+  const int64_t blocks = (int64_t)a.n_pieces * a.state_sub + (int64_t)((a.N + BR - 1) / BR) * a.H0 * a.B;
+  return a.d == 128 && a.H0 > 0 && has_state_pass(a) && a.scale >= 0.f && blocks < (1 << 22);
+}
+hipError_t launch_linear_state_mfma(const AttnArgs& a, bool with_windowed, hipStream_t s) {
+  if (!has_state_pass(a)) return hipSuccess;
+  return a.d == 64 ? launch_state_t<64>(a, false, s) : launch_state_t<128>(a, with_windowed, s);
 }
 
 hipError_t launch_linear_main_mfma(const AttnArgs& a, hipStream_t s) {

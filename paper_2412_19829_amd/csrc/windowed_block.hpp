@@ -303,6 +303,21 @@ __device__ __forceinline__ void windowed_block(const AttnArgs& a, int block, uns
       __builtin_nontemporal_store(o, reinterpret_cast<u32x4*>(op + (int64_t)(i0 + row) * a.osn + col));
     }
   }
+
+  // the hand-over to decoding: the block's rows among the last `window` keys and values go to their ring slots
+  if (a.kring && i0 + BR > N - a.window) {
+    uint16_t* kring = reinterpret_cast<uint16_t*>(a.kring) + ((int64_t)b * a.H0 + h) * a.window * D;
+    uint16_t* vring = reinterpret_cast<uint16_t*>(a.vring) + ((int64_t)b * a.H0 + h) * a.window * D;
+    const int col = 8 * (tid % (D / 8));
+#pragma unroll 4
+    for (int row = tid / (D / 8); row < BR; row += kMfmaWindowThreads / (D / 8)) {
+      const int t = i0 + row;
+      if (t >= N || t < N - a.window) continue;
+      const int64_t at = (int64_t)(t % a.window) * D + col;
+      *reinterpret_cast<u32x4*>(kring + at) = *reinterpret_cast<const u32x4*>(kp + (int64_t)t * a.k.sn + col);
+      *reinterpret_cast<u32x4*>(vring + at) = *reinterpret_cast<const u32x4*>(vp + (int64_t)t * a.v.sn + col);
+    }
+  }
 }
 
 }  // namespace
