@@ -6,11 +6,17 @@
 // den_i = fq_i.Z_i + eps, g_i = dO_i / den_i, c_i = g_i.(fq_i^T A_i) / den_i:
 //   dfq_i = A_i g_i - c_i Z_i,
 //   dfk_j = B_j v_j - Y_j,  dv_j = B_j^T fk_j,   B_j = sum_{i>=j} fq_i g_i^T,  Y_j = sum_{i>=j} c_i fq_i.
-// In chunks of 64 tokens, with S = tril(fq fk^T), T' = tril(g v^T - c 1^T) (row i, column j <= i)
+// In chunks of 64 tokens, with S = tril(fq fk^T), T = tril(dO v^T), T' = T / den - tril(c 1^T) (row i, column j <= i)
 // and the sums (A, Z) over earlier chunks, (B, Y) over later chunks:
-//   forward scan:  num = S v + fq A,  den = rowsum(S) + fq.Z + eps,  c = rowdot(dO, num) / den^2,
-//                  dfq = T' fk + g A^T - c Z^T;           then A += fk^T v, Z += colsum(fk)
-//   reverse scan:  dfk = T'^T fq + v B^T - 1 Y^T,  dv = S^T g + fk B;   then B += fq^T g, Y += fq^T c
+//   forward scan:  r = A dO,  den = rowsum(S) + fq.Z + eps,  c = (fq.r + rowsum(S * T)) / den^2 (which is
+//                  dO.num / den^2 without a numerator),  dfq = T' fk + r / den - c Z^T;   then A += fk^T v, Z += colsum(fk)
+//   reverse scan:  dfk = T'^T fq + v B^T - 1 Y^T,  dv = (S / den)^T dO + fk B;   then B += fq^T dO / den, Y += fq^T c
+// What bounds them: 13.3 tensors' worth of traffic (the scans' eight reads and three writes, and what light rounds
+// read again) at 4.2 TB/s on 128 heads x 8192, of the 4.9 a copy reaches; below that the LDS pipeline.  With the
+// numerator as two products of its own (S as a pair), dO and dO / den as tiles of their own, the 32 x 32 tile above the
+// diagonal computed and multiplied, and the column sums read from LDS element by element, the same scans took 953 us
+// (853 now; 4 x (6 + 26) heads x 8192 with the windowed heads 1083 and 1000; 32 x 1000 81.5 and 72.0).  Row stores
+// behind the next chunk's staging and loads instead of in front of it: 883.
 // These are the kernels of d = 128, and of d = 64 where the workspace holds no segment sums.
 // One workgroup per (batch, head), segment and scan: with fewer heads than compute units a head
 // is cut into up to four segments, and a workgroup first sums the chunks in front of (behind)
@@ -30,35 +36,97 @@ namespace {
 // T' is a difference of two nearly equal terms and a gradient row sums it against phi with
 // signs: its rounding to one bf16 is the largest single error of these kernels.  It is therefore
 // kept as a pair, bf16(T') in `tp` and bf16(T' - bf16(T')) in `tl` (16 mantissa bits), and every
-// product with T' runs over both.  The forward scan does the same with S (`sm`, `sl`) for the
-// numerator, and sums both halves into the denominator, because c = dO.num / den^2 enters every
-// T' of its row; dv = S^T g in the reverse scan takes the one-bf16 S (its rows do not cancel).
-template <int D, int RS_> struct LbSmemBase {
+// product with T' runs over both.  S and T enter den and c, which enter every T' of their row, as the fp32
+// products they are; dv = S^T g in the reverse scan takes S as one bf16 (its rows do not cancel).
+template <int D> struct LbSmemBase {
   using C = LbCfg<D>;
-  static constexpr int RS = RS_;      // row stride of the carried sum's operand copy
   uint16_t fq[CH * C::R], fk[CH * C::R], v[CH * C::R], g[CH * C::R];
-  uint16_t st[D * RS];                // bf16 copy of the carried sum, [feature][value]
-  uint16_t sm[CH * SR], tp[CH * SR];  // S and T' (forward scan: [i][j]; reverse scan: [j][i])
-  uint16_t tl[CH * SR];               // low half of T'
+  uint16_t st[D * C::R];              // bf16 copy of the carried sum, [feature][value]
+  uint16_t tp[CH * SR], tl[CH * SR];  // T' (forward scan: [i][j]; reverse scan: [j][i]), its low half
   float z[D];                         // Z (forward scan) or Y (reverse scan)
-  float zpart[C::ZP][D];
-  float dz[CH], den[CH], cc[CH];
+  float zpart[C::MT][D];
 };
-template <int D> struct LbSmem : LbSmemBase<D, LbCfg<D>::R> {
-  uint16_t sl[CH * SR];               // low half of S
-  float rs[2][CH], pd[LbCfg<D>::MT][CH];
+template <int D> struct LbSmem : LbSmemBase<D> {
+  float part[2][3][32];               // row sums of S and of S * T per 32 x 32 tile on or below the diagonal
+  float red[2][LbCfg<D>::MT][CH];     // phi(q).(A dO) and phi(q).Z per feature block
 };
 
-// the reverse scan also keeps dO itself: T' is formed as (dO.v)/den - c in fp32, exactly as the
-// forward scan forms c, so that the two cancel where they must (a token that only sees itself).
-// Its tiles fill the LDS of a compute unit at d = 128: the operand copy of the carried sum and
-// dO (read by rows only) take the narrower row stride there.
-template <int D> struct LbSmemKv : LbSmemBase<D, D + 8> {
-  static constexpr int RD = D + 8;
-  uint16_t dout[CH * RD];
+// the reverse scan scales by 1/den where a product needs it and keeps dO itself in the tile `g`: T' is formed as
+// (dO.v)/den - c in fp32, exactly as the forward scan forms c, so that the two cancel where they must (a token that
+// only sees itself).
+template <int D> struct LbSmemKv : LbSmemBase<D> {
+  uint16_t sm[CH * SR];               // S / den, [j][i]
+  float dz[CH], den[CH], cc[CH];      // den: the reciprocal
 };
 static_assert(sizeof(LbSmemKv<128>) <= 160 * 1024 && sizeof(LbSmem<128>) <= 160 * 1024,
               "one workgroup's tiles must fit the LDS of a compute unit");
+
+// Sum over this lane's eight tokens of w * operand, w in fp32.
+__device__ __forceinline__ float weighted8(bf16x8 x, const float* w, float acc) {
+  const u32x4 u = as_u32x4(x);
+  const float4 a = *reinterpret_cast<const float4*>(w), b = *reinterpret_cast<const float4*>(w + 4);
+  acc = fmaf(bf16_lo(u[0]), a.x, fmaf(bf16_hi(u[0]), a.y, acc));
+  acc = fmaf(bf16_lo(u[1]), a.z, fmaf(bf16_hi(u[1]), a.w, acc));
+  acc = fmaf(bf16_lo(u[2]), b.x, fmaf(bf16_hi(u[2]), b.y, acc));
+  return fmaf(bf16_lo(u[3]), b.z, fmaf(bf16_hi(u[3]), b.w, acc));
+}
+__device__ __forceinline__ float sum8(bf16x8 x, float acc) {
+  const u32x4 u = as_u32x4(x);
+#pragma unroll
+  for (int w = 0; w < 4; ++w) acc = dot2_ones_bf16(u[w], acc);
+  return acc;
+}
+// The operand with each of its eight tokens scaled.
+__device__ __forceinline__ bf16x8 scaled8(bf16x8 x, const float* w) {
+  const u32x4 u = as_u32x4(x);
+  const float4 a = *reinterpret_cast<const float4*>(w), b = *reinterpret_cast<const float4*>(w + 4);
+  u32x4 o;
+  o[0] = pack_bf16(bf16_lo(u[0]) * a.x, bf16_hi(u[0]) * a.y);
+  o[1] = pack_bf16(bf16_lo(u[1]) * a.z, bf16_hi(u[1]) * a.w);
+  o[2] = pack_bf16(bf16_lo(u[2]) * b.x, bf16_hi(u[2]) * b.y);
+  o[3] = pack_bf16(bf16_lo(u[3]) * b.z, bf16_hi(u[3]) * b.w);
+  return as_bf16x8(o);
+}
+// Carried sum, tile u of a wave: value block vt, feature block ft0 + u.  The waves of a feature block share the column
+// sums of a chunk: each adds up the operand of the steps kk with kk % MT == vt, picked out with wave-uniform selects
+// (a branch there splits the products' schedule: 1003 against 1001 us, 725 against 700 on short heads).
+template <int D> struct SumTiles {
+  int vt, ft0;
+  __device__ __forceinline__ explicit SumTiles(int wave) : vt(wave * LbCfg<D>::TPW / LbCfg<D>::MT), ft0(wave * LbCfg<D>::TPW % LbCfg<D>::MT) {}
+  static constexpr int STEPS = CH / 16 / LbCfg<D>::MT;   // steps a wave adds up: kk = x * MT + vt
+  struct Picked { bf16x8 x[STEPS]; };
+  __device__ __forceinline__ void pick(Picked& p, int kk, bf16x8 op) const {
+    constexpr int MT = LbCfg<D>::MT;
+    p.x[kk / MT] = kk % MT == 0 || kk % MT == vt ? op : p.x[kk / MT];
+  }
+  __device__ __forceinline__ float sum(const Picked& p, float acc) const {
+#pragma unroll
+    for (int x = 0; x < STEPS; ++x) acc = sum8(p.x[x], acc);
+    return acc;
+  }
+  __device__ __forceinline__ float sum(const Picked& p, const float* weights, int lh, float acc) const {
+#pragma unroll
+    for (int x = 0; x < STEPS; ++x) acc = weighted8(p.x[x], weights + 16 * (x * LbCfg<D>::MT + vt) + 8 * lh, acc);
+    return acc;
+  }
+  // the lane's column sums of its feature blocks for the other waves
+  __device__ __forceinline__ void put(float (&zpart)[LbCfg<D>::MT][D], const float (&zs)[LbCfg<D>::TPW], int ln, int lh) const {
+#pragma unroll
+    for (int u = 0; u < LbCfg<D>::TPW; ++u) {
+      const float z = sum_over_halves(zs[u]);
+      if (lh == 0) zpart[vt][32 * (ft0 + u) + ln] = z;
+    }
+  }
+  // bf16 copy of the sums, the operand of the next chunk's products
+  __device__ __forceinline__ void copy(uint16_t* st, const f32x16 (&sacc)[LbCfg<D>::TPW], int ln, int lh) const {
+#pragma unroll
+    for (int u = 0; u < LbCfg<D>::TPW; ++u)
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4)
+        put4(&st[(32 * (ft0 + u) + ln) * LbCfg<D>::R + 32 * vt + 8 * g4 + 4 * lh], sacc[u][4 * g4 + 0],
+             sacc[u][4 * g4 + 1], sacc[u][4 * g4 + 2], sacc[u][4 * g4 + 3]);
+  }
+};
 
 // ---------------------------------------------------------------------------------------
 // forward scan: dq, and (den_i, c_i) into the workspace
@@ -66,7 +134,7 @@ static_assert(sizeof(LbSmemKv<128>) <= 160 * 1024 && sizeof(LbSmem<128>) <= 160 
 template <int D, bool ELU1>
 __device__ __forceinline__ void scan_q(const BwdArgs& a, int h, int b, int seg, unsigned char* smem_raw) {
   using C = LbCfg<D>;
-  constexpr int MT = C::MT, KS = C::KS, NW = C::NW, NT = C::NT, R = C::R, TPW = C::TPW, PCS = C::PCS;
+  constexpr int MT = C::MT, KS = C::KS, NT = C::NT, R = C::R, TPW = C::TPW, PCS = C::PCS;
   LbSmem<D>& sm = *reinterpret_cast<LbSmem<D>*>(smem_raw);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ln = lane & 31, lh = lane >> 5;
   const HeadCtx<D> hc = head_ctx<D>(a, b, h);
@@ -112,12 +180,12 @@ __device__ __forceinline__ void scan_q(const BwdArgs& a, int h, int b, int seg, 
       *reinterpret_cast<u32x4*>(&sm.v[row * R + col]) = valid ? rv[i] : kZero4;
       if (full) {
         *reinterpret_cast<u32x4*>(&sm.fq[row * R + col]) = valid ? rq[i] : kZero4;
-        *reinterpret_cast<u32x4*>(&sm.g[row * R + col]) = valid ? rdo[i] : kZero4;   // dO until den is known
+        *reinterpret_cast<u32x4*>(&sm.g[row * R + col]) = valid ? rdo[i] : kZero4;   // dO
       }
     }
   };
 
-  // carried sum A^T in accumulators: tile u of this wave is value block vt, feature block ft
+  const SumTiles<D> tiles(wave);   // carried sum A^T in accumulators
   f32x16 sacc[TPW];
 #pragma unroll
   for (int u = 0; u < TPW; ++u)
@@ -155,43 +223,33 @@ __device__ __forceinline__ void scan_q(const BwdArgs& a, int h, int b, int seg, 
       }
       if (n0 + 4 <= cb) load_pair(n0 + 2);
       lds_barrier();
+      float zs[TPW];
+      typename SumTiles<D>::Picked z0[TPW], z1[TPW];
 #pragma unroll
-      for (int u = 0; u < TPW; ++u) {
-        const int stile = wave * TPW + u, vt = stile / MT, ft = stile % MT;
+      for (int kk = 0; kk < CH / 16; ++kk) {
+        const bf16x8 v0 = col_op(sm.v + trl, R, 16 * kk, 32 * tiles.vt), v1 = col_op(sm.g + trl, R, 16 * kk, 32 * tiles.vt);
 #pragma unroll
-        for (int kk = 0; kk < CH / 16; ++kk) {
-          sacc[u] = mfma32(col_op(sm.v + trl, R, 16 * kk, 32 * vt), col_op(sm.fk + trl, R, 16 * kk, 32 * ft), sacc[u]);
-          sacc[u] = mfma32(col_op(sm.g + trl, R, 16 * kk, 32 * vt), col_op(sm.fq + trl, R, 16 * kk, 32 * ft), sacc[u]);
+        for (int u = 0; u < TPW; ++u) {
+          const bf16x8 f0 = col_op(sm.fk + trl, R, 16 * kk, 32 * (tiles.ft0 + u));
+          const bf16x8 f1 = col_op(sm.fq + trl, R, 16 * kk, 32 * (tiles.ft0 + u));
+          sacc[u] = mfma32(v0, f0, sacc[u]);
+          sacc[u] = mfma32(v1, f1, sacc[u]);
+          tiles.pick(z0[u], kk, f0);
+          tiles.pick(z1[u], kk, f1);
         }
       }
-      {
-        const int f = tid % D, part = tid / D;
-        constexpr int RPP = CH / C::ZP;
-        float acc = 0.f;
 #pragma unroll
-        for (int r = 0; r < RPP; ++r)
-          acc += __uint_as_float((uint32_t)sm.fk[(part * RPP + r) * R + f] << 16) +
-                 __uint_as_float((uint32_t)sm.fq[(part * RPP + r) * R + f] << 16);
-        sm.zpart[part][f] = acc;
-      }
+      for (int u = 0; u < TPW; ++u) zs[u] = tiles.sum(z1[u], tiles.sum(z0[u], 0.f));
+      tiles.put(sm.zpart, zs, ln, lh);
       lds_barrier();
       if (tid < D) {
         float zz = sm.z[tid];
 #pragma unroll
-        for (int pz = 0; pz < C::ZP; ++pz) zz += sm.zpart[pz][tid];
+        for (int pz = 0; pz < MT; ++pz) zz += sm.zpart[pz][tid];
         sm.z[tid] = zz;
       }
     }
-    if (n0 >= cb) {   // the next round scans: it reads the operand copy of the carried sum
-#pragma unroll
-      for (int u = 0; u < TPW; ++u) {
-        const int stile = wave * TPW + u, vt = stile / MT, ft = stile % MT;
-#pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4)
-          put4(&sm.st[(32 * ft + ln) * R + 32 * vt + 8 * g4 + 4 * lh], sacc[u][4 * g4 + 0], sacc[u][4 * g4 + 1],
-               sacc[u][4 * g4 + 2], sacc[u][4 * g4 + 3]);
-      }
-    }
+    if (n0 >= cb) tiles.copy(sm.st, sacc, ln, lh);   // the next round scans: it reads the operand copy of the carried sum
   }
 
   load_chunk(n0);
@@ -200,214 +258,157 @@ __device__ __forceinline__ void scan_q(const BwdArgs& a, int h, int b, int seg, 
   if (n0 + 1 < ce) load_chunk(n0 + 1);
   lds_barrier();
 
-  const int ti = wave & 3, jt = ti & 1, it = ti >> 1;   // 32 x 32 tile of the 64 x 64 products
-  const bool do_s = NW == 4 || wave < 4, do_t = NW == 4 || wave >= 4;
+  // The 64 x 64 products are three 32 x 32 tiles on or below the diagonal, one per wave 0..2: tokens 32*it.., 32*jt..
+  const bool has_tile = wave < 3;
+  const int it = wave > 0, jt = wave > 1;
   const int ot = wave % MT, it2 = wave / MT;            // output tile of the 64 x d products
 
   for (int n = n0; n < ce; ++n) {
     const int t0 = n * CH;
     const bool full = n >= cb;   // uniform over the workgroup
-    f32x16 traw;
+    f32x16 traw, racc;
+    float inv = 1.f, ci = 0.f;   // 1 / den and c of token 32*it2 + ln
     if (full) {
-    // ---- (a) S^T and (dO v^T)^T tiles: rows j, columns i (a lane owns one token i) ----
-    if (do_s) {
+    // ---- (a) S and T = dO v^T of a tile (a lane owns one token i, registers are tokens j), their sums over j; the tile
+    //      (feature block ot, token block it2) of r = A dO with its part of phi(q).r and phi(q).Z ----
+    if (has_tile) {
       f32x16 s;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s[r] = 0.f;
+      for (int r = 0; r < 16; ++r) { s[r] = 0.f; traw[r] = 0.f; }
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
+      for (int ks = 0; ks < KS; ++ks) {
         s = mfma32(row_op(sm.fk, R, 32 * jt, ks, ln, lh), row_op(sm.fq, R, 32 * it, ks, ln, lh), s);
-      const int i = 32 * it + ln;
-      float rsum = 0.f;
-#pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        float x[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int j = 32 * jt + 8 * g4 + 4 * lh + e;
-          x[e] = j <= i ? s[4 * g4 + e] : 0.f;
-        }
-        u32x2 pk, pl;
-        pk[0] = pack_bf16(x[0], x[1]);
-        pk[1] = pack_bf16(x[2], x[3]);
-        pl[0] = pack_bf16(x[0] - bf16_lo(pk[0]), x[1] - bf16_hi(pk[0]));
-        pl[1] = pack_bf16(x[2] - bf16_lo(pk[1]), x[3] - bf16_hi(pk[1]));
-        rsum = dot2_ones_bf16(pk[0], rsum);   // the row sum of the weights the numerator sees:
-        rsum = dot2_ones_bf16(pk[1], rsum);   // both halves of the pair
-        rsum = dot2_ones_bf16(pl[0], rsum);
-        rsum = dot2_ones_bf16(pl[1], rsum);
-        *reinterpret_cast<u32x2*>(&sm.sm[i * SR + 32 * jt + 8 * g4 + 4 * lh]) = pk;
-        *reinterpret_cast<u32x2*>(&sm.sl[i * SR + 32 * jt + 8 * g4 + 4 * lh]) = pl;
-      }
-      rsum = sum_over_halves(rsum);
-      if (lh == 0) sm.rs[jt][i] = rsum;
-    }
-    if (do_t) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) traw[r] = 0.f;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
         traw = mfma32(row_op(sm.v, R, 32 * jt, ks, ln, lh), row_op(sm.g, R, 32 * it, ks, ln, lh), traw);
-    }
-    {
-      // fq_i . Z: NW threads per token, D / NW features each
-      constexpr int FP = D / NW;   // 16
-      const int i = tid / NW, part = tid % NW;
-      float acc = 0.f;
-#pragma unroll
-      for (int c = 0; c < FP; c += 8) {
-        const u32x4 f8 = *reinterpret_cast<const u32x4*>(&sm.fq[i * R + part * FP + c]);
-        const float4 z0 = *reinterpret_cast<const float4*>(&sm.z[part * FP + c]);
-        const float4 z1 = *reinterpret_cast<const float4*>(&sm.z[part * FP + c + 4]);
-        acc = fmaf(bf16_lo(f8[0]), z0.x, acc); acc = fmaf(bf16_hi(f8[0]), z0.y, acc);
-        acc = fmaf(bf16_lo(f8[1]), z0.z, acc); acc = fmaf(bf16_hi(f8[1]), z0.w, acc);
-        acc = fmaf(bf16_lo(f8[2]), z1.x, acc); acc = fmaf(bf16_hi(f8[2]), z1.y, acc);
-        acc = fmaf(bf16_lo(f8[3]), z1.z, acc); acc = fmaf(bf16_hi(f8[3]), z1.w, acc);
       }
+      float ss = 0.f, st = 0.f;
+      const int top = (it == jt ? ln : CH) - 4 * lh;
 #pragma unroll
-      for (int o = 1; o < NW; o <<= 1) acc += __shfl_xor(acc, o, 64);
-      if (part == 0) sm.dz[i] = acc;
-    }
-    lds_barrier();
-
-    // ---- (b) num^T tile (value block ot, token block it2) and its part of dO_i . num_i ----
-    {
-      f32x16 nacc;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) nacc[r] = 0.f;
-#pragma unroll
-      for (int kk = 0; kk < CH / 16; ++kk) {
-        const bf16x8 vop = col_op(sm.v + trl, R, 16 * kk, 32 * ot);
-        nacc = mfma32(vop, row_op(sm.sm, SR, 32 * it2, kk, ln, lh), nacc);
-        nacc = mfma32(vop, row_op(sm.sl, SR, 32 * it2, kk, ln, lh), nacc);
+      for (int r = 0; r < 16; ++r) {
+        const float x = 8 * (r / 4) + r % 4 <= top ? s[r] : 0.f;
+        ss += x;
+        st = fmaf(x, traw[r], st);
       }
+      ss = sum_over_halves(ss);
+      st = sum_over_halves(st);
+      if (lh == 0) {
+        sm.part[0][wave][ln] = ss;
+        sm.part[1][wave][ln] = st;
+      }
+    }
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        nacc = mfma32(col_op(sm.st + trl, R, 16 * ks, 32 * ot), row_op(sm.fq, R, 32 * it2, ks, ln, lh), nacc);
+    for (int r = 0; r < 16; ++r) racc[r] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+      racc = mfma32(row_op(sm.st, R, 32 * ot, ks, ln, lh), row_op(sm.g, R, 32 * it2, ks, ln, lh), racc);
+    {
       const int i = 32 * it2 + ln;
-      float dot = 0.f;
+      float qr = 0.f, qz = 0.f;
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {
-        float d4[4];
-        get4(&sm.g[i * R + 32 * ot + 8 * g4 + 4 * lh], d4);
+        const int f0 = 32 * ot + 8 * g4 + 4 * lh;
+        const float4 z4 = *reinterpret_cast<const float4*>(&sm.z[f0]);
+        float f[4];
+        get4(&sm.fq[i * R + f0], f);
+        qz = fmaf(f[0], z4.x, fmaf(f[1], z4.y, fmaf(f[2], z4.z, fmaf(f[3], z4.w, qz))));
 #pragma unroll
-        for (int e = 0; e < 4; ++e) dot = fmaf(d4[e], nacc[4 * g4 + e], dot);
+        for (int e = 0; e < 4; ++e) qr = fmaf(f[e], racc[4 * g4 + e], qr);
       }
-      dot = sum_over_halves(dot);
-      if (lh == 0) sm.pd[ot][i] = dot;
+      qr = sum_over_halves(qr);
+      qz = sum_over_halves(qz);
+      if (lh == 0) {
+        sm.red[0][ot][i] = qr;
+        sm.red[1][ot][i] = qz;
+      }
     }
     lds_barrier();
 
-    // ---- (c) den, c; T' tile; g = dO / den in place ----
-    auto den_of = [&](int i, bool valid) {
-      return valid ? sm.rs[0][i] + sm.rs[1][i] + sm.dz[i] + a.eps : 1.f;
-    };
-    auto c_of = [&](int i, float den) {
-      float dot = 0.f;
+    // ---- (b) den and c; the T' tile ----
+    auto den_and_c = [&](int tb, float& inv_out, float& c_out) {   // of token 32*tb + ln
+      const int i = 32 * tb + ln;
+      float qr = 0.f, qz = 0.f;
 #pragma unroll
-      for (int m = 0; m < MT; ++m) dot += sm.pd[m][i];
-      return dot / (den * den);
+      for (int m = 0; m < MT; ++m) {
+        qr += sm.red[0][m][i];
+        qz += sm.red[1][m][i];
+      }
+      qz += tb == 0 ? sm.part[0][0][ln] : sm.part[0][1][ln] + sm.part[0][2][ln];
+      qr += tb == 0 ? sm.part[1][0][ln] : sm.part[1][1][ln] + sm.part[1][2][ln];
+      const float den = t0 + i < N ? qz + a.eps : 1.f;   // rows past the end: dO is zero
+      inv_out = 1.f / den;
+      c_out = qr * inv_out * inv_out;
+      return den;
     };
-    if (do_t) {
-      const int i = 32 * it + ln;
-      const float den = den_of(i, t0 + i < N);
-      const float ci = c_of(i, den);
-      const float inv = 1.f / den;
+    const float den = den_and_c(it2, inv, ci);
+    if (ot == 0 && lh == 0 && t0 + 32 * it2 + ln < N)
+      *reinterpret_cast<float2*>(&hc.ws[2 * (int64_t)(t0 + 32 * it2 + ln)]) = make_float2(den, ci);
+    if (has_tile) {
+      float tinv, tc;
+      den_and_c(it, tinv, tc);
+      const int i = 32 * it + ln, top = (it == jt ? ln : CH) - 4 * lh;
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {
         float x[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int j = 32 * jt + 8 * g4 + 4 * lh + e;
-          x[e] = j <= i ? fmaf(traw[4 * g4 + e], inv, -ci) : 0.f;
-        }
+        for (int e = 0; e < 4; ++e) x[e] = 8 * g4 + e <= top ? fmaf(traw[4 * g4 + e], tinv, -tc) : 0.f;
         put4_split(&sm.tp[i * SR + 32 * jt + 8 * g4 + 4 * lh], &sm.tl[i * SR + 32 * jt + 8 * g4 + 4 * lh],
                    x[0], x[1], x[2], x[3]);
       }
     }
-#pragma unroll
-    for (int i = 0; i < PCS; ++i) {
-      const int p = tid + i * NT, row = p / C::C8, col = 8 * (p % C::C8);
-      const float den = den_of(row, t0 + row < N);
-      u32x4* gp = reinterpret_cast<u32x4*>(&sm.g[row * R + col]);
-      *gp = scale8(*gp, 1.f / den);
-    }
-    if (tid < CH) {
-      const bool valid = t0 + tid < N;
-      const float den = den_of(tid, valid);
-      const float ci = c_of(tid, den);
-      sm.cc[tid] = ci;
-      if (valid) {
-        float2 o;
-        o.x = den;
-        o.y = ci;
-        *reinterpret_cast<float2*>(&hc.ws[2 * (int64_t)(t0 + tid)]) = o;
-      }
-    }
-    lds_barrier();
     }  // full
 
-    // ---- (d) dfq^T tile (feature block ot, token block it2), then the carried sums ----
+    // ---- (c) the carried sums: nothing here waits for T', so the waves without a tile go ahead ----
+    float zs[TPW];
+    typename SumTiles<D>::Picked fz[TPW];
+#pragma unroll
+    for (int kk = 0; kk < CH / 16; ++kk) {
+      const bf16x8 vop = col_op(sm.v + trl, R, 16 * kk, 32 * tiles.vt);
+#pragma unroll
+      for (int u = 0; u < TPW; ++u) {
+        const bf16x8 fop = col_op(sm.fk + trl, R, 16 * kk, 32 * (tiles.ft0 + u));
+        sacc[u] = mfma32(vop, fop, sacc[u]);
+        tiles.pick(fz[u], kk, fop);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < TPW; ++u) zs[u] = tiles.sum(fz[u], 0.f);
+    tiles.put(sm.zpart, zs, ln, lh);
+    lds_barrier();
+
+    // ---- (d) dfq^T tile (feature block ot, token block it2) = r / den - c Z + T' fk ----
     if (full) {
       f32x16 dacc;
 #pragma unroll
       for (int r = 0; r < 16; ++r) dacc[r] = 0.f;
 #pragma unroll
-      for (int kk = 0; kk < CH / 16; ++kk) {
-        const bf16x8 kop = col_op(sm.fk + trl, R, 16 * kk, 32 * ot);
-        dacc = mfma32(kop, row_op(sm.tp, SR, 32 * it2, kk, ln, lh), dacc);
-        dacc = mfma32(kop, row_op(sm.tl, SR, 32 * it2, kk, ln, lh), dacc);
-      }
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        dacc = mfma32(row_op(sm.st, R, 32 * ot, ks, ln, lh), row_op(sm.g, R, 32 * it2, ks, ln, lh), dacc);
+      for (int kk = 0; kk < CH / 16; ++kk)
+        if (16 * kk < 32 || it2 > 0) {   // tokens 0..31 see no others
+          const bf16x8 kop = col_op(sm.fk + trl, R, 16 * kk, 32 * ot);
+          dacc = mfma32(kop, row_op(sm.tp, SR, 32 * it2, kk, ln, lh), dacc);
+          dacc = mfma32(kop, row_op(sm.tl, SR, 32 * it2, kk, ln, lh), dacc);
+        }
       const int i = 32 * it2 + ln;
-      const float ci = sm.cc[i];
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {
         const int f0 = 32 * ot + 8 * g4 + 4 * lh;
         const float4 z4 = *reinterpret_cast<const float4*>(&sm.z[f0]);
+        const float zv[4] = {z4.x, z4.y, z4.z, z4.w};
         uint16_t* fp = &sm.fq[i * R + f0];   // this wave's own corner of the tile: dq replaces phi(q)
-        float fv[4];
+        float fv[4], x[4];
         get4(fp, fv);
-        put4(fp, (dacc[4 * g4 + 0] - ci * z4.x) * slope_of<ELU1>(fv[0]),
-             (dacc[4 * g4 + 1] - ci * z4.y) * slope_of<ELU1>(fv[1]),
-             (dacc[4 * g4 + 2] - ci * z4.z) * slope_of<ELU1>(fv[2]),
-             (dacc[4 * g4 + 3] - ci * z4.w) * slope_of<ELU1>(fv[3]));
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          x[e] = (fmaf(racc[4 * g4 + e], inv, dacc[4 * g4 + e]) - ci * zv[e]) * slope_of<ELU1>(fv[e]);
+        put4(fp, x[0], x[1], x[2], x[3]);
       }
-    }
-#pragma unroll
-    for (int u = 0; u < TPW; ++u) {
-      const int stile = wave * TPW + u, vt = stile / MT, ft = stile % MT;
-#pragma unroll
-      for (int kk = 0; kk < CH / 16; ++kk)
-        sacc[u] = mfma32(col_op(sm.v + trl, R, 16 * kk, 32 * vt), col_op(sm.fk + trl, R, 16 * kk, 32 * ft), sacc[u]);
-    }
-    {
-      const int f = tid % D, part = tid / D;
-      constexpr int RPP = CH / C::ZP;
-      float acc = 0.f;
-#pragma unroll
-      for (int r = 0; r < RPP; ++r) acc += __uint_as_float((uint32_t)sm.fk[(part * RPP + r) * R + f] << 16);
-      sm.zpart[part][f] = acc;
     }
     lds_barrier();
 
     // ---- (e) hand the sums to the next chunk; dq rows out; next chunk in ----
-    if (n + 1 >= cb) {   // light rounds do not read the operand copy
-#pragma unroll
-    for (int u = 0; u < TPW; ++u) {
-      const int stile = wave * TPW + u, vt = stile / MT, ft = stile % MT;
-#pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4)
-        put4(&sm.st[(32 * ft + ln) * R + 32 * vt + 8 * g4 + 4 * lh], sacc[u][4 * g4 + 0], sacc[u][4 * g4 + 1],
-             sacc[u][4 * g4 + 2], sacc[u][4 * g4 + 3]);
-    }
-    }
+    if (n + 1 >= cb) tiles.copy(sm.st, sacc, ln, lh);   // light rounds do not read the operand copy
     if (tid < D) {
       float zz = sm.z[tid];
 #pragma unroll
-      for (int pz = 0; pz < C::ZP; ++pz) zz += sm.zpart[pz][tid];
+      for (int pz = 0; pz < MT; ++pz) zz += sm.zpart[pz][tid];
       sm.z[tid] = zz;
     }
     if (full) {
@@ -424,7 +425,7 @@ __device__ __forceinline__ void scan_q(const BwdArgs& a, int h, int b, int seg, 
       stage_chunk(n + 1);   // the same thread overwrites the pieces it has just read
     }
     if (n + 2 < ce) load_chunk(n + 2);
-      lds_barrier();
+    lds_barrier();
   }
 }
 
@@ -445,11 +446,8 @@ __device__ __forceinline__ void scan_kv(const BwdArgs& a, int h, int b, int seg,
   const int cb = nchunks - a.lin_bounds[seg + 1], ce = nchunks - a.lin_bounds[seg];
   if (cb >= ce) return;
   const int trl = lds_operand_tr_lane_offset(R, lane) + 8 * lh * R;
-  constexpr int RS = LbSmemKv<D>::RS, RD = LbSmemKv<D>::RD;   // strides of the carried-sum copy and of dO
-  const int trl_s = lds_operand_tr_lane_offset(RS, lane) + 8 * lh * RS;
 
   u32x4 rq[PCS], rk[PCS], rv[PCS], rdo[PCS];
-  float rden[PCS];
   float2 rstat = {1.f, 0.f};
   auto load_chunk = [&](int n) {
     const bool full = n < ce;   // uniform
@@ -459,7 +457,6 @@ __device__ __forceinline__ void scan_kv(const BwdArgs& a, int h, int b, int seg,
       const int64_t tok = min(n * CH + row, N - 1);
       rq[i] = *reinterpret_cast<const u32x4*>(hc.q + tok * a.q.sn + col);
       rdo[i] = *reinterpret_cast<const u32x4*>(hc.dout + tok * a.dout.sn + col);
-      rden[i] = hc.ws[2 * tok];
       if (full) {
         rk[i] = *reinterpret_cast<const u32x4*>(hc.k + tok * a.k.sn + col);
         rv[i] = *reinterpret_cast<const u32x4*>(hc.v + tok * a.v.sn + col);
@@ -482,32 +479,32 @@ __device__ __forceinline__ void scan_kv(const BwdArgs& a, int h, int b, int seg,
       const int p = tid + i * NT, row = p / C::C8, col = 8 * (p % C::C8);
       const bool valid = n * CH + row < N;
       *reinterpret_cast<u32x4*>(&sm.fq[row * R + col]) = valid ? rq[i] : kZero4;
-      *reinterpret_cast<u32x4*>(&sm.g[row * R + col]) = valid ? scale8(rdo[i], 1.f / rden[i]) : kZero4;
+      *reinterpret_cast<u32x4*>(&sm.g[row * R + col]) = valid ? rdo[i] : kZero4;
       if (full) {
         *reinterpret_cast<u32x4*>(&sm.fk[row * R + col]) = valid ? rk[i] : kZero4;
         *reinterpret_cast<u32x4*>(&sm.v[row * R + col]) = valid ? rv[i] : kZero4;
-        *reinterpret_cast<u32x4*>(&sm.dout[row * RD + col]) = valid ? rdo[i] : kZero4;
       }
     }
     if (tid < CH) {
       const bool valid = n * CH + tid < N;
       sm.cc[tid] = valid ? rstat.y : 0.f;
-      sm.den[tid] = valid ? 1.f / rstat.x : 1.f;   // the reciprocal
+      sm.den[tid] = valid ? 1.f / rstat.x : 1.f;
     }
   };
 
-  f32x16 sacc[TPW];   // B^T tiles: value block vt, feature block ft
+  const SumTiles<D> tiles(wave);   // B^T
+  f32x16 sacc[TPW];
 #pragma unroll
   for (int u = 0; u < TPW; ++u)
 #pragma unroll
     for (int r = 0; r < 16; ++r) sacc[u][r] = 0.f;
-  for (int i = tid; i < D * RS / 2; i += NT) reinterpret_cast<uint32_t*>(sm.st)[i] = 0u;
+  for (int i = tid; i < D * R / 2; i += NT) reinterpret_cast<uint32_t*>(sm.st)[i] = 0u;
   if (tid < D) sm.z[tid] = 0.f;
 
   // Light rounds, two chunks at a time (the chunks behind the segment only feed the carried
   // sums): phi(q), g and c of chunk n go to the fq / g tiles and cc, those of chunk n - 1 to the
   // fk / v tiles and dz (and travel in the k / v staging registers).
-  float rden2[PCS];
+  float rden[PCS], rden2[PCS];
   float2 rstat2 = {1.f, 0.f};
   auto load_pair = [&](int n) {
 #pragma unroll
@@ -545,45 +542,33 @@ __device__ __forceinline__ void scan_kv(const BwdArgs& a, int h, int b, int seg,
       }
       if (n1 - 3 >= ce) load_pair(n1 - 2);
       lds_barrier();
+      float zs[TPW];
+      typename SumTiles<D>::Picked z0[TPW], z1[TPW];
 #pragma unroll
-      for (int u = 0; u < TPW; ++u) {
-        const int stile = wave * TPW + u, vt = stile / MT, ft = stile % MT;
+      for (int kk = 0; kk < CH / 16; ++kk) {
+        const bf16x8 g0 = col_op(sm.g + trl, R, 16 * kk, 32 * tiles.vt), g1 = col_op(sm.v + trl, R, 16 * kk, 32 * tiles.vt);
 #pragma unroll
-        for (int kk = 0; kk < CH / 16; ++kk) {
-          sacc[u] = mfma32(col_op(sm.g + trl, R, 16 * kk, 32 * vt), col_op(sm.fq + trl, R, 16 * kk, 32 * ft), sacc[u]);
-          sacc[u] = mfma32(col_op(sm.v + trl, R, 16 * kk, 32 * vt), col_op(sm.fk + trl, R, 16 * kk, 32 * ft), sacc[u]);
+        for (int u = 0; u < TPW; ++u) {
+          const bf16x8 f0 = col_op(sm.fq + trl, R, 16 * kk, 32 * (tiles.ft0 + u));
+          const bf16x8 f1 = col_op(sm.fk + trl, R, 16 * kk, 32 * (tiles.ft0 + u));
+          sacc[u] = mfma32(g0, f0, sacc[u]);
+          sacc[u] = mfma32(g1, f1, sacc[u]);
+          tiles.pick(z0[u], kk, f0);
+          tiles.pick(z1[u], kk, f1);
         }
       }
-      {
-        const int f = tid % D, part = tid / D;
-        constexpr int RPP = CH / C::ZP;
-        float acc = 0.f;
 #pragma unroll
-        for (int r = 0; r < RPP; ++r) {
-          const int i = part * RPP + r;
-          acc = fmaf(sm.cc[i], __uint_as_float((uint32_t)sm.fq[i * R + f] << 16), acc);
-          acc = fmaf(sm.dz[i], __uint_as_float((uint32_t)sm.fk[i * R + f] << 16), acc);
-        }
-        sm.zpart[part][f] = acc;
-      }
+      for (int u = 0; u < TPW; ++u) zs[u] = tiles.sum(z1[u], sm.dz, lh, tiles.sum(z0[u], sm.cc, lh, 0.f));
+      tiles.put(sm.zpart, zs, ln, lh);
       lds_barrier();
       if (tid < D) {
         float yy = sm.z[tid];
 #pragma unroll
-        for (int pz = 0; pz < C::ZP; ++pz) yy += sm.zpart[pz][tid];
+        for (int pz = 0; pz < MT; ++pz) yy += sm.zpart[pz][tid];
         sm.z[tid] = yy;
       }
     }
-    if (n1 < ce) {   // the next round scans: it reads the operand copy of the carried sum
-#pragma unroll
-      for (int u = 0; u < TPW; ++u) {
-        const int stile = wave * TPW + u, vt = stile / MT, ft = stile % MT;
-#pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4)
-          put4(&sm.st[(32 * ft + ln) * RS + 32 * vt + 8 * g4 + 4 * lh], sacc[u][4 * g4 + 0], sacc[u][4 * g4 + 1],
-               sacc[u][4 * g4 + 2], sacc[u][4 * g4 + 3]);
-      }
-    }
+    if (n1 < ce) tiles.copy(sm.st, sacc, ln, lh);   // the next round scans: it reads the operand copy of the carried sum
   }
 
   load_chunk(n1);
@@ -593,13 +578,14 @@ __device__ __forceinline__ void scan_kv(const BwdArgs& a, int h, int b, int seg,
   lds_barrier();
 
   const int ti = wave & 3, it = ti & 1, jt = ti >> 1;   // here rows are i, columns j (a lane owns a key j)
-  const bool do_s = NW == 4 || wave < 4, do_t = NW == 4 || wave >= 4;
+  const bool none = it < jt;   // queries 0..31 see no keys 32..63: that tile is neither made nor read
+  const bool do_s = !none && (NW == 4 || wave < 4), do_t = !none && (NW == 4 || wave >= 4);
   const int ot = wave % MT, jt2 = wave / MT;
 
   for (int n = n1; n >= cb; --n) {
     const int t0 = n * CH;
     const bool full = n < ce;   // uniform over the workgroup
-    // ---- (a) S and T' tiles, stored transposed ([j][i]); column sums for Y ----
+    // ---- (a) S / den and T' tiles, stored transposed ([j][i]) ----
     if (full && do_s) {
       f32x16 s;
 #pragma unroll
@@ -610,11 +596,13 @@ __device__ __forceinline__ void scan_kv(const BwdArgs& a, int h, int b, int seg,
       const int j = 32 * jt + ln;
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {
+        const float4 r4 = *reinterpret_cast<const float4*>(&sm.den[32 * it + 8 * g4 + 4 * lh]);
+        const float rv4[4] = {r4.x, r4.y, r4.z, r4.w};
         float x[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int i = 32 * it + 8 * g4 + 4 * lh + e;
-          x[e] = j <= i ? s[4 * g4 + e] : 0.f;
+          x[e] = j <= i ? s[4 * g4 + e] * rv4[e] : 0.f;
         }
         put4(&sm.sm[j * SR + 32 * it + 8 * g4 + 4 * lh], x[0], x[1], x[2], x[3]);
       }
@@ -625,7 +613,7 @@ __device__ __forceinline__ void scan_kv(const BwdArgs& a, int h, int b, int seg,
       for (int r = 0; r < 16; ++r) tr[r] = 0.f;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
-        tr = mfma32(row_op(sm.dout, RD, 32 * it, ks, ln, lh), row_op(sm.v, R, 32 * jt, ks, ln, lh), tr);
+        tr = mfma32(row_op(sm.g, R, 32 * it, ks, ln, lh), row_op(sm.v, R, 32 * jt, ks, ln, lh), tr);
       const int j = 32 * jt + ln;
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {
@@ -642,17 +630,6 @@ __device__ __forceinline__ void scan_kv(const BwdArgs& a, int h, int b, int seg,
                    x[0], x[1], x[2], x[3]);
       }
     }
-    {
-      const int f = tid % D, part = tid / D;
-      constexpr int RPP = CH / C::ZP;
-      float acc = 0.f;
-#pragma unroll
-      for (int r = 0; r < RPP; ++r) {
-        const int i = part * RPP + r;
-        acc = fmaf(sm.cc[i], __uint_as_float((uint32_t)sm.fq[i * R + f] << 16), acc);
-      }
-      sm.zpart[part][f] = acc;
-    }
     lds_barrier();
 
     // ---- (b) dfk^T tile (feature block ot, key block jt2), dv^T tile (value block ot), B^T ----
@@ -661,28 +638,38 @@ __device__ __forceinline__ void scan_kv(const BwdArgs& a, int h, int b, int seg,
     for (int r = 0; r < 16; ++r) { kacc[r] = 0.f; vacc[r] = 0.f; }
     if (full) {
 #pragma unroll
-    for (int kk = 0; kk < CH / 16; ++kk) {
-      const bf16x8 qop = col_op(sm.fq + trl, R, 16 * kk, 32 * ot);
-      kacc = mfma32(qop, row_op(sm.tp, SR, 32 * jt2, kk, ln, lh), kacc);
-      kacc = mfma32(qop, row_op(sm.tl, SR, 32 * jt2, kk, ln, lh), kacc);
-    }
+    for (int kk = 0; kk < CH / 16; ++kk)
+      if (16 * kk >= 32 || jt2 == 0) {
+        const bf16x8 qop = col_op(sm.fq + trl, R, 16 * kk, 32 * ot);
+        kacc = mfma32(qop, row_op(sm.tp, SR, 32 * jt2, kk, ln, lh), kacc);
+        kacc = mfma32(qop, row_op(sm.tl, SR, 32 * jt2, kk, ln, lh), kacc);
+      }
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
-      kacc = mfma32(row_op(sm.st, RS, 32 * ot, ks, ln, lh), row_op(sm.v, R, 32 * jt2, ks, ln, lh), kacc);
+      kacc = mfma32(row_op(sm.st, R, 32 * ot, ks, ln, lh), row_op(sm.v, R, 32 * jt2, ks, ln, lh), kacc);
 #pragma unroll
     for (int kk = 0; kk < CH / 16; ++kk)
-      vacc = mfma32(col_op(sm.g + trl, R, 16 * kk, 32 * ot), row_op(sm.sm, SR, 32 * jt2, kk, ln, lh), vacc);
+      if (16 * kk >= 32 || jt2 == 0)
+        vacc = mfma32(col_op(sm.g + trl, R, 16 * kk, 32 * ot), row_op(sm.sm, SR, 32 * jt2, kk, ln, lh), vacc);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
-      vacc = mfma32(col_op(sm.st + trl_s, RS, 16 * ks, 32 * ot), row_op(sm.fk, R, 32 * jt2, ks, ln, lh), vacc);
+      vacc = mfma32(col_op(sm.st + trl, R, 16 * ks, 32 * ot), row_op(sm.fk, R, 32 * jt2, ks, ln, lh), vacc);
     }  // full
+    float zs[TPW];
+    typename SumTiles<D>::Picked fz[TPW];
 #pragma unroll
-    for (int u = 0; u < TPW; ++u) {
-      const int stile = wave * TPW + u, vt = stile / MT, ft = stile % MT;
+    for (int kk = 0; kk < CH / 16; ++kk) {
+      const bf16x8 gop = scaled8(col_op(sm.g + trl, R, 16 * kk, 32 * tiles.vt), sm.den + 16 * kk + 8 * lh);
 #pragma unroll
-      for (int kk = 0; kk < CH / 16; ++kk)
-        sacc[u] = mfma32(col_op(sm.g + trl, R, 16 * kk, 32 * vt), col_op(sm.fq + trl, R, 16 * kk, 32 * ft), sacc[u]);
+      for (int u = 0; u < TPW; ++u) {
+        const bf16x8 fop = col_op(sm.fq + trl, R, 16 * kk, 32 * (tiles.ft0 + u));
+        sacc[u] = mfma32(gop, fop, sacc[u]);
+        tiles.pick(fz[u], kk, fop);
+      }
     }
+#pragma unroll
+    for (int u = 0; u < TPW; ++u) zs[u] = tiles.sum(fz[u], sm.cc, lh, 0.f);
+    tiles.put(sm.zpart, zs, ln, lh);
     lds_barrier();   // every read of the phi(k) and v tiles is done
 
     // ---- (c) dk replaces phi(k), dv replaces v ----
@@ -703,20 +690,11 @@ __device__ __forceinline__ void scan_kv(const BwdArgs& a, int h, int b, int seg,
     lds_barrier();
 
     // ---- (d) hand the sums on; dk, dv rows out; next (earlier) chunk in ----
-    if (n - 1 < ce) {   // light rounds do not read the operand copy
-#pragma unroll
-    for (int u = 0; u < TPW; ++u) {
-      const int stile = wave * TPW + u, vt = stile / MT, ft = stile % MT;
-#pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4)
-        put4(&sm.st[(32 * ft + ln) * RS + 32 * vt + 8 * g4 + 4 * lh], sacc[u][4 * g4 + 0], sacc[u][4 * g4 + 1],
-             sacc[u][4 * g4 + 2], sacc[u][4 * g4 + 3]);
-    }
-    }
+    if (n - 1 < ce) tiles.copy(sm.st, sacc, ln, lh);   // light rounds do not read the operand copy
     if (tid < D) {
       float yy = sm.z[tid];
 #pragma unroll
-      for (int pz = 0; pz < C::ZP; ++pz) yy += sm.zpart[pz][tid];
+      for (int pz = 0; pz < MT; ++pz) yy += sm.zpart[pz][tid];
       sm.z[tid] = yy;
     }
     if (full) {
@@ -736,7 +714,7 @@ __device__ __forceinline__ void scan_kv(const BwdArgs& a, int h, int b, int seg,
       stage_chunk(n - 1);
     }
     if (n - 2 >= cb) load_chunk(n - 2);
-      lds_barrier();
+    lds_barrier();
   }
 }
 
