@@ -13,6 +13,7 @@ from typing import Optional
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libgformer_attn.so")
+CALL_PATH = os.path.join(HERE, "_decode_call.so")
 
 GF_OK, GF_ERR_INVALID_ARG, GF_ERR_UNSUPPORTED, GF_ERR_WORKSPACE, GF_ERR_DEVICE = range(5)
 GF_F32, GF_BF16 = 0, 1
@@ -128,8 +129,29 @@ def lib():
         L.gformer_status_string.argtypes = [ctypes.c_int]
         L.gformer_version.restype = ctypes.c_int
         L.gformer_version.argtypes = []
+        L.decode_address = ctypes.cast(L.gformer_attn_decode, ctypes.c_void_p).value
         _lib = L
     return _lib
+
+
+_native = None
+
+
+def _decode_call():
+    """The extension module with the host side of a decode step (host/decode_call.cpp).  Fails loudly."""
+    global _native
+    if _native is None:
+        import importlib.util
+
+        if not os.path.exists(CALL_PATH):
+            raise FileNotFoundError(f"{CALL_PATH} is missing: run `python -m paper_2412_19829_amd.build` "
+                                    "(or __graft_entry__.build()) first")
+        import torch  # noqa: F401  (its libraries are what the module links to)
+        spec = importlib.util.spec_from_file_location("_decode_call", CALL_PATH)
+        mod = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(mod)
+        _native = mod.decode
+    return _native
 
 
 def gformer_params_init() -> GformerParams:
@@ -327,6 +349,13 @@ def gformer_attn_decode(q, k, v, out, kcache, vcache, state, window: int, n_spar
                         *, phi=GF_PHI_ELU1, softmax_scale=1.0, eps=0.0, stream: Optional[int] = None):
     """One decode step on dense device tensors: q, k, v, out [B, H, d]; kcache, vcache
     [B, H0, window, d] (or None when H0 == 0); state fp32 [B, H - H0, d*d + d] (or None)."""
+    st = (_native or _decode_call())((_lib or lib()).decode_address, q, k, v, out, kcache, vcache, state, window,
+                                     n_sparse_heads, t, phi, softmax_scale, eps, stream)
+    if st is not None:
+        if st != GF_OK:
+            raise GformerError(st, gformer_status_string(st))
+        return out
+    # not the plain call (the module above says which those are): checked and called from here
     import torch
 
     for x in (q, k, v, out, kcache, vcache, state):

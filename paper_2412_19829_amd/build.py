@@ -1,4 +1,5 @@
-"""Compile the HIP sources under csrc/ into paper_2412_19829_amd/libgformer_attn.so (gfx950)."""
+"""Compile the HIP sources under csrc/ into paper_2412_19829_amd/libgformer_attn.so (gfx950), and the host code under
+host/ into the extension module _decode_call.so (needs torch's headers)."""
 from __future__ import annotations
 
 import glob
@@ -11,6 +12,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libgformer_attn.so")
+CALL_SRC = os.path.join(HERE, "host", "decode_call.cpp")
+CALL = os.path.join(HERE, "_decode_call.so")
 
 # packed-fp32 VALU forms are kept off for every device compilation unit
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
@@ -23,7 +26,7 @@ def sources():
 
 def _newest_input() -> float:
     deps = sources() + glob.glob(os.path.join(CSRC, "*.hpp")) + \
-        glob.glob(os.path.join(HERE, "..", "include", "*.h"))
+        glob.glob(os.path.join(HERE, "..", "include", "*.h")) + [CALL_SRC]
     return max(os.path.getmtime(p) for p in deps)
 
 
@@ -34,13 +37,26 @@ def _compile(src: str, extra) -> str:
     return obj
 
 
+def _build_call() -> None:
+    import sysconfig
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+                    f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+                    *(f"-isystem{p}" for p in [*include_paths(), sysconfig.get_paths()["include"]]),
+                    CALL_SRC, "-o", CALL, f"-L{libs}", "-ltorch_python", "-ltorch_cpu", "-lc10"], check=True)
+
+
 def build(force: bool = True, extra_flags=(), verbose: bool = False) -> str:
-    if not force and os.path.exists(LIB) and os.path.getmtime(LIB) >= _newest_input():
+    if not force and all(os.path.exists(x) and os.path.getmtime(x) >= _newest_input() for x in (LIB, CALL)):
         return LIB
     os.makedirs(OBJ_DIR, exist_ok=True)
     srcs = sources()
-    with ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
+    with ThreadPoolExecutor(max_workers=min(8, len(srcs) + 1)) as ex:
+        call = ex.submit(_build_call)
         objs = list(ex.map(lambda s: _compile(s, list(extra_flags)), srcs))
+        call.result()
     cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     subprocess.run(cmd, check=True)
     if verbose:

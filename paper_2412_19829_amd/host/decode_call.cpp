@@ -1,0 +1,131 @@
+// The host side of one decode step, for binding.gformer_attn_decode: a step of a few users takes 4 to 5 us on the
+// device, and checking and marshalling its seven tensors in Python took 8 (1 x 12 heads, d = 64: 8.2 us a step among
+// others, 4.3 with this, which is the kernel).
+//
+// decode(address, q, k, v, out, kcache, vcache, state, window, n_sparse_heads, t, phi, softmax_scale, eps, stream)
+// returns the gf_status of the call at `address` (gformer_attn_decode), or None for anything that is not the plain,
+// well-formed call: wrapped or traced tensors, shapes or types that do not fit, numbers out of range.  The
+// binding's own code then does or refuses the call, with its own messages.
+#include <Python.h>
+
+#include <ATen/core/Tensor.h>
+#include <c10/core/DispatchKeySet.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include <climits>
+#include <cstring>
+
+#include "../../include/gformer.h"
+
+namespace {
+
+using Decode = decltype(&gformer_attn_decode);
+
+// A dense tensor in device memory and nothing else: a wrapper's data pointer is not what the caller means.
+const at::Tensor* plain(PyObject* o) {
+  if (!THPVariable_CheckExact(o)) return nullptr;
+  const at::Tensor& t = THPVariable_Unpack(o);
+  if (!t.defined() || !t.is_cuda() || t.layout() != at::kStrided || !t.has_storage() || !t.is_contiguous()) return nullptr;
+  constexpr c10::DispatchKeySet wrapped({
+      c10::DispatchKey::Python, c10::DispatchKey::PythonTLSSnapshot, c10::DispatchKey::Functionalize,
+      c10::DispatchKey::FuncTorchBatched, c10::DispatchKey::FuncTorchGradWrapper, c10::DispatchKey::Conjugate,
+      c10::DispatchKey::Negative, c10::DispatchKey::ZeroTensor});
+  return t.key_set().has_any(wrapped) ? nullptr : &t;
+}
+
+bool to_long(PyObject* o, int64_t lo, int64_t hi, int64_t& x) {
+  if (!PyLong_CheckExact(o)) return false;
+  int over = 0;
+  x = PyLong_AsLongLongAndOverflow(o, &over);
+  return over == 0 && x >= lo && x <= hi;
+}
+bool to_float(PyObject* o, float& x) {
+  if (!PyFloat_CheckExact(o)) return false;
+  x = (float)PyFloat_AS_DOUBLE(o);
+  return true;
+}
+
+PyObject* raw_stream_getter = nullptr;   // torch._C._cuda_getCurrentRawStream
+
+PyObject* decode(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  if (n != 15) {
+    PyErr_SetString(PyExc_TypeError, "decode takes 15 arguments");
+    return nullptr;
+  }
+  const at::Tensor* x[7];   // q, k, v, out, kcache, vcache, state
+  for (int i = 0; i < 7; ++i) {
+    x[i] = nullptr;
+    if (i >= 4 && a[1 + i] == Py_None) continue;
+    if (!(x[i] = plain(a[1 + i]))) Py_RETURN_NONE;
+  }
+  int64_t window, h0, t, phi, stream = 0;
+  gformer_params p;
+  std::memset(&p, 0, sizeof(p));
+  if (!to_long(a[8], INT_MIN, INT_MAX, window) || !to_long(a[9], 0, INT_MAX, h0) || !to_long(a[10], LLONG_MIN, LLONG_MAX, t) ||
+      !to_long(a[11], INT_MIN, INT_MAX, phi) || !to_float(a[12], p.softmax_scale) || !to_float(a[13], p.eps))
+    Py_RETURN_NONE;
+  const at::Tensor& q = *x[0];
+  const auto type = q.scalar_type();
+  if ((type != at::kBFloat16 && type != at::kFloat) || q.dim() != 3) Py_RETURN_NONE;
+  for (int i = 1; i < 4; ++i)
+    if (x[i]->scalar_type() != type || x[i]->sizes() != q.sizes()) Py_RETURN_NONE;
+  const int64_t B = q.size(0), H = q.size(1), d = q.size(2);
+  if (B > INT_MAX || H > INT_MAX || d > INT_MAX || h0 > H) Py_RETURN_NONE;
+  if (h0 > 0) {
+    const int64_t ring[4] = {B, h0, window, d};
+    for (int i = 4; i < 6; ++i)
+      if (!x[i] || x[i]->scalar_type() != type || x[i]->sizes() != at::IntArrayRef(ring, 4)) Py_RETURN_NONE;
+  }
+  if (h0 < H) {
+    const int64_t sums[3] = {B, H - h0, d * d + d};
+    if (!x[6] || x[6]->scalar_type() != at::kFloat || x[6]->sizes() != at::IntArrayRef(sums, 3)) Py_RETURN_NONE;
+  }
+  for (int i = 1; i < 7; ++i)
+    if (x[i] && x[i]->get_device() != q.get_device()) Py_RETURN_NONE;
+  if (a[14] == Py_None) {
+    PyObject* index = PyLong_FromLong(q.get_device());
+    PyObject* handle = index ? PyObject_CallOneArg(raw_stream_getter, index) : nullptr;
+    Py_XDECREF(index);
+    if (!handle) return nullptr;
+    stream = (int64_t)PyLong_AsUnsignedLongLongMask(handle);
+    Py_DECREF(handle);
+  } else if (!to_long(a[14], 0, LLONG_MAX, stream)) {
+    Py_RETURN_NONE;
+  }
+  const Decode call = reinterpret_cast<Decode>(PyLong_AsVoidPtr(a[0]));
+  if (!call) {
+    if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "no function address");
+    return nullptr;
+  }
+  p.struct_size = sizeof(p);
+  p.dtype = type == at::kBFloat16 ? GF_BF16 : GF_F32;
+  p.phi = (int32_t)phi;
+  p.n_sparse_heads = (int32_t)h0;
+  void* at_[7];
+  try {
+    for (int i = 0; i < 7; ++i) at_[i] = x[i] ? x[i]->data_ptr() : nullptr;
+  } catch (...) {
+    Py_RETURN_NONE;   // no memory behind it: the binding's code says so
+  }
+  gf_status st;
+  Py_BEGIN_ALLOW_THREADS
+  st = call(at_[0], at_[1], at_[2], at_[3], at_[4], at_[5], static_cast<float*>(at_[6]), (int)B, (int)H, (int)d,
+            (int)window, t, &p, reinterpret_cast<void*>(stream));
+  Py_END_ALLOW_THREADS
+  return PyLong_FromLong((long)st);
+}
+
+PyMethodDef methods[] = {
+    {"decode", reinterpret_cast<PyCFunction>(reinterpret_cast<void*>(decode)), METH_FASTCALL, "one decode step"},
+    {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_decode_call", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__decode_call() {
+  PyObject* torch_c = PyImport_ImportModule("torch._C");
+  if (!torch_c) return nullptr;
+  raw_stream_getter = PyObject_GetAttrString(torch_c, "_cuda_getCurrentRawStream");
+  Py_DECREF(torch_c);
+  return raw_stream_getter ? PyModule_Create(&module) : nullptr;
+}

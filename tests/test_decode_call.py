@@ -1,0 +1,72 @@
+"""The native host side of a decode step: the same step as the binding's own code, which takes whatever is not a plain call
+and refuses what it refused."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2412_19829_amd import binding as gb
+
+
+def _step(B, H, H0, d, w, dtype, device):
+    gen = torch.Generator().manual_seed(7)
+    def normal(*shape, dt=dtype):
+        return torch.randn(*shape, generator=gen).to(dt).to(device)
+    q, k, v = (normal(B, H, d) for _ in range(3))
+    kc, vc = (normal(B, H0, w, d) if H0 else None for _ in range(2))
+    st = normal(B, H - H0, d * d + d, dt=torch.float32).abs() if H0 < H else None
+    return q, k, v, torch.empty_like(q), kc, vc, st
+
+
+def test_host_tensors_are_left_to_the_binding():
+    args = _step(1, 2, 1, 64, 8, torch.float32, "cpu")
+    assert gb._decode_call()(gb.lib().decode_address, *args, 8, 1, 3, 0, 1.0, 0.0, None) is None
+    assert gb._decode_call()(gb.lib().decode_address, 1, *args[1:], 8, 1, 3, 0, 1.0, 0.0, None) is None
+    with pytest.raises(ValueError, match="no CPU path"):
+        gb.gformer_attn_decode(*args, 8, 1, 3)
+    with pytest.raises(TypeError):
+        gb._decode_call()(gb.lib().decode_address, *args)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [(1, 12, 2, 64, 128, 2048), (3, 4, 4, 128, 300, 17), (2, 3, 0, 64, 8, 0), (2, 3, 1, 128, 1, 5)],
+                         ids=lambda c: "x".join(map(str, c)))
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "f32"])
+@pytest.mark.parametrize("kw", [{}, {"softmax_scale": 0.5, "eps": 0.25}, {"side": True}], ids=["plain", "options", "stream"])
+def test_same_step_either_way(case, dtype, kw):
+    B, H, H0, d, w, t = case
+    kw = dict(kw)
+    side = torch.cuda.Stream() if kw.pop("side", False) else None
+    args = [_step(B, H, H0, d, w, dtype, "cuda") for _ in range(2)]
+    torch.cuda.synchronize()
+    if side is not None:
+        kw["stream"] = side.cuda_stream
+    full = (w, H0, t, 0, kw.get("softmax_scale", 1.0), kw.get("eps", 0.0), kw.get("stream"))
+    assert gb._decode_call()(gb.lib().decode_address, *args[0], *full) == gb.GF_OK
+    gb.gformer_attn_decode(*args[1], np.int64(w), H0, t, **kw)   # not a plain int: the binding's own code
+    torch.cuda.synchronize()
+    for a, b in zip(*args):
+        assert a is None or torch.equal(a, b)
+
+
+@pytest.mark.gpu
+def test_refusals():
+    q, k, v, out, kc, vc, st = _step(2, 3, 1, 64, 8, torch.bfloat16, "cuda")
+    run = gb.gformer_attn_decode
+    for bad in ((q, k[:1], v, out, kc, vc, st), (q, k, v, out, None, vc, st), (q, k, v, out, kc, vc, st.bfloat16()),
+                (q, k, v, out, kc[:, :, :4], vc, st), (q.half(), k, v, out, kc, vc, st),
+                (q.transpose(0, 1), k, v, out, kc, vc, st), (q.float(), k, v, out, kc, vc, st)):
+        with pytest.raises(ValueError):
+            run(*bad, 8, 1, 3)
+    for kw in ({"t": -1}, {"t": 3, "phi": 9}, {"t": 3, "eps": -1.0}):
+        with pytest.raises(gb.GformerError):
+            run(q, k, v, out, kc, vc, st, 8, 1, **kw)
+    with pytest.raises(gb.GformerError):
+        run(q, k, v, q, kc, vc, st, 8, 1, 3)
+    with torch.inference_mode():
+        run(*(x.clone() for x in (q, k, v, out, kc, vc, st)), 8, 1, 3)
+    batched = torch.stack([q, q])   # vmap's wrappers have no memory of their own to hand over
+    with pytest.raises(Exception):
+        torch.func.vmap(lambda x: run(x, k, v, out, kc, vc, st, 8, 1, 3))(batched)
+    torch.cuda.synchronize()
