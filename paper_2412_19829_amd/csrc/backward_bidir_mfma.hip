@@ -459,7 +459,7 @@ template <int D, bool ELU1> hipError_t launch_bidir_mfma_t(const BwdArgs& a, hip
   hipError_t e = hipSuccess;
   auto launch = [&](auto kern) {
     if (e != hipSuccess) return;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    e = allow_lds(kern, smem);
     if (e == hipSuccess) kern<<<grid, block, smem, s>>>(a);
   };
   launch(linear_bidir_sum_mfma_kernel<D, ELU1>);

@@ -233,11 +233,9 @@ __global__ __launch_bounds__(kThreads) void linear_bidir_dkv_kernel(BwdArgs a) {
 
 template <typename T, int D> hipError_t launch_bidir_t(const BwdArgs& a, hipStream_t s) {
   const dim3 grid(a.H - a.H0, a.B), block(kThreads);
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(linear_bidir_dq_kernel<T, D>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)bidir_dq_smem<D>());
+  hipError_t e = allow_lds(linear_bidir_dq_kernel<T, D>, bidir_dq_smem<D>());
   if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute(reinterpret_cast<const void*>(linear_bidir_dkv_kernel<T, D>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)bidir_dkv_smem<D>());
+  e = allow_lds(linear_bidir_dkv_kernel<T, D>, bidir_dkv_smem<D>());
   if (e != hipSuccess) return e;
   linear_bidir_state_kernel<T, D><<<grid, block, 0, s>>>(a);
   linear_bidir_dq_kernel<T, D><<<grid, block, bidir_dq_smem<D>(), s>>>(a);

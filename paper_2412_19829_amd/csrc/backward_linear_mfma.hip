@@ -762,7 +762,7 @@ template <int D, bool ELU1, bool BAND> hipError_t launch_lin_bwd_t(const BwdArgs
   hipError_t e = hipSuccess;
   auto launch = [&](auto kern, size_t smem, int blocks) {
     if (e != hipSuccess) return;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    e = allow_lds(kern, smem);
     if (e == hipSuccess) kern<<<BAND ? dim3(blocks) : dim3(a.H - a.H0, a.B, a.lin_segments), dim3(NT), smem, s>>>(a, linear, rows);
   };
   launch(linear_bwd_scan_kernel<D, ELU1, false, BAND>, sizeof(LbSmem<D>), first + ((rows + 7) & ~7) + rows);

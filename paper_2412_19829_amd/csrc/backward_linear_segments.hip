@@ -715,7 +715,7 @@ template <int D, bool ELU1, bool CAUSAL, bool PAIR> hipError_t launch_t(const Bw
   auto launch = [&](auto kern, size_t smem, int linear, int band_blocks) {
     if (e != hipSuccess || linear + rows == 0) return;
     if (rows > 0 && smem < sizeof(BandSmem<D>)) smem = sizeof(BandSmem<D>);
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    e = allow_lds(kern, smem);
     if (e != hipSuccess) return;
     kern<<<dim3(rows > 0 ? ((linear + 7) & ~7) + band_blocks : linear), dim3(C::NT), smem, s>>>(a, linear, rows);
     e = hipGetLastError();

@@ -39,8 +39,7 @@ template <int D> hipError_t launch_windowed_bwd_t(const BwdArgs& a, bool statist
   hipError_t e = hipSuccess;
   auto launch = [&](auto kern) {
     if (e != hipSuccess) return;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    e = allow_lds(kern, smem);
     if (e == hipSuccess) kern<<<grid, block, smem, s>>>(a);
   };
   launch(windowed_bwd_band_kernel<D, kStats>);

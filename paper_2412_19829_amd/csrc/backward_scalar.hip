@@ -515,12 +515,9 @@ hipError_t launch_bwd_t(const BwdArgs& a, bool windowed_heads, bool linear_heads
   }
   if (linear_heads && a.H0 < a.H) {
     dim3 grid(a.H - a.H0, a.B);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(linear_bwd_q_kernel<T, D>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)linear_bwd_q_smem<D>());
+    hipError_t e = allow_lds(linear_bwd_q_kernel<T, D>, linear_bwd_q_smem<D>());
     if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(linear_bwd_kv_kernel<T, D>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)linear_bwd_kv_smem<D>());
+    e = allow_lds(linear_bwd_kv_kernel<T, D>, linear_bwd_kv_smem<D>());
     if (e != hipSuccess) return e;
     linear_bwd_q_kernel<T, D><<<grid, dim3(kBwdLinThreads), linear_bwd_q_smem<D>(), s>>>(a);
     linear_bwd_kv_kernel<T, D><<<grid, dim3(kBwdLinThreads), linear_bwd_kv_smem<D>(), s>>>(a);

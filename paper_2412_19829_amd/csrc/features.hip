@@ -150,8 +150,7 @@ template <int D> hipError_t launch_mfma_t(const FeatureArgs& a, hipStream_t s) {
   const long total = (long)a.B * heads * ((a.N + kFeatRows - 1) / kFeatRows);
   const int grid = (int)(total < 512 ? total : 512);   // two resident workgroups per compute unit
   const int smem = (int)sizeof(FeatSmem<D>);
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(random_features_mfma_kernel<D>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+  hipError_t e = allow_lds(random_features_mfma_kernel<D>, smem);
   if (e != hipSuccess) return e;
   random_features_mfma_kernel<D><<<dim3(grid), dim3(kFeatThreads), smem, s>>>(a);
   return hipGetLastError();

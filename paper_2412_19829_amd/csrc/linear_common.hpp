@@ -156,10 +156,5 @@ __device__ __forceinline__ void load_chunk(u32x4 (&dst)[LinCfg<D>::PIECES], cons
 
 constexpr u32x4 kZero4 = {0u, 0u, 0u, 0u};
 
-template <typename K> hipError_t allow_lds(K kern, int smem) {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-}
-
 }  // namespace
 }  // namespace gformer

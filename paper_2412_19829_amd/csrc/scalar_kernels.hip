@@ -322,8 +322,7 @@ template <typename T, int D>
 static hipError_t launch_linear_scalar_t(const AttnArgs& a, hipStream_t s) {
   const size_t smem = linear_scalar_smem<D>();
   auto kern = a.causal ? linear_scalar_kernel<T, D> : linear_scalar_bidir_kernel<T, D>;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+  hipError_t e = allow_lds(kern, smem);
   if (e != hipSuccess) return e;
   dim3 grid(a.H - a.H0, a.B);
   kern<<<grid, dim3(kScalarThreads), smem, s>>>(a);

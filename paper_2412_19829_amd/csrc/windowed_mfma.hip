@@ -41,8 +41,7 @@ hipError_t launch_windowed_mfma(const AttnArgs& a, hipStream_t s) {
   const bool neg = a.scale < 0.f;
   hipError_t e = hipSuccess;
   auto launch = [&](auto kern, int smem) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    e = allow_lds(kern, smem);
     if (e == hipSuccess) kern<<<grid, block, smem, s>>>(a);
   };
   if (a.d == 64) {
