@@ -267,7 +267,7 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
         pl.windowed_blocks = B * H0 * ((N + rows - 1) / rows);
       }
       if (H1 > 0) {
-        const Segments f = f32_segments(heads_lin, N, d, UINT64_MAX, 1);
+        const Segments f = f32_segments(heads_lin, N, d, p->bidirectional == 0, UINT64_MAX, 1);
         r->f32_seg_len = f.len;
         r->f32_nseg = f.count;
         pl.segment_len = f.len;
@@ -448,7 +448,7 @@ gf_status attn_forward(const void* q, const void* k, const void* v, void* out, v
     if (!workspace) workspace_bytes = 0;
     if (workspace_bytes < r.plan.workspace_bytes) {
       const int64_t heads = (int64_t)B * (H - p->n_sparse_heads);
-      const Segments f = f32_segments(heads, N, d, workspace_bytes, 1);
+      const Segments f = f32_segments(heads, N, d, p->bidirectional == 0, workspace_bytes, 1);
       r.f32_seg_len = f.len;
       r.f32_nseg = f.count;
     }
@@ -714,7 +714,7 @@ size_t gformer_attn_bwd_workspace_bytes(int B, int H, int N, int d, int window,
     // single precision on the matrix cores: two carried sums per segment (what the call needs is less,
     // see gformer_attn_bwd)
     const int64_t heads = (int64_t)B * (H - p->n_sparse_heads);
-    const Segments f = f32_segments(heads, N, d, UINT64_MAX, 2);
+    const Segments f = f32_segments(heads, N, d, p->bidirectional == 0, UINT64_MAX, 2);
     const size_t sums = (size_t)heads * f.count * 2 * ((size_t)d * d + d) * sizeof(float);
     const size_t least = bwd_least_bytes(B, H, N, d, p);
     if (f.count > 1 || p->bidirectional == 1) need += sums;
@@ -810,7 +810,7 @@ gf_status gformer_attn_bwd(const void* q, const void* k, const void* v, const vo
   hipError_t e = hipSuccess;
   if (f32_matrix(p, B, H, N)) {
     a.ws_state = reinterpret_cast<float*>(static_cast<char*>(workspace) + bwd_stats_bytes(B, H, N));
-    const Segments f = f32_segments(lin_heads, N, d, workspace_bytes - bwd_stats_bytes(B, H, N), 2);
+    const Segments f = f32_segments(lin_heads, N, d, a.causal, workspace_bytes - bwd_stats_bytes(B, H, N), 2);
     a.f32_seg_len = f.len;
     a.f32_nseg = f.count;
     const bool f32_together = !p->overlap && f32_takes_windowed(d, B, H, a.H0, N);

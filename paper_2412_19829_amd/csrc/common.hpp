@@ -184,13 +184,13 @@ hipError_t launch_random_features(const FeatureArgs& a, bool bf16, bool mfma, hi
 hipError_t launch_decode(const DecodeArgs& a, bool bf16, hipStream_t s);
 size_t decode_smem_bytes(int d, int window, int H0);
 
-// Single-precision matrix-core kernels.  A head's segments: as many as keep three workgroups on every
+// Single-precision matrix-core kernels.  A head's segments: at most three workgroups on every
 // compute unit, none shorter than 128 tokens, as far as `bytes` hold `sums` carried sums for each.
 constexpr int kMaxSegments = 64;
 struct Segments {
   int len, count;
 };
-Segments f32_segments(int64_t heads, int N, int d, uint64_t bytes, int sums);
+Segments f32_segments(int64_t heads, int N, int d, bool causal, uint64_t bytes, int sums);
 // In place over [heads][nseg][floats]: mode 0, the sum over the slots before each; 1, behind each; 2, slot 0
 // receives the total.
 hipError_t launch_segment_scan(float* sums, int heads, int nseg, int floats, int mode, hipStream_t s);

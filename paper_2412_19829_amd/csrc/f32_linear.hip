@@ -16,6 +16,7 @@
 // (27 us of work for 109 MB = 22 us at the copy rate); waits for memory are 29 % of a wave's time.
 //
 // Every sum lies in the workspace as A row-major [feature][value], then its vector.
+#include <algorithm>
 #include <type_traits>
 
 #include "f32_band.hpp"
@@ -790,21 +791,32 @@ template <int D> hipError_t backward(const BwdArgs& a, bool with_windowed, hipSt
 
 }  // namespace
 
-// Three workgroups per compute unit: on 52 heads of 2048 tokens the forward walk takes 51, 42 and 43 us
-// with two, three and four, the dq walk 71, 60 and 65, the dk/dv walk 78, 67 and 73 (more segments mean
-// more sums to read and a longer scan).
-Segments f32_segments(int64_t heads, int N, int d, uint64_t bytes, int sums) {
+// A causal call takes as long as the compute unit with the most chunks to walk, one after the other, so a cut is priced
+// by that number: 8 segments of 8 chunks a head are 2 x 8 on 256 units and 64 heads, 11 of 6 are 3 x 6 on some.  Two
+// workgroups a unit hide each other's barriers nearly as well as three (1.1: the matrix units bind either way), one
+// alone does not (1.7), and four are a second round (not considered).  Beyond kSumInPlace segments the sums are scanned
+// by launches of their own, which cost as much as three chunks on a full unit, half as many on one that runs fast
+// because it is alone; between equals the fewer segments.  Over all keys, where a walk adds up all of a head's sums
+// and chunks are cheap, as many segments as give three workgroups a unit.  Measured (a training step, us; three
+// workgroups a unit, this rule): 4 x (3 + 13) x 2048 x 64 291.3 -> 269.6 (13, 8 segments), without windowed heads
+// 258.2 -> 228.5 (11, 8); elsewhere the same to 1 %.
+Segments f32_segments(int64_t heads, int N, int d, bool causal, uint64_t bytes, int sums) {
   Segments f{N, 1};
   if (heads <= 0 || N <= 0) return f;
-  const int64_t chunks = (N + CH - 1) / CH;
-  int64_t n = 3 * (int64_t)device_compute_units() / heads;
-  if (n > kMaxSegments) n = kMaxSegments;
-  if (n > chunks / 4) n = chunks / 4;
-  const uint64_t each = (uint64_t)heads * sums * ((uint64_t)d * d + d) * sizeof(float);
-  if ((uint64_t)n > bytes / each) n = (int64_t)(bytes / each);
-  if (n <= 1) return f;
-  f.len = (int)((chunks + n - 1) / n) * CH;
-  f.count = (N + f.len - 1) / f.len;
+  const int64_t chunks = (N + CH - 1) / CH, cus = device_compute_units();
+  const uint64_t room = bytes / ((uint64_t)heads * sums * ((uint64_t)d * d + d) * sizeof(float));
+  int64_t most = std::min(std::min((int64_t)kMaxSegments, chunks / 4), 3 * cus / heads);
+  if ((uint64_t)most > room) most = (int64_t)room;
+  double best = 0.;
+  for (int64_t n = causal ? 1 : std::max((int64_t)1, most); n <= most; ++n) {
+    const int64_t len = (chunks + n - 1) / n, count = (chunks + len - 1) / len, per = (heads * count + cus - 1) / cus;
+    const double cost = per * len * (per == 1 ? 1.7 : per == 2 ? 1.1 : 1.) + (count <= kSumInPlace ? 0. : per == 1 ? 1.5 : 3.);
+    if (best == 0. || cost < best) {
+      best = cost;
+      f.count = (int)count;
+      f.len = count > 1 ? (int)len * CH : N;
+    }
+  }
   return f;
 }
 
