@@ -71,13 +71,7 @@ template <int D> struct Rows {
   static constexpr int TR = kF32Row<D>;
   int row, col;
   __device__ __forceinline__ explicit Rows(int tid) : row(tid / (D / 4)), col(4 * (tid % (D / 4))) {}
-  // rows past the end re-read the last row, in bounds
-  __device__ __forceinline__ void load(f32x4 (&x)[2], const float* base, int64_t sn, int t0, int N) const {
-#pragma unroll
-    for (int p = 0; p < 2; ++p)
-      x[p] = *reinterpret_cast<const f32x4*>(base + (int64_t)min(t0 + row + 16 * p, N - 1) * sn + col);
-  }
-  // ... and are stored as zeros: they contribute nothing
+  // rows past the end are stored as zeros: they contribute nothing
   __device__ __forceinline__ void store(float* tile, const f32x4 (&x)[2], int t0, int N) const {
 #pragma unroll
     for (int p = 0; p < 2; ++p)
@@ -106,6 +100,37 @@ template <int D> struct Rows {
         for (int j = 0; j < 4; ++j) f[p][j] = elu1_f32(x[p][j]);
     }
     store(tile, f, t0, N);
+  }
+};
+
+// One tensor as a thread reads it: a wave-uniform base and a 32-bit offset that never changes, under one clamp (rows
+// past the end re-read the last, in bounds).  As a 64-bit product per piece, four quarter-rate multiplies, the walks took
+// (a training step, us) 497 in place of 487 on 32 heads of 2048 x 128, 228 in place of 226.5 on 64 of 2048 x 64.
+template <int D> struct Piece {
+  uint32_t off, colb;
+  int sn;
+  __device__ __forceinline__ Piece(const Rows<D>& r, int64_t row_stride)
+      : off(4u * (uint32_t)(r.row * (int)row_stride + r.col)), colb(4u * (uint32_t)r.col), sn((int)row_stride) {}
+  __device__ __forceinline__ void load(f32x4 (&x)[2], const float* head, int t0, int N) const {
+    t0 = min(t0, N - 1);
+    const int last = min(N - 1 - t0, CH - 1);
+    const char* chunk = reinterpret_cast<const char*>(head + (int64_t)t0 * sn);
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const int first = min(16 * p, last);
+      const uint32_t lim = 4u * (uint32_t)((last - first) * sn) + colb;
+      x[p] = *reinterpret_cast<const f32x4*>(chunk + 4u * (uint32_t)(first * sn) + (size_t)min(off, lim));
+    }
+  }
+};
+// This lane's four columns of token 16*tb + i of a chunk, on their way out.
+struct OutPiece {
+  uint32_t off;
+  int sn;
+  __device__ __forceinline__ OutPiece(int64_t row_stride, int wave, int g, int i)
+      : off(4u * (uint32_t)(i * (int)row_stride + 16 * wave + 4 * g)), sn((int)row_stride) {}
+  __device__ __forceinline__ void store(float* head, int t, f32x4 x) const {   // t: uniform
+    *reinterpret_cast<f32x4*>(reinterpret_cast<char*>(head + (int64_t)t * sn) + (size_t)off) = x;
   }
 };
 
@@ -235,15 +260,16 @@ __global__ __launch_bounds__(kLinThreads<D>, 2) void linear_f32_state_kernel(Sta
   f32x4 s[D / 16], kr[2], vr[2];
   clear<D>(s);
   float z = 0.f;
-  st.load(kr, kp, a.k.sn, begin, a.N);
-  st.load(vr, vp, a.v.sn, begin, a.N);
+  const Piece<D> pk(st, a.k.sn), pv(st, a.v.sn);
+  pk.load(kr, kp, begin, a.N);
+  pv.load(vr, vp, begin, a.N);
   for (int t0 = begin; t0 < end; t0 += CH) {
     lds_barrier();
     st.store_mapped(fk, kr, t0, a.N, a.phi);
     st.store(vv, vr, t0, a.N);
     if (t0 + CH < end) {
-      st.load(kr, kp, a.k.sn, t0 + CH, a.N);
-      st.load(vr, vp, a.v.sn, t0 + CH, a.N);
+      pk.load(kr, kp, t0 + CH, a.N);
+      pv.load(vr, vp, t0 + CH, a.N);
     }
     lds_barrier();
     float vc[2][4], kc[2][4];
@@ -313,11 +339,13 @@ __device__ __forceinline__ void linear_f32(const AttnArgs& a, int block, unsigne
   float* op = reinterpret_cast<float*>(a.out) + b * a.osb + h * a.osh;
   const int begin = seg * a.f32_seg_len, end = min(N, begin + a.f32_seg_len);
   const Rows<D> st(tid);
+  const Piece<D> pq(st, a.q.sn), pk(st, a.k.sn), pv(st, a.v.sn);
+  const OutPiece oo(a.osn, wave, g, i);
   f32x4 s[D / 16], qr[2], kr[2], vr[2];
-  st.load(qr, qp, a.q.sn, begin, N);
+  pq.load(qr, qp, begin, N);
   if (CAUSAL) {
-    st.load(kr, kp, a.k.sn, begin, N);
-    st.load(vr, vp, a.v.sn, begin, N);
+    pk.load(kr, kp, begin, N);
+    pv.load(vr, vp, begin, N);
   }
   clear<D>(s);
   {
@@ -341,10 +369,10 @@ __device__ __forceinline__ void linear_f32(const AttnArgs& a, int block, unsigne
       st.store(sm.vv, vr, t0, N);
     }
     if (STEADY || t0 + CH < end) {
-      st.load(qr, qp, a.q.sn, t0 + CH, N);
+      pq.load(qr, qp, t0 + CH, N);
       if (CAUSAL) {
-        st.load(kr, kp, a.k.sn, t0 + CH, N);
-        st.load(vr, vp, a.v.sn, t0 + CH, N);
+        pk.load(kr, kp, t0 + CH, N);
+        pv.load(vr, vp, t0 + CH, N);
       }
     }
     lds_barrier();
@@ -396,7 +424,7 @@ __device__ __forceinline__ void linear_f32(const AttnArgs& a, int block, unsigne
       for (int j = 0; j < 4; ++j) o[j] = __builtin_amdgcn_ldexpf(num[tb][j] * inv, -e);
       const int n = t0 + 16 * tb + i;
       if (STEADY || n < N)
-        *reinterpret_cast<f32x4*>(op + (int64_t)n * a.osn + 16 * wave + 4 * g) = o;
+        oo.store(op, t0 + 16 * tb, o);
     }
     if (CAUSAL) {
       add_outer<D>(s, sm.fk, vc, g, i);
@@ -442,13 +470,15 @@ __device__ __forceinline__ void linear_bwd_q_f32(const BwdArgs& a, int block, un
   float* ws = a.ws + ((int64_t)b * a.H + h) * N * 2;
   const int begin = seg * a.f32_seg_len, end = min(N, begin + a.f32_seg_len);
   const Rows<D> st(tid);
+  const Piece<D> pq(st, a.q.sn), pk(st, a.k.sn), pv(st, a.v.sn), pd(st, a.dout.sn);
+  const OutPiece oq(a.q.sn, wave, g, i);
   f32x4 qr[2], kr[2], vr[2], dr[2];
   auto load = [&](int t0) {
-    st.load(qr, qp, a.q.sn, t0, N);
-    st.load(dr, dp, a.dout.sn, t0, N);
+    pq.load(qr, qp, t0, N);
+    pd.load(dr, dp, t0, N);
     if (CAUSAL) {
-      st.load(kr, kp, a.k.sn, t0, N);
-      st.load(vr, vp, a.v.sn, t0, N);
+      pk.load(kr, kp, t0, N);
+      pv.load(vr, vp, t0, N);
     }
   };
   load(begin);
@@ -560,7 +590,7 @@ __device__ __forceinline__ void linear_bwd_q_f32(const BwdArgs& a, int block, un
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[j] *= feature_map_slope(qc[tb][j], a.phi);
       if (STEADY || n < N) {
-        *reinterpret_cast<f32x4*>(dq + (int64_t)n * a.q.sn + 16 * wave + 4 * g) = acc;
+        oq.store(dq, t0 + 16 * tb, acc);
       }
     }
     // B += phi(q)^T (x) dO / den, Y += c phi(q); a token's 2^e / den and c sit in the lane that owns it
@@ -607,14 +637,16 @@ __device__ __forceinline__ void linear_bwd_kv_f32(const BwdArgs& a, int block, u
   const float* ws = a.ws + ((int64_t)b * a.H + h) * N * 2;
   const int begin = seg * a.f32_seg_len, end = min(N, begin + a.f32_seg_len);
   const Rows<D> st(tid);
+  const Piece<D> pq(st, a.q.sn), pk(st, a.k.sn), pv(st, a.v.sn), pd(st, a.dout.sn);
+  const OutPiece ok(a.k.sn, wave, g, i), ov(a.v.sn, wave, g, i);
   f32x4 qr[2], kr[2], vr[2], dr[2];
   float den[2], cr = 0.f;
   auto load = [&](int t0) {
-    st.load(kr, kp, a.k.sn, t0, N);
-    st.load(vr, vp, a.v.sn, t0, N);
+    pk.load(kr, kp, t0, N);
+    pv.load(vr, vp, t0, N);
     if (CAUSAL) {
-      st.load(qr, qp, a.q.sn, t0, N);
-      st.load(dr, dp, a.dout.sn, t0, N);
+      pq.load(qr, qp, t0, N);
+      pd.load(dr, dp, t0, N);
 #pragma unroll
       for (int p = 0; p < 2; ++p) den[p] = ws[2 * (int64_t)min(t0 + st.row + 16 * p, N - 1)];
       if (tid < CH) cr = t0 + tid < N ? ws[2 * (int64_t)(t0 + tid) + 1] : 0.f;
@@ -698,8 +730,8 @@ __device__ __forceinline__ void linear_bwd_kv_f32(const BwdArgs& a, int block, u
 #pragma unroll
       for (int j = 0; j < 4; ++j) dka[ub][j] *= feature_map_slope(kc[j], a.phi);
       if (STEADY || n < N) {
-        *reinterpret_cast<f32x4*>(dk + (int64_t)n * a.k.sn + 16 * wave + 4 * g) = dka[ub];
-        *reinterpret_cast<f32x4*>(dv + (int64_t)n * a.v.sn + 16 * wave + 4 * g) = dva[ub];
+        ok.store(dk, t0 + 16 * ub, dka[ub]);
+        ov.store(dv, t0 + 16 * ub, dva[ub]);
       }
     }
     if (CAUSAL) {
