@@ -688,8 +688,7 @@ size_t bwd_stats_bytes(int B, int H, int N) {
   return ((size_t)B * H * N * 2 * sizeof(float) + 255) / 256 * 256;
 }
 // bf16: the carried sums of the segments
-size_t bwd_segment_bytes(int64_t heads, int N, int d, bool causal) {
-  const Segments f = backward_segments(heads, N, d, causal);
+size_t bwd_segment_bytes(int64_t heads, const Segments& f, int d, bool causal) {
   if (causal && f.count == 1) return 0;
   return (size_t)heads * f.count * 2 * ((size_t)d * d + d) * sizeof(float);
 }
@@ -721,7 +720,10 @@ size_t gformer_attn_bwd_workspace_bytes(int B, int H, int N, int d, int window,
     return need > least ? need : least;
   }
   if (p && p->dtype == GF_BF16 && p->impl != GF_IMPL_SCALAR && d == 64 && p->n_sparse_heads >= 0 && p->n_sparse_heads < H) {
-    const size_t sums = bwd_segment_bytes((int64_t)B * (H - p->n_sparse_heads), N, d, p->bidirectional == 0);
+    // room for the most segments a call of this shape is cut into, with its windowed heads in launches of their own
+    const int64_t heads = (int64_t)B * (H - p->n_sparse_heads);
+    const bool causal = p->bidirectional == 0;
+    const size_t sums = bwd_segment_bytes(heads, backward_segments(heads, N, d, causal, 0), d, causal);
     const size_t least = bwd_least_bytes(B, H, N, d, p);
     return need + sums > least ? need + sums : least;
   }
@@ -790,9 +792,10 @@ gf_status gformer_attn_bwd(const void* q, const void* k, const void* v, const vo
   const int64_t lin_heads = (int64_t)B * (H - a.H0);
   const bool one_grid = lin_heads < (1 << 22);
   if (mfma && d == 64 && !a.causal && !one_grid) return GF_ERR_UNSUPPORTED;
-  const Segments segs = backward_segments(lin_heads, N, d, a.causal);
+  const int64_t band_tiles = p->overlap || a.H0 <= 0 ? 0 : backward_band_tiles((int64_t)B * a.H0, N, a.wleft, a.wright);
+  const Segments segs = backward_segments(lin_heads, N, d, a.causal, band_tiles);
   const bool segments = d == 64 && one_grid &&
-                        workspace_bytes >= bwd_stats_bytes(B, H, N) + bwd_segment_bytes(lin_heads, N, d, a.causal);
+                        workspace_bytes >= bwd_stats_bytes(B, H, N) + bwd_segment_bytes(lin_heads, segs, d, a.causal);
   // The linear heads' launches take the windowed heads' passes along: the walks all four, the d = 128 scans
   // three behind a launch for the statistics.
   const bool together = (segments || (d == 128 && a.causal && (int64_t)B * H < (1 << 20))) && a.H0 > 0 && a.H0 < a.H &&

@@ -31,6 +31,7 @@
 // Precision: S, T, den, c, Z, Y and the carried sums are fp32; the weights T/den - c, a difference a
 // gradient row sums with signs, enter their products as bf16 pairs (high half + rounded remainder), and so do some
 // of the carried sums and of phi(q) / den (which and why: launch_linear_backward_segments).
+#include <algorithm>
 #include <type_traits>
 
 #include "backward_band.hpp"
@@ -746,14 +747,28 @@ template <int D, bool ELU1, bool CAUSAL, bool PAIR> hipError_t launch_t(const Bw
 
 }  // namespace
 
+int64_t backward_band_tiles(int64_t windowed_heads, int N, int wleft, int wright) {
+  const int rows = band_rows(kBandThreads);
+  const int64_t tiles = std::min(((int64_t)wleft + wright + rows - 1 + BC - 1) / BC + 1, ((int64_t)N + BC - 1) / BC);
+  return windowed_heads * ((N + rows - 1) / rows) * tiles;
+}
+
 // Three workgroups per compute unit and no segment under 128 tokens: 52 heads of 4096 tokens take 50 + 44 us
 // (dq, dk/dv walk) with two, 46 + 40 with three, 51 + 38 with four.  Over all keys a walk reads every sum of
 // its head: four segments at most, as many as the workspace of that form has always held.
-Segments backward_segments(int64_t heads, int N, int d, bool causal) {
+// A causal call whose band passes weigh half of its walks or more (a tile about one and a half chunks) gets two walks a
+// unit: with three there is no room beside them, and the band runs behind them on a chip that empties.  All passes, us,
+// three and two a unit, by band's share: 6 x (1 + 7) x 8192, window 128 (0.3) 167.0 and 166.1; 8 x (2 + 10) x 4096, 128
+// (0.4) 161.9 and 165.4; 4 x (3 + 13) x 4096, 128 (0.45) 117.2 and 123.0; 8 x (2 + 10) x 4096, 256 (0.55) 175.8 and
+// 170.0; 1 x (2 + 10) x 8192, 256 (0.55) 81.4 and 74.7; 16 x (2 + 6) x 1500, 128 (0.65) 101.9 and 94.5; 4 x (5 + 27) x
+// 2048, 512 (0.8) 148.5 and 135.0; 8 x (4 + 8) x 2048, 256 (1.3) 121.4 and 113.2; 4 x (8 + 8) x 4096, 256 (2.6) 157.3
+// and 153.0.
+Segments backward_segments(int64_t heads, int N, int d, bool causal, int64_t band_tiles) {
   Segments f{N, 1};
   if (heads <= 0 || N <= 0 || d != 64) return f;
   const int64_t chunks = (N + SC - 1) / SC, most = causal ? kMaxSegments : kBidirStateSlots;
-  int64_t n = 3 * (int64_t)device_compute_units() / heads;
+  const int walks = causal && 3 * band_tiles >= heads * chunks ? 2 : 3;
+  int64_t n = walks * (int64_t)device_compute_units() / heads;
   if (n > most) n = most;
   if (n > chunks / 4) n = chunks / 4;
   if (n <= 1) return f;

@@ -203,7 +203,9 @@ hipError_t launch_windowed_backward_f32(const BwdArgs& a, hipStream_t s);
 hipError_t launch_linear_backward_f32(const BwdArgs& a, bool with_windowed, hipStream_t s);
 // bf16 backward pass of the linear heads at d = 64, heads cut into segments (lin_segments of lin_segment_len
 // tokens); ws_state holds [2][B*(H-H0)][lin_segments][d*d + d] fp32 sums unless there is one causal segment.
-Segments backward_segments(int64_t heads, int N, int d, bool causal);
+// band_tiles: 64-row tiles that a pass over the windowed heads' band walks in the same launches (0: none ride along).
+Segments backward_segments(int64_t heads, int N, int d, bool causal, int64_t band_tiles);
+int64_t backward_band_tiles(int64_t windowed_heads, int N, int wleft, int wright);
 // with_windowed: the windowed heads' passes ride in the same launches.
 hipError_t launch_linear_backward_segments(const BwdArgs& a, bool with_windowed, hipStream_t s);
 constexpr int64_t kF32MaxRows = (int64_t)1 << 26;   // B * heads * N / 16 workgroups stay inside a grid
