@@ -78,19 +78,9 @@ __device__ __forceinline__ void windowed_band(const BwdArgs& a, int block, unsig
   // resident operands (B operands of the score products); rows past N re-read row N-1
   const int ri = r0 + ln;
   const int ric = min(ri, N - 1);
-  bf16x8 reg1[KS], reg2[HAS_DP ? KS : 1];
-  {
-    const uint16_t* p1 = res1 + (int64_t)ric * res1_t.sn + 8 * lh;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-      reg1[ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(p1 + 16 * ks));
-    if (HAS_DP) {
-      const uint16_t* p2 = res2 + (int64_t)ric * res2_t.sn + 8 * lh;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        reg2[ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(p2 + 16 * ks));
-    }
-  }
+  WaveRows<D> rows1, rows2;
+  rows1.template load<false>(res1, res1_t.sn, r0, N - 1, lane);
+  if (HAS_DP) rows2.template load<false>(res2, res2_t.sn, r0, N - 1, lane);
   // statistics of the resident query (kDq)
   float lse_q = 0.f, dd_q = 0.f;
   if (PASS == kDq) {
@@ -164,6 +154,13 @@ __device__ __forceinline__ void windowed_band(const BwdArgs& a, int block, unsig
   const int trlane = lds_operand_tr_lane_offset(ROW, lane) + 4 * lh * ROW;
 
   load_tile(tfirst);
+  // the resident rows turn in the second buffer (those of a fifth wave on in the first), free until the barrier
+  bf16x8 reg1[KS], reg2[KS];
+  uint16_t* own = reinterpret_cast<uint16_t*>(&sm.buf[wave < 4 ? 1 : 0]) + (wave & 3) * WR * ROW;
+  static_assert(NT <= 512 && 4 * WR == 2 * BC, "the x and y tiles of a buffer hold four waves' rows");
+  rows1.template operands<ROW>(reg1, own, lane);
+  if (HAS_DP) rows2.template operands<ROW>(reg2, own, lane);
+  if (NT > 256) lds_barrier();
   store_tile(sm.buf[0]);
   if (tfirst < tlast) load_tile(tfirst + 1);
   lds_barrier();

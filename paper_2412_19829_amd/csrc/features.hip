@@ -33,13 +33,6 @@ template <int D> struct FeatSmem {
   uint16_t ot[kFeatWaves][kFeatRows * OROW];        // a wave's finished rows on their way to memory
 };
 
-// One wave's LDS traffic in order: its lanes see each other's writes.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <int D>
 __global__ __launch_bounds__(kFeatThreads, D == 64 ? 4 : 2) void random_features_mfma_kernel(FeatureArgs a) {
   constexpr int KS = D / 16, NT = D / 32;

@@ -152,4 +152,39 @@ __device__ __forceinline__ bf16x8 lds_operand_tr(const uint16_t* tile, int strid
   return as_bf16x8(r);
 }
 
+// One wave's LDS traffic in order: its lanes see each other's writes.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// 32 rows of D values as one wave's operands, lane = row.  Loaded in that layout an instruction touches 32 rows, 32
+// bytes of each, and the memory pipeline works through all of them; so the rows come whole, 16 bytes a lane, and
+// change layout in 32 * ROW elements of LDS that are the wave's own meanwhile.  The resident rows of the windowed
+// heads, us before and now: forward of 32 x 12 x 577 x 64 over all keys 39.5, 37.7, of 8 x 12 x 4096 x 64 66.2, 65.1;
+// backward of 4 x 32 x 8192 x 128 990, 986, of 16 x 8 x 1500 x 64 94.5, 93.9 (same bits).
+template <int D> struct WaveRows {
+  static constexpr int C8 = D / 8, RP = 64 / C8;   // pieces a row, rows an instruction
+  u32x4 x[D / 16];
+  // rows r0 .. r0 + 31 of `head`, those past `last` are row `last`
+  template <bool NT> __device__ __forceinline__ void load(const uint16_t* head, int64_t row_stride, int r0, int last, int lane) {
+#pragma unroll
+    for (int i = 0; i < D / 16; ++i) {
+      const u32x4* p = reinterpret_cast<const u32x4*>(
+          head + (int64_t)min(r0 + lane / C8 + i * RP, last) * row_stride + 8 * (lane % C8));
+      x[i] = NT ? __builtin_nontemporal_load(p) : *p;
+    }
+  }
+  template <int ROW> __device__ __forceinline__ void operands(bf16x8 (&reg)[D / 16], uint16_t* own, int lane) const {
+#pragma unroll
+    for (int i = 0; i < D / 16; ++i)
+      *reinterpret_cast<u32x4*>(own + (lane / C8 + i * RP) * ROW + 8 * (lane % C8)) = x[i];
+    wave_sync();
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) reg[ks] = lds_read16(own + (lane & 31) * ROW + 16 * ks + 8 * (lane >> 5));
+    wave_sync();
+  }
+};
+
 }  // namespace gformer

@@ -63,13 +63,8 @@ __device__ __forceinline__ void windowed_block(const AttnArgs& a, int block, uns
   // Q^T as B operands, resident for the whole kernel.  Rows past N re-read row N-1 (in bounds);
   // their columns are computed and dropped.
   bf16x8 qreg[KS];
-  {
-    const int qi = min(q0 + ln, N - 1);
-    const uint16_t* qr = qp + (int64_t)qi * a.q.sn + 8 * lh;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-      qreg[ks] = as_bf16x8(__builtin_nontemporal_load(reinterpret_cast<const u32x4*>(qr + 16 * ks)));
-  }
+  WaveRows<D> qrows;
+  qrows.template load<true>(qp, a.q.sn, q0, N - 1, lane);
   // Memory loads retire in issue order, so the wait for the first tile below also covers these
   // loads, but only if they stay in front of it: were they to slip behind, every later use of Q
   // would have to wait for whatever tile load is in flight at that point, and the prefetch
@@ -263,6 +258,9 @@ __device__ __forceinline__ void windowed_block(const AttnArgs& a, int block, uns
   };
 
   load_rows(kst, kp, ksn, koff, kfirst);
+  // the second key tile and the value tiles are free until the barrier: Q turns there
+  static_assert(BC * KROW + 2 * BC * VROW >= BR * KROW, "a piece for every wave");
+  qrows.template operands<KROW>(qreg, reinterpret_cast<uint16_t*>(smem_raw) + (BC + wave * WQ) * KROW, lane);
   store_rows(sm.k[0], KROW, kst);
   load_rows(vst, vp, vsn, voff, kfirst);
   if (kfirst < klast) load_rows(kst, kp, ksn, koff, kfirst + 1);
