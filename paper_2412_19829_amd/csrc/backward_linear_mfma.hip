@@ -284,9 +284,11 @@ __device__ __forceinline__ void scan_q(const BwdArgs& a, int h, int b, int seg, 
       const int top = (it == jt ? ln : CH) - 4 * lh;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float x = 8 * (r / 4) + r % 4 <= top ? s[r] : 0.f;
+        // T is masked as well: a later token's product may be infinite
+        const bool seen = 8 * (r / 4) + r % 4 <= top;
+        const float x = seen ? s[r] : 0.f;
         ss += x;
-        st = fmaf(x, traw[r], st);
+        st = fmaf(x, seen ? traw[r] : 0.f, st);
       }
       ss = sum_over_halves(ss);
       st = sum_over_halves(st);
