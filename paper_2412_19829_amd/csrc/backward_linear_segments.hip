@@ -406,9 +406,11 @@ __device__ __forceinline__ void seg_q(const BwdArgs& a, int block, unsigned char
       float ss = 0.f, st = 0.f;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float x = (tb != ub || 4 * g + r <= i) ? sv[r] : 0.f;
+        // T is masked as well: a later token's product may be infinite
+        const bool seen = tb != ub || 4 * g + r <= i;
+        const float x = seen ? sv[r] : 0.f;
         ss += x;
-        st = fmaf(x, tv[r], st);
+        st = fmaf(x, seen ? tv[r] : 0.f, st);
       }
       ss = sum_over_groups(ss);
       st = sum_over_groups(st);

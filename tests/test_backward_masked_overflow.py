@@ -8,9 +8,10 @@ import pytest
 from tests.test_gpu_parity import run_bwd, synth
 
 
-# query i, later key j of the same 32 x 32 tile and of neighbouring ones, first and second chunk
+# query i, later key j of the same 32 x 32 (d = 128) or 16 x 16 (d = 64) tile and of neighbouring ones, first and second chunk
 @pytest.mark.gpu
-@pytest.mark.parametrize("d,i,j", [(128, 0, 1), (128, 3, 31), (128, 1, 40), (128, 33, 62), (128, 70, 95), (128, 100, 127)])
+@pytest.mark.parametrize("d,i,j", [(128, 0, 1), (128, 3, 31), (128, 1, 40), (128, 33, 62), (128, 70, 95), (128, 100, 127),
+                                   (64, 0, 1), (64, 2, 15), (64, 5, 20), (64, 17, 31), (64, 33, 47), (64, 50, 63)])
 def test_rows_before_the_key_do_not_change(d, i, j):
     N = 130
     q, k, v = synth(1, 2, N, d, "bf16", 131)
