@@ -21,11 +21,13 @@ namespace {
 
 using Decode = decltype(&gformer_attn_decode);
 
-// A dense tensor in device memory and nothing else: a wrapper's data pointer is not what the caller means.
+// A dense tensor and nothing else: a wrapper's data pointer is not what the caller means.
 const at::Tensor* plain(PyObject* o) {
   if (!THPVariable_CheckExact(o)) return nullptr;
   const at::Tensor& t = THPVariable_Unpack(o);
-  if (!t.defined() || !t.is_cuda() || t.layout() != at::kStrided || !t.has_storage() || !t.is_contiguous()) return nullptr;
+  if (!t.defined() || t.layout() != at::kStrided || t.is_nested() || !t.has_storage() ||
+      t.unsafeGetTensorImpl()->has_symbolic_sizes_strides() || !t.is_contiguous())
+    return nullptr;
   constexpr c10::DispatchKeySet wrapped({
       c10::DispatchKey::Python, c10::DispatchKey::PythonTLSSnapshot, c10::DispatchKey::Functionalize,
       c10::DispatchKey::FuncTorchBatched, c10::DispatchKey::FuncTorchGradWrapper, c10::DispatchKey::Conjugate,
@@ -47,70 +49,85 @@ bool to_float(PyObject* o, float& x) {
 
 PyObject* raw_stream_getter = nullptr;   // torch._C._cuda_getCurrentRawStream
 
+// What the call takes from its arguments; the stream only where it was named.
+struct Step {
+  gformer_params p;
+  void* at[7];   // q, k, v, out, kcache, vcache, state
+  int64_t B, H, d, window, t, device, stream;
+};
+
+// False for anything but the plain call.  Asking a tensor may throw.
+bool gather(PyObject* const* a, Step& s) {
+  const at::Tensor* x[7];
+  for (int i = 0; i < 7; ++i) {
+    x[i] = nullptr;
+    if (i >= 4 && a[1 + i] == Py_None) continue;
+    if (!(x[i] = plain(a[1 + i]))) return false;
+  }
+  int64_t h0, phi;
+  std::memset(&s, 0, sizeof(s));
+  if (!to_long(a[8], INT_MIN, INT_MAX, s.window) || !to_long(a[9], 0, INT_MAX, h0) || !to_long(a[10], LLONG_MIN, LLONG_MAX, s.t) ||
+      !to_long(a[11], INT_MIN, INT_MAX, phi) || !to_float(a[12], s.p.softmax_scale) || !to_float(a[13], s.p.eps) ||
+      (a[14] != Py_None && !to_long(a[14], 0, LLONG_MAX, s.stream)))
+    return false;
+  const at::Tensor& q = *x[0];
+  const auto type = q.scalar_type();
+  if ((type != at::kBFloat16 && type != at::kFloat) || q.dim() != 3) return false;
+  for (int i = 1; i < 4; ++i)
+    if (x[i]->scalar_type() != type || x[i]->sizes() != q.sizes()) return false;
+  s.B = q.size(0);
+  s.H = q.size(1);
+  s.d = q.size(2);
+  if (s.B > INT_MAX || s.H > INT_MAX || s.d > INT_MAX || h0 > s.H) return false;
+  if (h0 > 0) {
+    const int64_t ring[4] = {s.B, h0, s.window, s.d};
+    for (int i = 4; i < 6; ++i)
+      if (!x[i] || x[i]->scalar_type() != type || x[i]->sizes() != at::IntArrayRef(ring, 4)) return false;
+  }
+  if (h0 < s.H) {
+    const int64_t sums[3] = {s.B, s.H - h0, s.d * s.d + s.d};
+    if (!x[6] || x[6]->scalar_type() != at::kFloat || x[6]->sizes() != at::IntArrayRef(sums, 3)) return false;
+  }
+  // the device is asked last, so that host tensors go through all of the above, which a process without a device can run
+  s.device = q.get_device();
+  for (int i = 0; i < 7; ++i)
+    if (x[i] && (!x[i]->is_cuda() || x[i]->get_device() != s.device)) return false;
+  for (int i = 0; i < 7; ++i) s.at[i] = x[i] ? x[i]->data_ptr() : nullptr;
+  s.p.struct_size = sizeof(s.p);
+  s.p.dtype = type == at::kBFloat16 ? GF_BF16 : GF_F32;
+  s.p.phi = (int32_t)phi;
+  s.p.n_sparse_heads = (int32_t)h0;
+  return true;
+}
+
 PyObject* decode(PyObject*, PyObject* const* a, Py_ssize_t n) {
   if (n != 15) {
     PyErr_SetString(PyExc_TypeError, "decode takes 15 arguments");
     return nullptr;
   }
-  const at::Tensor* x[7];   // q, k, v, out, kcache, vcache, state
-  for (int i = 0; i < 7; ++i) {
-    x[i] = nullptr;
-    if (i >= 4 && a[1 + i] == Py_None) continue;
-    if (!(x[i] = plain(a[1 + i]))) Py_RETURN_NONE;
+  Step s;
+  try {   // no C++ exception may leave a function that the interpreter called
+    if (!gather(a, s)) Py_RETURN_NONE;
+  } catch (...) {
+    Py_RETURN_NONE;   // the binding's code raises it, or says what is missing
   }
-  int64_t window, h0, t, phi, stream = 0;
-  gformer_params p;
-  std::memset(&p, 0, sizeof(p));
-  if (!to_long(a[8], INT_MIN, INT_MAX, window) || !to_long(a[9], 0, INT_MAX, h0) || !to_long(a[10], LLONG_MIN, LLONG_MAX, t) ||
-      !to_long(a[11], INT_MIN, INT_MAX, phi) || !to_float(a[12], p.softmax_scale) || !to_float(a[13], p.eps))
-    Py_RETURN_NONE;
-  const at::Tensor& q = *x[0];
-  const auto type = q.scalar_type();
-  if ((type != at::kBFloat16 && type != at::kFloat) || q.dim() != 3) Py_RETURN_NONE;
-  for (int i = 1; i < 4; ++i)
-    if (x[i]->scalar_type() != type || x[i]->sizes() != q.sizes()) Py_RETURN_NONE;
-  const int64_t B = q.size(0), H = q.size(1), d = q.size(2);
-  if (B > INT_MAX || H > INT_MAX || d > INT_MAX || h0 > H) Py_RETURN_NONE;
-  if (h0 > 0) {
-    const int64_t ring[4] = {B, h0, window, d};
-    for (int i = 4; i < 6; ++i)
-      if (!x[i] || x[i]->scalar_type() != type || x[i]->sizes() != at::IntArrayRef(ring, 4)) Py_RETURN_NONE;
-  }
-  if (h0 < H) {
-    const int64_t sums[3] = {B, H - h0, d * d + d};
-    if (!x[6] || x[6]->scalar_type() != at::kFloat || x[6]->sizes() != at::IntArrayRef(sums, 3)) Py_RETURN_NONE;
-  }
-  for (int i = 1; i < 7; ++i)
-    if (x[i] && x[i]->get_device() != q.get_device()) Py_RETURN_NONE;
   if (a[14] == Py_None) {
-    PyObject* index = PyLong_FromLong(q.get_device());
+    PyObject* index = PyLong_FromLong((long)s.device);
     PyObject* handle = index ? PyObject_CallOneArg(raw_stream_getter, index) : nullptr;
     Py_XDECREF(index);
     if (!handle) return nullptr;
-    stream = (int64_t)PyLong_AsUnsignedLongLongMask(handle);
+    s.stream = (int64_t)PyLong_AsUnsignedLongLongMask(handle);
     Py_DECREF(handle);
-  } else if (!to_long(a[14], 0, LLONG_MAX, stream)) {
-    Py_RETURN_NONE;
   }
   const Decode call = reinterpret_cast<Decode>(PyLong_AsVoidPtr(a[0]));
   if (!call) {
     if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "no function address");
     return nullptr;
   }
-  p.struct_size = sizeof(p);
-  p.dtype = type == at::kBFloat16 ? GF_BF16 : GF_F32;
-  p.phi = (int32_t)phi;
-  p.n_sparse_heads = (int32_t)h0;
-  void* at_[7];
-  try {
-    for (int i = 0; i < 7; ++i) at_[i] = x[i] ? x[i]->data_ptr() : nullptr;
-  } catch (...) {
-    Py_RETURN_NONE;   // no memory behind it: the binding's code says so
-  }
   gf_status st;
   Py_BEGIN_ALLOW_THREADS
-  st = call(at_[0], at_[1], at_[2], at_[3], at_[4], at_[5], static_cast<float*>(at_[6]), (int)B, (int)H, (int)d,
-            (int)window, t, &p, reinterpret_cast<void*>(stream));
+  st = call(s.at[0], s.at[1], s.at[2], s.at[3], s.at[4], s.at[5], static_cast<float*>(s.at[6]), (int)s.B, (int)s.H,
+            (int)s.d, (int)s.window, s.t, &s.p, reinterpret_cast<void*>(s.stream));
   Py_END_ALLOW_THREADS
   return PyLong_FromLong((long)st);
 }

@@ -2,6 +2,9 @@
 and refuses what it refused."""
 from __future__ import annotations
 
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -27,6 +30,25 @@ def test_host_tensors_are_left_to_the_binding():
         gb.gformer_attn_decode(*args, 8, 1, 3)
     with pytest.raises(TypeError):
         gb._decode_call()(gb.lib().decode_address, *args)
+
+
+# Each in a process of its own, which an exception that leaves the module's C function would end.
+@pytest.mark.parametrize("which", range(7))
+def test_a_nested_tensor_is_left_to_the_binding(which):
+    code = f"""
+import torch
+from paper_2412_19829_amd import binding as gb
+from tests.test_decode_call import _step
+args = list(_step(2, 3, 1, 64, 8, torch.float32, "cpu"))
+args[{which}] = torch.nested.nested_tensor([x.clone() for x in args[{which}]])
+assert gb._decode_call()(gb.lib().decode_address, *args, 8, 1, 3, 0, 1.0, 0.0, None) is None
+try:
+    gb.gformer_attn_decode(*args, 8, 1, 3)
+except (RuntimeError, ValueError):
+    print("refused")
+"""
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.strip() == "refused", r.stderr[-500:]
 
 
 @pytest.mark.gpu
@@ -66,7 +88,29 @@ def test_refusals():
         run(q, k, v, q, kc, vc, st, 8, 1, 3)
     with torch.inference_mode():
         run(*(x.clone() for x in (q, k, v, out, kc, vc, st)), 8, 1, 3)
-    batched = torch.stack([q, q])   # vmap's wrappers have no memory of their own to hand over
-    with pytest.raises(Exception):
-        torch.func.vmap(lambda x: run(x, k, v, out, kc, vc, st, 8, 1, 3))(batched)
+    for i in range(7):   # nested tensors are strided, contiguous, have storage, and no sizes
+        args = [q, k, v, out, kc, vc, st]
+        args[i] = torch.nested.nested_tensor([x.clone() for x in args[i]])
+        with pytest.raises((RuntimeError, ValueError)):
+            run(*args, 8, 1, 3)
+    native = gb._decode_call()   # vmap's wrappers have no memory of their own to hand over
+    def wrapped(x):
+        assert native(gb.lib().decode_address, x, k, v, out, kc, vc, st, 8, 1, 3, 0, 1.0, 0.0, None) is None
+        with pytest.raises(RuntimeError):
+            run(x, k, v, out, kc, vc, st, 8, 1, 3)
+        return x
+    torch.func.vmap(wrapped)(torch.stack([q, q]))
     torch.cuda.synchronize()
+
+
+@pytest.mark.gpu
+def test_parameters_and_views_are_plain():
+    """What is a dense tensor by another name takes the same way, with the same result."""
+    q, k, v, out, kc, vc, st = _step(2, 3, 1, 64, 8, torch.bfloat16, "cuda")
+    again = [x.clone() for x in (out, kc, vc, st)]
+    gb.gformer_attn_decode(q, k, v, out, kc, vc, st, 8, 1, 3)
+    wide = torch.stack([k, v])   # a contiguous part of a larger buffer
+    gb.gformer_attn_decode(torch.nn.Parameter(q), wide[0], wide[1], *again, 8, 1, 3)
+    torch.cuda.synchronize()
+    for a, b in zip((out, kc, vc, st), again):
+        assert torch.equal(a, b)
