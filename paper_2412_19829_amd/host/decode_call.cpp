@@ -47,7 +47,7 @@ bool to_float(PyObject* o, float& x) {
   return true;
 }
 
-PyObject* raw_stream_getter = nullptr;   // torch._C._cuda_getCurrentRawStream
+PyObject* raw_stream_getter = nullptr;   // torch._C._cuda_getCurrentRawStream, where torch has it
 
 // What the call takes from its arguments; the stream only where it was named.
 struct Step {
@@ -112,6 +112,7 @@ PyObject* decode(PyObject*, PyObject* const* a, Py_ssize_t n) {
     Py_RETURN_NONE;   // the binding's code raises it, or says what is missing
   }
   if (a[14] == Py_None) {
+    if (!raw_stream_getter) Py_RETURN_NONE;   // the binding knows another way
     PyObject* index = PyLong_FromLong((long)s.device);
     PyObject* handle = index ? PyObject_CallOneArg(raw_stream_getter, index) : nullptr;
     Py_XDECREF(index);
@@ -144,5 +145,6 @@ PyMODINIT_FUNC PyInit__decode_call() {
   if (!torch_c) return nullptr;
   raw_stream_getter = PyObject_GetAttrString(torch_c, "_cuda_getCurrentRawStream");
   Py_DECREF(torch_c);
-  return raw_stream_getter ? PyModule_Create(&module) : nullptr;
+  if (!raw_stream_getter) PyErr_Clear();
+  return PyModule_Create(&module);
 }

@@ -32,6 +32,51 @@ def test_host_tensors_are_left_to_the_binding():
         gb._decode_call()(gb.lib().decode_address, *args)
 
 
+@pytest.mark.parametrize("what", ["gb.CALL_PATH = '/none/_decode_call.so'", "del torch._C._cuda_getCurrentRawStream"],
+                         ids=["no module", "no raw stream"])
+def test_without_the_module_or_the_raw_stream(what):
+    """What the module lacks is no reason to refuse a call: host tensors get the binding's own message, not the loader's."""
+    code = f"""
+import warnings
+import torch
+from paper_2412_19829_amd import binding as gb
+from tests.test_decode_call import _step
+{what}
+args = _step(1, 2, 1, 64, 8, torch.float32, "cpu")
+with warnings.catch_warnings(record=True) as said:
+    for _ in range(2):
+        try:
+            gb.gformer_attn_decode(*args, 8, 1, 3)
+        except ValueError as e:
+            print(e)
+print(len([w for w in said if w.category is RuntimeWarning]))
+"""
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True)
+    lines = r.stdout.strip().splitlines()
+    assert r.returncode == 0 and len(lines) == 3, r.stderr[-500:]
+    assert "no CPU path" in lines[0] and "no CPU path" in lines[1] and lines[2] == ("1" if "none" in what else "0")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("what", ["gb.CALL_PATH = '/none/_decode_call.so'", "del torch._C._cuda_getCurrentRawStream"],
+                         ids=["no module", "no raw stream"])
+def test_the_same_step_without_them(what):
+    code = f"""
+import torch
+from paper_2412_19829_amd import binding as gb
+from tests.test_decode_call import _step
+args = [_step(2, 3, 1, 64, 8, torch.bfloat16, "cuda") for _ in range(2)]
+{what}
+gb.gformer_attn_decode(*args[0], 8, 1, 3)
+gb.gformer_attn_decode(*args[1], 8, 1, 3, stream=torch.cuda.current_stream().cuda_stream)
+torch.cuda.synchronize()
+assert all(torch.equal(a, b) for a, b in zip(*args))
+print("same")
+"""
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.strip() == "same", r.stderr[-500:]
+
+
 # Each in a process of its own, which an exception that leaves the module's C function would end.
 @pytest.mark.parametrize("which", range(7))
 def test_a_nested_tensor_is_left_to_the_binding(which):
