@@ -163,8 +163,9 @@ typedef struct gformer_plan {
  * strides. */
 void gformer_params_init(gformer_params* p);
 
-/* Bytes of device workspace gformer_attn_fwd needs for these arguments (0 if none).
- * Returns 0 as well when the arguments are invalid; gformer_attn_fwd reports why. */
+/* Bytes of device workspace gformer_attn_fwd needs for these arguments (0 if none): the same for
+ * every launch_mask, overlap, softmax_scale and window, and for GF_IMPL_AUTO, GF_IMPL_MFMA,
+ * GF_IMPL_MFMA_BLOCKED and GF_IMPL_MFMA_STREAM.  Returns 0 as well when the arguments are invalid; gformer_attn_fwd reports why. */
 size_t gformer_attn_workspace_bytes(int B, int H, int N, int d, int window,
                                     const gformer_params* p);
 

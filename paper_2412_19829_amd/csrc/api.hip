@@ -44,6 +44,7 @@ struct Resolved {
   bool general_chunk;  // MFMA path, causal: the linear read-out goes to the general-chunk kernel
   bool f32;            // single precision on the matrix cores
   int f32_seg_len, f32_nseg;
+  uint64_t needed;     // workspace of this cut; plan.workspace_bytes, which is reported, serves every form of the shape
 };
 
 // Single-precision calls run on the matrix cores (fp32 operands and accumulation) unless the caller
@@ -275,7 +276,7 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
         pl.linear_threads = 4 * d;
         pl.state_blocks = (int)(heads_lin * (p->bidirectional ? f.count : f.count - 1));
         if (pl.state_blocks > 0)
-          pl.workspace_bytes = (uint64_t)pl.n_segments * ((uint64_t)d * d + d) * sizeof(float);
+          pl.workspace_bytes = r->needed = (uint64_t)pl.n_segments * ((uint64_t)d * d + d) * sizeof(float);
       }
     }
     return GF_OK;
@@ -304,7 +305,7 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
       pl.windowed_blocks = (int)sp.blocks;
     }
   }
-  long piece = 0, vcph = cph, pieces = 0, mid = 0, sub = 1;
+  long piece = 0, vcph = cph, pieces = 0, mid = 0, sub = 1, most_sub = 0;
   if (p->segment_len != 0 && p->segment_len % pl.chunk != 0) return GF_ERR_INVALID_ARG;
   long own_piece = aligned_piece(heads_lin, cph, kComputeUnits);
   if (own_piece == 0 && !r->general_chunk && short_pieces) own_piece = short_piece(heads_lin, cph, kComputeUnits, d);
@@ -347,10 +348,16 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
     // sub-pieces stay 4 chunks or longer and fit two workgroups per compute unit.  At d = 128 the windowed heads' query
     // blocks share its launch: where both fit the chip at once without a cut, the cut leaves room for them (prefill of
     // 2 x 32 x 3001: 156 sums of 12 chunks beside 288 query blocks 36 us, 312 of 6, which need a second round, 43).
+    // The workspace reported has room for the sums of the finer cut, so that its size depends on the shape alone.
     const long carried = heads_lin * (per_head > 0 ? per_head - 1 : 0);
     const long beside = d == 128 && !r->stream && carried + query_blocks <= 2 * kComputeUnits ? query_blocks : 0;
-    for (sub = 4; sub > 1; sub /= 2)
-      if (piece % sub == 0 && piece / sub >= 4 && carried * sub + beside <= 2 * kComputeUnits) break;
+    auto cut_beside = [&](long blocks) {
+      long n = 4;
+      while (n > 1 && !(piece % n == 0 && piece / n >= 4 && carried * n + blocks <= 2 * kComputeUnits)) n /= 2;
+      return n;
+    };
+    sub = cut_beside(beside);
+    most_sub = cut_beside(0);
     mid = carried * sub;
   } else if (heads_lin > 0 && cph > 0) {
     // One workgroup per compute unit (its LDS holds one), each with the same number of chunks;
@@ -381,7 +388,9 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
   pl.linear_threads = mfma_linear_threads(d);
   pl.linear_blocks = (int)pieces;
   pl.state_blocks = (int)mid;
-  pl.workspace_bytes = mid > 0 ? (uint64_t)pieces * sub * ((uint64_t)d * d + d) * sizeof(float) : 0;
+  const uint64_t slots = mid > 0 ? (uint64_t)pieces * ((uint64_t)d * d + d) * sizeof(float) : 0;
+  r->needed = slots * sub;
+  pl.workspace_bytes = slots * (most_sub > 0 ? most_sub : sub);
   return GF_OK;
 }
 
@@ -433,8 +442,7 @@ gf_status attn_forward(const void* q, const void* k, const void* v, void* out, v
   if (st != GF_OK) return st;
   // a workspace the short pieces cannot use (too small, or not aligned) still serves the longer cut, which often
   // needs none
-  if (!r.f32 && r.plan.workspace_bytes > 0 &&
-      (!workspace || ((uintptr_t)workspace & 255u) || workspace_bytes < r.plan.workspace_bytes))
+  if (!r.f32 && r.needed > 0 && (!workspace || ((uintptr_t)workspace & 255u) || workspace_bytes < r.needed))
     st = resolve(B, H, N, d, window, p, &r, false);
   if (st != GF_OK) return st;
   if (B == 0 || H == 0 || N == 0) return GF_OK;
@@ -446,14 +454,14 @@ gf_status attn_forward(const void* q, const void* k, const void* v, void* out, v
     // the layer is computed all the same, from fewer segments.
     if ((uintptr_t)workspace & 255u) workspace = nullptr;
     if (!workspace) workspace_bytes = 0;
-    if (workspace_bytes < r.plan.workspace_bytes) {
+    if (workspace_bytes < r.needed) {
       const int64_t heads = (int64_t)B * (H - p->n_sparse_heads);
       const Segments f = f32_segments(heads, N, d, p->bidirectional == 0, workspace_bytes, 1);
       r.f32_seg_len = f.len;
       r.f32_nseg = f.count;
     }
-  } else if (r.plan.workspace_bytes > 0) {
-    if (!workspace || workspace_bytes < r.plan.workspace_bytes) return GF_ERR_WORKSPACE;
+  } else if (r.needed > 0) {
+    if (!workspace || workspace_bytes < r.needed) return GF_ERR_WORKSPACE;
     if ((uintptr_t)workspace & 255u) return GF_ERR_INVALID_ARG;
   }
   // only the kernel specialised for chunks of 64 writes the states a decode step continues from
@@ -483,7 +491,7 @@ gf_status attn_forward(const void* q, const void* k, const void* v, void* out, v
   a.state_sub = r.state_sub;
   a.f32_seg_len = r.f32_seg_len;
   a.f32_nseg = r.f32_nseg;
-  a.ws_states = r.plan.workspace_bytes > 0 ? reinterpret_cast<float*>(workspace) : nullptr;
+  a.ws_states = r.needed > 0 ? reinterpret_cast<float*>(workspace) : nullptr;
   a.final_state = final_state;
   a.kring = kring;
   a.vring = vring;
@@ -570,10 +578,10 @@ gf_status gformer_attn_fwd_noalloc(const void* q, const void* k, const void* v, 
   if (st != GF_OK) return st;
   if (p->overlap != 0) return GF_ERR_UNSUPPORTED;   // the side stream is created on first use
   // (a single-precision call runs with whatever sums fit)
-  if (!r.f32 && r.plan.workspace_bytes > kScratchBytes) return GF_ERR_WORKSPACE;
+  if (!r.f32 && r.needed > kScratchBytes) return GF_ERR_WORKSPACE;
   if (B == 0 || H == 0 || N == 0) return GF_OK;
   void* ws = nullptr;
-  if (r.plan.workspace_bytes > 0) {
+  if (r.needed > 0) {
     std::lock_guard<std::mutex> lock(g_enqueue_mutex);
     if (scratch_for_current_device(reinterpret_cast<hipStream_t>(hip_stream), &ws) != hipSuccess) {
       (void)hipGetLastError();
