@@ -758,25 +758,33 @@ int64_t backward_band_tiles(int64_t windowed_heads, int N, int wleft, int wright
 // Three workgroups per compute unit and no segment under 128 tokens: 52 heads of 4096 tokens take 50 + 44 us
 // (dq, dk/dv walk) with two, 46 + 40 with three, 51 + 38 with four.  Over all keys a walk reads every sum of
 // its head: four segments at most, as many as the workspace of that form has always held.
-// A causal call whose band passes weigh half of its walks or more (a tile about one and a half chunks) gets two walks a
+// A causal call whose band passes weigh half of its walks or more (a tile about one and a half chunks) may get two walks a
 // unit: with three there is no room beside them, and the band runs behind them on a chip that empties.  All passes, us,
 // three and two a unit, by band's share: 6 x (1 + 7) x 8192, window 128 (0.3) 167.0 and 166.1; 8 x (2 + 10) x 4096, 128
-// (0.4) 161.9 and 165.4; 4 x (3 + 13) x 4096, 128 (0.45) 117.2 and 123.0; 8 x (2 + 10) x 4096, 256 (0.55) 175.8 and
-// 170.0; 1 x (2 + 10) x 8192, 256 (0.55) 81.4 and 74.7; 16 x (2 + 6) x 1500, 128 (0.65) 101.9 and 94.5; 4 x (5 + 27) x
-// 2048, 512 (0.8) 148.5 and 135.0; 8 x (4 + 8) x 2048, 256 (1.3) 121.4 and 113.2; 4 x (8 + 8) x 4096, 256 (2.6) 157.3
-// and 153.0.
+// (0.4) 161.9 and 165.4; 4 x (3 + 13) x 4096, 128 (0.45) 117.2 and 123.0; 8 x (2 + 10) x 4096, 256 (0.55) 180.1 and
+// 174.3; 1 x (2 + 10) x 8192, 256 (0.55) 81.5 and 74.9; 16 x (2 + 6) x 1500, 128 (0.65) 101.9 and 96.5; 4 x (5 + 27) x
+// 2048, 512 (0.8) 149.0 and 135.4; 8 x (4 + 8) x 2048, 256 (1.3) 122.1 and 115.6; 4 x (8 + 8) x 4096, 256 (2.6) 159.2
+// and 156.1.  Up to a share of 4/3 that holds only where the cut into fewer segments is no worse for the fullest unit,
+// whose chunks may be an eighth more: with a few heads more than a unit count divides they are a third more, and 12 x
+// (8 + 24) x 1024, 128 (0.6) takes 154.1 and 196.9, 22 x (4 + 12) x 2000, 256 (0.9) 304.0 and 374.3, 21 x (3 + 9) x 3297,
+// 32 (0.5) 316.0 and 353.3, 15 x (14 + 18) x 2880, 22 (1.2) 530.4 and 597.3; above, 24 x (8 + 8) x 2500, 128 (1.9) 435.4 and
+// 416.5.  Nor where a walk is longer than 48 chunks, as the band is gone long before it ends: 8 x (6 + 26) x 4096, 256
+// (0.6, 64 chunks) 440.0 and 450.0, x 3000 (47 chunks) 324.1 and 327.9, 16 x (3 + 13) x 2048 (32) 224.6 and 216.7.
 Segments backward_segments(int64_t heads, int N, int d, bool causal, int64_t band_tiles) {
-  Segments f{N, 1};
-  if (heads <= 0 || N <= 0 || d != 64) return f;
-  const int64_t chunks = (N + SC - 1) / SC, most = causal ? kMaxSegments : kBidirStateSlots;
-  const int walks = causal && 3 * band_tiles >= heads * chunks ? 2 : 3;
-  int64_t n = walks * (int64_t)device_compute_units() / heads;
-  if (n > most) n = most;
-  if (n > chunks / 4) n = chunks / 4;
-  if (n <= 1) return f;
-  f.len = (int)((chunks + n - 1) / n) * SC;
-  f.count = (N + f.len - 1) / f.len;
-  return f;
+  if (heads <= 0 || N <= 0 || d != 64) return Segments{N, 1};
+  const int64_t chunks = (N + SC - 1) / SC, most = causal ? kMaxSegments : kBidirStateSlots, cus = device_compute_units();
+  auto cut = [&](int walks) {
+    const int64_t n = std::min(std::min(walks * cus / heads, most), chunks / 4);
+    if (n <= 1) return Segments{N, 1};
+    const int len = (int)((chunks + n - 1) / n) * SC;
+    return Segments{len, (N + len - 1) / len};
+  };
+  const Segments three = cut(3);
+  if (!causal || 3 * band_tiles < heads * chunks) return three;
+  const Segments two = cut(2);
+  if (9 * band_tiles >= 8 * heads * chunks) return two;
+  auto fullest = [&](const Segments& f) { return (heads * f.count + cus - 1) / cus * ((f.len + SC - 1) / SC); };
+  return 8 * fullest(two) <= 9 * fullest(three) && two.len <= 48 * SC ? two : three;
 }
 
 // Roundings.  Over all keys, and for causal calls of less than 256 tokens, the sums in the read-outs and phi(q) / den
