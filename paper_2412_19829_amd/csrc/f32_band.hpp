@@ -19,19 +19,13 @@ template <int D> struct F32Stage {
   static constexpr int C4 = D / 4, RP = kF32BandThreads / C4, PIECES = kF32Tile / RP;
   int row, col;
   __device__ __forceinline__ explicit F32Stage(int tid) : row(tid / C4), col(4 * (tid % C4)) {}
-  // a wave-uniform base and a 32-bit offset `off` (offset_of) that never changes, under one clamp: rows past N - 1
-  // re-read row N - 1 (in bounds; never visible)
-  __device__ __forceinline__ uint32_t offset_of(int64_t sn) const { return 4u * (uint32_t)(row * (int)sn + col); }
-  __device__ __forceinline__ void load(f32x4 (&dst)[PIECES], const float* base, int64_t row_stride, uint32_t off, int t0,
-                                       int N) const {
-    const int sn = (int)row_stride, last = min(N - 1 - t0, kF32Tile - 1);
-    const char* tile = reinterpret_cast<const char*>(base + (int64_t)t0 * sn);
+  // rows past N - 1 re-read row N - 1 (in bounds; never visible).  (A uniform base and 32-bit offsets under a clamp, which
+  // the linear walks gain by, cost this one: training steps of windowed heads 7 x 8 x 1242 x 64 155.3 -> 157.0 us, 4 x
+  // (2 + 10) x 876 150.8 -> 153.0, 4 x (3 + 13) x 2048 269.7 -> 271.8.)
+  __device__ __forceinline__ void load(f32x4 (&dst)[PIECES], const float* base, int64_t sn, int t0, int N) const {
 #pragma unroll
-    for (int i = 0; i < PIECES; ++i) {
-      const int first = min(i * RP, last);
-      const uint32_t lim = 4u * (uint32_t)((last - first) * sn + col);
-      dst[i] = *reinterpret_cast<const f32x4*>(tile + 4u * (uint32_t)(first * sn) + (size_t)min(off, lim));
-    }
+    for (int i = 0; i < PIECES; ++i)
+      dst[i] = *reinterpret_cast<const f32x4*>(base + (int64_t)min(t0 + row + i * RP, N - 1) * sn + col);
   }
   __device__ __forceinline__ void store(float* tile, const f32x4 (&src)[PIECES]) const {
 #pragma unroll
@@ -167,18 +161,17 @@ __device__ __forceinline__ void walk_band(F32WinSmem<D>& sm, const float* xb, in
   // spill; the other workgroup of the compute unit covers the wait instead
   constexpr bool AHEAD = D == 64;
   const F32Stage<D> st(tid);
-  const uint32_t xo = st.offset_of(xsn), yo = st.offset_of(ysn);
   f32x4 xr[F32Stage<D>::PIECES], yr[F32Stage<D>::PIECES];
   if (tid < 2) sm.bad[tid] = 0;
   if (AHEAD) {
-    st.load(xr, xb, xsn, xo, lo, N);
-    st.load(yr, yb, ysn, yo, lo, N);
+    st.load(xr, xb, xsn, lo, N);
+    st.load(yr, yb, ysn, lo, N);
   }
   int it = 0;
   for (int t0 = lo; t0 <= hi; t0 += kF32Tile, ++it) {
     if (!AHEAD) {
-      st.load(xr, xb, xsn, xo, t0, N);
-      st.load(yr, yb, ysn, yo, t0, N);
+      st.load(xr, xb, xsn, t0, N);
+      st.load(yr, yb, ysn, t0, N);
     }
     lds_barrier();   // the tile before is consumed (first round: the flags are clear)
     st.store(sm.x, xr);
@@ -187,8 +180,8 @@ __device__ __forceinline__ void walk_band(F32WinSmem<D>& sm, const float* xb, in
       sm.bad[it & 1] = 1;
     extra(t0);
     if (AHEAD && t0 + kF32Tile <= hi) {
-      st.load(xr, xb, xsn, xo, t0 + kF32Tile, N);
-      st.load(yr, yb, ysn, yo, t0 + kF32Tile, N);
+      st.load(xr, xb, xsn, t0 + kF32Tile, N);
+      st.load(yr, yb, ysn, t0 + kF32Tile, N);
     }
     lds_barrier();
     const bool bad = __builtin_amdgcn_readfirstlane(sm.bad[it & 1]) != 0;   // uniform
