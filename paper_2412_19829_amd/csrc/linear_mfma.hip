@@ -822,6 +822,8 @@ __global__ __launch_bounds__(256, 2) void linear_main_windowed_kernel(AttnArgs a
   else if (block < a.n_pieces) linear_main_block<64, ELU1, CAUSAL, EMIT>(a, block, smem_raw);
 }
 
+// key tiles of a query block's band
+int block_tiles(const AttnArgs& a) { return std::min((a.wleft + a.wright + BR - 1) / BC, (a.N - 1) / BC) + 1; }
 int state_blocks(const AttnArgs& a) { return a.n_pieces * a.state_sub - (a.causal ? 1 : 0); }
 
 template <int D> hipError_t launch_state_t(const AttnArgs& a, bool with_windowed, hipStream_t s) {
@@ -833,8 +835,7 @@ template <int D> hipError_t launch_state_t(const AttnArgs& a, bool with_windowed
     if (with_windowed) {
       if (smem < (int)sizeof(WinSmem<D>)) smem = (int)sizeof(WinSmem<D>);
       const int blocks = (a.N + BR - 1) / BR * a.H0 * a.B;
-      const int tiles = std::min((a.wleft + a.wright + BR - 1) / BC, (a.N - 1) / BC) + 1;   // of a query block's band
-      const bool sums_first = a.piece_chunks / a.state_sub > tiles;
+      const bool sums_first = a.piece_chunks / a.state_sub > block_tiles(a);
       const dim3 grid(sums_first ? ((sums + 7) & ~7) + blocks : ((blocks + 7) & ~7) + sums);
       const auto kern = a.phi == 0 ? linear_state_windowed_kernel<true> : linear_state_windowed_kernel<false>;
       if ((e = allow_lds(kern, smem)) != hipSuccess) return e;
@@ -903,9 +904,17 @@ hipError_t launch_linear_main_windowed_mfma(const AttnArgs& a, hipStream_t s) {
 static bool has_state_pass(const AttnArgs& a) {
   return a.H - a.H0 > 0 && a.N > 0 && a.B > 0 && a.ws_states && !(a.causal && a.n_pieces <= 1);
 }
+// Not beside long sums that outweigh the query blocks by far: such sums are what the launch takes, and of 256 threads they
+// take longer than of 512.  Chains of more than 30 chunks, and less than a third as many tiles as linear chunks; the
+// whole layer, us, one launch and two, chunks a chain, tiles a chunk: 2 x 32 x 12000, window 64, H0 = 1 222.8 and 214.7 (47,
+// 0.05); 4 x 32 x 7800, 300, 2 257.0 and 253.5 (61, 0.23); 2 x 32 x 9000, 64, 1 159.0 and 156.4 (36, 0.05); 1 x 32 x 15900, 64,
+// 1 150.1 and 149.4 (32, 0.05); 2 x 32 x 12000, 300, 4 214.0 and 220.4 (47, 0.5); 4 x 32 x 7800, 512, 4 272.8 and 276.4 (61,
+// 0.7); 2 x 32 x 8700, 64, 1 155.2 and 157.4 (17, 0.05); 1 x 16 x 32000, 64, 1 159.7 and 159.2 (30, 0.1).
 bool linear_state_takes_windowed(const AttnArgs& a) {
-  const int64_t blocks = (int64_t)a.n_pieces * a.state_sub + (int64_t)((a.N + BR - 1) / BR) * a.H0 * a.B;
-  return a.d == 128 && a.H0 > 0 && has_state_pass(a) && a.scale >= 0.f && blocks < (1 << 22);
+  if (a.d != 128 || a.H0 <= 0 || !has_state_pass(a) || a.scale < 0.f) return false;
+  const int64_t query_blocks = (int64_t)((a.N + BR - 1) / BR) * a.H0 * a.B;
+  if (a.piece_chunks / a.state_sub > 30 && 3 * query_blocks * block_tiles(a) < (int64_t)a.B * (a.H - a.H0) * a.cph) return false;
+  return (int64_t)a.n_pieces * a.state_sub + query_blocks < (1 << 22);
 }
 hipError_t launch_linear_state_mfma(const AttnArgs& a, bool with_windowed, hipStream_t s) {
   if (!has_state_pass(a)) return hipSuccess;

@@ -20,6 +20,7 @@ D = 128
     (3, 4, 577, 64, 1, {"bidirectional": 1}), (1, 3, 129, 33, 2, {"bidirectional": 1}),
     (1, 4, 640, 50, 1, {"phi": gb.GF_PHI_IDENTITY}), (1, 4, 640, 50, 1, {"softmax_scale": -0.5}),
     (1, 3, 2600, 200, 1, {"chunk": 128}),
+    (1, 3, 8100, 16, 1, {"segment_len": 3968}), (1, 4, 8100, 3000, 3, {"segment_len": 3968}),   # chains of 31: apart, together
 ], ids=lambda c: "x".join(map(str, c[:5])) + "".join(f"-{k}" for k in c[5]))
 def test_one_launch_gives_the_bits_of_two(case):
     import torch
