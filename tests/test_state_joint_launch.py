@@ -58,3 +58,19 @@ def test_rings_after_prefill(case, d):
         for t in range(max(0, N - w), N):
             want[:, :, t % w] = x[:, :H0, t]
         assert torch.equal(ring.view(torch.int16), want.view(torch.int16))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d", [64, 128])
+def test_rings_under_a_negative_scale(d):
+    """The kernels of a negative scale are others, in launches of their own."""
+    import torch
+    B, H, N, w, H0 = 2, 3, 450, 130, 2
+    q, k, v = (to_device(x, "bf16") for x in synth(B, H, N, d, "bf16", 85))
+    kc, vc = (torch.full((B, H0, w, d), -7.0, dtype=q.dtype, device="cuda") for _ in range(2))
+    st = torch.zeros(B, H - H0, d * d + d, device="cuda")
+    gb.gformer_attn_prefill(q, k, v, torch.empty_like(q), kc, vc, st, w, H0, softmax_scale=-0.5)
+    torch.cuda.synchronize()
+    for ring, x in ((kc, k), (vc, v)):
+        for t in range(N - w, N):
+            assert torch.equal(ring[:, :, t % w].view(torch.int16), x[:, :H0, t].view(torch.int16))
