@@ -10,7 +10,7 @@ from oracle import cpu_oracle as co
 from paper_2412_19829_amd import binding as gb
 from paper_2412_19829_amd import inputs as gi
 from tests.gpu_util import to_device, to_host
-from tests.test_backward_rounding_model import chunked_linear_bwd
+from tests.test_backward_rounding_model import numerator_scans
 from tests.test_gpu_parity import check_grad, run_bwd, synth
 
 # B, H, N, bidirectional, segments per head (256 compute units)
@@ -57,7 +57,7 @@ def test_no_further_from_64_bits_than_the_scans(N):
     for b in range(B):
         for h in range(H):
             one = (x[b, h].astype(np.float64) for x in (q, k, v, dout))
-            for s, g in zip(scans, chunked_linear_bwd(*one, rounded=True, pairs=True)):
+            for s, g in zip(scans, numerator_scans(*one, rounded=True, pairs=True)):
                 s[b, h] = gi.round_to_bf16(g.astype(np.float32))
     for g, s, r, name in zip(run_bwd(q, k, v, dout, "bf16", 8, 0), scans, ref, ("dq", "dk", "dv")):
         assert np.linalg.norm(g - r) <= 1.01 * np.linalg.norm(s - r), name
