@@ -165,7 +165,8 @@ void gformer_params_init(gformer_params* p);
 
 /* Bytes of device workspace gformer_attn_fwd needs for these arguments (0 if none): the same for
  * every launch_mask, overlap, softmax_scale and window, and for GF_IMPL_AUTO, GF_IMPL_MFMA,
- * GF_IMPL_MFMA_BLOCKED and GF_IMPL_MFMA_STREAM.  Returns 0 as well when the arguments are invalid; gformer_attn_fwd reports why. */
+ * GF_IMPL_MFMA_BLOCKED and GF_IMPL_MFMA_STREAM.  Returns 0 as well when the arguments are
+ * invalid; gformer_attn_fwd reports why. */
 size_t gformer_attn_workspace_bytes(int B, int H, int N, int d, int window,
                                     const gformer_params* p);
 
@@ -261,8 +262,8 @@ gf_status gformer_attn_prefill(const void* q, const void* k, const void* v, void
  * Kernels: a bf16 call runs on the matrix cores (params.impl GF_IMPL_AUTO or GF_IMPL_MFMA: bf16
  * products, fp32 accumulation, softmax statistics, denominators and carried sums in fp32; the
  * operands of the linear heads whose rounding would cost more than the bf16 mode's 2e-2 per row
- * travel as bf16 pairs: T' = dO.v / den - c; at d = 128 the in-chunk weights of the numerator,
- * which the d = 64 kernels keep in fp32; at d = 64 the carried sum that dk reads);
+ * travel as bf16 pairs: T' = dO.v / den - c; at d = 64 the carried sum that dk reads,
+ * and below 256 tokens two more);
  * an fp32 call (GF_IMPL_AUTO) on the matrix cores in single precision; GF_IMPL_SCALAR on plain-FMA
  * kernels (fp32 arithmetic on either storage type).  The linear heads of a bidirectional call
  * take three sweeps over each head (the sums over all keys, dq with the sums over all queries, dk

@@ -170,8 +170,10 @@ long aligned_piece(long heads_lin, long cph, long kComputeUnits) {
 // (2), 10x32 26.0 / 20.5 (4), 10x64 34.7 / 28.8 (4), 26x16 25.5 / 17.4 (3), 52x16 26.7 / 22.4 (4), 100x10
 // 26.9 / 21.1 (5), 300x5 27.9 / 18.1 (5: a whole head, no carried sums at all).  d = 128, where a sum is
 // four times as large and a compute unit holds one piece: 10x8 33.0 / 30.6 (2), 10x16 42.8 / 38.1 (4),
-// 10x64 61.8 / 55.1 (4), 26x32 60.9 / 54.8 (6), 52x10 47.8 / 40.4 (5).  Two-chunk pieces lose again as
-// soon as a head has more than eight of them (10x32: 23.2) or they crowd the chip (26x16: 19.3).
+// 10x64 61.8 / 55.1 (4), 26x32 60.9 / 54.8 (6), 52x10 47.8 / 40.4 (5).  Two-chunk pieces lose where they crowd the chip
+// (the present build, pieces of two, three, four: 26x16 18.9, 17.8, 19.5; 52x16 25.6, 25.1, 21.0).  That a head gets no more
+// than eight of them was drawn when the sums of more were added up more slowly (10x32 23.2 then); now they would be
+// faster there too (10x18 15.3, 16.5, 18.7; 10x25 18.3, 17.7, 19.3; 10x32 19.1, 20.7, 20.5; 10x48 21.4, 22.0, 23.7).
 long short_piece(long heads, long cph, long cus, int d) {
   if (cph < 4 || heads <= 0 || heads > 2 * cus) return 0;
   if (heads * cph > 5 * cus && (heads * 5 < 4 * cus || cph > 8)) return 0;
@@ -347,7 +349,10 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
     // its own chunk-by-chunk walk, so segments are cut into up to four sub-pieces as long as the
     // sub-pieces stay 4 chunks or longer and fit two workgroups per compute unit.  At d = 128 the windowed heads' query
     // blocks share its launch: where both fit the chip at once without a cut, the cut leaves room for them (prefill of
-    // 2 x 32 x 3001: 156 sums of 12 chunks beside 288 query blocks 36 us, 312 of 6, which need a second round, 43).
+    // 2 x 32 x 3001: 156 sums of 12 chunks beside 288 query blocks 36 us, 312 of 6, which need a second round, 43).  The
+    // same cut where the query blocks have a launch of their own (negative scale, overlap, long sums): calls with a
+    // launch mask, which share the sums, must agree on it, and it is no slower (finer, this: the same prefill's forward
+    // with a negative scale 86.5, 78.5, with overlap 92.5, 81; 1 x 32 x 5338, H0 = 5 83.6, 76.1 and 85.3, 75.9).
     // The workspace reported has room for the sums of the finer cut, so that its size depends on the shape alone.
     const long carried = heads_lin * (per_head > 0 ? per_head - 1 : 0);
     const long beside = d == 128 && !r->stream && carried + query_blocks <= 2 * kComputeUnits ? query_blocks : 0;
@@ -526,7 +531,7 @@ gf_status attn_forward(const void* q, const void* k, const void* v, void* out, v
     if (win && lin && p->overlap) e = side_stream_for_current_device(s, &side);
     // d = 64: the windowed heads' query blocks ride in the read-out's launch (linear_mfma.hip).  Not the
     // streaming kernel (other block size), a forced overlap, or a launch mask that names one of the two.
-    // d = 128: in the state pass's, under the same conditions.
+    // d = 128: in the state pass's, under the same conditions, but for long sums beside few blocks.
     const bool joint = win && !p->overlap && !stream;
     const bool together = joint && (mask & GF_LAUNCH_LINEAR_MAIN) && !r.general_chunk && linear_main_takes_windowed(a);
     const bool with_state = joint && (mask & GF_LAUNCH_LINEAR_STATE) && linear_state_takes_windowed(a);

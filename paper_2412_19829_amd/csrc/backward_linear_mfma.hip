@@ -12,7 +12,8 @@
 //                  dO.num / den^2 without a numerator),  dfq = T' fk + r / den - c Z^T;   then A += fk^T v, Z += colsum(fk)
 //   reverse scan:  dfk = T'^T fq + v B^T - 1 Y^T,  dv = (S / den)^T dO + fk B;   then B += fq^T dO / den, Y += fq^T c
 // What bounds them: 13.3 tensors' worth of traffic (the scans' eight reads and three writes, and what light rounds
-// read again) at 4.2 TB/s on 128 heads x 8192, of the 4.9 a copy reaches; below that the LDS pipeline.  With the
+// read again) at 4.0 (forward) and 4.1 TB/s (reverse) on 128 heads x 8192, of the 4.9 a copy reaches; of a unit's cycles the
+// LDS pipeline takes 45 and 50 %, a fifth of that in conflicts, the vector unit 40 %, the matrix core 15 %.  With the
 // numerator as two products of its own (S as a pair), dO and dO / den as tiles of their own, the 32 x 32 tile above the
 // diagonal computed and multiplied, and the column sums read from LDS element by element, the same scans took 953 us
 // (853 now; 4 x (6 + 26) heads x 8192 with the windowed heads 1083 and 1000; 32 x 1000 81.5 and 72.0).  Row stores

@@ -10,10 +10,11 @@
 // them).  One workgroup per head, as the plain-FMA kernels have it, leaves a serial chain of the
 // whole sequence on a part of the chip.
 //
-// Measured, B=4, 52 linear heads, N=2048, d=64 (plain-FMA kernels -> these, us): forward 1017 -> 18
-// (sums) + 7 (scan) + 41, backward 859 + 1558 -> 18 + 7 + 60 + 7 + 67.  The bound is the SIMDs' issue: in the
-// forward walk the matrix core is busy 42 % of the time and the vector unit 31 %, hardly ever both
-// (27 us of work for 109 MB = 22 us at the copy rate); waits for memory are 29 % of a wave's time.
+// Measured, B=4, 52 linear heads, N=2048, d=64, eight segments a head and no scan of their sums (plain-FMA kernels ->
+// these, us): forward 1017 -> 18 (sums) + 48, backward 859 + 1558 -> 18 + 71 + 75.  The bound is the SIMDs' issue: the
+// matrix core is busy 32 % of the forward walk's time (33 and 42 % of the others'), the vector unit 22 % (24 and 19 %)
+// at four cycles an instruction, hardly ever both; with two workgroups a unit the barriers between a chunk's steps
+// leave the rest.
 //
 // Every sum lies in the workspace as A row-major [feature][value], then its vector.
 #include <algorithm>
