@@ -225,18 +225,21 @@ template <int D> __device__ __forceinline__ f32x4 rows_product(const uint16_t* a
 
 // Whole chunks run as body(t0, true_type), without a condition in front of their loads and stores: with
 // one the compiler waits for everything outstanding, the last stores included, before it stages a
-// chunk.  Loads past the end are clamped to the last row.
-template <typename Body> __device__ __forceinline__ void walk_up(int begin, int end, Body body) {
+// chunk.  Loads past the end are clamped to the last row.  With STORES a chunk stores the rows of the one
+// before it, so the first chunk, which has none to store, runs as body(t0, false_type) too, and so does the
+// chunk that stores a ragged one's.
+template <bool STORES, typename Body> __device__ __forceinline__ void walk_up(int begin, int end, Body body) {
   int t0 = begin;
+  if (STORES) {
+    body(t0, std::false_type{});
+    t0 += SC;
+  }
   for (; t0 + SC <= end; t0 += SC) body(t0, std::true_type{});
   if (t0 < end) body(t0, std::false_type{});
 }
 template <typename Body> __device__ __forceinline__ void walk_down(int begin, int end, Body body) {
   int t0 = begin + (end - begin - 1) / SC * SC;
-  if (t0 + SC > end) {
-    body(t0, std::false_type{});
-    t0 -= SC;
-  }
+  for (int general = t0 + SC > end ? 2 : 1; general > 0 && t0 >= begin; --general, t0 -= SC) body(t0, std::false_type{});
   for (; t0 >= begin; t0 -= SC) body(t0, std::true_type{});
 }
 
@@ -309,7 +312,7 @@ __device__ __forceinline__ void seg_sum(const BwdArgs& a, int block, unsigned ch
   const Piece<D> pk(s, a.k.sn), pv(s, a.v.sn);
   u32x4 kr = pk.load(kp, s.begin, N), vr = pv.load(vp, s.begin, N);
   int it = 0;
-  walk_up(s.begin, s.end, [&](int t0, auto) {
+  walk_up<false>(s.begin, s.end, [&](int t0, auto) {
     const bool valid = t0 + s.row < N;
     uint16_t *fkt = sm.fk[it & 1], *vvt = sm.vv[it & 1];   // one barrier a chunk: two buffers
     ++it;
@@ -384,10 +387,10 @@ __device__ __forceinline__ void seg_q(const BwdArgs& a, int block, unsigned char
   auto store_rows = [&](int t0, bool all) {   // the chunk's dq rows, left in the phi(q) tile
     if (all || t0 + s.row < N) pq.store(dq, t0, *reinterpret_cast<const u32x4*>(piece_q));
   };
-  walk_up(s.begin, s.end, [&](int t0, auto steady) {
+  walk_up<true>(s.begin, s.end, [&](int t0, auto steady) {
     constexpr bool STEADY = decltype(steady)::value;
     lds_barrier();   // the chunk before is consumed, its dq rows are complete
-    if (t0 > s.begin) store_rows(t0 - SC, true);
+    if (STEADY || t0 > s.begin) store_rows(t0 - SC, true);
     const bool valid = STEADY || t0 + s.row < N;
     *reinterpret_cast<u32x4*>(piece_q) = valid ? map8<ELU1>(qr) : kZero4;
     *reinterpret_cast<u32x4*>(sm.dd + s.row * R + s.col) = valid ? dr : kZero4;
@@ -600,7 +603,7 @@ __device__ __forceinline__ void seg_kv(const BwdArgs& a, int block, unsigned cha
   walk_down(s.begin, s.end, [&](int t0, auto steady) {
     constexpr bool STEADY = decltype(steady)::value;
     lds_barrier();   // the chunk before is consumed, its dk and dv rows are complete
-    if (t0 < last) store_rows(t0 + SC, t0 + 2 * SC <= N);
+    if (STEADY || t0 < last) store_rows(t0 + SC, STEADY || t0 + 2 * SC <= N);
     const bool valid = STEADY || t0 + s.row < N;
     *reinterpret_cast<u32x4*>(piece_k) = valid ? map8<ELU1>(kr) : kZero4;
     *reinterpret_cast<u32x4*>(piece_v) = valid ? vr : kZero4;
