@@ -385,14 +385,19 @@ __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, 
     // NSETS further on as soon as it has been staged
     constexpr int NSETS = GF_MAIN_SETS;
     u32x4 qs[NSETS][C::PIECES], ks[NSETS][C::PIECES], vs[NSETS][C::PIECES];
+    // V is staged before (a) at d = 64, after it at d = 128.  Cycles a chunk, d = 64, staged after (a): consumers 2110 +
+    // 1750 with 820 of waiting, producers 1220 + 2400 with 1100; before it the layer of 8 x (2 + 10) x 4096 takes 63.4 us
+    // in place of 65.4, a training step of 4 x 16 x 4096 172.1 in place of 174.9.  d = 128 (consumers 1810 + 2270, producers
+    // 1850 + 3040) waits for memory besides: before (a) the prefill of 2 x 32 x 3001 takes 73.0 us in place of 71.7.
+    constexpr bool V_FIRST = D == 64;
     int nl = 0, no = 0;  // chunks loaded / written so far
     auto load_q = [&](u32x4 (&qr)[C::PIECES]) { load_chunk<D>(qr, cl.hp.q, cl.t0(), N, qo); };
+    auto load_v = [&](u32x4 (&vr)[C::PIECES]) {
+      if constexpr (CAUSAL) load_chunk<D>(vr, cl.hp.v, cl.t0(), N, vo);
+    };
     auto load_kv = [&](u32x4 (&kr)[C::PIECES], u32x4 (&vr)[C::PIECES]) {
-      if constexpr (CAUSAL) {
-        const int t0 = cl.t0();
-        load_chunk<D>(kr, cl.hp.k, t0, N, ko);
-        load_chunk<D>(vr, cl.hp.v, t0, N, vo);
-      }
+      if constexpr (CAUSAL) load_chunk<D>(kr, cl.hp.k, cl.t0(), N, ko);
+      if (!V_FIRST) load_v(vr);
       ++nl;
       cl.next(a, nl < nchunks);
     };
@@ -407,19 +412,30 @@ __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, 
         *reinterpret_cast<u32x2*>(qd + 8) = u32x2{fqv[2], fqv[3]};
       }
     };
-    // phi(K) and V of the chunk at `cs` -> buf[n % 2]; rows past the head's end become zeros
+    // V (with V_FIRST) and phi(K) and V (without) of the chunk at `cs` -> buf[n % 2]; rows past the head's end become zeros
+    auto stage_v = [&](const u32x4 (&vr)[C::PIECES], int n) {
+      if constexpr (CAUSAL) {
+        const int t0 = cs.t0();
+        const bool full = t0 + CH <= N;  // uniform; only a head's last chunk can be ragged
+#pragma unroll
+        for (int i = 0; i < C::PIECES; ++i) {
+          const int row = st.r0 + i * C::RP;
+          *reinterpret_cast<u32x4*>(&sm.buf[n & 1].v[row * C::VROW + st.col]) = full || t0 + row < N ? vr[i] : kZero4;
+        }
+      }
+    };
     auto stage_kv = [&](const u32x4 (&kr)[C::PIECES], const u32x4 (&vr)[C::PIECES], int n) {
       if constexpr (CAUSAL) {
         const int t0 = cs.t0();
         ChunkTiles<D>& b = sm.buf[n & 1];
-        const bool full = t0 + CH <= N;  // uniform; only a head's last chunk can be ragged
+        const bool full = t0 + CH <= N;
 #pragma unroll
         for (int i = 0; i < C::PIECES; ++i) {
           const int row = st.r0 + i * C::RP;
           const bool valid = full || t0 + row < N;
           const u32x4 fk = map_features<ELU1>(kr[i]);
           *reinterpret_cast<u32x4*>(&b.fk[row * C::KROW + st.col]) = valid ? fk : kZero4;
-          *reinterpret_cast<u32x4*>(&b.v[row * C::VROW + st.col]) = valid ? vr[i] : kZero4;
+          if (!V_FIRST) *reinterpret_cast<u32x4*>(&b.v[row * C::VROW + st.col]) = valid ? vr[i] : kZero4;
         }
       }
       cs.next(a, n + 1 < nchunks);
@@ -440,7 +456,7 @@ __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, 
     };
     // Per chunk n the consumers run [products, state read-out] (a) [denominators, in-chunk
     // part, state update] (b).  The producers' work for chunk n+1 is split the same way: phi(Q)
-    // and its staging before (a); after (a) the write-out of chunk n-1, then phi(K), V and their
+    // and its staging (V_FIRST: V's too) before (a); after (a) the write-out of chunk n-1, then phi(K), V and their
     // staging; each set's reload (chunk n+3) follows its staging.  The feature map is applied
     // where a tensor is staged: mapping parts of Q and K one phase early, in their registers, was
     // measured and is 2 % slower.  Two chunks per round (one per register set).
@@ -457,12 +473,15 @@ __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, 
       for (int i = 0; i < NSETS; ++i)
         if (S || nchunks > i) {
           load_q(qs[i]);
+          if (V_FIRST) load_v(vs[i]);
           load_kv(ks[i], vs[i]);
         }
       stage_q(qs[0], 0);
+      if (V_FIRST) stage_v(vs[0], 0);
       stage_kv(ks[0], vs[0], 0);
       if (S || nchunks > NSETS) {
         load_q(qs[0]);
+        if (V_FIRST) load_v(vs[0]);
         load_kv(ks[0], vs[0]);
       }
       lds_barrier();  // chunk 0 staged
@@ -473,8 +492,14 @@ __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, 
       constexpr int SET = decltype(set_tag)::value;
       constexpr int M = decltype(mode)::value;
       constexpr bool S = M != kGeneral;
-      if (S || n + 1 < nchunks) stage_q(qs[SET], n + 1);
-      if (S || n + 1 + NSETS < nchunks) load_q(qs[SET]);
+      if (S || n + 1 < nchunks) {
+        stage_q(qs[SET], n + 1);
+        if (V_FIRST) stage_v(vs[SET], n + 1);
+      }
+      if (S || n + 1 + NSETS < nchunks) {
+        load_q(qs[SET]);
+        if (V_FIRST) load_v(vs[SET]);
+      }
       lds_barrier();  // (a)
       if (M == kSteady || n > 0) store_out();
       if (S || n + 1 < nchunks) stage_kv(ks[SET], vs[SET], n + 1);
