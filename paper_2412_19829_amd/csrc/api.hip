@@ -529,9 +529,9 @@ gf_status attn_forward(const void* q, const void* k, const void* v, void* out, v
     std::lock_guard<std::mutex> lock(g_enqueue_mutex);
     SideStream* side = nullptr;
     if (win && lin && p->overlap) e = side_stream_for_current_device(s, &side);
-    // d = 64: the windowed heads' query blocks ride in the read-out's launch (linear_mfma.hip).  Not the
+    // The windowed heads' query blocks ride in the state pass's launch, but for long sums beside few blocks, or, in
+    // small calls at d = 64, in the read-out's (linear_mfma.hip).  Not the
     // streaming kernel (other block size), a forced overlap, or a launch mask that names one of the two.
-    // d = 128: in the state pass's, under the same conditions, but for long sums beside few blocks.
     const bool joint = win && !p->overlap && !stream;
     const bool together = joint && (mask & GF_LAUNCH_LINEAR_MAIN) && !r.general_chunk && linear_main_takes_windowed(a);
     const bool with_state = joint && (mask & GF_LAUNCH_LINEAR_STATE) && linear_state_takes_windowed(a);

@@ -138,15 +138,15 @@ template <int D> struct PieceOffsets {
       : off(2u * (uint32_t)(st.r0 * (int)row_stride + st.col)), colb(2u * (uint32_t)st.col),
         sn((int)row_stride) {}
 };
-template <int D, bool NT = true>
-__device__ __forceinline__ void load_chunk(u32x4 (&dst)[LinCfg<D>::PIECES], const uint16_t* head,
-                                           int t0, int N, const PieceOffsets<D>& po) {
-  using C = LinCfg<D>;
+template <int D, bool NT = true, int PIECES>
+__device__ __forceinline__ void load_chunk(u32x4 (&dst)[PIECES], const uint16_t* head, int t0, int N,
+                                           const PieceOffsets<D>& po) {
+  constexpr int RP = CH / PIECES;            // rows a pass of the producers covers
   const int last = min(N - 1 - t0, CH - 1);  // last valid row of the chunk
   const char* chunk = reinterpret_cast<const char*>(head + (int64_t)t0 * po.sn);
 #pragma unroll
-  for (int i = 0; i < C::PIECES; ++i) {
-    const int first = min(i * C::RP, last);  // uniform: the piece's first row, clamped
+  for (int i = 0; i < PIECES; ++i) {
+    const int first = min(i * RP, last);  // uniform: the piece's first row, clamped
     const char* base = chunk + 2u * (uint32_t)(first * po.sn);
     const uint32_t lim = 2u * (uint32_t)((last - first) * po.sn) + po.colb;
     const u32x4* src = reinterpret_cast<const u32x4*>(base + (size_t)min(po.off, lim));

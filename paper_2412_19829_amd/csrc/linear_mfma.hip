@@ -73,6 +73,17 @@ template <int D> struct StateSmem {
   StateTiles<D> buf[2];
 };
 
+// The read-out's workgroup: QS = 2 (d = 64) splits the chunk's queries over twice as many matrix waves, each with a carried
+// sum of its own, and stages with as many.  At d = 64 a workgroup is the only one of its unit: with QS = 1 its four waves
+// sit on a SIMD each and nothing hides a wave's waits, a chunk is a chain of 3900 cycles; with QS = 2 matrix and staging waves
+// share the SIMDs.  us, QS = 1 and 2: read-out launch of 8 x 10 heads x 4096 47 and 36; layer of 16 x 16 x 1024 33.4 and 28.4.
+template <int D, int QS_> struct MainCfg : LinCfg<D> {
+  using L = LinCfg<D>;
+  static constexpr int QS = QS_, NW = L::NWC * QS;
+  static constexpr int NTC = 64 * NW, NT = 2 * NTC;
+  static constexpr int RP = NTC / L::C8, PIECES = CH / RP;
+};
+
 // Walks the chunk list of a piece: (linear head, chunk inside the head), one step at a time.
 // All state is wave-uniform; the head's pointers are recomputed only when a head boundary is
 // crossed.
@@ -292,21 +303,37 @@ __global__ __launch_bounds__(LinCfg<D>::NT, 2) void linear_state_kernel(AttnArgs
   linear_state_block<D, ELU1, LinCfg<D>::NT>(a, blockIdx.x, gridDim.x, smem_raw);
 }
 
-// The sums and the windowed heads in one launch (d = 128): first one kind's blocks, from the next multiple of 8 on
-// (the XCDs keep their runs) the other's.  Either kernel by itself leaves part of the chip idle (few blocks, each a
-// chain through its chunks or tiles) and the two wait on different things (memory; vector and matrix units).  Whichever
+// The sums and the windowed heads in one launch.  Either kernel by itself leaves part of the chip idle (few blocks, each a
+// chain through its chunks or tiles) and the two wait on different things (memory; vector and matrix units).  First come one
+// kind's blocks, from the next multiple of 8 on (the XCDs keep their runs) the other's: whichever
 // block is the longer chain goes first, so that the short ones fill what it leaves.  Same bits as two launches; the
-// whole layer (us, two launches -> one, windowed blocks first / sums first): prefill of 2 x 32 x 3001, window 256, H0 = 6
+// whole layer, d = 128 (us, two launches -> one, windowed blocks first / sums first): prefill of 2 x 32 x 3001, window 256, H0 = 6
 // (7 tiles, 12 chunks) 91.2 -> 70.8 / 71.1; 1 x 32 x 4096, window 512 (11 tiles, 8 chunks) 80.8 -> 62.4 / 66.7;
 // 2 x 32 x 3001, window 64, H0 = 16 (4, 4) 87.6 -> 78.8 / 84.4; 1 x 16 x 20000, window 256 (7, 17) 108.9 -> 117.3 / 106.7;
 // 1 x 32 x 32768, window 512 (11, 57) 343 -> 346 / 342; 2 x 16 x 1000, window 128 42.7 -> 33.3 either way.
-template <bool ELU1>
-__global__ __launch_bounds__(kMfmaWindowThreads, 2) void linear_state_windowed_kernel(AttnArgs a, int sums, int blocks, bool sums_first) {
+// At d = 64, where three blocks share a unit, the kinds alternate in groups of 8 (one per XCD) where the query blocks are
+// half of the sums' chunks in tiles or more, so that every second unit takes one kind.  The layer, us, sums first and alternating:
+// 8 x (2 + 10) x 4096, window 256 63.2 and 62.3, two maps and 4 x (3 + 13) x 4096, 128 74.2 and 72.6, but (few tiles)
+// 1 x (2 + 14) x 16384, 128 48.2 and 52.4; d = 128, prefill of 2 x 32 x 3001 71.1 and 74.7.
+enum StateOrder { kSumsFirst, kBlocksFirst, kAlternate };
+template <int D, bool ELU1>
+__global__ __launch_bounds__(kMfmaWindowThreads, D == 64 ? 3 : 2) void linear_state_windowed_kernel(AttnArgs a, int sums, int blocks, StateOrder order) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  const int sum_at = sums_first ? 0 : (blocks + 7) & ~7, win_at = sums_first ? (sums + 7) & ~7 : 0;
-  const int sum = (int)blockIdx.x - sum_at, block = (int)blockIdx.x - win_at;
-  if (sum >= 0 && sum < sums) linear_state_block<128, ELU1, kMfmaWindowThreads>(a, sum, sums, smem_raw);
-  else if (block >= 0 && block < blocks) windowed_block<128, false>(a, block, smem_raw);
+  const int S = (sums + 7) / 8, W = (blocks + 7) / 8, both = order == kAlternate ? min(S, W) : 0;   // groups of 8
+  const int group = blockIdx.x / 8, in = blockIdx.x % 8, behind = group - 2 * both;   // behind the alternating ones
+  const int first = order == kBlocksFirst ? W : S - both;                             // groups of the kind that comes first there
+  bool is_sum;
+  int at;
+  if (behind < 0) {
+    is_sum = group % 2 == 0;
+    at = group / 2;
+  } else {
+    is_sum = (behind < first) != (order == kBlocksFirst);
+    at = both + (behind < first ? behind : behind - first);
+  }
+  at = 8 * at + in;
+  if (is_sum && at < sums) linear_state_block<D, ELU1, kMfmaWindowThreads>(a, at, sums, smem_raw);
+  else if (!is_sum && at < blocks) windowed_block<D, false>(a, at, smem_raw);
 }
 
 // (2) Slot j holds the sums over the part of its head that lies in sub-piece j-1.  Inside every
@@ -364,9 +391,10 @@ __global__ __launch_bounds__(256) void linear_prefix_kernel(float* ws, int n_hea
 //     the normalisation remain (same barriers, same producer/consumer split).
 //     EMIT (causal only): every head's (A, Z) after its last token is also written out, for a
 //     decode step to continue from; a separate instantiation so that the plain layer pays nothing.
-template <int D, bool ELU1, bool CAUSAL, bool EMIT>
+template <int D, int QS, bool ELU1, bool CAUSAL, bool EMIT>
 __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, unsigned char* smem_raw) {
-  using C = LinCfg<D>;
+  using C = MainCfg<D, QS>;
+  constexpr int NQ = 2 / QS;   // query halves a wave takes
   LinSmem<D>& sm = *reinterpret_cast<LinSmem<D>*>(smem_raw);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int ln = lane & 31, lh = lane >> 5;
@@ -376,7 +404,7 @@ __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, 
   if (nchunks <= 0) return;  // uniform
   const int N = a.N;
 
-  if (wave >= C::NWC) {
+  if (wave >= C::NW) {
     // ---- producers ----
     const Staging<D> st(tid - C::NTC);
     const PieceOffsets<D> qo(st, a.q.sn), ko(st, a.k.sn), vo(st, a.v.sn);
@@ -385,9 +413,9 @@ __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, 
     // NSETS further on as soon as it has been staged
     constexpr int NSETS = GF_MAIN_SETS;
     u32x4 qs[NSETS][C::PIECES], ks[NSETS][C::PIECES], vs[NSETS][C::PIECES];
-    // V is staged before (a) at d = 64, after it at d = 128.  Cycles a chunk, d = 64, staged after (a): consumers 2110 +
-    // 1750 with 820 of waiting, producers 1220 + 2400 with 1100; before it the layer of 8 x (2 + 10) x 4096 takes 63.4 us
-    // in place of 65.4, a training step of 4 x 16 x 4096 172.1 in place of 174.9.  d = 128 (consumers 1810 + 2270, producers
+    // V is staged before (a) at d = 64, after it at d = 128.  Cycles a chunk, four waves at d = 64, staged after (a): consumers
+    // 2110 + 1750 with 820 of waiting, producers 1220 + 2400 with 1100; before it the layer of 8 x (2 + 10) x 4096 took 63.1 us
+    // in place of 65.3, a training step of 4 x 16 x 4096 175.7 in place of 178.7.  d = 128 (consumers 1810 + 2270, producers
     // 1850 + 3040) waits for memory besides: before (a) the prefill of 2 x 32 x 3001 takes 73.0 us in place of 71.7.
     constexpr bool V_FIRST = D == 64;
     int nl = 0, no = 0;  // chunks loaded / written so far
@@ -539,6 +567,8 @@ __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, 
     sm.zh[buf][zi] = hi;
     sm.zl[buf][zi] = (uint16_t)(pack_bf16(zval - __uint_as_float((uint32_t)hi << 16), 0.f) & 0xffffu);
   };
+  const int vw = QS == 1 ? wave : wave % C::NWC, qh = QS == 1 ? 0 : wave / C::NWC;   // value tile, query half
+  const bool second = QS == 2 && __builtin_amdgcn_readfirstlane(qh) == 1;
   f32x16 sacc[C::ET];
   int lc = g0 % a.vcph;  // chunk index inside the current head
 #pragma unroll
@@ -569,14 +599,14 @@ __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, 
       float4 t0[C::ET][4], t1[C::ET][4];
 #pragma unroll
       for (int ct = 0; ct < C::ET; ++ct) {
-        const int off = state_tile_offset<D>(ct, wave, lane);
+        const int off = state_tile_offset<D>(ct, vw, lane);
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           t0[ct][g] = reinterpret_cast<const float4*>(s0 + off)[g];
           t1[ct][g] = reinterpret_cast<const float4*>(s1 + off)[g];
         }
       }
-      const float za = s0[D * D + 32 * wave + ln], zb = s1[D * D + 32 * wave + ln];
+      const float za = s0[D * D + 32 * vw + ln], zb = s1[D * D + 32 * vw + ln];
 #pragma unroll
       for (int ct = 0; ct < C::ET; ++ct)
 #pragma unroll
@@ -589,9 +619,9 @@ __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, 
       z0 += za + w1 * zb;
     }
   }
-  if (lh == 0) {
-    put_z(0, 32 * wave + kperm32(ln), z0);
-    if (!CAUSAL) put_z(1, 32 * wave + kperm32(ln), z0);   // Z never moves: both buffers hold it
+  if (lh == 0 && qh == 0) {
+    put_z(0, 32 * vw + kperm32(ln), z0);
+    if (!CAUSAL) put_z(1, 32 * vw + kperm32(ln), z0);   // Z never moves: both buffers hold it
   }
   // the product tile above the diagonal (keys 32.., queries ..31) is never computed: it stays 0
   for (int x = tid; x < 32 * 32 / 8; x += C::NTC)
@@ -602,16 +632,17 @@ __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, 
 
   constexpr int PPT = C::NTC / CH;  // threads per query in the denominator
   // finished rows: divide by the denominators and hand them to the producers through LDS
-  auto normalise = [&](const f32x16 (&num)[2]) {
+  auto normalise = [&](const f32x16 (&num)[NQ]) {
 #pragma unroll
-    for (int tq = 0; tq < 2; ++tq) {
+    for (int x = 0; x < NQ; ++x) {
+      const int tq = x + qh;
       const float inv = __builtin_amdgcn_rcpf(sm.den[32 * tq + ln]);
-      uint16_t* orow = &sm.ot[(32 * tq + ln) * C::OROW + 32 * wave + 4 * lh];
+      uint16_t* orow = &sm.ot[(32 * tq + ln) * C::OROW + 32 * vw + 4 * lh];
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         u32x2 pk;
-        pk[0] = pack_bf16(num[tq][4 * g + 0] * inv, num[tq][4 * g + 1] * inv);
-        pk[1] = pack_bf16(num[tq][4 * g + 2] * inv, num[tq][4 * g + 3] * inv);
+        pk[0] = pack_bf16(num[x][4 * g + 0] * inv, num[x][4 * g + 1] * inv);
+        pk[1] = pack_bf16(num[x][4 * g + 2] * inv, num[x][4 * g + 3] * inv);
         *reinterpret_cast<u32x2*>(orow + 8 * g) = pk;
       }
     }
@@ -621,13 +652,13 @@ __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, 
   // without a tile repeats tile 0 and stores the same values to the same place, which keeps the
   // code free of branches: the products and the state read-out then interleave in one block and
   // neither chain of dependent matrix instructions has to wait for its own results.
-  constexpr int NTILE = (3 + C::NWC - 1) / C::NWC;  // product tiles per wave
+  constexpr int NTILE = (3 + C::NW - 1) / C::NW;    // product tiles per wave
   constexpr int KS = D / 16;                        // contraction steps per product tile
   constexpr int G1N = NTILE * KS;                   // product steps per chunk
   static_assert(KS == 2 * C::ET, "a product tile and the read-out take the same contraction steps");
-  f32x16 num[2];
+  f32x16 num[NQ];
 #pragma unroll
-  for (int tq = 0; tq < 2; ++tq)
+  for (int tq = 0; tq < NQ; ++tq)
 #pragma unroll
     for (int r = 0; r < 16; ++r) num[tq][r] = 0.f;
   for (int n = 0; n < nchunks; ++n) {
@@ -641,13 +672,14 @@ __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, 
     int tk[NTILE], tqa[NTILE];
 #pragma unroll
     for (int rep = 0; rep < NTILE; ++rep) {
-      const int tile = (wave + rep * C::NWC) % 3;
+      // with the halves apart a wave's tile lies in its own half: tiles 0, 0, 1, 2
+      const int tile = QS == 2 ? max(wave - 1, 0) : (wave + rep * C::NW) % 3;
       tk[rep] = tile == 2 ? 1 : 0;
       tqa[rep] = tile == 0 ? 0 : 1;
     }
     // operands are fetched from LDS one step ahead of the matrix instructions that use them
     struct StepOps {
-      bf16x8 kt, q0, q1;
+      bf16x8 kt, q[NQ];
     };
     auto fetch = [&](int i) {
       StepOps o;
@@ -661,8 +693,8 @@ __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, 
       }
       // phi(Q) rows 0..31 and 32..63, features of contraction step ks: the read-out step
       // 2*ct + kb = ks uses both, the product tile the one of its query half
-      o.q0 = lds_read16(&b.fq[ln * C::QROW + 16 * ks + 8 * lh]);
-      o.q1 = lds_read16(&b.fq[(32 + ln) * C::QROW + 16 * ks + 8 * lh]);
+#pragma unroll
+      for (int x = 0; x < NQ; ++x) o.q[x] = lds_read16(&b.fq[(32 * (x + qh) + ln) * C::QROW + 16 * ks + 8 * lh]);
       return o;
     };
     constexpr int PD = 2;  // steps between an operand fetch and its use (measured: 2 beats 1, 3 and 4)
@@ -675,7 +707,7 @@ __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, 
     // first operands are on their way
     normalise(num);
 #pragma unroll
-    for (int tq = 0; tq < 2; ++tq)
+    for (int tq = 0; tq < NQ; ++tq)
 #pragma unroll
       for (int r = 0; r < 16; ++r) num[tq][r] = 0.f;
 #pragma unroll
@@ -686,7 +718,7 @@ __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, 
     for (int i = 0; i < NSTEP; ++i) {
       if (i + PD < NSTEP) ops[i + PD] = fetch(i + PD);
       const StepOps& cur = ops[i];
-      if constexpr (CAUSAL) p[i / KS] = mfma32(cur.kt, tqa[i / KS] ? cur.q1 : cur.q0, p[i / KS]);
+      if constexpr (CAUSAL) p[i / KS] = mfma32(cur.kt, NQ == 2 && tqa[i / KS] ? cur.q[NQ - 1] : cur.q[0], p[i / KS]);
       if (i / KS == 0) {
         // num^T = A^T phiQ^T with A straight from the state registers
         const int ct = i / 2, kb_ = i % 2;
@@ -695,8 +727,8 @@ __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, 
         for (int x = 0; x < 4; ++x)
           sw[x] = pack_bf16(sacc[ct][8 * kb_ + 2 * x], sacc[ct][8 * kb_ + 2 * x + 1]);
         const bf16x8 sa = as_bf16x8(sw);
-        num[0] = mfma32(sa, cur.q0, num[0]);
-        num[1] = mfma32(sa, cur.q1, num[1]);
+#pragma unroll
+        for (int x = 0; x < NQ; ++x) num[x] = mfma32(sa, cur.q[x], num[x]);
       }
       __builtin_amdgcn_sched_barrier(0);  // keep the fetches PD steps ahead of their use
     }
@@ -723,15 +755,15 @@ __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, 
     // fetched PDB steps ahead; the denominators are computed while the first ones arrive.
     {
       struct TokOps {
-        bf16x8 vt, pb[2], fa[C::ET], fz;
+        bf16x8 vt, pb[NQ], fa[C::ET], fz;
       };
       auto fetch_tok = [&](int kk) {
         TokOps o;
-        o.vt = lds_operand_tr(b.v, C::VROW, 16 * kk + 8 * lh, 16 * kk + 8 * lh + 4, 32 * wave, lane);
+        o.vt = lds_operand_tr(b.v, C::VROW, 16 * kk + 8 * lh, 16 * kk + 8 * lh + 4, 32 * vw, lane);
 #pragma unroll
-        for (int tq = 0; tq < 2; ++tq)
-          if (16 * kk < 32 * (tq + 1))
-            o.pb[tq] = lds_read16(&sm.pt[(32 * tq + ln) * C::PROW + 16 * kk + 8 * lh]);
+        for (int x = 0; x < NQ; ++x)
+          if (16 * kk < 32 * (x + 1) || second)
+            o.pb[x] = lds_read16(&sm.pt[(32 * (x + qh) + ln) * C::PROW + 16 * kk + 8 * lh]);
 #pragma unroll
         for (int ct = 0; ct < C::ET; ++ct)
           o.fa[ct] = lds_operand_tr(b.fk, C::KROW, 16 * kk + 8 * lh, 16 * kk + 8 * lh + 4, 32 * ct, lane);
@@ -740,7 +772,7 @@ __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, 
         // tile costs it 9 cycles per wave)
         o.fz = o.fa[0];
 #pragma unroll
-        for (int ct = 1; ct < C::ET; ++ct) o.fz = wave == ct ? o.fa[ct] : o.fz;
+        for (int ct = 1; ct < C::ET; ++ct) o.fz = vw == ct ? o.fa[ct] : o.fz;
         return o;
       };
       constexpr int NK = CAUSAL ? CH / 16 : 0, PDB = 2;   // no token work in the bidirectional read-out
@@ -782,8 +814,8 @@ __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, 
         if (kk + PDB < NK) tok[kk + PDB] = fetch_tok(kk + PDB);
         const TokOps& cur = tok[kk];
 #pragma unroll
-        for (int tq = 0; tq < 2; ++tq)
-          if (16 * kk < 32 * (tq + 1)) num[tq] = mfma32(cur.vt, cur.pb[tq], num[tq]);
+        for (int x = 0; x < NQ; ++x)
+          if (16 * kk < 32 * (x + 1) || second) num[x] = mfma32(cur.vt, cur.pb[x], num[x]);
         zs = sum8_bf16(cur.fz, zs);
 #pragma unroll
         for (int ct = 0; ct < C::ET; ++ct) sacc[ct] = mfma32(cur.fa[ct], cur.vt, sacc[ct]);
@@ -791,9 +823,9 @@ __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, 
       }
       if constexpr (CAUSAL) {
         zs += __shfl_xor(zs, 32, 64);
-        const int zi = 32 * wave + kperm32(ln);
+        const int zi = 32 * vw + kperm32(ln);
         const float znew = sm.z[zc][zi] + zs;
-        if (EMIT && head_done) {
+        if (EMIT && head_done && qh == 0) {
           // the state after the head's last token, for a decode step to continue from:
           // A row-major [feature][value] (lane = value column, register = feature row), then Z
           float* fs = a.final_state + (int64_t)((g0 + n) / a.vcph) * C::STATE;
@@ -803,14 +835,14 @@ __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, 
           for (int ct = 0; ct < C::ET; ++ct)
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-              float* row = fs + (32 * ct + 8 * g + 4 * lh) * D + 32 * wave + ln;
+              float* row = fs + (32 * ct + 8 * g + 4 * lh) * D + 32 * vw + ln;
 #pragma unroll
               for (int x = 0; x < 4; ++x) row[x * D] = sacc[ct][4 * g + x];
               __builtin_amdgcn_sched_barrier(0);
             }
-          if (lh == 0) fs[D * D + 32 * wave + ln] = znew;
+          if (lh == 0) fs[D * D + 32 * vw + ln] = znew;
         }
-        if (lh == 0) put_z(zc ^ 1, zi, head_ends ? 0.f : znew);
+        if (lh == 0 && qh == 0) put_z(zc ^ 1, zi, head_ends ? 0.f : znew);
         if (head_ends) {
 #pragma unroll
           for (int ct = 0; ct < C::ET; ++ct)
@@ -825,26 +857,23 @@ __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, 
   lds_barrier();  // (c)
 }
 
-template <int D, bool ELU1, bool CAUSAL, bool EMIT>
-__global__ __launch_bounds__(LinCfg<D>::NT, D == 64 ? 2 : 1) void linear_main_kernel(AttnArgs a) {
+template <int D, int QS, bool ELU1, bool CAUSAL, bool EMIT>
+__global__ __launch_bounds__((MainCfg<D, QS>::NT), D == 64 ? 2 : 1) void linear_main_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  linear_main_block<D, ELU1, CAUSAL, EMIT>(a, blockIdx.x, smem_raw);
+  linear_main_block<D, QS, ELU1, CAUSAL, EMIT>(a, blockIdx.x, smem_raw);
 }
 
-// The read-out and the windowed heads in one launch (d = 64): blocks [0, n_pieces) are the read-out's,
-// those from the next multiple of 8 on (the XCDs keep their runs) are query blocks of the windowed
-// heads.  At d = 64 a compute unit holds two workgroups and the plan gives it one piece, so the query
-// blocks run beside the pieces instead of in front of them.
-// Same bits as two launches; the whole layer (us, two launches -> one): B=1 H=12 N=2048 w=128 H0=2
-// 36.1 -> 28.1, B=8 H=12 N=4096 w=256 H0=2 78.4 -> 67.4.  At d = 128 a piece's LDS fills its compute unit and
-// nothing can run beside it.
+// The read-out and the windowed heads in one launch (d = 64, calls that leave units idle): blocks [0, n_pieces) are the
+// read-out's in its form of four waves, those from the next multiple of 8 on (the XCDs keep their runs) are query blocks of the
+// windowed heads, which find units of their own.  Same bits as two launches; the whole layer (us, two launches -> one):
+// B=1 H=12 N=2048 w=128 H0=2 36.1 -> 28.1.
 template <bool ELU1, bool CAUSAL, bool EMIT>
 __global__ __launch_bounds__(256, 2) void linear_main_windowed_kernel(AttnArgs a) {
-  static_assert(LinCfg<64>::NT == kMfmaWindowThreads, "one block size for both kinds of workgroup");
+  static_assert(MainCfg<64, 1>::NT == kMfmaWindowThreads, "one block size for both kinds of workgroup");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   const int first = (a.n_pieces + 7) & ~7, block = blockIdx.x;
   if (block >= first) windowed_block<64, false>(a, block - first, smem_raw);
-  else if (block < a.n_pieces) linear_main_block<64, ELU1, CAUSAL, EMIT>(a, block, smem_raw);
+  else if (block < a.n_pieces) linear_main_block<64, 1, ELU1, CAUSAL, EMIT>(a, block, smem_raw);
 }
 
 // key tiles of a query block's band
@@ -856,18 +885,16 @@ template <int D> hipError_t launch_state_t(const AttnArgs& a, bool with_windowed
   const int heads = a.B * (a.H - a.H0), sums = state_blocks(a);
   int smem = (int)sizeof(StateSmem<D>);
   hipError_t e = hipSuccess;
-  if constexpr (D == 128) {
-    if (with_windowed) {
-      if (smem < (int)sizeof(WinSmem<D>)) smem = (int)sizeof(WinSmem<D>);
-      const int blocks = (a.N + BR - 1) / BR * a.H0 * a.B;
-      const bool sums_first = a.piece_chunks / a.state_sub > block_tiles(a);
-      const dim3 grid(sums_first ? ((sums + 7) & ~7) + blocks : ((blocks + 7) & ~7) + sums);
-      const auto kern = a.phi == 0 ? linear_state_windowed_kernel<true> : linear_state_windowed_kernel<false>;
-      if ((e = allow_lds(kern, smem)) != hipSuccess) return e;
-      kern<<<grid, dim3(kMfmaWindowThreads), smem, s>>>(a, sums, blocks, sums_first);
-    }
-  }
-  if (!with_windowed) {
+  if (with_windowed) {
+    if (smem < (int)sizeof(WinSmem<D>)) smem = (int)sizeof(WinSmem<D>);
+    const int blocks = (a.N + BR - 1) / BR * a.H0 * a.B;
+    const int64_t chunks = a.piece_chunks / a.state_sub, tiles = block_tiles(a);
+    const StateOrder order = D == 64 && 2 * blocks * tiles >= sums * chunks ? kAlternate : chunks > tiles ? kSumsFirst : kBlocksFirst;
+    const dim3 grid(((sums + 7) & ~7) + ((blocks + 7) & ~7));
+    const auto kern = a.phi == 0 ? linear_state_windowed_kernel<D, true> : linear_state_windowed_kernel<D, false>;
+    if ((e = allow_lds(kern, smem)) != hipSuccess) return e;
+    kern<<<grid, dim3(kMfmaWindowThreads), smem, s>>>(a, sums, blocks, order);
+  } else {
     const auto kern = a.phi == 0 ? linear_state_kernel<D, true> : linear_state_kernel<D, false>;
     if ((e = allow_lds(kern, smem)) != hipSuccess) return e;
     kern<<<dim3(sums), dim3(C::NT), smem, s>>>(a);
@@ -882,24 +909,23 @@ template <int D> hipError_t launch_state_t(const AttnArgs& a, bool with_windowed
   return e;
 }
 
-template <int D> hipError_t launch_main_t(const AttnArgs& a, hipStream_t s) {
-  using C = LinCfg<D>;
+template <int D, int QS> hipError_t launch_main_t(const AttnArgs& a, hipStream_t s) {
   const int smem = (int)sizeof(LinSmem<D>);
-  const dim3 grid(a.n_pieces), block(C::NT);
+  const dim3 grid(a.n_pieces), block(MainCfg<D, QS>::NT);
   hipError_t e = hipSuccess;
   auto launch = [&](auto kern) {
     e = allow_lds(kern, smem);
     if (e == hipSuccess) kern<<<grid, block, smem, s>>>(a);
   };
   if (a.causal && a.final_state) {
-    if (a.phi == 0) launch(linear_main_kernel<D, true, true, true>);
-    else launch(linear_main_kernel<D, false, true, true>);
+    if (a.phi == 0) launch(linear_main_kernel<D, QS, true, true, true>);
+    else launch(linear_main_kernel<D, QS, false, true, true>);
   } else if (a.causal) {
-    if (a.phi == 0) launch(linear_main_kernel<D, true, true, false>);
-    else launch(linear_main_kernel<D, false, true, false>);
+    if (a.phi == 0) launch(linear_main_kernel<D, QS, true, true, false>);
+    else launch(linear_main_kernel<D, QS, false, true, false>);
   } else {
-    if (a.phi == 0) launch(linear_main_kernel<D, true, false, false>);
-    else launch(linear_main_kernel<D, false, false, false>);
+    if (a.phi == 0) launch(linear_main_kernel<D, QS, true, false, false>);
+    else launch(linear_main_kernel<D, QS, false, false, false>);
   }
   return e != hipSuccess ? e : hipGetLastError();
 }
@@ -917,18 +943,27 @@ template <bool CAUSAL, bool EMIT> hipError_t launch_main_windowed_t(const AttnAr
 
 }  // namespace
 
+static int64_t query_block_count(const AttnArgs& a) { return (int64_t)((a.N + BR - 1) / BR) * a.H0 * a.B; }
+static bool has_state_pass(const AttnArgs& a) {
+  return a.H - a.H0 > 0 && a.N > 0 && a.B > 0 && a.ws_states && !(a.causal && a.n_pieces <= 1);
+}
+// The four-wave read-out, with the query blocks in its launch where a call allows that: d = 64, and hardly more pieces and
+// query blocks than units (or no state pass that could take the query blocks along).  Otherwise the eight-wave form, the query
+// blocks in the state pass's launch.  The layer, us, four waves and eight, window 128: 1 x (2 + 10) heads x 2048 (112 blocks)
+// 20.0 and 21.2, x 512 13.0 and 15.6; 3 x (2 + 10) x 2048 (336) 26.5 and 26.9; 8 x (2 + 10) x 1024 (368) 26.3 and 25.5;
+// 1 x (2 + 14) x 16384 (480) 57.5 and 48.3; window 256, 8 x (2 + 10) x 4096 (752) 63.1 and 62.6; a training step of
+// 32 x (3 + 9) x 577 over all keys 123 and 116.
+static bool four_waves(const AttnArgs& a) {
+  return a.d == 64 && a.H0 > 0 && (3 * (a.n_pieces + query_block_count(a)) <= 4 * device_compute_units() || !has_state_pass(a));
+}
 bool linear_main_takes_windowed(const AttnArgs& a) {
-  const int64_t blocks = a.n_pieces + (int64_t)((a.N + BR - 1) / BR) * a.H0 * a.B;
-  return a.d == 64 && a.H0 > 0 && a.H0 < a.H && a.n_pieces > 0 && a.scale >= 0.f && blocks < (1 << 22);
+  return four_waves(a) && a.H0 < a.H && a.n_pieces > 0 && a.scale >= 0.f && a.n_pieces + query_block_count(a) < (1 << 22);
 }
 hipError_t launch_linear_main_windowed_mfma(const AttnArgs& a, hipStream_t s) {
   if (!a.causal) return launch_main_windowed_t<false, false>(a, s);
   return a.final_state ? launch_main_windowed_t<true, true>(a, s) : launch_main_windowed_t<true, false>(a, s);
 }
 
-static bool has_state_pass(const AttnArgs& a) {
-  return a.H - a.H0 > 0 && a.N > 0 && a.B > 0 && a.ws_states && !(a.causal && a.n_pieces <= 1);
-}
 // Not beside long sums that outweigh the query blocks by far: such sums are what the launch takes, and of 256 threads they
 // take longer than of 512.  Chains of more than 30 chunks, and less than a third as many tiles as linear chunks; the
 // whole layer, us, one launch and two, chunks a chain, tiles a chunk: 2 x 32 x 12000, window 64, H0 = 1 222.8 and 214.7 (47,
@@ -936,19 +971,20 @@ static bool has_state_pass(const AttnArgs& a) {
 // 1 150.1 and 149.4 (32, 0.05); 2 x 32 x 12000, 300, 4 214.0 and 220.4 (47, 0.5); 4 x 32 x 7800, 512, 4 272.8 and 276.4 (61,
 // 0.7); 2 x 32 x 8700, 64, 1 155.2 and 157.4 (17, 0.05); 1 x 16 x 32000, 64, 1 159.7 and 159.2 (30, 0.1).
 bool linear_state_takes_windowed(const AttnArgs& a) {
-  if (a.d != 128 || a.H0 <= 0 || !has_state_pass(a) || a.scale < 0.f) return false;
-  const int64_t query_blocks = (int64_t)((a.N + BR - 1) / BR) * a.H0 * a.B;
+  if (a.H0 <= 0 || !has_state_pass(a) || a.scale < 0.f || four_waves(a)) return false;
+  const int64_t query_blocks = query_block_count(a);
   if (a.piece_chunks / a.state_sub > 30 && 3 * query_blocks * block_tiles(a) < (int64_t)a.B * (a.H - a.H0) * a.cph) return false;
   return (int64_t)a.n_pieces * a.state_sub + query_blocks < (1 << 22);
 }
 hipError_t launch_linear_state_mfma(const AttnArgs& a, bool with_windowed, hipStream_t s) {
   if (!has_state_pass(a)) return hipSuccess;
-  return a.d == 64 ? launch_state_t<64>(a, false, s) : launch_state_t<128>(a, with_windowed, s);
+  return a.d == 64 ? launch_state_t<64>(a, with_windowed, s) : launch_state_t<128>(a, with_windowed, s);
 }
 
 hipError_t launch_linear_main_mfma(const AttnArgs& a, hipStream_t s) {
   if (a.H - a.H0 <= 0 || a.N <= 0 || a.B <= 0 || a.n_pieces <= 0) return hipSuccess;
-  return a.d == 64 ? launch_main_t<64>(a, s) : launch_main_t<128>(a, s);
+  if (a.d == 128) return launch_main_t<128, 1>(a, s);
+  return four_waves(a) ? launch_main_t<64, 1>(a, s) : launch_main_t<64, 2>(a, s);
 }
 
 }  // namespace gformer

@@ -1,0 +1,62 @@
+"""d = 64: the read-out with twice the waves, and the query blocks beside the state pass.  Against the oracle where its tiles
+and pieces end (chunks of 64 tokens, queries split in halves of 32), and the bits of the kernels launched one by one on both
+sides of the rule that chooses it, the prefill's carried states included."""
+from __future__ import annotations
+
+import pytest
+
+from oracle import cpu_oracle as co
+from paper_2412_19829_amd import binding as gb
+from tests.gpu_util import run_gpu, to_device
+from tests.test_gpu_parity import check, synth
+
+
+# B, H, N, options; every head linear
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [
+    (1, 2, 1, {}), (1, 3, 31, {}), (1, 3, 33, {}), (2, 3, 64, {}), (1, 3, 65, {}), (3, 5, 97, {}), (1, 40, 777, {}),
+    (7, 40, 150, {}),                     # more heads than units: pieces straddle heads
+    (1, 3, 1055, {"eps": 0.5}), (1, 3, 1000, {"segment_len": 64}), (2, 4, 577, {"bidirectional": 1}), (1, 1, 33, {"bidirectional": 1}),
+], ids=lambda c: "x".join(map(str, c[:3])) + "".join(f"-{k}" for k in c[3]))
+def test_against_oracle(case):
+    B, H, N, kw = case
+    q, k, v = synth(B, H, N, 64, "bf16", 91)
+    args = {x: kw[x] for x in ("eps", "bidirectional") if x in kw}
+    check(run_gpu(q, k, v, "bf16", 16, 0, **kw), co.attn_fwd(q, k, v, 16, 0, **args), "bf16", str(case))
+
+
+# B, H, N, window, H0, options: pieces and query blocks on either side of four to three units
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [
+    (3, 12, 2048, 128, 2, {}), (8, 12, 1000, 128, 2, {}), (4, 40, 777, 64, 20, {}), (2, 12, 4100, 300, 4, {}),
+    (16, 12, 577, 64, 3, {"bidirectional": 1}), (8, 12, 1000, 50, 2, {"phi": gb.GF_PHI_IDENTITY}),
+    (8, 12, 1000, 50, 2, {"softmax_scale": -0.5}),
+], ids=lambda c: "x".join(map(str, c[:5])) + "".join(f"-{k}" for k in c[5]))
+def test_one_launch_gives_the_bits_of_two(case):
+    import torch
+    B, H, N, w, H0, kw = case
+    q, k, v = (to_device(x, "bf16") for x in synth(B, H, N, 64, "bf16", 92))
+    if "phi" in kw:
+        q, k = q.abs() + 0.125, k.abs() + 0.125
+    p = gb.make_params(n_sparse_heads=H0, **kw)
+    ws = torch.empty(max(gb.gformer_attn_workspace_bytes(B, H, N, 64, w, p), 256), dtype=torch.uint8, device="cuda")
+    got, want = torch.full_like(q, float("nan")), torch.full_like(q, float("nan"))
+    gb.gformer_attn_fwd(q, k, v, got, w, H0, workspace=ws, **kw)
+    for m in (gb.GF_LAUNCH_WINDOWED, gb.GF_LAUNCH_LINEAR_STATE, gb.GF_LAUNCH_LINEAR_MAIN):
+        gb.gformer_attn_fwd(q, k, v, want, w, H0, workspace=ws, launch_mask=m, **kw)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(want.float()).all())
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    if not kw:   # the prefill's read-out leaves the carried states: A and Z over all tokens
+        kc, vc = (torch.zeros(B, H0, w, 64, dtype=q.dtype, device="cuda") for _ in range(2))
+        st = torch.zeros(B, H - H0, 64 * 64 + 64, device="cuda")
+        pre = torch.full_like(q, float("nan"))
+        gb.gformer_attn_prefill(q, k, v, pre, kc, vc, st, w, H0)
+        torch.cuda.synchronize()
+        assert torch.equal(pre.view(torch.int16), want.view(torch.int16))
+        fk = k[:, H0:].double()
+        fk = torch.where(fk > 0, fk + 1, torch.exp(fk))
+        A = torch.matmul(fk.transpose(2, 3).contiguous(), v[:, H0:].double())
+        # phi(k) enters as bf16 (2^-9 of each of N terms, independent: far below 2^-8 of the norm)
+        assert float((st[..., :4096].double().view_as(A) - A).norm() / A.norm()) < 2.0 ** -8
+        assert float((st[..., 4096:].double() - fk.sum(2)).norm() / fk.sum(2).norm()) < 2.0 ** -8
