@@ -621,10 +621,19 @@ __device__ __forceinline__ void linear_bwd_q_f32(const BwdArgs& a, int block, un
 }
 
 // ---- backward, reverse walk: dk and dv -----------------------------------------------------------
+// B is an operand by feature column (dk) and by value column (dv).  Accumulated in both orders it took a fifth of the
+// walk's matrix instructions twice, and twice the loads of the sums it starts from; now the waves keep it by feature column and
+// leave a copy, turned, in LDS.
+template <int D> struct F32BwdKvSmem : F32BwdSmem<D> {
+  float b[D * kF32Row<D>];           // [value][feature], row v rotated by 16 * (v / 16) floats: writes and reads miss each other's banks
+};
+template <int D> __device__ __forceinline__ int turned(int value, int feature) {
+  return value * kF32Row<D> + (feature + (value & ~15)) % D;
+}
 template <int D, bool CAUSAL>
 __device__ __forceinline__ void linear_bwd_kv_f32(const BwdArgs& a, int block, unsigned char* smem_raw) {
   constexpr int TR = kF32Row<D>, NW = D / 16;
-  F32BwdSmem<D>& sm = *reinterpret_cast<F32BwdSmem<D>*>(smem_raw);
+  F32BwdKvSmem<D>& sm = *reinterpret_cast<F32BwdKvSmem<D>*>(smem_raw);
   float* cvec = &sm.red[0][0][0];   // c of the chunk's tokens
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, i = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -655,9 +664,8 @@ __device__ __forceinline__ void linear_bwd_kv_f32(const BwdArgs& a, int block, u
       if (tid < CH) cr = t0 + tid < N ? ws[2 * (int64_t)(t0 + tid) + 1] : 0.f;
     }
   };
-  f32x4 b1[D / 16], b2[D / 16];   // B by feature column (for dk) and by value column (for dv)
+  f32x4 b1[D / 16];   // B by feature column
   clear<D>(b1);
-  clear<D>(b2);
   const int last_chunk = begin + (end - begin - 1) / CH * CH;
   load(last_chunk);
   {
@@ -668,11 +676,19 @@ __device__ __forceinline__ void linear_bwd_kv_f32(const BwdArgs& a, int block, u
     for (int j = first; j < last; ++j) {
       const float* src = sums + (int64_t)j * kLinState<D>;
       add_sum<D, false>(b1, src, wave, g, i);
-      add_sum<D, true>(b2, src, wave, g, i);
       if (tid < D) yz += src[D * D + tid];
     }
     if (tid < D) sm.z[tid] = yz;
   }
+  auto copy_b = [&]() {
+#pragma unroll
+    for (int hh = 0; hh < D / 64; ++hh)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) sm.b[turned<D>(64 * hh + 16 * g + 4 * r + x, 16 * wave + i)] = b1[4 * hh + x][r];
+  };
+  copy_b();
   walk_backward(begin, end, [&](int t0, auto steady) {
     constexpr bool STEADY = decltype(steady)::value;
     lds_barrier();
@@ -707,7 +723,19 @@ __device__ __forceinline__ void linear_bwd_kv_f32(const BwdArgs& a, int block, u
 #pragma unroll
     for (int ub = 0; ub < 2; ++ub) { dka[ub] = -yc; dva[ub] = kZeroF4; }
     read_out<D>(dka, b1, sm.vv, g, i);
-    read_out<D>(dva, b2, sm.fk, g, i);
+#pragma unroll
+    for (int hh = 0; hh < D / 64; ++hh)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int f0 = 64 * hh + 16 * g + 4 * r;
+        const f32x4 s = lds4(sm.b + turned<D>(16 * wave + i, f0));
+        const f32x4 x0 = lds4(sm.fk + i * TR + f0), x1 = lds4(sm.fk + (16 + i) * TR + f0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          dva[0] = mfma_f32(s[j], x0[j], dva[0]);
+          dva[1] = mfma_f32(s[j], x1[j], dva[1]);
+        }
+      }
     float qcol[2][4], gcol[2][4];
     if (CAUSAL) {
       lds_barrier();   // products visible
@@ -739,7 +767,7 @@ __device__ __forceinline__ void linear_bwd_kv_f32(const BwdArgs& a, int block, u
     }
     if (CAUSAL) {
       add_outer<D>(b1, sm.dd, qcol, g, i);
-      add_outer<D>(b2, sm.fq, gcol, g, i);
+      copy_b();   // last read in front of the barrier above
       float dy = 0.f;
 #pragma unroll
       for (int tb = 0; tb < 2; ++tb) {
@@ -820,7 +848,7 @@ template <int D> hipError_t backward(const BwdArgs& a, bool with_windowed, hipSt
     e = launch_walk<D, kQWalk>(a, blocks, band, sizeof(F32BwdSmem<D>), s);
   if (e == hipSuccess) e = launch_scan(bsums, heads, a.f32_nseg, kLinState<D>, a.causal ? 1 : 2, s);
   if (e == hipSuccess)
-    e = launch_walk<D, kKvWalk>(a, blocks, band, sizeof(F32BwdSmem<D>), s);
+    e = launch_walk<D, kKvWalk>(a, blocks, band, sizeof(F32BwdKvSmem<D>), s);
   return e;
 }
 
