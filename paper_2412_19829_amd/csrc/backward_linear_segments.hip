@@ -15,8 +15,10 @@
 // Wave w owns columns 16w..16w+15 of the carried sums as 16x16 accumulator tiles whose registers,
 // packed to bf16, are the operand of the read-out (v_mfma_f32_16x16x32_bf16, K = 32: tiles 2*kk and
 // 2*kk + 1 hold rows 32*kk + 8*g + 0..3 and + 4..7 of lane group g, which is that instruction's order
-// of k-slots).  So no copy of the sums goes through LDS, the tiles of a chunk are all a workgroup
-// needs there, and several workgroups share a compute unit and cover each other's barriers.
+// of k-slots).  So the sums go through LDS for one product alone, dv's, which wants B by value column (kept in registers in
+// both orders, updated twice a chunk: 149 against 147 us for a training step of 52 heads x 4096, and dv 2 to 6 % further from 64
+// bits); the tiles of a chunk are nearly all a workgroup needs there, and several workgroups share a compute unit and cover
+// each other's barriers.
 //
 // Head size 64.  Measured (us, the scans of backward_linear_mfma.hip and the sweeps of backward_bidir_mfma.hip
 // against these): causal, 52 heads x 4096 tokens, 103 + 99 -> 14 (sums) + 6 (scan) + 45 (dq) + 6 + 40 (dk, dv);
@@ -132,20 +134,12 @@ template <int R> __device__ __forceinline__ bf16x8 col8(const uint16_t* at) {
 }
 
 // Carried sum of wave w, element [feature][value] of the fp32 array in memory: tile 2*kk + y,
-// register r of lane (g, i) is row 32*kk + 8*g + 4*y + r of column 16*w + i, where the column is a
-// feature and the row a value (BY_VALUE = false) or the other way round.
-template <int D, bool BY_VALUE>
+// register r of lane (g, i) is value 32*kk + 8*g + 4*y + r of feature 16*w + i.
+template <int D>
 __device__ __forceinline__ void add_sum(f32x4 (&s)[D / 16], const float* src, int wave, int g, int i) {
 #pragma unroll
-  for (int x = 0; x < D / 16; ++x) {
-    const int row = 32 * (x / 2) + 8 * g + 4 * (x % 2), col = 16 * wave + i;
-    if constexpr (BY_VALUE) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) s[x][r] += src[(row + r) * D + col];
-    } else {
-      s[x] += *reinterpret_cast<const f32x4*>(src + col * D + row);
-    }
-  }
+  for (int x = 0; x < D / 16; ++x)
+    s[x] += *reinterpret_cast<const f32x4*>(src + (16 * wave + i) * D + 32 * (x / 2) + 8 * g + 4 * (x % 2));
 }
 template <int D> __device__ __forceinline__ void put_sum(const f32x4 (&s)[D / 16], float* dst, int wave, int g, int i) {
 #pragma unroll
@@ -378,7 +372,7 @@ __device__ __forceinline__ void seg_q(const BwdArgs& a, int block, unsigned char
     float z = 0.f;
     for (int j = first; j < end; ++j) {
       const float* src = a.ws_state + ((int64_t)s.head * a.lin_segments + j) * C::STATE;
-      add_sum<D, false>(as, src, wave, g, i);
+      add_sum<D>(as, src, wave, g, i);
       if (s.tid < D) z += src[D * D + s.tid];
     }
     if (s.tid < D) sm.z[s.tid] = z;
@@ -545,6 +539,7 @@ template <int D> struct SegKvSmem {
   using C = SegCfg<D>;
   uint16_t fq[SC * C::R], fk[SC * C::R], vv[SC * C::R], dd[SC * C::R];
   uint16_t sw[SC * WRW], wh[SC * WRW], wl[SC * WRW];   // S / den and the pair of T / den - c, [key][query]
+  uint16_t bt[D * C::R];                               // bf16 copy of B, [feature][value]
   float inv[SC], cc[SC];
   float y[D];
 };
@@ -577,21 +572,25 @@ __device__ __forceinline__ void seg_kv(const BwdArgs& a, int block, unsigned cha
   };
   const int last = s.begin + (s.total - 1) * SC;
   load(last);
-  f32x4 b1[C::XT], b2[C::XT];   // B, columns are features (for dk) and columns are values (for dv)
+  f32x4 b1[C::XT];   // B, columns are features: dk's operand; dv takes it by value column, from a copy in LDS
   clear<D>(b1);
-  clear<D>(b2);
   {
     int first = CAUSAL ? s.seg + 1 : 0, end = a.lin_segments;   // the segments behind, or their total
     if (a.lin_segments > kSegmentsInPlace) first = s.seg, end = s.seg + 1;
     float yz = 0.f;
     for (int j = first; j < end; ++j) {
       const float* src = a.ws_state + ((int64_t)(a.B * (a.H - a.H0) + s.head) * a.lin_segments + j) * C::STATE;
-      add_sum<D, false>(b1, src, wave, g, i);
-      add_sum<D, true>(b2, src, wave, g, i);
+      add_sum<D>(b1, src, wave, g, i);
       if (s.tid < D) yz += src[D * D + s.tid];
     }
     if (s.tid < D) sm.y[s.tid] = yz;
   }
+  auto copy_b = [&]() {
+#pragma unroll
+    for (int x = 0; x < C::XT; ++x)
+      put4(sm.bt + (16 * wave + i) * R + 32 * (x / 2) + 8 * g + 4 * (x % 2), b1[x][0], b1[x][1], b1[x][2], b1[x][3]);
+  };
+  copy_b();
   uint16_t* const piece_k = sm.fk + s.row * R + s.col;
   uint16_t* const piece_v = sm.vv + s.row * R + s.col;
   auto store_rows = [&](int t0, bool all) {
@@ -650,7 +649,12 @@ __device__ __forceinline__ void seg_kv(const BwdArgs& a, int block, unsigned cha
     f32x4 dka[2] = {-yc, -yc}, dva[2] = {kZeroF4, kZeroF4};
     read_out_pair<D>(dka, b1, sm.vv + s.row_at);
     __builtin_amdgcn_sched_barrier(0);
-    read_out<D>(dva, b2, sm.fk + s.row_at);
+#pragma unroll
+    for (int kk = 0; kk < C::KS; ++kk) {
+      const bf16x8 bv = col8<R>(sm.bt + 32 * kk * R + s.own_at);
+      dva[0] = mfma16(bv, row8(sm.fk + s.row_at, kk), dva[0]);
+      dva[1] = mfma16(bv, row8(sm.fk + s.row_at + 16 * R, kk), dva[1]);
+    }
     bf16x8 qcol, dcol;
     lds_barrier();   // weights visible; every row read of the phi(k) and v tiles is done
     if (CAUSAL) {
@@ -681,19 +685,16 @@ __device__ __forceinline__ void seg_kv(const BwdArgs& a, int block, unsigned cha
     if (CAUSAL) {
       const f32x4 i0 = lds4f(sm.inv + 8 * g), i1 = lds4f(sm.inv + 8 * g + 4);
       const f32x4 c0 = lds4f(sm.cc + 8 * g), c1 = lds4f(sm.cc + 8 * g + 4);
-      float qx[8], dx[8], dy = 0.f;
+      float qx[8], dy = 0.f;
       widen8(qcol, qx);
-      widen8(dcol, dx);
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        const float iv = j < 4 ? i0[j % 4] : i1[j % 4];
         dy = fmaf(j < 4 ? c0[j % 4] : c1[j % 4], qx[j], dy);
-        qx[j] *= iv;
-        dx[j] *= iv;
+        qx[j] *= j < 4 ? i0[j % 4] : i1[j % 4];
       }
       if constexpr (PAIR) add_outer_pair<D>(b1, sm.dd + s.wide_at, qx);
       else add_outer<D>(b1, sm.dd + s.wide_at, pack8(qx));
-      add_outer<D>(b2, sm.fq + s.wide_at, pack8(dx));
+      copy_b();   // last read in front of the barrier above
       dy = sum_over_groups(dy);
       if (g == 0) sm.y[16 * wave + i] += dy;   // read by this wave alone
     }
