@@ -23,8 +23,11 @@ template <int D> struct LbCfg {
   static constexpr int ZP = NT / D;                    // threads per column in the column sums
 };
 
+// elu(x) + 1 = max(x + 1, min(exp(x), 1)): the clamp rides on v_exp, and v_maximum3 lets a NaN through, which comes in
+// x + 1.  A comparison and a select instead: 839 against 829 us for the scans of 128 heads x 8192 x 128.
 __device__ __forceinline__ float phi_elu1(float x) {
-  return x > 0.f ? x + 1.f : __builtin_amdgcn_exp2f(x * kLog2e);
+  const float e = __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(x * kLog2e), 0.f, 1.f);
+  return __builtin_elementwise_maximum(x + 1.f, e);
 }
 template <bool ELU1> __device__ __forceinline__ u32x4 map8(u32x4 v) {
   if (!ELU1) return v;

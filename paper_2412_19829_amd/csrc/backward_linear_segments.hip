@@ -73,9 +73,11 @@ __device__ __forceinline__ float sum_over_groups(float x) {
 }
 __device__ __forceinline__ f32x4 lds4f(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
 
+// elu(x) + 1 = max(x + 1, min(exp(x), 1)): the clamp rides on v_exp, and v_maximum3 lets a NaN through, which comes in
+// x + 1.  A comparison and a select instead: 327.7 against 324.9 us for the backward pass of 208 heads x 4096.
 __device__ __forceinline__ float phi_elu1(float x) {
-  const float e = __builtin_amdgcn_exp2f(x * kLog2e);
-  return x > 0.f ? x + 1.f : e;
+  const float e = __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(x * kLog2e), 0.f, 1.f);
+  return __builtin_elementwise_maximum(x + 1.f, e);
 }
 template <bool ELU1> __device__ __forceinline__ u32x4 map8(u32x4 v) {
   if (!ELU1) return v;
