@@ -313,8 +313,8 @@ __global__ __launch_bounds__(LinCfg<D>::NT, 2) void linear_state_kernel(AttnArgs
 // 1 x 32 x 32768, window 512 (11, 57) 343 -> 346 / 342; 2 x 16 x 1000, window 128 42.7 -> 33.3 either way.
 // At d = 64, where three blocks share a unit, the kinds alternate in groups of 8 (one per XCD) where the query blocks are
 // half of the sums' chunks in tiles or more, so that every second unit takes one kind.  The layer, us, sums first and alternating:
-// 8 x (2 + 10) x 4096, window 256 63.2 and 62.3, two maps and 4 x (3 + 13) x 4096, 128 74.2 and 72.6, but (few tiles)
-// 1 x (2 + 14) x 16384, 128 48.2 and 52.4; d = 128, prefill of 2 x 32 x 3001 71.1 and 74.7.
+// 8 x (2 + 10) x 4096, window 256 63.2 and 62.3, but (few tiles) 1 x (2 + 14) x 16384, 128 48.2 and 52.4; d = 128, prefill of
+// 2 x 32 x 3001 71.1 and 74.7.
 enum StateOrder { kSumsFirst, kBlocksFirst, kAlternate };
 template <int D, bool ELU1>
 __global__ __launch_bounds__(kMfmaWindowThreads, D == 64 ? 3 : 2) void linear_state_windowed_kernel(AttnArgs a, int sums, int blocks, StateOrder order) {
@@ -417,7 +417,7 @@ __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, 
     // 2110 + 1750 with 820 of waiting, producers 1220 + 2400 with 1100; before it the layer of 8 x (2 + 10) x 4096 took 63.1 us
     // in place of 65.3, a training step of 4 x 16 x 4096 175.7 in place of 178.7.  d = 128 (consumers 1810 + 2270, producers
     // 1850 + 3040) waits for memory besides: before (a) the prefill of 2 x 32 x 3001 takes 73.0 us in place of 71.7.
-    constexpr bool V_FIRST = D == 64;
+    constexpr bool V_FIRST = D == 64 && ELU1;   // (nothing is mapped: 73.1 us for two maps and the layer of 4 x 16 x 4096, 73.6 before (a))
     int nl = 0, no = 0;  // chunks loaded / written so far
     auto load_q = [&](u32x4 (&qr)[C::PIECES]) { load_chunk<D>(qr, cl.hp.q, cl.t0(), N, qo); };
     auto load_v = [&](u32x4 (&vr)[C::PIECES]) {
@@ -879,6 +879,7 @@ __global__ __launch_bounds__(256, 2) void linear_main_windowed_kernel(AttnArgs a
 // key tiles of a query block's band
 int block_tiles(const AttnArgs& a) { return std::min((a.wleft + a.wright + BR - 1) / BC, (a.N - 1) / BC) + 1; }
 int state_blocks(const AttnArgs& a) { return a.n_pieces * a.state_sub - (a.causal ? 1 : 0); }
+int64_t query_block_count(const AttnArgs& a) { return (int64_t)((a.N + BR - 1) / BR) * a.H0 * a.B; }
 
 template <int D> hipError_t launch_state_t(const AttnArgs& a, bool with_windowed, hipStream_t s) {
   using C = LinCfg<D>;
@@ -943,18 +944,20 @@ template <bool CAUSAL, bool EMIT> hipError_t launch_main_windowed_t(const AttnAr
 
 }  // namespace
 
-static int64_t query_block_count(const AttnArgs& a) { return (int64_t)((a.N + BR - 1) / BR) * a.H0 * a.B; }
 static bool has_state_pass(const AttnArgs& a) {
   return a.H - a.H0 > 0 && a.N > 0 && a.B > 0 && a.ws_states && !(a.causal && a.n_pieces <= 1);
 }
 // The four-wave read-out, with the query blocks in its launch where a call allows that: d = 64, and hardly more pieces and
-// query blocks than units (or no state pass that could take the query blocks along).  Otherwise the eight-wave form, the query
+// query blocks than units, or features mapped beforehand (the staging waves have little to do then), or no state pass that could
+// take the query blocks along.  Otherwise the eight-wave form, the query
 // blocks in the state pass's launch.  The layer, us, four waves and eight, window 128: 1 x (2 + 10) heads x 2048 (112 blocks)
 // 20.0 and 21.2, x 512 13.0 and 15.6; 3 x (2 + 10) x 2048 (336) 26.5 and 26.9; 8 x (2 + 10) x 1024 (368) 26.3 and 25.5;
-// 1 x (2 + 14) x 16384 (480) 57.5 and 48.3; window 256, 8 x (2 + 10) x 4096 (752) 63.1 and 62.6; a training step of
-// 32 x (3 + 9) x 577 over all keys 123 and 116.
+// 1 x (2 + 14) x 16384 (480) 57.5 and 48.3; window 256, 8 x (2 + 10) x 4096 (752) 63.1 and 62.0; a training step of
+// 32 x (3 + 9) x 577 over all keys 123 and 116.  Mapped beforehand (with the two maps): 4 x (3 + 13) x 4096 72.7 and 73.2,
+// 1 x (3 + 13) x 16384 75.9 and 77.4, 2 x (3 + 13) x 9000, window 300 81.3 and 85.3, 4 x (8 + 8) x 4096 71.7 and 70.1.
 static bool four_waves(const AttnArgs& a) {
-  return a.d == 64 && a.H0 > 0 && (3 * (a.n_pieces + query_block_count(a)) <= 4 * device_compute_units() || !has_state_pass(a));
+  return a.d == 64 && a.H0 > 0 &&
+         (a.phi != 0 || 3 * (a.n_pieces + query_block_count(a)) <= 4 * device_compute_units() || !has_state_pass(a));
 }
 bool linear_main_takes_windowed(const AttnArgs& a) {
   return four_waves(a) && a.H0 < a.H && a.n_pieces > 0 && a.scale >= 0.f && a.n_pieces + query_block_count(a) < (1 << 22);
