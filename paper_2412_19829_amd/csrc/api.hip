@@ -395,6 +395,16 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
   pl.state_blocks = (int)mid;
   const uint64_t slots = mid > 0 ? (uint64_t)pieces * ((uint64_t)d * d + d) * sizeof(float) : 0;
   r->needed = slots * sub;
+  if (!r->general_chunk) {
+    float sums;   // stands for the workspace: there is one or not
+    AttnArgs a;
+    memset(&a, 0, sizeof(a));
+    a.B = B; a.H = H; a.N = N; a.d = d; a.H0 = H0; a.phi = p->phi;
+    a.causal = p->bidirectional ? 0 : 1;
+    a.n_pieces = (int)pieces;
+    a.ws_states = r->needed > 0 ? &sums : nullptr;
+    pl.linear_threads = linear_main_threads(a);
+  }
   pl.workspace_bytes = slots * (most_sub > 0 ? most_sub : sub);
   return GF_OK;
 }

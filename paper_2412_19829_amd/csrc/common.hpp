@@ -173,6 +173,7 @@ hipError_t launch_windowed_stream(const AttnArgs& a, hipStream_t s);
 bool linear_state_takes_windowed(const AttnArgs& a);
 hipError_t launch_linear_state_mfma(const AttnArgs& a, bool with_windowed, hipStream_t s);
 hipError_t launch_linear_main_mfma(const AttnArgs& a, hipStream_t s);
+int linear_main_threads(const AttnArgs& a);   // of a read-out's workgroup
 // The read-out and the windowed heads' query blocks in one launch, where the former takes them along.
 bool linear_main_takes_windowed(const AttnArgs& a);
 hipError_t launch_linear_main_windowed_mfma(const AttnArgs& a, hipStream_t s);

@@ -959,6 +959,7 @@ static bool four_waves(const AttnArgs& a) {
   return a.d == 64 && a.H0 > 0 &&
          (a.phi != 0 || 3 * (a.n_pieces + query_block_count(a)) <= 4 * device_compute_units() || !has_state_pass(a));
 }
+int linear_main_threads(const AttnArgs& a) { return a.d == 128 ? MainCfg<128, 1>::NT : four_waves(a) ? MainCfg<64, 1>::NT : MainCfg<64, 2>::NT; }
 bool linear_main_takes_windowed(const AttnArgs& a) {
   return four_waves(a) && a.H0 < a.H && a.n_pieces > 0 && a.scale >= 0.f && a.n_pieces + query_block_count(a) < (1 << 22);
 }

@@ -11,6 +11,18 @@ from tests.gpu_util import run_gpu, to_device
 from tests.test_gpu_parity import check, synth
 
 
+# B, H, N, window, H0, identity map, threads of a read-out's workgroup
+@pytest.mark.parametrize("case", [
+    (1, 12, 2048, 128, 2, 0, 256), (3, 12, 2048, 128, 2, 0, 256), (8, 12, 1024, 128, 2, 0, 512), (8, 12, 4096, 256, 2, 0, 512),
+    (8, 12, 4096, 256, 0, 0, 512), (4, 16, 4096, 128, 3, 1, 256), (1, 2, 10, 4, 1, 0, 256),
+], ids=lambda c: "x".join(map(str, c)))
+def test_plan(case):
+    B, H, N, w, H0, identity, threads = case
+    phi = gb.GF_PHI_IDENTITY if identity else gb.GF_PHI_ELU1
+    st, pl = gb.gformer_attn_plan(B, H, N, 64, w, gb.make_params(n_sparse_heads=H0, phi=phi))
+    assert st == gb.GF_OK and pl.linear_threads == threads
+
+
 # B, H, N, options; every head linear
 @pytest.mark.gpu
 @pytest.mark.parametrize("case", [
