@@ -11,8 +11,9 @@
 // whole sequence on a part of the chip.
 //
 // Measured, B=4, 52 linear heads, N=2048, d=64, eight segments a head and no scan of their sums (plain-FMA kernels ->
-// these, us): forward 1017 -> 18 (sums) + 48, backward 859 + 1558 -> 18 + 71 + 75.  The bound is the SIMDs' issue: the
-// matrix core is busy 32 % of the forward walk's time (33 and 42 % of the others'), the vector unit 22 % (24 and 19 %)
+// these, us): forward 1017 -> 18 (sums) + 48, backward 859 + 1558 -> 18 + 71 + 68.  The bound is the SIMDs' issue: the
+// matrix core is busy 32 % of the forward walk's time (33 % of the dq walk's, 42 % of the last while it summed B twice, in 75
+// us), the vector unit 22 % (24 and 19 %)
 // at four cycles an instruction, hardly ever both; with two workgroups a unit the barriers between a chunk's steps
 // leave the rest.
 //
@@ -623,7 +624,8 @@ __device__ __forceinline__ void linear_bwd_q_f32(const BwdArgs& a, int block, un
 // ---- backward, reverse walk: dk and dv -----------------------------------------------------------
 // B is an operand by feature column (dk) and by value column (dv).  Accumulated in both orders it took a fifth of the
 // walk's matrix instructions twice, and twice the loads of the sums it starts from; now the waves keep it by feature column and
-// leave a copy, turned, in LDS.
+// leave a copy, turned, in LDS.  A training step, us, before and after: 4 x (3 + 13) x 2048 x 64 266.5 and 260.0, 4 x 16 x
+// 1024 x 128 540 and 517.
 template <int D> struct F32BwdKvSmem : F32BwdSmem<D> {
   float b[D * kF32Row<D>];           // [value][feature], row v rotated by 16 * (v / 16) floats: writes and reads miss each other's banks
 };
