@@ -32,10 +32,11 @@ template <int D> struct LinCfg {
   static constexpr int STATE = D * D + D;     // floats per (A, Z) state
 };
 
-// phi(x) = elu(x) + 1 = max(x + 1, min(exp(x), 1))   (section II-B); the clamp rides on v_exp
+// phi(x) = elu(x) + 1 = max(x + 1, min(exp(x), 1))   (section II-B); the clamp rides on v_exp, and the maximum is the one
+// that lets a NaN through, which comes in x + 1 (fmaxf takes the other operand and made a finite feature of it)
 __device__ __forceinline__ float elu1(float x) {
   const float e = __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(x * kLog2e), 0.0f, 1.0f);
-  return fmaxf(x + 1.0f, e);
+  return __builtin_elementwise_maximum(x + 1.0f, e);
 }
 
 // Feature map on 8 packed bf16 values (ELU1 = true: phi(x) = elu(x)+1; false: identity).
