@@ -12,7 +12,7 @@
 
 namespace gformer {
 
-int mfma_linear_threads(int d) { return d == 128 ? 512 : 256; }
+int mfma_linear_threads(int d, int query_halves) { return d == 128 ? 512 : 256 * query_halves; }
 
 // Compute units of the current device, asked once per device; a process without a device (the
 // planner is host arithmetic and is also called there) plans for an MI355X.
@@ -39,7 +39,7 @@ namespace {
 struct Resolved {
   gformer_plan plan;
   int64_t qs[3], ks[3], vs[3], os[3];
-  int cph, vcph, piece_chunks, state_sub;
+  int cph, vcph, piece_chunks, state_sub, query_halves;
   bool stream;   // MFMA path: the windowed heads go to the streaming kernel
   bool general_chunk;  // MFMA path, causal: the linear read-out goes to the general-chunk kernel
   bool f32;            // single precision on the matrix cores
@@ -192,6 +192,19 @@ long short_piece(long heads, long cph, long cus, int d) {
   if (per > 8 && piece < 4) piece = 4;
   else if (piece < 3 && heads * per > cus / 2) piece = 3;
   return piece;
+}
+
+// d = 64: whether the read-out's workgroup splits a chunk's queries over twice the waves (MainCfg, linear_mfma.hip).  With four
+// waves the windowed heads' query blocks ride in its launch where a call allows that, with eight in the state pass's.  Four:
+// hardly more pieces and query blocks than units, or features mapped beforehand (the staging waves have little to do
+// then), or no state pass that could take the query blocks along.  The layer, us, four waves and eight, window 128:
+// 1 x (2 + 10) heads x 2048 (112 blocks)
+// 20.0 and 21.2, x 512 13.0 and 15.6; 3 x (2 + 10) x 2048 (336) 26.5 and 26.9; 8 x (2 + 10) x 1024 (368) 26.3 and 25.5;
+// 1 x (2 + 14) x 16384 (480) 57.5 and 48.3; window 256, 8 x (2 + 10) x 4096 (752) 63.1 and 62.0; a training step of
+// 32 x (3 + 9) x 577 over all keys 123 and 116.  Mapped beforehand (with the two maps): 4 x (3 + 13) x 4096 72.7 and 73.2,
+// 1 x (3 + 13) x 16384 75.9 and 77.4, 2 x (3 + 13) x 9000, window 300 81.3 and 85.3, 4 x (8 + 8) x 4096 71.7 and 70.1.
+bool halves_apart(int H0, int phi, long pieces, long query_blocks, bool state_pass, long cus) {
+  return H0 == 0 || (phi == GF_PHI_ELU1 && 3 * (pieces + query_blocks) > 4 * cus && state_pass);
 }
 
 // Shared by gformer_attn_plan, gformer_attn_workspace_bytes and gformer_attn_fwd.
@@ -390,21 +403,12 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
   r->state_sub = (int)sub;
   pl.segment_len = (int)(piece * kStrip);
   pl.n_segments = (int)pieces;
-  pl.linear_threads = mfma_linear_threads(d);
+  r->query_halves = d == 64 && halves_apart(H0, p->phi, pieces, query_blocks, mid > 0, kComputeUnits) ? 2 : 1;
+  pl.linear_threads = mfma_linear_threads(d, r->general_chunk ? 1 : r->query_halves);
   pl.linear_blocks = (int)pieces;
   pl.state_blocks = (int)mid;
   const uint64_t slots = mid > 0 ? (uint64_t)pieces * ((uint64_t)d * d + d) * sizeof(float) : 0;
   r->needed = slots * sub;
-  if (!r->general_chunk) {
-    float sums;   // stands for the workspace: there is one or not
-    AttnArgs a;
-    memset(&a, 0, sizeof(a));
-    a.B = B; a.H = H; a.N = N; a.d = d; a.H0 = H0; a.phi = p->phi;
-    a.causal = p->bidirectional ? 0 : 1;
-    a.n_pieces = (int)pieces;
-    a.ws_states = r->needed > 0 ? &sums : nullptr;
-    pl.linear_threads = linear_main_threads(a);
-  }
   pl.workspace_bytes = slots * (most_sub > 0 ? most_sub : sub);
   return GF_OK;
 }
@@ -504,6 +508,7 @@ gf_status attn_forward(const void* q, const void* k, const void* v, void* out, v
   a.piece_chunks = r.piece_chunks;
   a.n_pieces = r.plan.n_segments;
   a.state_sub = r.state_sub;
+  a.query_halves = r.query_halves;
   a.f32_seg_len = r.f32_seg_len;
   a.f32_nseg = r.f32_nseg;
   a.ws_states = r.needed > 0 ? reinterpret_cast<float*>(workspace) : nullptr;

@@ -37,6 +37,7 @@ struct AttnArgs {
   int piece_chunks;  // chunks per piece
   int n_pieces;      // pieces = workgroups of the read-out kernel
   int state_sub;     // the state pass cuts every piece into this many equal sub-pieces (1, 2 or 4)
+  int query_halves;  // the read-out's matrix waves, in sets: 2 (d = 64) where they split a chunk's queries
   float* final_state; // optional [B*(H-H0), d*d + d] fp32: every linear head's (A, Z) after its last
                      // token, A row-major [feature][value] (what the decode step carries on from)
   void *kring, *vring; // optional [B, H0, window, d] rings: the last `window` keys / values of every
@@ -173,7 +174,6 @@ hipError_t launch_windowed_stream(const AttnArgs& a, hipStream_t s);
 bool linear_state_takes_windowed(const AttnArgs& a);
 hipError_t launch_linear_state_mfma(const AttnArgs& a, bool with_windowed, hipStream_t s);
 hipError_t launch_linear_main_mfma(const AttnArgs& a, hipStream_t s);
-int linear_main_threads(const AttnArgs& a);   // of a read-out's workgroup
 // The read-out and the windowed heads' query blocks in one launch, where the former takes them along.
 bool linear_main_takes_windowed(const AttnArgs& a);
 hipError_t launch_linear_main_windowed_mfma(const AttnArgs& a, hipStream_t s);
@@ -224,7 +224,7 @@ constexpr int kScalarWindowRows = 16;   // query rows per workgroup, scalar wind
 constexpr int kScalarThreads = 256;
 constexpr int kMfmaWindowRows = 128;    // query rows per workgroup, MFMA windowed kernel
 constexpr int kMfmaWindowThreads = 256;
-int mfma_linear_threads(int d);
+int mfma_linear_threads(int d, int query_halves);   // of a read-out's workgroup
 int device_compute_units();   // of the current device; 256 (MI355X) in a process without one
 
 }  // namespace gformer

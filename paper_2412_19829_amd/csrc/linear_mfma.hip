@@ -947,21 +947,8 @@ template <bool CAUSAL, bool EMIT> hipError_t launch_main_windowed_t(const AttnAr
 static bool has_state_pass(const AttnArgs& a) {
   return a.H - a.H0 > 0 && a.N > 0 && a.B > 0 && a.ws_states && !(a.causal && a.n_pieces <= 1);
 }
-// The four-wave read-out, with the query blocks in its launch where a call allows that: d = 64, and hardly more pieces and
-// query blocks than units, or features mapped beforehand (the staging waves have little to do then), or no state pass that could
-// take the query blocks along.  Otherwise the eight-wave form, the query
-// blocks in the state pass's launch.  The layer, us, four waves and eight, window 128: 1 x (2 + 10) heads x 2048 (112 blocks)
-// 20.0 and 21.2, x 512 13.0 and 15.6; 3 x (2 + 10) x 2048 (336) 26.5 and 26.9; 8 x (2 + 10) x 1024 (368) 26.3 and 25.5;
-// 1 x (2 + 14) x 16384 (480) 57.5 and 48.3; window 256, 8 x (2 + 10) x 4096 (752) 63.1 and 62.0; a training step of
-// 32 x (3 + 9) x 577 over all keys 123 and 116.  Mapped beforehand (with the two maps): 4 x (3 + 13) x 4096 72.7 and 73.2,
-// 1 x (3 + 13) x 16384 75.9 and 77.4, 2 x (3 + 13) x 9000, window 300 81.3 and 85.3, 4 x (8 + 8) x 4096 71.7 and 70.1.
-static bool four_waves(const AttnArgs& a) {
-  return a.d == 64 && a.H0 > 0 &&
-         (a.phi != 0 || 3 * (a.n_pieces + query_block_count(a)) <= 4 * device_compute_units() || !has_state_pass(a));
-}
-int linear_main_threads(const AttnArgs& a) { return a.d == 128 ? MainCfg<128, 1>::NT : four_waves(a) ? MainCfg<64, 1>::NT : MainCfg<64, 2>::NT; }
 bool linear_main_takes_windowed(const AttnArgs& a) {
-  return four_waves(a) && a.H0 < a.H && a.n_pieces > 0 && a.scale >= 0.f && a.n_pieces + query_block_count(a) < (1 << 22);
+  return a.d == 64 && a.query_halves == 1 && a.H0 > 0 && a.H0 < a.H && a.n_pieces > 0 && a.scale >= 0.f && a.n_pieces + query_block_count(a) < (1 << 22);
 }
 hipError_t launch_linear_main_windowed_mfma(const AttnArgs& a, hipStream_t s) {
   if (!a.causal) return launch_main_windowed_t<false, false>(a, s);
@@ -975,7 +962,7 @@ hipError_t launch_linear_main_windowed_mfma(const AttnArgs& a, hipStream_t s) {
 // 1 150.1 and 149.4 (32, 0.05); 2 x 32 x 12000, 300, 4 214.0 and 220.4 (47, 0.5); 4 x 32 x 7800, 512, 4 272.8 and 276.4 (61,
 // 0.7); 2 x 32 x 8700, 64, 1 155.2 and 157.4 (17, 0.05); 1 x 16 x 32000, 64, 1 159.7 and 159.2 (30, 0.1).
 bool linear_state_takes_windowed(const AttnArgs& a) {
-  if (a.H0 <= 0 || !has_state_pass(a) || a.scale < 0.f || four_waves(a)) return false;
+  if (a.H0 <= 0 || !has_state_pass(a) || a.scale < 0.f || (a.d == 64 && a.query_halves == 1)) return false;
   const int64_t query_blocks = query_block_count(a);
   if (a.piece_chunks / a.state_sub > 30 && 3 * query_blocks * block_tiles(a) < (int64_t)a.B * (a.H - a.H0) * a.cph) return false;
   return (int64_t)a.n_pieces * a.state_sub + query_blocks < (1 << 22);
@@ -988,7 +975,7 @@ hipError_t launch_linear_state_mfma(const AttnArgs& a, bool with_windowed, hipSt
 hipError_t launch_linear_main_mfma(const AttnArgs& a, hipStream_t s) {
   if (a.H - a.H0 <= 0 || a.N <= 0 || a.B <= 0 || a.n_pieces <= 0) return hipSuccess;
   if (a.d == 128) return launch_main_t<128, 1>(a, s);
-  return four_waves(a) ? launch_main_t<64, 1>(a, s) : launch_main_t<64, 2>(a, s);
+  return a.query_halves == 1 ? launch_main_t<64, 1>(a, s) : launch_main_t<64, 2>(a, s);
 }
 
 }  // namespace gformer
