@@ -168,7 +168,7 @@ long aligned_piece(long heads_lin, long cph, long kComputeUnits) {
 // shorter than eight chunks, trade the former for the latter.  Whole layer, us, pieces of eight
 // against these:  d = 64, linear heads x chunks:  10x8 18.2 / 13.0 (2 chunks a piece), 10x16 24.8 / 14.9
 // (2), 10x32 26.0 / 20.5 (4), 10x64 34.7 / 28.8 (4), 26x16 25.5 / 17.4 (3), 52x16 26.7 / 22.4 (4), 100x10
-// 26.9 / 21.1 (5), 300x5 27.9 / 18.1 (5: a whole head, no carried sums at all).  d = 128, where a sum is
+// 26.9 / 21.1 (5), 300x5 27.9 / 18.1 (5: a whole head, no carried sums at all; 17.6 in the present build).  d = 128, where a sum is
 // four times as large and a compute unit holds one piece: 10x8 33.0 / 30.6 (2), 10x16 42.8 / 38.1 (4),
 // 10x64 61.8 / 55.1 (4), 26x32 60.9 / 54.8 (6), 52x10 47.8 / 40.4 (5).  Two-chunk pieces lose where they crowd the chip
 // (the present build, pieces of two, three, four: 26x16 18.9, 17.8, 19.5; 52x16 25.6, 25.1, 21.0).  That a head gets no more
@@ -196,14 +196,19 @@ long short_piece(long heads, long cph, long cus, int d) {
 
 // d = 64: whether the read-out's workgroup splits a chunk's queries over twice the waves (MainCfg, linear_mfma.hip).  With four
 // waves the windowed heads' query blocks ride in its launch where a call allows that, with eight in the state pass's.  Four:
-// hardly more pieces and query blocks than units, or features mapped beforehand (the staging waves have little to do
-// then), or no state pass that could take the query blocks along.  The layer, us, four waves and eight, window 128:
-// 1 x (2 + 10) heads x 2048 (112 blocks)
-// 20.0 and 21.2, x 512 13.0 and 15.6; 3 x (2 + 10) x 2048 (336) 26.5 and 26.9; 8 x (2 + 10) x 1024 (368) 26.3 and 25.5;
-// 1 x (2 + 14) x 16384 (480) 57.5 and 48.3; window 256, 8 x (2 + 10) x 4096 (752) 63.1 and 62.0; a training step of
-// 32 x (3 + 9) x 577 over all keys 123 and 116.  Mapped beforehand (with the two maps): 4 x (3 + 13) x 4096 72.7 and 73.2,
-// 1 x (3 + 13) x 16384 75.9 and 77.4, 2 x (3 + 13) x 9000, window 300 81.3 and 85.3, 4 x (8 + 8) x 4096 71.7 and 70.1.
-bool halves_apart(int H0, int phi, long pieces, long query_blocks, bool state_pass, long cus) {
+// * more causal pieces than units: of four waves a unit holds two workgroups, of eight one, and the pieces take two rounds.
+//   All heads linear, us, four waves and eight: 257 x 320 16.6 and 19.2, 300 x 512 24.8 and 28.2, 384 x 400 22.1 and 25.2,
+//   512 x 512 28.2 and 31.8, segments of 64 tokens 4 x 12 x 4096 77.7 and 94.0, of 512 1 x 48 x 4096 47.3 and 54.2 (256 x
+//   400 16.2 and 14.6, 230 x 512 18.1 and 16.1).  Over all keys, where a chunk is short, they are level: 384 x 577 35.3 and 34.7.
+// * windowed heads beside them and hardly more pieces and query blocks than units, or features mapped beforehand (the
+//   staging waves have little to do then), or no state pass that could take the query blocks along.  The layer, us, four waves
+//   and eight, window 128: 1 x (2 + 10) heads x 2048 (112 blocks)
+//   20.0 and 21.2, x 512 13.0 and 15.6; 3 x (2 + 10) x 2048 (336) 26.5 and 26.9; 8 x (2 + 10) x 1024 (368) 26.3 and 25.5;
+//   1 x (2 + 14) x 16384 (480) 57.5 and 48.3; window 256, 8 x (2 + 10) x 4096 (752) 63.1 and 62.0; a training step of
+//   32 x (3 + 9) x 577 over all keys 123 and 116.  Mapped beforehand (with the two maps): 4 x (3 + 13) x 4096 72.7 and 73.2,
+//   1 x (3 + 13) x 16384 75.9 and 77.4, 2 x (3 + 13) x 9000, window 300 81.3 and 85.3, 4 x (8 + 8) x 4096 71.7 and 70.1.
+bool halves_apart(bool causal, int H0, int phi, long pieces, long query_blocks, bool state_pass, long cus) {
+  if (causal && pieces > cus) return false;
   return H0 == 0 || (phi == GF_PHI_ELU1 && 3 * (pieces + query_blocks) > 4 * cus && state_pass);
 }
 
@@ -403,7 +408,7 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
   r->state_sub = (int)sub;
   pl.segment_len = (int)(piece * kStrip);
   pl.n_segments = (int)pieces;
-  r->query_halves = d == 64 && halves_apart(H0, p->phi, pieces, query_blocks, mid > 0, kComputeUnits) ? 2 : 1;
+  r->query_halves = d == 64 && halves_apart(!p->bidirectional, H0, p->phi, pieces, query_blocks, mid > 0, kComputeUnits) ? 2 : 1;
   pl.linear_threads = mfma_linear_threads(d, r->general_chunk ? 1 : r->query_halves);
   pl.linear_blocks = (int)pieces;
   pl.state_blocks = (int)mid;

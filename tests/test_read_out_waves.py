@@ -23,11 +23,24 @@ def test_plan(case):
     assert st == gb.GF_OK and pl.linear_threads == threads
 
 
+# more causal pieces than units: B, H, N, H0, options, pieces, threads
+@pytest.mark.parametrize("case", [
+    (32, 12, 400, 0, {}, 384, 256), (1, 257, 320, 0, {}, 257, 256), (16, 16, 400, 0, {}, 256, 512), (1, 12, 4096, 0, {"segment_len": 64}, 768, 256),
+    (4, 12, 4096, 2, {"segment_len": 64}, 2560, 256), (1, 300, 256, 0, {"phi": gb.GF_PHI_IDENTITY}, 300, 256),
+    (32, 12, 577, 0, {"bidirectional": 1}, 384, 512),
+], ids=lambda c: "x".join(map(str, c[:4])) + "".join(f"-{k}" for k in c[4]))
+def test_plan_of_more_pieces_than_units(case):
+    B, H, N, H0, kw, pieces, threads = case
+    st, pl = gb.gformer_attn_plan(B, H, N, 64, 16, gb.make_params(n_sparse_heads=H0, **kw))
+    assert st == gb.GF_OK and (pl.n_segments, pl.linear_threads) == (pieces, threads)
+
+
 # B, H, N, options; every head linear
 @pytest.mark.gpu
 @pytest.mark.parametrize("case", [
     (1, 2, 1, {}), (1, 3, 31, {}), (1, 3, 33, {}), (2, 3, 64, {}), (1, 3, 65, {}), (3, 5, 97, {}), (1, 40, 777, {}),
     (7, 40, 150, {}),                     # more heads than units: pieces straddle heads
+    (1, 260, 197, {}), (2, 12, 1000, {"segment_len": 64}),   # more pieces than units
     (1, 3, 1055, {"eps": 0.5}), (1, 3, 1000, {"segment_len": 64}), (2, 4, 577, {"bidirectional": 1}), (1, 1, 33, {"bidirectional": 1}),
 ], ids=lambda c: "x".join(map(str, c[:3])) + "".join(f"-{k}" for k in c[3]))
 def test_against_oracle(case):
@@ -42,7 +55,7 @@ def test_against_oracle(case):
 @pytest.mark.parametrize("case", [
     (3, 12, 2048, 128, 2, {}), (8, 12, 1000, 128, 2, {}), (4, 40, 777, 64, 20, {}), (2, 12, 4100, 300, 4, {}),
     (16, 12, 577, 64, 3, {"bidirectional": 1}), (8, 12, 1000, 50, 2, {"phi": gb.GF_PHI_IDENTITY}),
-    (8, 12, 1000, 50, 2, {"softmax_scale": -0.5}),
+    (8, 12, 1000, 50, 2, {"softmax_scale": -0.5}), (2, 16, 1000, 50, 2, {"segment_len": 64}),
 ], ids=lambda c: "x".join(map(str, c[:5])) + "".join(f"-{k}" for k in c[5]))
 def test_one_launch_gives_the_bits_of_two(case):
     import torch
