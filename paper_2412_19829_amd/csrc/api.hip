@@ -194,22 +194,36 @@ long short_piece(long heads, long cph, long cus, int d) {
   return piece;
 }
 
-// d = 64: whether the read-out's workgroup splits a chunk's queries over twice the waves (MainCfg, linear_mfma.hip).  With four
-// waves the windowed heads' query blocks ride in its launch where a call allows that, with eight in the state pass's.  Four:
+// d = 64: whether the read-out's workgroup splits a chunk's queries over twice the waves (MainCfg, linear_mfma.hip), which makes
+// a chunk shorter and a carried sum, which every set of waves loads, dearer.  Figures are us, four waves and eight.  Four waves:
+// * pieces of one chunk, and pieces of up to four that start from more sums than they have chunks.  1 x 12 x 1024 (2 chunks, 7
+//   sums) 14.7 and 15.6, x 512 (2, 3) 12.0 and 12.3, x 2048 (4, 7) 19.7 and 20.3, over all keys 1 x 12 x 512 (1, 8) 11.9 and
+//   14.5; but 4 x 12 x 512 (3, 2) 15.9 and 15.0, 1 x 8 x 686 (3, 3) 14.4 and 13.6, 1 x 12 x 4096 (4, 1: scanned) 24.7 and 23.5.
 // * more causal pieces than units: of four waves a unit holds two workgroups, of eight one, and the pieces take two rounds.
-//   All heads linear, us, four waves and eight: 257 x 320 16.6 and 19.2, 300 x 512 24.8 and 28.2, 384 x 400 22.1 and 25.2,
+//   All heads linear: 257 x 320 16.6 and 19.2, 300 x 512 24.8 and 28.2, 384 x 400 22.1 and 25.2,
 //   512 x 512 28.2 and 31.8, segments of 64 tokens 4 x 12 x 4096 77.7 and 94.0, of 512 1 x 48 x 4096 47.3 and 54.2 (256 x
-//   400 16.2 and 14.6, 230 x 512 18.1 and 16.1).  Over all keys, where a chunk is short, they are level: 384 x 577 35.3 and 34.7.
-// * windowed heads beside them and hardly more pieces and query blocks than units, or features mapped beforehand (the
-//   staging waves have little to do then), or no state pass that could take the query blocks along.  The layer, us, four waves
-//   and eight, window 128: 1 x (2 + 10) heads x 2048 (112 blocks)
+//   400 16.2 and 14.6, 230 x 512 18.1 and 16.1).
+// * over all keys, where a chunk is short: two to three pieces a unit (600 x 200 28.0 and 28.3; 384 x 577 35.3 and 34.7), and
+//   features mapped beforehand, which leave nothing to hide (8 x 12 x 1000 19.0 and 19.5, 2 x 12 x 1325 15.7 and 18.2, but 3 x 8 x
+//   31024 79.4 and 78.1; causal the staging still counts: 16 x 16 x 1024 30.4 and 26.3, 1 x 32 x 16384 87.6 and 79.1).
+// * windowed heads whose query blocks share a launch (with four waves the read-out's, with eight the state pass's) and hardly
+//   more pieces and query blocks than units, or features mapped beforehand (the
+//   staging waves have little to do then), or no state pass that could take the query blocks along.  The layer,
+//   window 128: 1 x (2 + 10) heads x 2048 (112 blocks)
 //   20.0 and 21.2, x 512 13.0 and 15.6; 3 x (2 + 10) x 2048 (336) 26.5 and 26.9; 8 x (2 + 10) x 1024 (368) 26.3 and 25.5;
 //   1 x (2 + 14) x 16384 (480) 57.5 and 48.3; window 256, 8 x (2 + 10) x 4096 (752) 63.1 and 62.0; a training step of
 //   32 x (3 + 9) x 577 over all keys 123 and 116.  Mapped beforehand (with the two maps): 4 x (3 + 13) x 4096 72.7 and 73.2,
 //   1 x (3 + 13) x 16384 75.9 and 77.4, 2 x (3 + 13) x 9000, window 300 81.3 and 85.3, 4 x (8 + 8) x 4096 71.7 and 70.1.
-bool halves_apart(bool causal, int H0, int phi, long pieces, long query_blocks, bool state_pass, long cus) {
-  if (causal && pieces > cus) return false;
-  return H0 == 0 || (phi == GF_PHI_ELU1 && 3 * (pieces + query_blocks) > 4 * cus && state_pass);
+struct ReadOutCut {
+  bool causal, mapped;   // mapped: features mapped beforehand
+  long pieces, chunks;   // chunks of a piece
+  long sums;             // carried sums a piece starts from, at most
+  long query_blocks;     // of the windowed heads, where they can share a launch
+};
+bool halves_apart(const ReadOutCut& c, long cus) {
+  if (c.chunks == 1 || (c.chunks <= 4 && c.sums > c.chunks)) return false;
+  if (c.causal ? c.pieces > cus : c.mapped || (c.pieces > 2 * cus && c.pieces <= 3 * cus)) return false;
+  return c.query_blocks == 0 || (!c.mapped && c.sums > 0 && 3 * (c.pieces + c.query_blocks) > 4 * cus);
 }
 
 // Shared by gformer_attn_plan, gformer_attn_workspace_bytes and gformer_attn_fwd.
@@ -408,7 +422,13 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
   r->state_sub = (int)sub;
   pl.segment_len = (int)(piece * kStrip);
   pl.n_segments = (int)pieces;
-  r->query_halves = d == 64 && halves_apart(!p->bidirectional, H0, p->phi, pieces, query_blocks, mid > 0, kComputeUnits) ? 2 : 1;
+  r->query_halves = 1;
+  if (d == 64 && pieces > 0) {
+    long sums = mid > 0 ? sums_to_add(!p->bidirectional, (int)vcph, (int)piece, (int)(piece / sub)) : 0;
+    if (mid > 0 && (sums == 0 || sums > sums_in_place(d))) sums = 1;   // scanned beforehand, where there are many
+    const ReadOutCut c{!p->bidirectional, p->phi != GF_PHI_ELU1, pieces, piece, sums, r->stream ? 0 : query_blocks};
+    if (halves_apart(c, kComputeUnits)) r->query_halves = 2;
+  }
   pl.linear_threads = mfma_linear_threads(d, r->general_chunk ? 1 : r->query_halves);
   pl.linear_blocks = (int)pieces;
   pl.state_blocks = (int)mid;

@@ -52,17 +52,19 @@ struct AttnArgs {
                      // before global chunk j*piece_chunks/state_sub (piece p reads slot p*state_sub)
 };
 
+// Sub-piece sums of `ls` chunks that a piece of `piece` chunks starts from, at most (0 for one where heads are no longer than `ls`).
+__host__ __device__ inline int sums_to_add(bool causal, int vcph, int piece, int ls) {
+  if (!causal) return vcph / ls;   // every piece adds up its whole head
+  // a causal piece adds up the sub-pieces in front of it inside its head; the latest start is
+  // the head's last piece when pieces never straddle heads, else the head's last chunk
+  return (vcph % piece == 0 ? vcph - piece : vcph - 1) / ls;
+}
 // With few carried boundaries per head the read-out kernel adds up the per-sub-piece sums
 // itself (independent loads, no extra launch); with many, a prefix kernel runs first and the
 // read-out kernel reads a single slot.
+__host__ __device__ inline int sums_in_place(int d) { return d == 64 ? 8 : 6; }   // sums of 16 KB and of 66 KB
 __host__ __device__ inline bool uses_prefix_kernel(const AttnArgs& a) {
-  const int ls = a.piece_chunks / a.state_sub;
-  const int most = a.d == 64 ? 8 : 6;   // sums of 16 KB and of 66 KB
-  if (!a.causal) return a.vcph / ls > most;   // every piece adds up its whole head
-  // a causal piece adds up the sub-pieces in front of it inside its head; the latest start is
-  // the head's last piece when pieces never straddle heads, else the head's last chunk
-  const int last_start = a.vcph % a.piece_chunks == 0 ? a.vcph - a.piece_chunks : a.vcph - 1;
-  return last_start / ls > most;
+  return sums_to_add(a.causal, a.vcph, a.piece_chunks, a.piece_chunks / a.state_sub) > sums_in_place(a.d);
 }
 
 // bf16 storage helpers (round to nearest even on store).

@@ -926,7 +926,8 @@ template <int D, int QS> hipError_t launch_main_t(const AttnArgs& a, hipStream_t
     else launch(linear_main_kernel<D, QS, false, true, false>);
   } else {
     if (a.phi == 0) launch(linear_main_kernel<D, QS, true, false, false>);
-    else launch(linear_main_kernel<D, QS, false, false, false>);
+    else if constexpr (QS == 1) launch(linear_main_kernel<D, QS, false, false, false>);
+    else e = hipErrorInvalidValue;   // the planner keeps four waves there
   }
   return e != hipSuccess ? e : hipGetLastError();
 }

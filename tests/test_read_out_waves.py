@@ -35,6 +35,21 @@ def test_plan_of_more_pieces_than_units(case):
     assert st == gb.GF_OK and (pl.n_segments, pl.linear_threads) == (pieces, threads)
 
 
+# every head linear, or the windowed ones with the streaming kernel: B, H, N, window, H0, options, threads
+@pytest.mark.parametrize("case", [
+    (1, 12, 512, 16, 0, {}, 256), (1, 12, 1024, 16, 0, {}, 256), (1, 12, 2048, 16, 0, {}, 256),      # more sums than chunks
+    (4, 12, 512, 16, 0, {}, 512), (1, 8, 686, 16, 0, {}, 512), (1, 12, 4096, 16, 0, {}, 512), (1, 12, 64, 16, 0, {}, 512),
+    (1, 12, 512, 16, 0, {"bidirectional": 1}, 256), (1, 12, 64, 16, 0, {"bidirectional": 1}, 256),   # pieces of one chunk
+    (8, 12, 1000, 16, 0, {"bidirectional": 1}, 512), (1, 600, 200, 16, 0, {"bidirectional": 1}, 256),
+    (8, 12, 1000, 16, 0, {"bidirectional": 1, "phi": gb.GF_PHI_IDENTITY}, 256), (4, 16, 4096, 16, 0, {"phi": gb.GF_PHI_IDENTITY}, 512),
+    (1, 12, 512, 16, 0, {"phi": gb.GF_PHI_IDENTITY}, 256), (10, 16, 10491, 256, 3, {"phi": gb.GF_PHI_IDENTITY}, 512),
+], ids=lambda c: "x".join(map(str, c[:5])) + "".join(f"-{k}" for k in c[5]))
+def test_plan_without_query_blocks_beside(case):
+    B, H, N, w, H0, kw, threads = case
+    st, pl = gb.gformer_attn_plan(B, H, N, 64, w, gb.make_params(n_sparse_heads=H0, **kw))
+    assert st == gb.GF_OK and pl.linear_threads == threads
+
+
 # B, H, N, options; every head linear
 @pytest.mark.gpu
 @pytest.mark.parametrize("case", [
