@@ -4,6 +4,7 @@
 
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "common.hpp"
@@ -206,24 +207,41 @@ long short_piece(long heads, long cph, long cus, int d) {
 // * over all keys, where a chunk is short: two to three pieces a unit (600 x 200 28.0 and 28.3; 384 x 577 35.3 and 34.7), and
 //   features mapped beforehand, which leave nothing to hide (8 x 12 x 1000 19.0 and 19.5, 2 x 12 x 1325 15.7 and 18.2, but 3 x 8 x
 //   31024 79.4 and 78.1; causal the staging still counts: 16 x 16 x 1024 30.4 and 26.3, 1 x 32 x 16384 87.6 and 79.1).
-// * windowed heads whose query blocks share a launch (with four waves the read-out's, with eight the state pass's) and hardly
-//   more pieces and query blocks than units, or features mapped beforehand (the
-//   staging waves have little to do then), or no state pass that could take the query blocks along.  The layer,
-//   window 128: 1 x (2 + 10) heads x 2048 (112 blocks)
-//   20.0 and 21.2, x 512 13.0 and 15.6; 3 x (2 + 10) x 2048 (336) 26.5 and 26.9; 8 x (2 + 10) x 1024 (368) 26.3 and 25.5;
-//   1 x (2 + 14) x 16384 (480) 57.5 and 48.3; window 256, 8 x (2 + 10) x 4096 (752) 63.1 and 62.0; a training step of
-//   32 x (3 + 9) x 577 over all keys 123 and 116.  Mapped beforehand (with the two maps): 4 x (3 + 13) x 4096 72.7 and 73.2,
-//   1 x (3 + 13) x 16384 75.9 and 77.4, 2 x (3 + 13) x 9000, window 300 81.3 and 85.3, 4 x (8 + 8) x 4096 71.7 and 70.1.
+// With windowed heads the rule also says whose launch their query blocks share: the read-out's (four waves), which costs least
+// where the layer is short, or the state pass's (eight).  The whole layer, heads as windowed + linear, window:
+// * no state pass to share: four.  16 x (2 + 10) x 300, 64 13.2 and 17.5; 14 x (1 + 15) x 1089, 331 36.4 and 41.5.
+// * pieces of two to four chunks: four, but for more workgroups of four waves than the chip holds.  1 x (2 + 10) x 512, 128 12.4
+//   and 15.5; 18 x (3 + 5) x 364, 64 16.9 and 18.1; 1 x (1 + 7) x 5615, 256 25.3 and 27.0; 1 x (11 + 5) x 5484, 256 35.1 and 32.1.
+//   Of five on: eight.  8 x (2 + 10) x 1024, 128 (6 chunks) 26.4 and 25.8; 3 x (1 + 11) x 2472, 38 (8) 35.8 and 32.9; 1 x (2 + 14)
+//   x 16384, 128 (15) 56.0 and 49.4; 8 x (2 + 10) x 4096, 256 (22) 65.1 and 62.7; 4 x (1 + 31) x 16384, 64 (128) 284 and 258.
+// * a query block's tiles a chain half as long again as a sum's chunks: four.  6 x (4 + 12) x 1241, 278 (7 tiles, 4 chunks) 32.4
+//   and 34.0; mapped 2 x (1 + 31) x 1533, 274 (7, 4) 28.2 and 30.4.
+// * mapped beforehand: eight for pieces of eight chunks on beside few tiles, two or less to five chunks.  Tiles a chunk, chunks
+//   a piece: 8 x (2 + 10) x 1024, 128 (0.36, 6) 23.3 and 24.8; 9 x (2 + 6) x 5166, 256 (0.97, 21) 60.4 and 64.6; 20 x (2 + 10) x
+//   1318, 256 (0.63, 18) 49.9 and 51.6; 4 x (3 + 13) x 4096, 128 (0.46, 16) 49.2 and 49.1; but 8 x (2 + 10) x 2048, 128 (0.39, 11)
+//   35.0 and 31.5; 2 x (1 + 15) x 13337, 47 (0.1, 27) 73.5 and 65.6.
+// * over all keys: the same from ten chunks on (10 x (2 + 10) x 1056, 256 (0.60, 9) 26.0 and 28.0; 3 x (2 + 10) x 8811, 256
+//   (0.58, 18) 47.6 and 53.3; 6 x (2 + 10) x 2863, 64 (0.29, 12) 35.1 and 33.9), and of more pieces than units all of five chunks
+//   on (32 x (3 + 9) x 577, 64 38.2 and 35.6; 31 x (1 + 15) x 695, 256 46.7 and 42.5; 45 x (1 + 15) x 437, 128, two to three pieces
+//   a unit, 41.7 and 47.5).
 struct ReadOutCut {
   bool causal, mapped;   // mapped: features mapped beforehand
   long pieces, chunks;   // chunks of a piece
   long sums;             // carried sums a piece starts from, at most
+  long sum_chunks;       // chunks of a sum
   long query_blocks;     // of the windowed heads, where they can share a launch
+  long tiles;            // key tiles of a query block, at most
 };
 bool halves_apart(const ReadOutCut& c, long cus) {
   if (c.chunks == 1 || (c.chunks <= 4 && c.sums > c.chunks)) return false;
   if (c.causal ? c.pieces > cus : c.mapped || (c.pieces > 2 * cus && c.pieces <= 3 * cus)) return false;
-  return c.query_blocks == 0 || (!c.mapped && c.sums > 0 && 3 * (c.pieces + c.query_blocks) > 4 * cus);
+  if (c.query_blocks == 0) return true;
+  if (c.sums == 0) return false;
+  const bool few = 5 * c.query_blocks * c.tiles <= 2 * c.pieces * c.chunks;
+  if (!c.causal) return c.pieces > cus ? c.chunks >= 5 : c.chunks >= 10 && few;
+  if (2 * c.tiles > 3 * c.sum_chunks) return false;
+  if (c.mapped) return c.chunks >= 8 && few;
+  return c.chunks >= 5 || (c.chunks == 4 && c.pieces + c.query_blocks > 2 * cus);
 }
 
 // Shared by gformer_attn_plan, gformer_attn_workspace_bytes and gformer_attn_fwd.
@@ -426,7 +444,10 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
   if (d == 64 && pieces > 0) {
     long sums = mid > 0 ? sums_to_add(!p->bidirectional, (int)vcph, (int)piece, (int)(piece / sub)) : 0;
     if (mid > 0 && (sums == 0 || sums > sums_in_place(d))) sums = 1;   // scanned beforehand, where there are many
-    const ReadOutCut c{!p->bidirectional, p->phi != GF_PHI_ELU1, pieces, piece, sums, r->stream ? 0 : query_blocks};
+    const long reach = (long)window_left(window, p->bidirectional, N) + window_right(window, p->bidirectional, N);
+    const long tiles = std::min((reach + kMfmaWindowRows - 1) / kStrip, (N - 1) / kStrip) + 1;
+    const ReadOutCut c{!p->bidirectional, p->phi != GF_PHI_ELU1, pieces, piece, sums, piece / sub,
+                       r->stream ? 0 : query_blocks, tiles};
     if (halves_apart(c, kComputeUnits)) r->query_halves = 2;
   }
   pl.linear_threads = mfma_linear_threads(d, r->general_chunk ? 1 : r->query_halves);
@@ -569,8 +590,8 @@ gf_status attn_forward(const void* q, const void* k, const void* v, void* out, v
     std::lock_guard<std::mutex> lock(g_enqueue_mutex);
     SideStream* side = nullptr;
     if (win && lin && p->overlap) e = side_stream_for_current_device(s, &side);
-    // The windowed heads' query blocks ride in the state pass's launch, but for long sums beside few blocks, or, in
-    // small calls at d = 64, in the read-out's (linear_mfma.hip).  Not the
+    // The windowed heads' query blocks ride in the state pass's launch, but for long sums beside few blocks, or, beside a
+    // four-wave read-out at d = 64, in that one's (halves_apart, linear_mfma.hip).  Not the
     // streaming kernel (other block size), a forced overlap, or a launch mask that names one of the two.
     const bool joint = win && !p->overlap && !stream;
     const bool together = joint && (mask & GF_LAUNCH_LINEAR_MAIN) && !r.general_chunk && linear_main_takes_windowed(a);

@@ -50,6 +50,24 @@ def test_plan_without_query_blocks_beside(case):
     assert st == gb.GF_OK and pl.linear_threads == threads
 
 
+# query blocks beside: B, H, N, window, H0, options, threads
+@pytest.mark.parametrize("case", [
+    (16, 12, 300, 64, 2, {}, 256),                                          # no state pass to share
+    (18, 8, 364, 64, 3, {}, 256), (1, 8, 5615, 256, 1, {}, 256), (1, 16, 5484, 256, 11, {}, 512),    # three and four chunks a piece
+    (8, 12, 1024, 128, 2, {}, 512), (3, 12, 2472, 38, 1, {}, 512), (1, 16, 16384, 128, 2, {}, 512),
+    (6, 16, 1241, 278, 4, {}, 256), (6, 16, 1241, 128, 4, {}, 512),         # long chains of tiles
+    (8, 12, 1024, 128, 2, {"phi": gb.GF_PHI_IDENTITY}, 256), (9, 8, 5166, 256, 2, {"phi": gb.GF_PHI_IDENTITY}, 256),
+    (8, 12, 2048, 128, 2, {"phi": gb.GF_PHI_IDENTITY}, 512), (4, 32, 16384, 64, 1, {"phi": gb.GF_PHI_IDENTITY}, 512),
+    (8, 12, 1000, 64, 3, {"bidirectional": 1}, 256), (3, 12, 8811, 256, 2, {"bidirectional": 1}, 256),
+    (6, 12, 2863, 64, 2, {"bidirectional": 1}, 512), (32, 12, 577, 64, 3, {"bidirectional": 1}, 512),
+    (45, 16, 437, 128, 1, {"bidirectional": 1}, 256), (32, 12, 577, 64, 3, {"bidirectional": 1, "phi": gb.GF_PHI_IDENTITY}, 256),
+], ids=lambda c: "x".join(map(str, c[:5])) + "".join(f"-{k}" for k in c[5]))
+def test_plan_with_query_blocks_beside(case):
+    B, H, N, w, H0, kw, threads = case
+    st, pl = gb.gformer_attn_plan(B, H, N, 64, w, gb.make_params(n_sparse_heads=H0, **kw))
+    assert st == gb.GF_OK and pl.linear_threads == threads
+
+
 # B, H, N, options; every head linear
 @pytest.mark.gpu
 @pytest.mark.parametrize("case", [
@@ -65,12 +83,13 @@ def test_against_oracle(case):
     check(run_gpu(q, k, v, "bf16", 16, 0, **kw), co.attn_fwd(q, k, v, 16, 0, **args), "bf16", str(case))
 
 
-# B, H, N, window, H0, options: pieces and query blocks on either side of four to three units
+# B, H, N, window, H0, options: both forms of the read-out, the query blocks in its launch and in the state pass's
 @pytest.mark.gpu
 @pytest.mark.parametrize("case", [
     (3, 12, 2048, 128, 2, {}), (8, 12, 1000, 128, 2, {}), (4, 40, 777, 64, 20, {}), (2, 12, 4100, 300, 4, {}),
     (16, 12, 577, 64, 3, {"bidirectional": 1}), (8, 12, 1000, 50, 2, {"phi": gb.GF_PHI_IDENTITY}),
     (8, 12, 1000, 50, 2, {"softmax_scale": -0.5}), (2, 16, 1000, 50, 2, {"segment_len": 64}),
+    (8, 12, 2011, 50, 2, {"phi": gb.GF_PHI_IDENTITY}), (23, 12, 577, 33, 1, {"bidirectional": 1}), (26, 12, 577, 64, 2, {"bidirectional": 1}),
 ], ids=lambda c: "x".join(map(str, c[:5])) + "".join(f"-{k}" for k in c[5]))
 def test_one_launch_gives_the_bits_of_two(case):
     import torch
