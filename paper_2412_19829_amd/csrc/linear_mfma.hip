@@ -956,16 +956,18 @@ hipError_t launch_linear_main_windowed_mfma(const AttnArgs& a, hipStream_t s) {
   return a.final_state ? launch_main_windowed_t<true, true>(a, s) : launch_main_windowed_t<true, false>(a, s);
 }
 
-// Not beside long sums that outweigh the query blocks by far: such sums are what the launch takes, and of 256 threads they
-// take longer than of 512.  Chains of more than 30 chunks, and less than a third as many tiles as linear chunks; the
+// At d = 128 not beside long sums that outweigh the query blocks by far: such sums are what the launch takes, and of 256 threads
+// they take longer than of 512.  Chains of more than 30 chunks, and less than a third as many tiles as linear chunks; the
 // whole layer, us, one launch and two, chunks a chain, tiles a chunk: 2 x 32 x 12000, window 64, H0 = 1 222.8 and 214.7 (47,
 // 0.05); 4 x 32 x 7800, 300, 2 257.0 and 253.5 (61, 0.23); 2 x 32 x 9000, 64, 1 159.0 and 156.4 (36, 0.05); 1 x 32 x 15900, 64,
 // 1 150.1 and 149.4 (32, 0.05); 2 x 32 x 12000, 300, 4 214.0 and 220.4 (47, 0.5); 4 x 32 x 7800, 512, 4 272.8 and 276.4 (61,
 // 0.7); 2 x 32 x 8700, 64, 1 155.2 and 157.4 (17, 0.05); 1 x 16 x 32000, 64, 1 159.7 and 159.2 (30, 0.1).
+// At d = 64 the sums have 256 threads either way: 4 x (1 + 31) x 16384, 64 258.3 and 262.3 (64, 0.02), 2 x (1 + 15) x 32000, 64
+// 153.2 and 160.3 (63, 0.1), 6 x (1 + 15) x 20000, 64 265.9 and 272.1 (56, 0.1).
 bool linear_state_takes_windowed(const AttnArgs& a) {
   if (a.H0 <= 0 || !has_state_pass(a) || a.scale < 0.f || (a.d == 64 && a.query_halves == 1)) return false;
   const int64_t query_blocks = query_block_count(a);
-  if (a.piece_chunks / a.state_sub > 30 && 3 * query_blocks * block_tiles(a) < (int64_t)a.B * (a.H - a.H0) * a.cph) return false;
+  if (a.d == 128 && a.piece_chunks / a.state_sub > 30 && 3 * query_blocks * block_tiles(a) < (int64_t)a.B * (a.H - a.H0) * a.cph) return false;
   return (int64_t)a.n_pieces * a.state_sub + query_blocks < (1 << 22);
 }
 hipError_t launch_linear_state_mfma(const AttnArgs& a, bool with_windowed, hipStream_t s) {

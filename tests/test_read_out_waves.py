@@ -90,6 +90,7 @@ def test_against_oracle(case):
     (16, 12, 577, 64, 3, {"bidirectional": 1}), (8, 12, 1000, 50, 2, {"phi": gb.GF_PHI_IDENTITY}),
     (8, 12, 1000, 50, 2, {"softmax_scale": -0.5}), (2, 16, 1000, 50, 2, {"segment_len": 64}),
     (8, 12, 2011, 50, 2, {"phi": gb.GF_PHI_IDENTITY}), (23, 12, 577, 33, 1, {"bidirectional": 1}), (26, 12, 577, 64, 2, {"bidirectional": 1}),
+    (1, 8, 6000, 64, 1, {"segment_len": 3008}),   # sums of 47 chunks
 ], ids=lambda c: "x".join(map(str, c[:5])) + "".join(f"-{k}" for k in c[5]))
 def test_one_launch_gives_the_bits_of_two(case):
     import torch
@@ -119,3 +120,30 @@ def test_one_launch_gives_the_bits_of_two(case):
         # phi(k) enters as bf16 (2^-9 of each of N terms, independent: far below 2^-8 of the norm)
         assert float((st[..., :4096].double().view_as(A) - A).norm() / A.norm()) < 2.0 ** -8
         assert float((st[..., 4096:].double() - fk.sum(2)).norm() / fk.sum(2).norm()) < 2.0 ** -8
+
+
+# B, H, N, d, window, H0, options: sums of 47 chunks and few query blocks are two launches at d = 64 and three at d = 128
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [
+    (4, 32, 6000, 64, 64, 1, {"segment_len": 3008}, 2), (1, 8, 6000, 128, 64, 1, {"segment_len": 3008}, 3),
+    (1, 8, 6000, 64, 64, 0, {"segment_len": 3008}, 2), (1, 8, 6000, 64, 64, 1, {"segment_len": 3008, "softmax_scale": -0.5}, 3),
+    (1, 12, 2048, 64, 128, 2, {}, 2), (8, 12, 1000, 64, 128, 2, {}, 2),
+], ids=lambda c: "x".join(map(str, c[:6])) + "".join(f"-{k}" for k in c[6]))
+def test_launches(case):
+    import ctypes
+
+    import torch
+    B, H, N, d, w, H0, kw, launches = case
+    q, k, v = (torch.randn(B, H, N, d, device="cuda").to(torch.bfloat16) for _ in range(3))
+    out = torch.empty_like(q)
+    p = gb.make_params(n_sparse_heads=H0, **kw)
+    ws = torch.empty(max(gb.gformer_attn_workspace_bytes(B, H, N, d, w, p), 256), dtype=torch.uint8, device="cuda")
+    graph, side = torch.cuda.CUDAGraph(keep_graph=True), torch.cuda.Stream()
+    gb.gformer_attn_fwd(q, k, v, out, w, H0, workspace=ws, **kw)   # loads the kernels before the capture
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        gb.gformer_attn_fwd(q, k, v, out, w, H0, workspace=ws, **kw)
+    nodes = ctypes.c_size_t()
+    hip = ctypes.CDLL("libamdhip64.so")
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(nodes)) == 0
+    assert nodes.value == launches
