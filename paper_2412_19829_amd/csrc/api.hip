@@ -357,7 +357,13 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
       pl.windowed_blocks = (int)sp.blocks;
     }
   }
-  long piece = 0, vcph = cph, pieces = 0, mid = 0, sub = 1, most_sub = 0;
+  long piece = 0, vcph = cph, pieces = 0, mid = 0, sub = 1, most_sub = 0, carried = 0;
+  // sub-pieces of the `carried` pieces that the state pass sums, beside `blocks` others and `per_unit` of both on a unit
+  auto cut_beside = [&](long blocks, long per_unit) {
+    long n = 4;
+    while (n > 1 && !(piece % n == 0 && piece / n >= 4 && carried * n + blocks <= per_unit * kComputeUnits)) n /= 2;
+    return n;
+  };
   if (p->segment_len != 0 && p->segment_len % pl.chunk != 0) return GF_ERR_INVALID_ARG;
   long own_piece = aligned_piece(heads_lin, cph, kComputeUnits);
   if (own_piece == 0 && !r->general_chunk && short_pieces) own_piece = short_piece(heads_lin, cph, kComputeUnits, d);
@@ -397,22 +403,9 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
     pieces = heads_lin * per_head;
     // The state pass walks a head's segments but the last one.  A workgroup of it is bound by
     // its own chunk-by-chunk walk, so segments are cut into up to four sub-pieces as long as the
-    // sub-pieces stay 4 chunks or longer and fit two workgroups per compute unit.  At d = 128 the windowed heads' query
-    // blocks share its launch: where both fit the chip at once without a cut, the cut leaves room for them (prefill of
-    // 2 x 32 x 3001: 156 sums of 12 chunks beside 288 query blocks 36 us, 312 of 6, which need a second round, 43).  The
-    // same cut where the query blocks have a launch of their own (negative scale, overlap, long sums): calls with a
-    // launch mask, which share the sums, must agree on it, and it is no slower (finer, this: the same prefill's forward
-    // with a negative scale 86.5, 78.5, with overlap 92.5, 81; 1 x 32 x 5338, H0 = 5 83.6, 76.1 and 85.3, 75.9).
-    // The workspace reported has room for the sums of the finer cut, so that its size depends on the shape alone.
-    const long carried = heads_lin * (per_head > 0 ? per_head - 1 : 0);
-    const long beside = d == 128 && !r->stream && carried + query_blocks <= 2 * kComputeUnits ? query_blocks : 0;
-    auto cut_beside = [&](long blocks) {
-      long n = 4;
-      while (n > 1 && !(piece % n == 0 && piece / n >= 4 && carried * n + blocks <= 2 * kComputeUnits)) n /= 2;
-      return n;
-    };
-    sub = cut_beside(beside);
-    most_sub = cut_beside(0);
+    // sub-pieces stay 4 chunks or longer and fit two workgroups per compute unit.
+    carried = heads_lin * (per_head > 0 ? per_head - 1 : 0);
+    sub = most_sub = cut_beside(0, 2);
     mid = carried * sub;
   } else if (heads_lin > 0 && cph > 0) {
     // One workgroup per compute unit (its LDS holds one), each with the same number of chunks;
@@ -437,7 +430,6 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
   r->cph = (int)cph;
   r->vcph = (int)vcph;
   r->piece_chunks = (int)piece;
-  r->state_sub = (int)sub;
   pl.segment_len = (int)(piece * kStrip);
   pl.n_segments = (int)pieces;
   r->query_halves = 1;
@@ -450,6 +442,22 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
                        r->stream ? 0 : query_blocks, tiles};
     if (halves_apart(c, kComputeUnits)) r->query_halves = 2;
   }
+  // Where the query blocks share the state pass's launch and both fit the chip at once without a cut, the cut leaves room for
+  // them.  d = 128, two on a unit: prefill of 2 x 32 x 3001, 156 sums of 12 chunks beside 288 query blocks 36 us, 312 of 6,
+  // which need a second round, 43.  d = 64, three on a unit: sums of whole pieces are few, so only where they still come to three
+  // of four units.  The layer, us, finest cut and this: 1 x (2 + 10) x 18682 (240 sums) 52.0 and 44.6, 2 x (3 + 13) x 9000 (208) 63.3
+  // and 58.7, 4 x (1 + 7) x 15727 (224) 79.5 and 80.1, but 8 x (2 + 10) x 4096 (160) 63.4 and 69.0, 11 x (1 + 7) x 5282 (154) 69.2 and 73.2.
+  // The same cut where the query blocks have a launch of their own (negative scale, overlap, long sums): calls with a
+  // launch mask, which share the sums, must agree on it, and it is no slower (finer, this: the same prefill's forward
+  // with a negative scale 86.5, 78.5, with overlap 92.5, 81; 1 x 32 x 5338, H0 = 5 83.6, 76.1 and 85.3, 75.9; d = 64, apart
+  // 1 x (2 + 10) x 18682 55.1, 53.7, 4 x (1 + 7) x 15727 83.5, 86.5).
+  // The workspace reported has room for the sums of the finer cut, so that its size depends on the shape alone.
+  if (carried > 0 && !r->stream && (d == 128 || (r->query_halves == 2 && 4 * carried >= 3 * kComputeUnits))) {
+    const long per_unit = d == 128 ? 2 : 3;
+    if (carried + query_blocks <= per_unit * kComputeUnits) sub = std::min(sub, cut_beside(query_blocks, per_unit));
+    mid = carried * sub;
+  }
+  r->state_sub = (int)sub;
   pl.linear_threads = mfma_linear_threads(d, r->general_chunk ? 1 : r->query_halves);
   pl.linear_blocks = (int)pieces;
   pl.state_blocks = (int)mid;
