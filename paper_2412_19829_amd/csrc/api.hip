@@ -358,10 +358,20 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
     }
   }
   long piece = 0, vcph = cph, pieces = 0, mid = 0, sub = 1, most_sub = 0, carried = 0;
-  // sub-pieces of the `carried` pieces that the state pass sums, beside `blocks` others and `per_unit` of both on a unit
-  auto cut_beside = [&](long blocks, long per_unit) {
+  // sums of equal pieces with no regard to heads, cut into n
+  auto straddling_sums = [&](long n) {
+    const long total = heads_lin * cph, ls = piece / n;
+    long count = 0;
+    for (long j = 1; j < pieces * n; ++j) {
+      const long e = j * ls, next_main = (j + n - 1) / n * piece;
+      count += (e % cph) != 0 && next_main < (e / cph + 1) * cph && next_main < total;
+    }
+    return count;
+  };
+  // sub-pieces of the `carried` pieces that the state pass sums, beside `blocks` others where the chip holds `room` of both
+  auto cut_beside = [&](long blocks, long room) {
     long n = 4;
-    while (n > 1 && !(piece % n == 0 && piece / n >= 4 && carried * n + blocks <= per_unit * kComputeUnits)) n /= 2;
+    while (n > 1 && !(piece % n == 0 && piece / n >= 4 && carried * n + blocks <= room)) n /= 2;
     return n;
   };
   if (p->segment_len != 0 && p->segment_len % pl.chunk != 0) return GF_ERR_INVALID_ARG;
@@ -405,7 +415,7 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
     // its own chunk-by-chunk walk, so segments are cut into up to four sub-pieces as long as the
     // sub-pieces stay 4 chunks or longer and fit two workgroups per compute unit.
     carried = heads_lin * (per_head > 0 ? per_head - 1 : 0);
-    sub = most_sub = cut_beside(0, 2);
+    sub = most_sub = cut_beside(0, 2 * kComputeUnits);
     mid = carried * sub;
   } else if (heads_lin > 0 && cph > 0) {
     // One workgroup per compute unit (its LDS holds one), each with the same number of chunks;
@@ -419,12 +429,8 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
     pieces = (total + piece - 1) / piece;
     // Here the state pass works on half pieces (two workgroups per compute unit fit there), which
     // evens out its load: a sub-piece is summed iff a piece boundary follows it inside its head.
-    sub = piece % 2 == 0 ? 2 : 1;
-    const long ls = piece / sub;
-    for (long j = 1; j < pieces * sub; ++j) {
-      const long e = j * ls, next_main = (j + sub - 1) / sub * piece;
-      mid += (e % cph) != 0 && next_main < (e / cph + 1) * cph && next_main < total;
-    }
+    sub = most_sub = piece % 2 == 0 ? 2 : 1;
+    mid = straddling_sums(sub);
   }
   if (pieces > 0x7fffffffL / 64) return GF_ERR_UNSUPPORTED;
   r->cph = (int)cph;
@@ -432,30 +438,47 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
   r->piece_chunks = (int)piece;
   pl.segment_len = (int)(piece * kStrip);
   pl.n_segments = (int)pieces;
+  // Where the query blocks share the state pass's launch and both fit the chip at once without a cut, the cut leaves room for
+  // them.  d = 128, two on a unit: prefill of 2 x 32 x 3001, 156 sums of 12 chunks beside 288 query blocks 36 us, 312 of 6,
+  // which need a second round, 43.  d = 64, three on a unit: uncut sums are few and long, so only where they come to three
+  // of four units or have no more than 20 chunks.  The layer, us, finest cut and this: 1 x (2 + 10) x 18682 (240 sums of 12)
+  // 52.0 and 44.6, 2 x (3 + 13) x 9000 (208 of 16) 63.3 and 58.7, 3 x (6 + 26) x 3750 (156 of 20) 69.3 and 63.3, 4 x (1 + 7) x 15727
+  // (224 of 28) 79.5 and 80.1, but 8 x (2 + 10) x 4096 (160 of 22) 63.4 and 69.0, 11 x (1 + 7) x 5282 (154 of 28) 69.2 and 73.2.
+  // Pieces across heads where they have no more than 20 chunks: 3 x (7 + 9) x 3096
+  // (8 chunks) 1.25 times as fast, 5 x (3 + 13) x 3936 (16) 1.13, 9 x (2 + 10) x 3267 (20) 1.03, but 13 x (2 + 10) x 2520 (22) 0.99,
+  // 19 x (1 + 7) x 2968 (26) 0.98, 9 x (1 + 31) x 6795 (118) 0.93.
+  // The same cut where the query blocks have a launch of their own (negative scale, overlap, long sums): calls with a
+  // launch mask, which share the sums, must agree on it, and it is no slower (finer, this: the same prefill's forward
+  // with a negative scale 86.5, 78.5, with overlap 92.5, 81; 1 x 32 x 5338, H0 = 5 83.6, 76.1 and 85.3, 75.9; d = 64, apart
+  // 1 x (2 + 10) x 18682 55.1, 53.7, 4 x (1 + 7) x 15727 83.5, 86.5).
+  // The workspace reported has room for the sums of the finer cut, so that its size depends on the shape alone.
+  const long room = (d == 128 ? 2 : 3) * kComputeUnits;
+  long sub_beside = sub, mid_beside = mid;
+  if (sub > 1 && query_blocks > 0 && !r->stream && !p->bidirectional) {
+    if (carried > 0 && (d == 128 || 4 * carried >= 3 * kComputeUnits || piece <= 20)) {
+      if (carried + query_blocks <= room) sub_beside = std::min(sub, cut_beside(query_blocks, room));
+      mid_beside = carried * sub_beside;
+    } else if (d == 64 && carried == 0 && piece <= 20 && mid + query_blocks > room) {
+      const long whole = straddling_sums(1);
+      if (whole + query_blocks <= room) {
+        sub_beside = 1;
+        mid_beside = whole;
+      }
+    }
+  }
   r->query_halves = 1;
   if (d == 64 && pieces > 0) {
     long sums = mid > 0 ? sums_to_add(!p->bidirectional, (int)vcph, (int)piece, (int)(piece / sub)) : 0;
     if (mid > 0 && (sums == 0 || sums > sums_in_place(d))) sums = 1;   // scanned beforehand, where there are many
     const long reach = (long)window_left(window, p->bidirectional, N) + window_right(window, p->bidirectional, N);
     const long tiles = std::min((reach + kMfmaWindowRows - 1) / kStrip, (N - 1) / kStrip) + 1;
-    const ReadOutCut c{!p->bidirectional, p->phi != GF_PHI_ELU1, pieces, piece, sums, piece / sub,
+    const ReadOutCut c{!p->bidirectional, p->phi != GF_PHI_ELU1, pieces, piece, sums, piece / sub_beside,
                        r->stream ? 0 : query_blocks, tiles};
     if (halves_apart(c, kComputeUnits)) r->query_halves = 2;
   }
-  // Where the query blocks share the state pass's launch and both fit the chip at once without a cut, the cut leaves room for
-  // them.  d = 128, two on a unit: prefill of 2 x 32 x 3001, 156 sums of 12 chunks beside 288 query blocks 36 us, 312 of 6,
-  // which need a second round, 43.  d = 64, three on a unit: sums of whole pieces are few, so only where they still come to three
-  // of four units.  The layer, us, finest cut and this: 1 x (2 + 10) x 18682 (240 sums) 52.0 and 44.6, 2 x (3 + 13) x 9000 (208) 63.3
-  // and 58.7, 4 x (1 + 7) x 15727 (224) 79.5 and 80.1, but 8 x (2 + 10) x 4096 (160) 63.4 and 69.0, 11 x (1 + 7) x 5282 (154) 69.2 and 73.2.
-  // The same cut where the query blocks have a launch of their own (negative scale, overlap, long sums): calls with a
-  // launch mask, which share the sums, must agree on it, and it is no slower (finer, this: the same prefill's forward
-  // with a negative scale 86.5, 78.5, with overlap 92.5, 81; 1 x 32 x 5338, H0 = 5 83.6, 76.1 and 85.3, 75.9; d = 64, apart
-  // 1 x (2 + 10) x 18682 55.1, 53.7, 4 x (1 + 7) x 15727 83.5, 86.5).
-  // The workspace reported has room for the sums of the finer cut, so that its size depends on the shape alone.
-  if (carried > 0 && !r->stream && (d == 128 || (r->query_halves == 2 && 4 * carried >= 3 * kComputeUnits))) {
-    const long per_unit = d == 128 ? 2 : 3;
-    if (carried + query_blocks <= per_unit * kComputeUnits) sub = std::min(sub, cut_beside(query_blocks, per_unit));
-    mid = carried * sub;
+  if (d == 128 || r->query_halves == 2) {
+    sub = sub_beside;
+    mid = mid_beside;
   }
   r->state_sub = (int)sub;
   pl.linear_threads = mfma_linear_threads(d, r->general_chunk ? 1 : r->query_halves);

@@ -72,13 +72,16 @@ def test_plan_with_query_blocks_beside(case):
 @pytest.mark.parametrize("case", [
     (1, 12, 18682, 128, 2, {}, 1), (2, 16, 9000, 300, 3, {}, 1), (8, 12, 4096, 256, 2, {}, 2), (11, 8, 5282, 128, 1, {}, 2),
     (1, 12, 18682, 128, 0, {}, 2), (2, 16, 11123, 256, 3, {}, 1), (1, 12, 21000, 128, 5, {}, 2),
-    (1, 12, 18682, 128, 2, {"impl": gb.GF_IMPL_MFMA_STREAM}, 2),
+    (1, 12, 18682, 128, 2, {"impl": gb.GF_IMPL_MFMA_STREAM}, 2), (3, 32, 3750, 508, 6, {}, 1),
+    (4, 14, 4096, 64, 1, {}, 2),   # no finer than the workspace has room for
+    (3, 16, 3096, 312, 7, {}, 1), (5, 16, 3936, 128, 3, {}, 1), (13, 12, 2520, 256, 2, {}, 2), (9, 32, 6795, 128, 1, {}, 2),
 ], ids=lambda c: "x".join(map(str, c[:5])) + "".join(f"-{k}" for k in c[5]))
 def test_plan_of_sums(case):
     B, H, N, w, H0, kw, sub = case
     st, pl = gb.gformer_attn_plan(B, H, N, 64, w, gb.make_params(n_sparse_heads=H0, **kw))
-    heads = B * (H - H0)
-    assert st == gb.GF_OK and pl.state_blocks == sub * (pl.n_segments - heads)
+    assert st == gb.GF_OK
+    if pl.n_segments % (B * (H - H0)) == 0: assert pl.state_blocks == sub * (pl.n_segments - B * (H - H0))
+    else: assert pl.state_blocks <= sub * pl.n_segments and (sub == 1 or pl.state_blocks > pl.n_segments)   # pieces across heads
     slots = pl.workspace_bytes // (4 * (64 * 64 + 64))
     assert slots % pl.n_segments == 0 and slots >= sub * pl.n_segments
 
@@ -106,7 +109,7 @@ def test_against_oracle(case):
     (8, 12, 1000, 50, 2, {"softmax_scale": -0.5}), (2, 16, 1000, 50, 2, {"segment_len": 64}),
     (8, 12, 2011, 50, 2, {"phi": gb.GF_PHI_IDENTITY}), (23, 12, 577, 33, 1, {"bidirectional": 1}), (26, 12, 577, 64, 2, {"bidirectional": 1}),
     (1, 8, 6000, 64, 1, {"segment_len": 3008}),   # sums of 47 chunks
-    (1, 12, 18682, 100, 2, {}), (2, 16, 9001, 300, 3, {}),   # sums of whole pieces
+    (1, 12, 18682, 100, 2, {}), (2, 16, 9001, 300, 3, {}), (3, 16, 3096, 312, 7, {}),   # sums of whole pieces
 ], ids=lambda c: "x".join(map(str, c[:5])) + "".join(f"-{k}" for k in c[5]))
 def test_one_launch_gives_the_bits_of_two(case):
     import torch
