@@ -1,4 +1,4 @@
-"""d = 64: the read-out with twice the waves, and the query blocks beside the state pass.  Against the oracle where its tiles
+"""d = 64: the read-out's two forms, the rule that chooses, and the query blocks beside the state pass.  Against the oracle where its tiles
 and pieces end (chunks of 64 tokens, queries split in halves of 32), and the bits of the kernels launched one by one on both
 sides of the rule that chooses it, the prefill's carried states included."""
 from __future__ import annotations
@@ -7,7 +7,7 @@ import pytest
 
 from oracle import cpu_oracle as co
 from paper_2412_19829_amd import binding as gb
-from tests.gpu_util import run_gpu, to_device
+from tests.gpu_util import run_gpu, to_device, to_host
 from tests.test_gpu_parity import check, synth
 
 
@@ -90,6 +90,7 @@ def test_plan_of_sums(case):
 @pytest.mark.gpu
 @pytest.mark.parametrize("case", [
     (1, 2, 1, {}), (1, 3, 31, {}), (1, 3, 33, {}), (2, 3, 64, {}), (1, 3, 65, {}), (3, 5, 97, {}), (1, 40, 777, {}),
+    (2, 12, 300, {}), (1, 3, 700, {}),
     (7, 40, 150, {}),                     # more heads than units: pieces straddle heads
     (1, 260, 197, {}), (2, 12, 1000, {"segment_len": 64}),   # more pieces than units
     (1, 3, 1055, {"eps": 0.5}), (1, 3, 1000, {"segment_len": 64}), (2, 4, 577, {"bidirectional": 1}), (1, 1, 33, {"bidirectional": 1}),
@@ -101,12 +102,53 @@ def test_against_oracle(case):
     check(run_gpu(q, k, v, "bf16", 16, 0, **kw), co.attn_fwd(q, k, v, 16, 0, **args), "bf16", str(case))
 
 
+# rows of the [B, N, H, d] storage: B, H, N, window, H0, options
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [
+    (2, 12, 300, 16, 0, {}), (7, 40, 150, 16, 0, {}), (1, 3, 1000, 16, 0, {"segment_len": 512}), (2, 12, 300, 16, 0, {"bidirectional": 1}),
+    (8, 12, 1000, 50, 2, {}),   # query blocks beside the state pass
+], ids=lambda c: "x".join(map(str, c[:5])) + "".join(f"-{k}" for k in c[5]))
+def test_strided_rows(case):
+    B, H, N, w, H0, kw = case
+    q, k, v = synth(B, H, N, 64, "bf16", 93)
+    dense, rows = (run_gpu(q, k, v, "bf16", w, H0, layout=x, **kw) for x in ("bhnd", "bnhd"))
+    assert (dense == rows).all()
+    if H0 == 0: check(rows, co.attn_fwd(q, k, v, w, H0, bidirectional=bool(kw.get("bidirectional"))), "bf16", str(case))
+
+
+# features mapped beforehand, every head linear: B, H, N, options
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [
+    (1, 3, 1, {}), (1, 3, 33, {}), (1, 3, 65, {}), (3, 5, 97, {}), (1, 3, 700, {}), (7, 40, 150, {}), (1, 40, 777, {}),
+    (1, 3, 1000, {"segment_len": 512}), (2, 4, 577, {"bidirectional": 1}),
+], ids=lambda c: "x".join(map(str, c[:3])) + "".join(f"-{k}" for k in c[3]))
+def test_mapped_features_against_oracle(case):
+    import torch
+    B, H, N, kw = case
+    q, k, v = synth(B, H, N, 64, "bf16", 94)
+    q, k = (to_host((to_device(x, "bf16").abs() + 0.125)) for x in (q, k))
+    want = co.attn_fwd(q, k, v, 16, 0, phi=co.PHI_IDENTITY, bidirectional=bool(kw.get("bidirectional")))
+    got = run_gpu(q, k, v, "bf16", 16, 0, phi=gb.GF_PHI_IDENTITY, **kw)
+    check(got, want, "bf16", str(case))
+    if kw: return
+    # the prefill's read-out: same rows, and the states after the last token
+    tq, tk, tv = (to_device(x, "bf16") for x in (q, k, v))
+    out, st = torch.full_like(tq, float("nan")), torch.zeros(B, H, 64 * 64 + 64, device="cuda")
+    gb.gformer_attn_prefill(tq, tk, tv, out, None, None, st, 16, 0, phi=gb.GF_PHI_IDENTITY)
+    torch.cuda.synchronize()
+    assert (to_host(out) == got).all()
+    A = torch.matmul(tk.double().transpose(2, 3).contiguous(), tv.double())
+    # bf16 features and values, fp32 sums of N <= 777 terms (2^-24 each)
+    assert float((st[..., :4096].double().view_as(A) - A).norm() / A.norm()) < 2.0 ** -14
+    assert float((st[..., 4096:].double() - tk.double().sum(2)).norm() / tk.double().sum(2).norm()) < 2.0 ** -14
+
+
 # B, H, N, window, H0, options: both forms of the read-out, the query blocks in its launch and in the state pass's
 @pytest.mark.gpu
 @pytest.mark.parametrize("case", [
     (3, 12, 2048, 128, 2, {}), (8, 12, 1000, 128, 2, {}), (4, 40, 777, 64, 20, {}), (2, 12, 4100, 300, 4, {}),
     (16, 12, 577, 64, 3, {"bidirectional": 1}), (8, 12, 1000, 50, 2, {"phi": gb.GF_PHI_IDENTITY}),
-    (8, 12, 1000, 50, 2, {"softmax_scale": -0.5}), (2, 16, 1000, 50, 2, {"segment_len": 64}),
+    (8, 12, 1000, 50, 2, {"softmax_scale": -0.5}), (2, 16, 1000, 50, 2, {"segment_len": 64}), (8, 12, 1000, 128, 2, {"chunk": 128}),
     (8, 12, 2011, 50, 2, {"phi": gb.GF_PHI_IDENTITY}), (23, 12, 577, 33, 1, {"bidirectional": 1}), (26, 12, 577, 64, 2, {"bidirectional": 1}),
     (1, 8, 6000, 64, 1, {"segment_len": 3008}),   # sums of 47 chunks
     (1, 12, 18682, 100, 2, {}), (2, 16, 9001, 300, 3, {}), (3, 16, 3096, 312, 7, {}),   # sums of whole pieces
@@ -141,12 +183,12 @@ def test_one_launch_gives_the_bits_of_two(case):
         assert float((st[..., 4096:].double() - fk.sum(2)).norm() / fk.sum(2).norm()) < 2.0 ** -8
 
 
-# B, H, N, d, window, H0, options: sums of 47 chunks and few query blocks are two launches at d = 64 and three at d = 128
+# B, H, N, d, window, H0, options, launches: sums of 47 chunks and few query blocks are two at d = 64 and three at d = 128
 @pytest.mark.gpu
 @pytest.mark.parametrize("case", [
     (4, 32, 6000, 64, 64, 1, {"segment_len": 3008}, 2), (1, 8, 6000, 128, 64, 1, {"segment_len": 3008}, 3),
     (1, 8, 6000, 64, 64, 0, {"segment_len": 3008}, 2), (1, 8, 6000, 64, 64, 1, {"segment_len": 3008, "softmax_scale": -0.5}, 3),
-    (1, 12, 2048, 64, 128, 2, {}, 2), (8, 12, 1000, 64, 128, 2, {}, 2),
+    (1, 12, 2048, 64, 128, 2, {}, 2), (8, 12, 1000, 64, 128, 2, {}, 2), (8, 12, 1000, 64, 128, 2, {"chunk": 128}, 2),
 ], ids=lambda c: "x".join(map(str, c[:6])) + "".join(f"-{k}" for k in c[6]))
 def test_launches(case):
     import ctypes
