@@ -584,8 +584,8 @@ gf_status attn_forward(const void* q, const void* k, const void* v, void* out, v
   a.vcph = r.vcph;
   a.piece_chunks = r.piece_chunks;
   a.n_pieces = r.plan.n_segments;
-  a.state_sub = r.state_sub;
-  a.query_halves = r.query_halves;
+  a.state_sub = (int16_t)r.state_sub;
+  a.query_halves = (int16_t)r.query_halves;
   a.f32_seg_len = r.f32_seg_len;
   a.f32_nseg = r.f32_nseg;
   a.ws_states = r.needed > 0 ? reinterpret_cast<float*>(workspace) : nullptr;

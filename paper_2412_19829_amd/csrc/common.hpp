@@ -36,8 +36,8 @@ struct AttnArgs {
   int vcph;          // virtual chunks per head
   int piece_chunks;  // chunks per piece
   int n_pieces;      // pieces = workgroups of the read-out kernel
-  int state_sub;     // the state pass cuts every piece into this many equal sub-pieces (1, 2 or 4)
-  int query_halves;  // the read-out's matrix waves, in sets: 2 (d = 64) where they split a chunk's queries
+  int16_t state_sub;     // the state pass cuts every piece into this many equal sub-pieces (1, 2 or 4)
+  int16_t query_halves;  // the read-out's matrix waves, in sets: 2 (d = 64) where they split a chunk's queries
   float* final_state; // optional [B*(H-H0), d*d + d] fp32: every linear head's (A, Z) after its last
                      // token, A row-major [feature][value] (what the decode step carries on from)
   void *kring, *vring; // optional [B, H0, window, d] rings: the last `window` keys / values of every
@@ -51,6 +51,7 @@ struct AttnArgs {
   float* ws_states;  // [n_pieces*state_sub, d*d + d] fp32: slot j = (A, Z) of its head just
                      // before global chunk j*piece_chunks/state_sub (piece p reads slot p*state_sub)
 };
+static_assert(sizeof(AttnArgs) <= 248, "with two ints beside it a launch's arguments are four cache lines");
 
 // Sub-piece sums of `ls` chunks that a piece of `piece` chunks starts from, at most (0 for one where heads are no longer than `ls`).
 __host__ __device__ inline int sums_to_add(bool causal, int vcph, int piece, int ls) {
