@@ -11,13 +11,12 @@
 //   forward scan:  r = A dO,  den = rowsum(S) + fq.Z + eps,  c = (fq.r + rowsum(S * T)) / den^2 (which is
 //                  dO.num / den^2 without a numerator),  dfq = T' fk + r / den - c Z^T;   then A += fk^T v, Z += colsum(fk)
 //   reverse scan:  dfk = T'^T fq + v B^T - 1 Y^T,  dv = (S / den)^T dO + fk B;   then B += fq^T dO / den, Y += fq^T c
-// What bounds them: the phases of the one workgroup a unit, one after the other (104 heads x 8192: 778 us, 720 with every load
-// and store served by L2), of whose cycles the LDS pipeline takes 45 and 50 %, a fifth of that in conflicts, the vector unit 40 %,
-// the matrix core 15 %; and 13.3 tensors' worth of traffic (the scans' eight reads and three writes, and what light rounds
+// What bounds them: the phases of the one workgroup a unit, one after the other, of whose cycles
+// the LDS pipeline takes 45 and 50 %, a fifth of that in conflicts, the vector unit 40 %, the matrix core 15 %; and 13.3 tensors' worth of traffic (the scans' eight reads and three writes, and what light rounds
 // read again) at 4.0 (forward) and 4.1 TB/s (reverse) on 128 heads x 8192, of the 4.9 a copy reaches.  With the
 // numerator as two products of its own (S as a pair), dO and dO / den as tiles of their own, the 32 x 32 tile above the
 // diagonal computed and multiplied, and the column sums read from LDS element by element, the same scans took 953 us
-// (853 without, 840 with the feature map as a maximum; 4 x (6 + 26) heads x 8192 with the windowed heads 1083 and 1000; 32 x 1000
+// (841 without, 826 with the feature map as a maximum; 4 x (6 + 26) heads x 8192 with the windowed heads 1083 and 1000; 32 x 1000
 // 81.5 and 72.0).  Row stores behind the next chunk's staging and loads instead of in front of it: 883.  Of a forward chunk 25 %
 // go to (a), where three waves work twice as long as the others, 22 to (b) and (c), 16 to (d), 37 to (e).
 // These are the kernels of d = 128, and of d = 64 where the workspace holds no segment sums.

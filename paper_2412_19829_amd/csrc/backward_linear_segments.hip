@@ -74,7 +74,7 @@ __device__ __forceinline__ float sum_over_groups(float x) {
 __device__ __forceinline__ f32x4 lds4f(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
 
 // elu(x) + 1 = max(x + 1, min(exp(x), 1)): the clamp rides on v_exp, and v_maximum3 lets a NaN through, which comes in
-// x + 1.  A comparison and a select instead: 327.7 against 324.9 us for the backward pass of 208 heads x 4096.
+// x + 1.  A comparison and a select instead: 328.9 against 325.6 us for the backward pass of 208 heads x 4096.
 __device__ __forceinline__ float phi_elu1(float x) {
   const float e = __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(x * kLog2e), 0.f, 1.f);
   return __builtin_elementwise_maximum(x + 1.f, e);
@@ -221,9 +221,9 @@ template <int D> __device__ __forceinline__ f32x4 rows_product(const uint16_t* a
 
 // Whole chunks run as body(t0, true_type), without a condition in front of their loads and stores: with
 // one the compiler waits for everything outstanding, the last stores included, before it stages a
-// chunk.  Loads past the end are clamped to the last row.  With STORES a chunk stores the rows of the one
-// before it, so the first chunk, which has none to store, runs as body(t0, false_type) too, and so does the
-// chunk that stores a ragged one's.
+// chunk.  Loads past the end are clamped to the last row.  On the way down a chunk also stores the rows of the one
+// before it, so the first one, which has none to store, runs as body(t0, false_type), and so does the
+// one that stores a ragged chunk's.
 template <typename Body> __device__ __forceinline__ void walk_up(int begin, int end, Body body) {
   int t0 = begin;
   for (; t0 + SC <= end; t0 += SC) body(t0, std::true_type{});

@@ -11,9 +11,8 @@
 // whole sequence on a part of the chip.
 //
 // Measured, B=4, 52 linear heads, N=2048, d=64, eight segments a head and no scan of their sums (plain-FMA kernels ->
-// these, us): forward 1017 -> 18 (sums) + 48, backward 859 + 1558 -> 18 + 71 + 68.  The bound is the SIMDs' issue: the
-// matrix core is busy 32 % of the forward walk's time (33 % of the dq walk's, 42 % of the last while it summed B twice, in 75
-// us), the vector unit 22 % (24 and 19 %)
+// these, us): forward 1017 -> 17 (sums) + 46, backward 859 + 1558 -> 17 + 68 + 65.  The bound is the SIMDs' issue: the
+// matrix core is busy 33 % of the forward walk's time (34 and 39 % of the others'), the vector unit 22 % (24 and 20 %)
 // at four cycles an instruction, hardly ever both; with two workgroups a unit the barriers between a chunk's steps
 // leave the rest.
 //
@@ -799,7 +798,8 @@ hipError_t launch_scan(float* sums, int heads, int nseg, int floats, int mode, h
 // their runs) the `band` workgroups of the windowed heads that go with it.  Same bits as apart.
 // Measured (a training step of 4 x (3 + 13 heads) x 2048 x 64, window 128, us): 319 apart, 294 together; read-out
 // 39 + 22 -> 58, dq 57 + 45 -> 98, dk and dv 64 + 35 -> 99, and three launches less.  The last keeps the windowed
-// heads' 194 registers, so two workgroups share a compute unit where the walk alone has three.
+// heads' 194 registers; the walk's own LDS, 63 KB with the turned copy of B (147 at d = 128), lets no more than two workgroups
+// (one) share a compute unit either.
 enum Walk { kReadOut, kQWalk, kKvWalk };
 template <int D, bool CAUSAL, int WALK, typename Args>
 __global__ __launch_bounds__(kLinThreads<D>, 2) void linear_f32_walk_kernel(Args a, int linear, int band) {
@@ -864,7 +864,8 @@ template <int D> hipError_t backward(const BwdArgs& a, bool with_windowed, hipSt
 // because it is alone; between equals the fewer segments.  Over all keys, where a walk adds up all of a head's sums
 // and chunks are cheap, as many segments as give three workgroups a unit.  Measured (a training step, us; three
 // workgroups a unit, this rule): 4 x (3 + 13) x 2048 x 64 291.3 -> 269.6 (13, 8 segments), without windowed heads
-// 258.2 -> 228.5 (11, 8); elsewhere the same to 1 %.
+// 258.2 -> 228.5 (11, 8); elsewhere the same to 1 %.  (Then the dk/dv walk had room for three a unit as well; it has for
+// two now, and 109 random backward calls, over all keys among them, are none of them slower by more than 1 %.)
 Segments f32_segments(int64_t heads, int N, int d, bool causal, uint64_t bytes, int sums) {
   Segments f{N, 1};
   if (heads <= 0 || N <= 0) return f;

@@ -74,9 +74,10 @@ template <int D> struct StateSmem {
 };
 
 // The read-out's workgroup: QS = 2 (d = 64) splits the chunk's queries over twice as many matrix waves, each with a carried
-// sum of its own, and stages with as many.  At d = 64 a workgroup is the only one of its unit: with QS = 1 its four waves
-// sit on a SIMD each and nothing hides a wave's waits, a chunk is a chain of 3900 cycles; with QS = 2 matrix and staging waves
-// share the SIMDs.  us, QS = 1 and 2: read-out launch of 8 x 10 heads x 4096 47 and 36; layer of 16 x 16 x 1024 33.4 and 28.4.
+// sum of its own, and stages with as many.  At d = 64 a workgroup is mostly the only one of its unit: with QS = 1 its four waves
+// sit on a SIMD each and nothing hides a wave's waits; with QS = 2 matrix and staging waves
+// share the SIMDs.  us, QS = 1 and 2: read-out launch of 8 x 10 heads x 4096 42.0 and 36.1; layer of 16 x 16 x 1024 32.1 and
+// 28.3.  Which calls take which: halves_apart (api.hip).
 template <int D, int QS_> struct MainCfg : LinCfg<D> {
   using L = LinCfg<D>;
   static constexpr int QS = QS_, NW = L::NWC * QS;
@@ -648,8 +649,8 @@ __device__ __forceinline__ void linear_main_block(const AttnArgs& a, int block, 
     }
   };
   // Masked products P^T[key][query] = phi(k_key).phi(q_query), key <= query, are three 32x32
-  // tiles (the fourth lies above the diagonal); tile t goes to wave t % NWC.  A wave left
-  // without a tile repeats tile 0 and stores the same values to the same place, which keeps the
+  // tiles (the fourth lies above the diagonal), dealt out in turn, with the queries split to waves of
+  // their own half.  A wave left without a tile repeats tile 0 and stores the same values to the same place, which keeps the
   // code free of branches: the products and the state read-out then interleave in one block and
   // neither chain of dependent matrix instructions has to wait for its own results.
   constexpr int NTILE = (3 + C::NW - 1) / C::NW;    // product tiles per wave
@@ -863,9 +864,9 @@ __global__ __launch_bounds__((MainCfg<D, QS>::NT), D == 64 ? 2 : 1) void linear_
   linear_main_block<D, QS, ELU1, CAUSAL, EMIT>(a, blockIdx.x, smem_raw);
 }
 
-// The read-out and the windowed heads in one launch (d = 64, calls that leave units idle): blocks [0, n_pieces) are the
-// read-out's in its form of four waves, those from the next multiple of 8 on (the XCDs keep their runs) are query blocks of the
-// windowed heads, which find units of their own.  Same bits as two launches; the whole layer (us, two launches -> one):
+// The read-out and the windowed heads in one launch (d = 64, the read-out's form of four waves): blocks [0, n_pieces) are the
+// read-out's, those from the next multiple of 8 on (the XCDs keep their runs) are query blocks of the
+// windowed heads, which find units or the second place of one.  Same bits as two launches; the whole layer (us, two launches -> one):
 // B=1 H=12 N=2048 w=128 H0=2 36.1 -> 28.1.
 template <bool ELU1, bool CAUSAL, bool EMIT>
 __global__ __launch_bounds__(256, 2) void linear_main_windowed_kernel(AttnArgs a) {
