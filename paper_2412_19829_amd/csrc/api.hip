@@ -213,7 +213,7 @@ long short_piece(long heads, long cph, long cus, int d) {
 // * pieces of two to four chunks: four, but for more workgroups of four waves than the chip holds.  1 x (2 + 10) x 512, 128 12.4
 //   and 15.5; 18 x (3 + 5) x 364, 64 16.9 and 18.1; 1 x (1 + 7) x 5615, 256 25.3 and 27.0; 1 x (11 + 5) x 5484, 256 35.1 and 32.1.
 //   Of five on: eight.  8 x (2 + 10) x 1024, 128 (6 chunks) 26.4 and 25.8; 3 x (1 + 11) x 2472, 38 (8) 35.8 and 32.9; 1 x (2 + 14)
-//   x 16384, 128 (15) 56.0 and 49.4; 8 x (2 + 10) x 4096, 256 (22) 65.1 and 62.7; 4 x (1 + 31) x 16384, 64 (128) 284 and 258.
+//   x 16384, 128 (15) 56.0 and 49.4; 8 x (2 + 10) x 4096, 256 (22) 65.2 and 62.5; 4 x (1 + 31) x 16384, 64 (128) 284 and 258.
 // * a query block's tiles a chain half as long again as a sum's chunks: four.  6 x (4 + 12) x 1241, 278 (7 tiles, 4 chunks) 32.4
 //   and 34.0; mapped 2 x (1 + 31) x 1533, 274 (7, 4) 28.2 and 30.4.
 // * mapped beforehand: eight for pieces of eight chunks on beside few tiles, two or less to five chunks.  Tiles a chunk, chunks
