@@ -198,8 +198,10 @@ long short_piece(long heads, long cph, long cus, int d) {
 // d = 64: whether the read-out's workgroup splits a chunk's queries over twice the waves (MainCfg, linear_mfma.hip), which makes
 // a chunk shorter and a carried sum, which every set of waves loads, dearer.  Figures are us, four waves and eight.  Four waves:
 // * pieces of one chunk, and pieces of up to four that start from more sums than they have chunks.  1 x 12 x 1024 (2 chunks, 7
-//   sums) 14.7 and 15.6, x 512 (2, 3) 12.0 and 12.3, x 2048 (4, 7) 19.7 and 20.3, over all keys 1 x 12 x 512 (1, 8) 11.9 and
-//   14.5; but 4 x 12 x 512 (3, 2) 15.9 and 15.0, 1 x 8 x 686 (3, 3) 14.4 and 13.6, 1 x 12 x 4096 (4, 1: scanned) 24.7 and 23.5.
+//   sums) 14.7 and 15.6, x 512 (2, 3) 12.0 and 12.3, x 2048 (4, 7) 19.7 and 20.3; but 4 x 12 x 512 (3, 2) 15.9 and 15.0,
+//   1 x 8 x 686 (3, 3) 14.4 and 13.6, 1 x 12 x 4096 (4, 1: scanned) 24.7 and 23.5.  Over all keys, where a chunk is short, more
+//   sums than half the chunks: 1 x 12 x 512 (1, 8) 11.9 and 14.5, 3 x 12 x 1951 (5, 7) 23.1 and 24.2, 4 x 12 x 2857 (9, 5) 27.4 and
+//   28.3; but 5 x 8 x 4578 (12, 6) 33.6 and 34.0, 2 x 32 x 2326 (10, 4) 29.5 and 28.6.
 // * more causal pieces than units: of four waves a unit holds two workgroups, of eight one, and the pieces take two rounds.
 //   All heads linear: 257 x 320 16.6 and 19.2, 300 x 512 24.8 and 28.2, 384 x 400 22.1 and 25.2,
 //   512 x 512 28.2 and 31.8, segments of 64 tokens 4 x 12 x 4096 77.7 and 94.0, of 512 1 x 48 x 4096 47.3 and 54.2 (256 x
@@ -215,7 +217,9 @@ long short_piece(long heads, long cph, long cus, int d) {
 //   Of five on: eight.  8 x (2 + 10) x 1024, 128 (6 chunks) 26.4 and 25.8; 3 x (1 + 11) x 2472, 38 (8) 35.8 and 32.9; 1 x (2 + 14)
 //   x 16384, 128 (15) 56.0 and 49.4; 8 x (2 + 10) x 4096, 256 (22) 65.2 and 62.5; 4 x (1 + 31) x 16384, 64 (128) 284 and 258.
 // * a query block's tiles a chain half as long again as a sum's chunks: four.  6 x (4 + 12) x 1241, 278 (7 tiles, 4 chunks) 32.4
-//   and 34.0; mapped 2 x (1 + 31) x 1533, 274 (7, 4) 28.2 and 30.4.
+//   and 34.0; mapped 2 x (1 + 31) x 1533, 274 (7, 4) 28.2 and 30.4.  Longer at all, where sums are few (five of eight units) and the
+//   four-wave launch fits the chip: 3 x (1 + 31) x 613, 256, prefill (6, 5; 93 sums) 21.5 and 23.9; but 1 x (1 + 11) x 6288, 256 (6,
+//   5; 209) 31.0 and 29.6.
 // * mapped beforehand: eight for pieces of eight chunks on beside few tiles, two or less to five chunks.  Tiles a chunk, chunks
 //   a piece: 8 x (2 + 10) x 1024, 128 (0.36, 6) 23.3 and 24.8; 9 x (2 + 6) x 5166, 256 (0.97, 21) 60.4 and 64.6; 20 x (2 + 10) x
 //   1318, 256 (0.63, 18) 49.9 and 51.6; 4 x (3 + 13) x 4096, 128 (0.46, 16) 49.2 and 49.1; but 8 x (2 + 10) x 2048, 128 (0.39, 11)
@@ -223,25 +227,30 @@ long short_piece(long heads, long cph, long cus, int d) {
 // * over all keys: the same from ten chunks on (10 x (2 + 10) x 1056, 256 (0.60, 9) 26.0 and 28.0; 3 x (2 + 10) x 8811, 256
 //   (0.58, 18) 47.6 and 53.3; 6 x (2 + 10) x 2863, 64 (0.29, 12) 35.1 and 33.9), and of more pieces than units all of five chunks
 //   on (32 x (3 + 9) x 577, 64 38.2 and 35.6; 31 x (1 + 15) x 695, 256 46.7 and 42.5; 45 x (1 + 15) x 437, 128, two to three pieces
-//   a unit, 41.7 and 47.5).
+//   a unit, 41.7 and 47.5).  Eight also beside more query blocks than that launch holds, where they weigh more than the chunks: 11 x
+//   (11 + 5) x 8014, 282 256 and 223, 6 x (20 + 12) x 6407, 369 220 and 199, 21 x (12 + 4) x 595, 265 50.2 and 46.6; 13 x (13 + 3) x 644,
+//   256 (pieces of two chunks) 36.3 and 36.4.
 struct ReadOutCut {
   bool causal, mapped;   // mapped: features mapped beforehand
   long pieces, chunks;   // chunks of a piece
   long sums;             // carried sums a piece starts from, at most
+  long sum_blocks;       // sums of the state pass
   long sum_chunks;       // chunks of a sum
   long query_blocks;     // of the windowed heads, where they can share a launch
   long tiles;            // key tiles of a query block, at most
 };
 bool halves_apart(const ReadOutCut& c, long cus) {
-  if (c.chunks == 1 || (c.chunks <= 4 && c.sums > c.chunks)) return false;
+  if (c.chunks == 1 || (c.causal ? c.chunks <= 4 && c.sums > c.chunks : 2 * c.sums > c.chunks)) return false;
   if (c.causal ? c.pieces > cus : c.mapped || (c.pieces > 2 * cus && c.pieces <= 3 * cus)) return false;
   if (c.query_blocks == 0) return true;
   if (c.sums == 0) return false;
-  const bool few = 5 * c.query_blocks * c.tiles <= 2 * c.pieces * c.chunks;
-  if (!c.causal) return c.pieces > cus ? c.chunks >= 5 : c.chunks >= 10 && few;
-  if (2 * c.tiles > 3 * c.sum_chunks) return false;
+  const long beside = c.query_blocks * c.tiles, own = c.pieces * c.chunks;
+  const bool few = 5 * beside <= 2 * own, fits = c.pieces + c.query_blocks <= 2 * cus;
+  if (!c.causal)
+    return (c.pieces > cus ? c.chunks >= 5 : c.chunks >= 10 && few) || (c.chunks >= 4 && c.query_blocks > 3 * cus && beside >= own);
+  if (2 * c.tiles > 3 * c.sum_chunks || (c.tiles > c.sum_chunks && 8 * c.sum_blocks < 5 * cus && fits)) return false;
   if (c.mapped) return c.chunks >= 8 && few;
-  return c.chunks >= 5 || (c.chunks == 4 && c.pieces + c.query_blocks > 2 * cus);
+  return c.chunks >= 5 || (c.chunks == 4 && !fits);
 }
 
 // Shared by gformer_attn_plan, gformer_attn_workspace_bytes and gformer_attn_fwd.
@@ -472,7 +481,7 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
     if (mid > 0 && (sums == 0 || sums > sums_in_place(d))) sums = 1;   // scanned beforehand, where there are many
     const long reach = (long)window_left(window, p->bidirectional, N) + window_right(window, p->bidirectional, N);
     const long tiles = std::min((reach + kMfmaWindowRows - 1) / kStrip, (N - 1) / kStrip) + 1;
-    const ReadOutCut c{!p->bidirectional, p->phi != GF_PHI_ELU1, pieces, piece, sums, piece / sub_beside,
+    const ReadOutCut c{!p->bidirectional, p->phi != GF_PHI_ELU1, pieces, piece, sums, mid_beside, piece / sub_beside,
                        r->stream ? 0 : query_blocks, tiles};
     if (halves_apart(c, kComputeUnits)) r->query_halves = 2;
   }

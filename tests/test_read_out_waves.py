@@ -40,6 +40,7 @@ def test_plan_of_more_pieces_than_units(case):
     (1, 12, 512, 16, 0, {}, 256), (1, 12, 1024, 16, 0, {}, 256), (1, 12, 2048, 16, 0, {}, 256),      # more sums than chunks
     (4, 12, 512, 16, 0, {}, 512), (1, 8, 686, 16, 0, {}, 512), (1, 12, 4096, 16, 0, {}, 512), (1, 12, 64, 16, 0, {}, 512),
     (1, 12, 512, 16, 0, {"bidirectional": 1}, 256), (1, 12, 64, 16, 0, {"bidirectional": 1}, 256),   # pieces of one chunk
+    (3, 12, 1951, 16, 0, {"bidirectional": 1}, 256), (4, 12, 2857, 16, 0, {"bidirectional": 1}, 256), (2, 32, 2326, 16, 0, {"bidirectional": 1}, 512),
     (8, 12, 1000, 16, 0, {"bidirectional": 1}, 512), (1, 600, 200, 16, 0, {"bidirectional": 1}, 256),
     (8, 12, 1000, 16, 0, {"bidirectional": 1, "phi": gb.GF_PHI_IDENTITY}, 256), (4, 16, 4096, 16, 0, {"phi": gb.GF_PHI_IDENTITY}, 512),
     (1, 12, 512, 16, 0, {"phi": gb.GF_PHI_IDENTITY}, 256), (10, 16, 10491, 256, 3, {"phi": gb.GF_PHI_IDENTITY}, 512),
@@ -56,10 +57,12 @@ def test_plan_without_query_blocks_beside(case):
     (18, 8, 364, 64, 3, {}, 256), (1, 8, 5615, 256, 1, {}, 256), (1, 16, 5484, 256, 11, {}, 512),    # three and four chunks a piece
     (8, 12, 1024, 128, 2, {}, 512), (3, 12, 2472, 38, 1, {}, 512), (1, 16, 16384, 128, 2, {}, 512),
     (6, 16, 1241, 278, 4, {}, 256), (6, 16, 1241, 128, 4, {}, 512),         # long chains of tiles
+    (3, 32, 613, 256, 1, {}, 256), (1, 12, 6288, 256, 1, {}, 512), (3, 32, 613, 128, 1, {}, 512),   # ... beside few sums
     (8, 12, 1024, 128, 2, {"phi": gb.GF_PHI_IDENTITY}, 256), (9, 8, 5166, 256, 2, {"phi": gb.GF_PHI_IDENTITY}, 256),
     (8, 12, 2048, 128, 2, {"phi": gb.GF_PHI_IDENTITY}, 512), (4, 32, 16384, 64, 1, {"phi": gb.GF_PHI_IDENTITY}, 512),
     (8, 12, 1000, 64, 3, {"bidirectional": 1}, 256), (3, 12, 8811, 256, 2, {"bidirectional": 1}, 256),
     (6, 12, 2863, 64, 2, {"bidirectional": 1}, 512), (32, 12, 577, 64, 3, {"bidirectional": 1}, 512),
+    (11, 16, 8014, 282, 11, {"bidirectional": 1}, 512), (13, 16, 644, 256, 13, {"bidirectional": 1}, 256),
     (45, 16, 437, 128, 1, {"bidirectional": 1}, 256), (32, 12, 577, 64, 3, {"bidirectional": 1, "phi": gb.GF_PHI_IDENTITY}, 256),
 ], ids=lambda c: "x".join(map(str, c[:5])) + "".join(f"-{k}" for k in c[5]))
 def test_plan_with_query_blocks_beside(case):
