@@ -220,6 +220,15 @@ long short_piece(long heads, long cph, long cus, int d) {
 //   and 34.0; mapped 2 x (1 + 31) x 1533, 274 (7, 4) 28.2 and 30.4.  Longer at all, where sums are few (five of eight units) and the
 //   four-wave launch fits the chip: 3 x (1 + 31) x 613, 256, prefill (6, 5; 93 sums) 21.5 and 23.9; but 1 x (1 + 11) x 6288, 256 (6,
 //   5; 209) 31.0 and 29.6.
+// * pieces longer than a head, beside query blocks of fewer tiles than a sum has chunks that weigh more and with the pieces come to
+//   nearly two a unit (19 to 10): four.  Few sums are left then, the query blocks run alone, and the read-out leaves most units idle
+//   behind them.  29 x (12 + 4) x 188, 256 (44 pieces, 696 query blocks) 24.9 and 29.8; 20 x (24 + 8) x 136, 39 (60, 960) 24.6 and 29.1;
+//   15 x (13 + 19) x 133, 256 (107, 390) 24.3 and 26.1; but 17 x (13 + 3) x 191, 64 (20, 442) 23.8 and 22.8; 22 x (17 + 15) x 624, 378
+//   (more tiles) 76.5 and 71.5; 12 x (2 + 30) x 2578, 256 (lighter) 128.8 and 118.4.
+// * sums of four chunks that with the query blocks take a second round (three a unit), where the four-wave launch takes no third (two a
+//   unit): four where the query blocks are five times the weight, or the sums half as many again as the pieces.  11 x (7 + 1) x 1278, 128
+//   (44 sums, 770 query blocks) 27.8 and 29.8; 6 x (8 + 8) x 1700, 28 (288, 672; 162 pieces) 33.7 and 37.7; 5 x (8 + 8) x 2267, 256 (300,
+//   720; 180) 42.5 and 45.6; but 2 x (14 + 2) x 2850, 256 (44, 644) 33.5 and 30.8; 25 x (4 + 4) x 1009, 64 (200, 800; 200) 38.3 and 36.7.
 // * mapped beforehand: eight for pieces of eight chunks on beside few tiles, two or less to five chunks.  Tiles a chunk, chunks
 //   a piece: 8 x (2 + 10) x 1024, 128 (0.36, 6) 23.3 and 24.8; 9 x (2 + 6) x 5166, 256 (0.97, 21) 60.4 and 64.6; 20 x (2 + 10) x
 //   1318, 256 (0.63, 18) 49.9 and 51.6; 4 x (3 + 13) x 4096, 128 (0.46, 16) 49.2 and 49.1; but 8 x (2 + 10) x 2048, 128 (0.39, 11)
@@ -233,6 +242,7 @@ long short_piece(long heads, long cph, long cus, int d) {
 struct ReadOutCut {
   bool causal, mapped;   // mapped: features mapped beforehand
   long pieces, chunks;   // chunks of a piece
+  long head;             // chunks of a head
   long sums;             // carried sums a piece starts from, at most
   long sum_blocks;       // sums of the state pass
   long sum_chunks;       // chunks of a sum
@@ -249,6 +259,10 @@ bool halves_apart(const ReadOutCut& c, long cus) {
   if (!c.causal)
     return (c.pieces > cus ? c.chunks >= 5 : c.chunks >= 10 && few) || (c.chunks >= 4 && c.query_blocks > 3 * cus && beside >= own);
   if (2 * c.tiles > 3 * c.sum_chunks || (c.tiles > c.sum_chunks && 8 * c.sum_blocks < 5 * cus && fits)) return false;
+  if (c.chunks > c.head && c.tiles < c.sum_chunks && beside >= own && 10 * (c.pieces + c.query_blocks) >= 19 * cus) return false;
+  if (c.sum_chunks <= 4 && c.sum_blocks + c.query_blocks > 3 * cus && c.pieces + c.query_blocks <= 4 * cus &&
+      (beside > 5 * own || 2 * c.sum_blocks > 3 * c.pieces))
+    return false;
   if (c.mapped) return c.chunks >= 8 && few;
   return c.chunks >= 5 || (c.chunks == 4 && !fits);
 }
@@ -481,7 +495,7 @@ gf_status resolve(int B, int H, int N, int d, int window, const gformer_params* 
     if (mid > 0 && (sums == 0 || sums > sums_in_place(d))) sums = 1;   // scanned beforehand, where there are many
     const long reach = (long)window_left(window, p->bidirectional, N) + window_right(window, p->bidirectional, N);
     const long tiles = std::min((reach + kMfmaWindowRows - 1) / kStrip, (N - 1) / kStrip) + 1;
-    const ReadOutCut c{!p->bidirectional, p->phi != GF_PHI_ELU1, pieces, piece, sums, mid_beside, piece / sub_beside,
+    const ReadOutCut c{!p->bidirectional, p->phi != GF_PHI_ELU1, pieces, piece, cph, sums, mid_beside, piece / sub_beside,
                        r->stream ? 0 : query_blocks, tiles};
     if (halves_apart(c, kComputeUnits)) r->query_halves = 2;
   }

@@ -58,6 +58,8 @@ def test_plan_without_query_blocks_beside(case):
     (8, 12, 1024, 128, 2, {}, 512), (3, 12, 2472, 38, 1, {}, 512), (1, 16, 16384, 128, 2, {}, 512),
     (6, 16, 1241, 278, 4, {}, 256), (6, 16, 1241, 128, 4, {}, 512),         # long chains of tiles
     (3, 32, 613, 256, 1, {}, 256), (1, 12, 6288, 256, 1, {}, 512), (3, 32, 613, 128, 1, {}, 512),   # ... beside few sums
+    (29, 16, 188, 256, 12, {}, 256), (15, 32, 133, 256, 13, {}, 256), (17, 16, 191, 64, 13, {}, 512), (22, 32, 624, 378, 17, {}, 512),   # pieces longer than heads
+    (6, 16, 1700, 28, 8, {}, 256), (11, 8, 1278, 128, 7, {}, 256), (2, 16, 2850, 256, 14, {}, 512), (25, 8, 1009, 64, 4, {}, 512),    # two rounds of sums and query blocks
     (8, 12, 1024, 128, 2, {"phi": gb.GF_PHI_IDENTITY}, 256), (9, 8, 5166, 256, 2, {"phi": gb.GF_PHI_IDENTITY}, 256),
     (8, 12, 2048, 128, 2, {"phi": gb.GF_PHI_IDENTITY}, 512), (4, 32, 16384, 64, 1, {"phi": gb.GF_PHI_IDENTITY}, 512),
     (8, 12, 1000, 64, 3, {"bidirectional": 1}, 256), (3, 12, 8811, 256, 2, {"bidirectional": 1}, 256),
